@@ -68,7 +68,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 8 || D == 256) ? 1 : (D == 64 ? 3 :
     for (size_t i = gid; i < p.dz_n; i += nth) p.dz[i] = 0.f;
   }
   int h, item;
-  if (!xcd_map_interleaved(wg_id(), p.H_q, p.nblk_cap * HALVES, h, item)) return;
+  if (!xcd_map(wg_id(), p.H_q, p.nblk_cap * HALVES, h, item)) return;
   const int bi = p.nblk_cap - 1 - item / HALVES;  // long blocks first
   const int4 info = p.blk[bi];
   if (info.x < 0) return;
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
   const int ngrp = PARTIAL ? MAXPART / SG : p.kpad / SG;
   const int nchunk = (p.nblk_cap + (PARTIAL ? p.seg_part : p.seg) - 1) / (PARTIAL ? p.seg_part : p.seg);
   int h, item;
-  if (!xcd_map_interleaved(wg_id(), p.H_q, ngrp * nchunk, h, item)) return;
+  if (!xcd_map(wg_id(), p.H_q, ngrp * nchunk, h, item)) return;
   // Clean mode: the groups of a chunk are neighbours.  Partial mode: group-major, because the high
   // groups of most chunks are empty and workgroups go to the shader engines in turn: with the
   // groups as the fast index all the work would land on the engines that get groups 0 and 1.

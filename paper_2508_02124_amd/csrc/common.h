@@ -346,18 +346,26 @@ __device__ __forceinline__ int wg_id() { return (int)__builtin_amdgcn_workgroup_
 __device__ __forceinline__ int thread_id() { return (int)__builtin_amdgcn_workitem_id_x(); }
 
 // Workgroups are dealt round-robin to the chip's 8 XCDs in launch order, and each XCD has its own
-// L2.  A 1-D grid of 8 * ceil(H / 8) * items_per_head workgroups is mapped so that XCD x works on
-// heads x, x + 8, ...: neighbouring query blocks of a head gather almost the same keys, and the slot
-// groups of a head sweep the same Q / dO tiles, so those re-reads hit in that L2.  The heads of an
-// XCD take turns item by item: with items ordered from long to short the whole XCD then works from
-// long to short, and its last items are the shortest ones.
-__device__ __forceinline__ bool xcd_map_interleaved(int wg, int H, int items_per_head, int& h, int& item) {
-  const int x = wg & 7, idx = wg >> 3, hb = (H + 7) >> 3;
-  item = idx / hb;
-  h = x + 8 * (idx - item * hb);
-  return h < H;
+// L2.  A 1-D grid maps so that XCD x works on consecutive heads: neighbouring query blocks of a
+// head gather almost the same keys, the slot groups of a head sweep the same Q / dO tiles, and the
+// q-heads of a kv-group read the same K / V rows and add to the same dK / dV rows, so all of those
+// meet in one L2.  Where the heads do not divide by 8, every head is cut into m = 8 / gcd(8, H)
+// phases (item mod m) and the H * m pieces are dealt out instead, so that no XCD idles with few
+// heads (fwd / dq, us before -> after: 36271 tokens x 2 heads 113 -> 46 / 192 -> 86; 16384 x 12 heads
+// 176 -> 144 / 272 -> 228; 32 heads unchanged).  The pieces of an XCD take turns item by item: with items ordered from long to short the
+// whole XCD then works from long to short, and its last items are the shortest ones.
+__host__ __device__ __forceinline__ int xcd_phases(int H) { return H & 1 ? 8 : H & 2 ? 4 : H & 4 ? 2 : 1; }
+__device__ __forceinline__ bool xcd_map(int wg, int H, int items_per_head, int& h, int& item) {
+  const int x = wg & 7, idx = wg >> 3, m = xcd_phases(H), pb = (H * m) >> 3;  // pieces per XCD
+  const int turn = idx / pb, piece = x * pb + (idx - turn * pb);
+  h = piece / m;
+  item = turn * m + (piece - h * m);
+  return item < items_per_head;
 }
-static inline unsigned xcd_grid(int H, long items_per_head) { return (unsigned)(8l * ((H + 7) / 8) * items_per_head); }
+static inline unsigned xcd_grid(int H, long items_per_head) {
+  const int m = xcd_phases(H);
+  return (unsigned)((long)H * m * ((items_per_head + m - 1) / m));
+}
 
 // document of a global row: largest d with cu[d] <= t
 __device__ __forceinline__ int find_doc(const int32_t* __restrict__ cu, int n_docs, int t) {

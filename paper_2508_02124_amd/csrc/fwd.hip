@@ -60,7 +60,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || D == 256) ? 1 :
   __shared__ __align__(16) int e_ring[NS][KT];
 
   int h, item;
-  if (!xcd_map_interleaved(wg_id(), p.H_q, p.nblk_cap * HALVES, h, item)) return;
+  if (!xcd_map(wg_id(), p.H_q, p.nblk_cap * HALVES, h, item)) return;
   const int bi = p.nblk_cap - 1 - item / HALVES;  // long blocks first
   const int4 info = p.blk[bi];
   if (info.x < 0) return;
