@@ -89,7 +89,8 @@ size_t dma_workspace_bytes(const dma_shape* shape);
  * entry points need none of this.  `out` is a HOST pointer; offsets are bytes from the start of the
  * mask buffer.  Returns DMA_OK or the error of an invalid shape.
  *   blocks         int32[nblk_cap][4]: {document, first row, end row, document start}; document -1 past the end
- *   slot_table     int32[H_q][nblk_cap][kpad]: resident key of each slot column, -1 = none
+ *   slot_table     int32[H_q][nblk_cap][kpad]: resident key of each slot column; below 0 = none for the whole
+ *                  block (-2 - key: that key enters inside the block and stays to its end; -1 otherwise)
  *   partial_count  int32[H_q][nblk_cap];  partial_list int32[H_q][nblk_cap][max_partial]
  *   header         int32[16], [0] = number of blocks;  zq float[H_q][T] = z / softmax_scale
  */

@@ -34,9 +34,10 @@ struct BwdArgs {
   const int4* blk;
   const int32_t* slot_tab;
   const int32_t* pcnt;
+  const int32_t* pent;
   const int32_t* plist;
   const char* consts;  // [0,256) zeros; +256: float -inf; +260: int 0; +264: int -1; +268: float +inf; +272: softmax scale, scale * log2(e)
-  int T, H_q, H_kv, k, nblk_cap, kpad;
+  int T, H_q, H_kv, k, nblk_cap, kpad, causal;
   int seg;       // query blocks swept by one clean-mode work item of dkv_kernel
   int seg_part;  // ... by one partial-mode work item
   size_t zero_n4;  // float4 elements from dK32 to the end of dV32 (cleared by dq_kernel)
@@ -337,6 +338,8 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
   constexpr int NS = D == 256 ? 3 : 5;    // ring stages (a stage of 512-byte rows is 32 KiB)
   constexpr int STILE = SUB * D;
   constexpr int LDS_ST = 32 + 4;          // staging row: the 32 channels of one flush pass, padded
+  constexpr bool ENTER = D != 256;        // a key's first block belongs to its column (at 256 channels the mask costs more
+                                          // spilled registers than the listing: 1.78 -> 1.92 ms against 0.45 -> 0.39)
   constexpr int NCH = D == 256 ? 2 : 1;   // column halves of a flush pass (LDS is short at 256 channels)
   constexpr int STC = 32 / NCH;           // columns staged at a time
   __shared__ __align__(16) uint16_t ringQ[NS * STILE];
@@ -370,8 +373,9 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
   const int seg = PARTIAL ? p.seg_part : p.seg;
   const int bi_begin = chunk * seg, bi_end = min(bi_begin + seg, p.nblk_cap);
   // Block table of this sweep, kept in LDS so that the copy-ring loop issues no ordinary loads:
-  // {block index, first row, end row, columns of this group} of every block of the chunk in which
-  // the group has at least one column (clean mode: resident slots; partial mode: listed keys).
+  // {block index, first row, rows | columns of this group << 16, x} of every block of the chunk in which
+  // the group has at least one column (clean mode: slots in use at the block's end, x = the document's
+  // first row; partial mode: listed keys, x = first list entry).
   __shared__ int nblocks_s;
   for (int i = tid; i < MAXSWEEP + 1; i += 512) binfo[i] = make_int4(-1, 0, 0, 0);
   __syncthreads();
@@ -384,12 +388,19 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
       if (bi < bi_end) {
         info = p.blk[bi];
         if (info.x >= 0) {
-          const int total = PARTIAL ? p.pcnt[(size_t)h * p.nblk_cap + bi] : min(p.k, info.y - info.w);
+          int total;
+          if (PARTIAL) {
+            const int first = ENTER ? p.pent[(size_t)h * p.nblk_cap + bi] : 0;  // the slot sweep has the keys before it
+            total = p.pcnt[(size_t)h * p.nblk_cap + bi] - first;
+            info.w = first;
+          } else {
+            total = min(p.k, (ENTER && p.causal ? info.z : info.y) - info.w);
+          }
           nc = max(0, min(SG, total - grp * SG));
         }
       }
       const unsigned long long m = __ballot(nc > 0);
-      if (nc > 0) binfo[cnt + __popcll(m & ((1ull << l) - 1ull))] = make_int4(bi, info.y, info.z, nc);
+      if (nc > 0) binfo[cnt + __popcll(m & ((1ull << l) - 1ull))] = make_int4(bi, info.y, (info.z - info.y) | nc << 16, info.w);
       cnt += __popcll(m);
     }
     if (l == 0) nblocks_s = cnt;
@@ -403,15 +414,17 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
   // refreshed only when a stream (producer or consumer) enters the next block.  Past the end of
   // the sweep it is a dummy without columns.
   struct Cursor {
-    int bi, row0, row1, ncols;
+    int bi, row0, row1, ncols, x;
   };
   auto load_cursor = [&](int bl) -> Cursor {
     const int4 info = binfo[min(bl, MAXSWEEP)];
     Cursor c;
     c.bi = __builtin_amdgcn_readfirstlane(info.x);
     c.row0 = __builtin_amdgcn_readfirstlane(info.y);
-    c.row1 = __builtin_amdgcn_readfirstlane(info.z);
-    c.ncols = __builtin_amdgcn_readfirstlane(info.w);
+    const int z = __builtin_amdgcn_readfirstlane(info.z);
+    c.row1 = c.row0 + (z & 0xffff);
+    c.ncols = z >> 16;
+    c.x = __builtin_amdgcn_readfirstlane(info.w);
     return c;
   };
 
@@ -438,7 +451,7 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
   }
   const char* Qh = (const char*)uniform_ptr(reinterpret_cast<const char*>(p.Q) + (size_t)h * D * 2);   // row 0 of this head
   const char* dOh = (const char*)uniform_ptr(reinterpret_cast<const char*>(p.dO) + (size_t)h * D * 2);
-  Cursor pc = {-1, 0, 0, 0};
+  Cursor pc = {-1, 0, 0, 0, 0};
   int issue_st = 0;   // ring stage of the next step to issue (steps are issued in order: v mod NS without a division)
   auto issue = [&](int v) {
     if (role != 0) return;
@@ -478,14 +491,18 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
       const int cl = (w - 1) * 64 + l;
       const int32_t* src = c_m1;
       if (cl < pc.ncols) {
-        src = PARTIAL ? p.plist + ((size_t)h * p.nblk_cap + bi) * MAXPART + grp * SG + cl
+        src = PARTIAL ? p.plist + ((size_t)h * p.nblk_cap + bi) * MAXPART + pc.x + grp * SG + cl
                       : p.slot_tab + ((size_t)h * p.nblk_cap + bi) * p.kpad + grp * SG + cl;
       }
       dma4(src, &idbuf[(v / NSUB) & 1][(w - 1) * 64]);
     }
   };
 
-  int curid = -1, kj = 0x7fffffff, ke = 0;
+  // kj: first row of this lane's key (partial mode also ke: its end row).  A clean-mode column needs the row
+  // mask only in the block its key entered in (`entering`: some column of this wave is in that state).
+  constexpr int KJ_NONE = PARTIAL ? 0x7fffffff : -1;
+  int curid = -1, kj = KJ_NONE, ke = 0;
+  bool entering = false;
   float zq = -INFINITY;  // z / scale of this lane's key: the start value of its S accumulator
   bf16x8 breg[KS];  // B-operand fragments of this lane's key: K rows (role 0) or V rows (role 1)
 #pragma unroll
@@ -559,7 +576,7 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
 
   FragOffsets<D> fo;
   fo.init(l);
-  Cursor cc = {-1, 0, 0, 0};
+  Cursor cc = {-1, 0, 0, 0, 0};
   f32x16 sacc;        // role 0: S of the current step; role 1: dP of the step it has in flight
   bool pend = false;  // role 1: step pstep has its dP computed; dS, dz and dK^T are still due
   int pstep = 0;
@@ -609,7 +626,19 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
     const int ncols = cc.ncols, row0 = cc.row0, row1 = cc.row1;
     if (qs == 0) {
       const int cl = 32 * kb4 + n;
-      const int newid = (cl < ncols) ? idbuf[(v / NSUB) & 1][cl] : -1;
+      int newid = (cl < ncols) ? idbuf[(v / NSUB) & 1][cl] : -1;
+      if (!PARTIAL) {
+        if (newid < -1) newid = ENTER ? -2 - newid : -1;  // enters inside this block
+        // Columns that are new in this block (the first k rows of a document) are not in the table: column
+        // c takes the document's key c, unless that key is gone again before the block ends.
+        const int col = grp * SG + cl, old = row0 - cc.x;
+        if (ENTER && p.causal && grp * SG + 32 * kb4 + 31 >= old && cl < ncols && col >= old) {
+          const int key = cc.x + col;
+          if (p.expiry[(size_t)h * p.T + key] >= row1) newid = key;
+        }
+        entering = ENTER && p.causal && __any(newid > row0);
+        if (newid != curid) kj = newid >= 0 ? newid : KJ_NONE;
+      }
       const bool changed = newid != curid;
       if (__any(changed)) {
         // The new keys' rows are requested first and arrive while the finished keys are flushed
@@ -629,8 +658,10 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
 #pragma unroll
             for (int ks = 0; ks < KS; ks++) breg[ks] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
             zq = -INFINITY;
-            kj = 0x7fffffff;
-            ke = 0;
+            if (PARTIAL) {
+              kj = KJ_NONE;
+              ke = 0;
+            }
           }
         }
         flush(changed);  // finished keys out, then re-arm the changed columns
@@ -654,6 +685,8 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
       // first row, expiring ones by ascending end row); both roles of a column block agree
       const int rf = row0 + SUB * qs;
       if (!__any((kj < rf + SUB) & (ke > rf))) continue;
+    } else if (entering && !__any((curid >= 0) & (kj < row0 + SUB * qs + SUB))) {
+      continue;  // none of this wave's keys has entered yet
     }
 
     const int st = v % NS;
@@ -663,8 +696,19 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
     // role 0: S = Q K^T ; role 1: dP = dO V^T   (this lane's key column against the step's 32 rows)
     const uint16_t* As = role == 0 ? Qs : dOs;
     if (role == 0) {  // S starts at z / scale, so that scale * S is the biased score
+      // (a key that enters in a later step: all of its rows stay at -inf, so P = 0 and dS = 0 exactly; in
+      // the step it enters in, the rows before it do)
+      const int rf = row0 + SUB * qs;
+      float z0 = zq;
+      if (!PARTIAL && entering) z0 = kj >= rf + SUB ? -INFINITY : zq;
+      if (!PARTIAL && entering && __any((kj > rf) & (kj < rf + SUB))) {
+        const int first = kj - rf - 4 * hh;
 #pragma unroll
-      for (int vv = 0; vv < 16; vv++) sacc[vv] = zq;
+        for (int vv = 0; vv < 16; vv++) sacc[vv] = 8 * (vv >> 2) + (vv & 3) >= first ? z0 : -INFINITY;
+      } else {
+#pragma unroll
+        for (int vv = 0; vv < 16; vv++) sacc[vv] = z0;
+      }
     } else {  // dP starts at -D_i of the accumulator's rows: the products then leave dP - D, what dS needs
       const float* Dss = meta[st] + 32;
 #pragma unroll
@@ -752,9 +796,10 @@ int launch_bwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
   a.blk = (const int4*)(p.plan + L.off_blk);
   a.slot_tab = (const int32_t*)(p.plan + L.off_slot);
   a.pcnt = (const int32_t*)(p.plan + L.off_pcnt);
+  a.pent = (const int32_t*)(p.plan + L.off_pent);
   a.plist = (const int32_t*)(p.plan + L.off_plist);
   a.consts = p.plan + L.off_consts;
-  a.T = s.T; a.H_q = s.H_q; a.H_kv = s.H_kv; a.k = s.k; a.nblk_cap = L.nblk_cap; a.kpad = L.kpad;
+  a.T = s.T; a.H_q = s.H_q; a.H_kv = s.H_kv; a.k = s.k; a.nblk_cap = L.nblk_cap; a.kpad = L.kpad; a.causal = s.causal;
   {  // sweep length of a clean-mode work item: as long as possible while keeping >= 512 work items
     const long groups = (long)(L.kpad / SG) * s.H_q;
     long seg = (long)L.nblk_cap * groups / 512;
@@ -762,7 +807,12 @@ int launch_bwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
     if (seg > L.nblk_cap) seg = L.nblk_cap;
     if (seg > MAXSWEEP) seg = MAXSWEEP;
     a.seg = (int)seg;
-    a.seg_part = L.nblk_cap < 8 ? L.nblk_cap : 8;  // blocks per partial-mode work item: amortises the pipeline fill
+    // Blocks per partial-mode work item: up to 8, which amortises the pipeline fill, but at least about 256
+    // items with keys in them (most blocks list at most one group of them), else the launch is one long
+    // chain on an idle chip: 2 x 4096 tokens x 16 heads 0.135 ms at 8 blocks, 0.070 at 2; 10007 tokens x 8
+    // heads, window 333: 0.110 at 8, 0.052 at 1; 16384 x 32 heads: 0.194 at 2, 0.166 at 8.
+    long sp = (long)L.nblk_cap * s.H_q / 256;
+    a.seg_part = sp < 1 ? 1 : sp > 8 ? 8 : (int)sp;
   }
 
   const size_t nkv = (size_t)s.T * s.H_kv * s.d;

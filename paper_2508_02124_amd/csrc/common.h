@@ -43,8 +43,11 @@ struct PlanLayout {
   size_t off_zq;       // float[H_q][T]: z / softmax_scale, the bias as the start value of a Q K^T accumulator
   size_t off_blk;      // int4[nblk_cap]: {doc, row0, row1, doc_start}; doc = -1 past the end
   size_t off_docblk;   // int32[n_docs + 1]: first block of each document
-  size_t off_slot;     // int32[H_q][nblk_cap][kpad]: clean resident key of each slot, or -1
+  size_t off_slot;     // int32[H_q][nblk_cap][kpad]: clean resident key of each slot; -2 - key for a key that enters
+                       // inside the block and stays to its end (the slot's next resident); else -1
   size_t off_pcnt;     // int32[H_q][nblk_cap]
+  size_t off_pent;     // int32[H_q][nblk_cap]: leading keys of the list that enter here and stay to the block's end
+                       // in a slot column of their own (the key-stationary backward takes them in its slot sweep)
   size_t off_plist;    // int32[H_q][nblk_cap][MAXPART]: keys partially active in the block
   size_t off_parent;   // int32[H_q][T]: key evicted when this key entered (global index) or -1
   size_t off_slotid;   // int32[H_q][T]: slot column of the key (local), valid if the key ever enters
@@ -86,6 +89,7 @@ static inline PlanLayout plan_layout(const dma_shape& s) {
   p.off_docblk = take((size_t)(s.n_docs + 1) * 4);
   p.off_slot = take(H * p.nblk_cap * (size_t)p.kpad * 4);
   p.off_pcnt = take(H * p.nblk_cap * 4);
+  p.off_pent = take(H * p.nblk_cap * 4);
   p.off_plist = take(H * p.nblk_cap * (size_t)MAXPART * 4);
   p.off_parent = take(H * T * 4);
   p.off_slotid = take(H * T * 4);

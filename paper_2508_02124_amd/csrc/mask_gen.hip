@@ -593,13 +593,17 @@ __global__ __launch_bounds__(256) void slot_table_kernel(const int32_t* __restri
     if (e <= i_hi) break;
     slot_tab[((size_t)h * nblk_cap + blk0 + bl) * kpad + slot] = t;
   }
+  // its own block: entered there and still resident at its end (columns that are new in this block hold
+  // the document's first keys in order and stay -1)
+  const int b0 = j / BQ;
+  if (slot < b0 * BQ && e >= min(b0 * BQ + BQ, n)) slot_tab[((size_t)h * nblk_cap + blk0 + b0) * kpad + slot] = -2 - t;
 }
 
 // The same table, row by row, in tiles of SLOT_TILE columns.  One workgroup per (chunk of
-// consecutive blocks, head, column tile) keeps in LDS, per slot, the latest key of the slot's chain among the keys
-// before the current block, with its expiry; a block's row is then one coalesced pass (the key if
-// it outlives the block, else -1; nothing is left for a fill launch), after which the block's own
-// keys are taken in.  The state at the chunk's first block comes from one scan of the document's
+// consecutive blocks, head, column tile) keeps in LDS, per slot, the latest key of the slot's chain, with its
+// expiry; a block's own keys are taken in and its row is then one coalesced pass (the key if it
+// outlives the block, -2 - key if it also entered inside it, else -1; nothing is left for a fill
+// launch).  The state at the chunk's first block comes from one scan of the document's
 // earlier keys (exactly one key per chain is still kept at a given row; every column tile repeats
 // the scan, so this kernel serves windows of up to SLOT_TILES_MAX tiles).  The scattered 4-byte
 // stores of the kernel above cost a 64-byte write each; these rows are written whole.
@@ -637,11 +641,6 @@ __global__ __launch_bounds__(512) void slot_rows_kernel(const int4* __restrict__
       }
       __syncthreads();
     }
-    for (int c = tid; c < nc; c += 512) {
-      const unsigned long long v = cur[c];
-      row[c] = (v != 0ull && (int)(unsigned)v > hi) ? (int)(v >> 32) - 1 : -1;
-    }
-    __syncthreads();
     for (int j = lo + tid; j <= hi; j += 512) {
       const int e = ex[j];
       if (e > j) {
@@ -650,45 +649,70 @@ __global__ __launch_bounds__(512) void slot_rows_kernel(const int4* __restrict__
       }
     }
     __syncthreads();
+    for (int c = tid; c < nc; c += 512) {
+      const unsigned long long v = cur[c];
+      const int key = (int)(v >> 32) - 1;
+      int entry = -1;
+      if (v != 0ull && (int)(unsigned)v > hi) {  // resident at the block's end
+        if (key < lo) entry = key;
+        else if (c0 + c < lo - a) entry = -2 - key;  // (a column that is new in this block stays -1)
+      }
+      row[c] = entry;
+    }
+    __syncthreads();
   }
 }
 
-// One workgroup (BQ threads) per (block, head): keys that enter inside the block (ascending), then
-// keys that were resident at the block's first row and are evicted inside it (by ascending evictor).
+// One workgroup (BQ threads) per (block, head): keys that enter inside the block and stay to its end
+// in a slot column of their own (ascending; pent counts them: the key-stationary backward takes them in
+// its slot sweep), then the other keys that enter inside the block (ascending), then keys that were
+// resident at the block's first row and are evicted inside it (by ascending evictor).
 __global__ __launch_bounds__(BQ) void partial_list_kernel(const int4* __restrict__ blk,
                                                           const int32_t* __restrict__ expiry,
-                                                          const int32_t* __restrict__ parent, int32_t* pcnt,
-                                                          int32_t* plist, int T, int nblk_cap) {
+                                                          const int32_t* __restrict__ parent,
+                                                          const int32_t* __restrict__ slotid, int32_t* pcnt,
+                                                          int32_t* pent, int32_t* plist, int T, int nblk_cap) {
   const int bi = blockIdx.x, h = blockIdx.y;
   const int4 info = blk[bi];
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   if (info.x < 0) {
-    if (tid == 0) pcnt[(size_t)h * nblk_cap + bi] = 0;
+    if (tid == 0) pcnt[(size_t)h * nblk_cap + bi] = pent[(size_t)h * nblk_cap + bi] = 0;
     return;
   }
   const int i = info.y + tid;
-  const bool ent = (i < info.z) && expiry[(size_t)h * T + i] > i;
+  const int e = i < info.z ? expiry[(size_t)h * T + i] : 0;
+  const bool ent = (i < info.z) && e > i;
   int m = -1;
-  if (ent) m = parent[(size_t)h * T + i];
+  bool stays = false;  // its slot column belongs to it alone from here to the block's end: an older column, or its own new one
+  if (ent) {
+    m = parent[(size_t)h * T + i];
+    const int col = slotid[(size_t)h * T + i];
+    stays = e >= info.z && (col < info.y - info.w || col == i - info.w);  // (causal plan: w = first row of the document)
+  }
   const bool exq = ent && m >= 0 && m < info.y && i > info.y;  // evicted at the block's first row: not active here
-  __shared__ int cnt[2][BQ / 64];
-  const unsigned long long em = __ballot(ent), xm = __ballot(exq);
+  __shared__ int cnt[3][BQ / 64];
+  const unsigned long long sm = __ballot(ent && stays), em = __ballot(ent && !stays), xm = __ballot(exq);
   const unsigned long long lt = (1ull << l) - 1ull;
   if (l == 0) {
-    cnt[0][w] = __popcll(em);
-    cnt[1][w] = __popcll(xm);
+    cnt[0][w] = __popcll(sm);
+    cnt[1][w] = __popcll(em);
+    cnt[2][w] = __popcll(xm);
   }
   __syncthreads();
-  int ebase = 0, xbase = 0, etot = 0, xtot = 0;
+  int sbase = 0, ebase = 0, xbase = 0, stot = 0, etot = 0, xtot = 0;
   for (int i2 = 0; i2 < BQ / 64; i2++) {
-    if (i2 < w) { ebase += cnt[0][i2]; xbase += cnt[1][i2]; }
-    etot += cnt[0][i2];
-    xtot += cnt[1][i2];
+    if (i2 < w) { sbase += cnt[0][i2]; ebase += cnt[1][i2]; xbase += cnt[2][i2]; }
+    stot += cnt[0][i2];
+    etot += cnt[1][i2];
+    xtot += cnt[2][i2];
   }
   int32_t* out = plist + ((size_t)h * nblk_cap + bi) * MAXPART;
-  if (ent) out[ebase + __popcll(em & lt)] = i;
-  if (exq) out[etot + xbase + __popcll(xm & lt)] = m;
-  if (tid == 0) pcnt[(size_t)h * nblk_cap + bi] = etot + xtot;
+  if (ent) out[stays ? sbase + __popcll(sm & lt) : stot + ebase + __popcll(em & lt)] = i;
+  if (exq) out[stot + etot + xbase + __popcll(xm & lt)] = m;
+  if (tid == 0) {
+    pcnt[(size_t)h * nblk_cap + bi] = stot + etot + xtot;
+    pent[(size_t)h * nblk_cap + bi] = stot;
+  }
 }
 
 // Without the causal restriction every row of a document keeps the same min(k, n) best keys.  One
@@ -797,6 +821,7 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
   int32_t* docblk = (int32_t*)(base + L.off_docblk);
   int32_t* slot_tab = (int32_t*)(base + L.off_slot);
   int32_t* pcnt = (int32_t*)(base + L.off_pcnt);
+  int32_t* pent = (int32_t*)(base + L.off_pent);
   int32_t* plist = (int32_t*)(base + L.off_plist);
   int32_t* parent = (int32_t*)(base + L.off_parent);
   int32_t* slotid = (int32_t*)(base + L.off_slotid);
@@ -854,7 +879,7 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
     prof_end(DMA_STAGE_EXPIRY, st);
     prof_begin(DMA_STAGE_PLAN, st);
     fill(slot_tab, (size_t)s.H_q * L.nblk_cap * L.kpad, -1);
-    fill(pcnt, (size_t)s.H_q * L.nblk_cap, 0);
+    fill(pcnt, (L.off_plist - L.off_pcnt) / 4, 0);  // pcnt and pent
     // (documents of several segments get their whole-document rank order from the merge kernel)
     if (s.T > L.seg) merge_expiry_kernel<true><<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
     noncausal_plan_kernel<<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(cu, s.n_docs, sa.si0, docblk, expiry, slot_tab,
@@ -876,7 +901,7 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
       slot_table_kernel<<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(cu, s.n_docs, expiry, slotid, docblk, slot_tab,
                                                                       s.T, L.nblk_cap, L.kpad);
     }
-    partial_list_kernel<<<dim3(L.nblk_cap, s.H_q), BQ, 0, st>>>(blk, expiry, parent, pcnt, plist, s.T, L.nblk_cap);
+    partial_list_kernel<<<dim3(L.nblk_cap, s.H_q), BQ, 0, st>>>(blk, expiry, parent, slotid, pcnt, pent, plist, s.T, L.nblk_cap);
   }
   if (topk_idx) topk_idx_kernel<<<dim3(s.T, s.H_q), 64, 0, st>>>(cu, s.n_docs, s.causal, expiry, topk_idx, s.T, s.k);
   prof_end(DMA_STAGE_PLAN, st);
