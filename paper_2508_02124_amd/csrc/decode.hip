@@ -5,6 +5,8 @@
 // few times for the selection, then min(k, n) rows of K and V are gathered.
 #include "common.h"
 
+#include <algorithm>
+
 namespace dma {
 
 __device__ __forceinline__ uint32_t desc_key_u32(float z) {
@@ -15,8 +17,8 @@ __device__ __forceinline__ uint32_t desc_key_u32(float z) {
   return ~u;
 }
 
-// ---- selection of the kept set, spread over nsl slices of every (sequence, q-head) so that it
-// uses the whole chip: four histogram launches (radix select of the kk-th best score, most
+// ---- selection of the kept set of one very long sequence, spread over nsl slices of every (sequence,
+// q-head) so that it uses the whole chip: four histogram launches (radix select of the kk-th best score, most
 // significant byte first, per-pass histograms accumulated in global memory), one counting launch
 // and one ordered-compaction launch.  Every workgroup re-derives the digits already fixed from the
 // finished histograms (256 counters per pass), so no launch has to hand state to the next one.
@@ -216,6 +218,249 @@ __global__ __launch_bounds__(256) void decode_write_kernel(DecSel p) {
   }
 }
 
+// ---- selection in one launch: one workgroup per (sequence, q-head).  A wave owns a contiguous run of the
+// keys and holds it in registers (R per lane; longer sequences are read again from L2 in every pass).  A
+// histogram of 2048 equal bins between the sequence's smallest and largest key finds the bin of the kk-th
+// best; that bin's keys (few, unless scores are tied) move to LDS, where they are ranked against each other
+// -- or, if they are many, counted digit by digit -- for the exact threshold; the kept keys are then
+// counted and written in index order.  What bounds it is instruction issue on one compute unit (five passes
+// over the registers) and, for short sequences, the chain of barriers between the passes.  The sliced launches
+// above pay a launch and a pass over z for every one of those links: whole call, us, sliced -> this, k = 2048,
+// 32 heads: one cache of 65536 keys 59 -> 45, 24 caches of 5461 keys on average 213 -> 154.  Past the registers
+// the passes read L2 at one compute unit's rate (131072 keys: 140 us of selection against 50 sliced).
+template <int R>
+__global__ __launch_bounds__(1024, 4) void decode_select_kernel(DecSel p) {
+  constexpr int NW = 16, REP = 4, BITS = 11, NDIG = 1 << BITS, CAND = 8192, RANK = 512, STEP = 4;
+  constexpr uint32_t NONE = 0xffffffffu;  // behind every key
+  const int bh = blockIdx.x, b = bh / p.H_q, h = bh % p.H_q;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+  const int a = p.cu[b], n = dec_len(p.cu, p.lens, b);
+  if (n <= 0) return;
+  const int kk = p.k < n ? p.k : n, kcap = p.k < p.T ? p.k : p.T;
+  int32_t* list = p.kept + (size_t)bh * kcap;
+  if (kk == n) {  // everything is kept
+    for (int j = tid; j < n; j += 1024) list[j] = a + j;
+    return;
+  }
+  __shared__ __align__(16) uint32_t hist[NDIG * REP];
+  __shared__ __align__(16) uint32_t cand[CAND];
+  __shared__ uint32_t wsum[NW][2];
+  __shared__ uint32_t st[4];  // digit, rank inside it, its count; [3] number of candidates
+  const float* zh = p.z + (size_t)h * p.T + a;
+  const int wlen = (n + NW * 64 - 1) / (NW * 64) * 64;  // keys per wave
+  const int jw = w * wlen, chunks = wlen / 64, own = min(wlen, n - jw);  // (own <= 0: a wave without keys)
+  const bool in_regs = chunks <= R;  // (workgroup-uniform)
+  auto sort_key = [](float z) { return min(desc_key_u32(z), NONE - 1); };  // (never NONE, whatever z holds)
+  uint32_t key[R];
+  // f(key, index) for every key of this wave, 64 consecutive ones at a time, ascending; lanes without a key
+  // get NONE (in the first pass: another key of the sequence)
+  auto each = [&](auto f) {
+    if (in_regs) {
+      int ch = chunks;
+      asm volatile("" : "+s"(ch));  // (comparisons kept from one pass to the next would spill)
+#pragma unroll
+      for (int u0 = 0; u0 < R; u0 += STEP)
+        if (u0 < ch) {
+#pragma unroll
+          for (int u = u0; u < u0 + STEP; u++) f(key[u], jw + u * 64 + l);
+        }
+    } else {
+      for (int c0 = 0; c0 < chunks; c0 += 8) {
+        float zv[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) zv[u] = zh[jw + min((c0 + u) * 64 + l, own - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+          const int jl = (c0 + u) * 64 + l;
+          f(jl < own ? sort_key(zv[u]) : NONE, jw + jl);
+        }
+      }
+    }
+  };
+  uint4* hist4 = reinterpret_cast<uint4*>(hist);
+  uint32_t kmin = NONE, kmax = 0;
+  if (in_regs) {
+#pragma unroll
+    for (int u = 0; u < R; u++)
+      if (u / STEP * STEP < chunks) key[u] = __float_as_uint(zh[jw + min(u * 64 + l, own - 1)]);
+  }
+  hist4[2 * tid] = make_uint4(0, 0, 0, 0);
+  hist4[2 * tid + 1] = make_uint4(0, 0, 0, 0);
+  if (tid == 0) st[3] = 0;
+  if (in_regs) {
+#pragma unroll
+    for (int u = 0; u < R; u++)
+      if (u / STEP * STEP < chunks) {
+        key[u] = sort_key(__uint_as_float(key[u]));
+        kmin = min(kmin, key[u]);
+        kmax = max(kmax, key[u]);
+      }
+    if (own < (chunks + STEP - 1) / STEP * STEP * 64) {
+#pragma unroll
+      for (int u = 0; u < R; u++)
+        if (u * 64 + l >= own) key[u] = NONE;
+    }
+  } else {
+    each([&](uint32_t k32, int) {
+      kmin = min(kmin, k32);
+      kmax = max(kmax, k32 == NONE ? 0u : k32);
+    });
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, off));
+    kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off));
+  }
+  if (l == 0) {
+    wsum[w][0] = kmin;
+    wsum[w][1] = kmax;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NW; i++) {
+    kmin = min(kmin, wsum[i][0]);
+    kmax = max(kmax, wsum[i][1]);
+  }
+  kmin = (uint32_t)__builtin_amdgcn_readfirstlane((int)kmin);
+  const uint32_t range = (uint32_t)__builtin_amdgcn_readfirstlane((int)(kmax - kmin));
+  const int sh0 = max(0, 32 - (range ? __clz((int)range) : 32) - BITS);  // (key - kmin) >> sh0 < NDIG
+  // The digit at which the running count of the histogram reaches `remaining` (st[0..2]); leaves it cleared.
+  auto pick = [&](uint32_t remaining) {
+    __syncthreads();
+    const uint4 x = hist4[2 * tid], y = hist4[2 * tid + 1];  // this thread's two digits
+    hist4[2 * tid] = make_uint4(0, 0, 0, 0);
+    hist4[2 * tid + 1] = make_uint4(0, 0, 0, 0);
+    const uint32_t cx = x.x + x.y + x.z + x.w, cy = y.x + y.y + y.z + y.w;
+    uint32_t inc = cx + cy;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t t = __shfl_up(inc, off);
+      if (l >= off) inc += t;
+    }
+    if (l == 63) wsum[w][0] = inc;
+    __syncthreads();
+    uint32_t run = inc - cx - cy;
+#pragma unroll
+    for (int i = 0; i < NW; i++) run += i < w ? wsum[i][0] : 0u;
+    if (run < remaining && remaining <= run + cx + cy) {  // exactly one thread
+      const bool second = remaining > run + cx;
+      st[0] = 2u * tid + (second ? 1u : 0u);
+      st[1] = remaining - run - (second ? cx : 0u);
+      st[2] = second ? cy : cx;
+    }
+    __syncthreads();
+  };
+  // (lanes without a key count in the last bin, behind every key of it)
+  each([&](uint32_t k32, int) {
+    atomicAdd(&hist[min((k32 - kmin) >> sh0, (uint32_t)NDIG - 1) * REP + (l & (REP - 1))], 1u);
+  });
+  pick((uint32_t)kk);
+  const uint32_t base = kmin + (st[0] << sh0);  // first key of the bin
+  uint32_t need_eq = st[1], n_eq = st[2], sub = 0;
+  if (sh0 > 0) {
+    const bool listed = n_eq <= CAND;
+    uint32_t ncand = 0;
+    if (listed) {
+      each([&](uint32_t k32, int) {
+        const uint32_t x = k32 - base;
+        if ((x >> sh0) == 0 && k32 != NONE) cand[atomicAdd(&st[3], 1u)] = x;
+      });
+      __syncthreads();
+      ncand = st[3];
+    }
+    if (listed && ncand <= RANK) {  // every candidate counts those before it
+      if (tid < (int)ncand) {
+        const uint32_t x = cand[tid];
+        uint32_t less = 0, equal = 0;
+        for (uint32_t i = 0; i < ncand; i += 4) {
+          const uint4 c = *reinterpret_cast<const uint4*>(&cand[i]);
+          const uint32_t cs[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            less += i + e < ncand && cs[e] < x;
+            equal += i + e < ncand && cs[e] == x;
+          }
+        }
+        if (less < need_eq && need_eq <= less + equal) {  // (tied candidates write the same values)
+          st[0] = x;
+          st[1] = need_eq - less;
+          st[2] = equal;
+        }
+      }
+      __syncthreads();
+      sub = st[0];
+      need_eq = st[1];
+      n_eq = st[2];
+    } else {
+      for (int sh = sh0; sh > 0;) {  // (at most 21 bits are left: two rounds)
+        const int bits = min(BITS, sh), s2 = sh - bits;
+        auto count = [&](uint32_t x) {
+          if ((x >> sh) == sub) atomicAdd(&hist[((x >> s2) & ((1u << bits) - 1u)) * REP + (l & (REP - 1))], 1u);
+        };
+        if (listed) {
+          for (uint32_t i = tid; i < ncand; i += 1024) count(cand[i]);
+        } else {
+          uint32_t from = base;
+          asm volatile("" : "+v"(from));
+          each([&](uint32_t k32, int) {
+            if (k32 != NONE) count(k32 - from);  // (keys below the bin wrap round to the far end: never equal to `sub`)
+          });
+        }
+        pick(need_eq);
+        sub = (sub << bits) | st[0];
+        need_eq = st[1];
+        n_eq = st[2];
+        sh = s2;
+      }
+    }
+  }
+  const uint32_t thr = (uint32_t)__builtin_amdgcn_readfirstlane((int)(base + sub));
+  const bool ties = n_eq != need_eq;  // some keys equal to the threshold are left out: those with the highest indices
+  uint32_t rb = 0, re = 0;
+  if (!ties) {
+    each([&](uint32_t k32, int) { rb += (uint32_t)__popcll(__ballot(k32 <= thr)); });
+  } else {
+    each([&](uint32_t k32, int) {
+      rb += (uint32_t)__popcll(__ballot(k32 < thr));
+      re += (uint32_t)__popcll(__ballot(k32 == thr));
+    });
+  }
+  if (l == 0) {
+    wsum[w][0] = rb;
+    wsum[w][1] = re;
+  }
+  __syncthreads();
+  rb = re = 0;
+#pragma unroll
+  for (int i = 0; i < NW; i++) {  // better / equal keys of the waves before this one
+    rb += i < w ? wsum[i][0] : 0u;
+    re += i < w ? wsum[i][1] : 0u;
+  }
+  rb = (uint32_t)__builtin_amdgcn_readfirstlane((int)rb);
+  re = (uint32_t)__builtin_amdgcn_readfirstlane((int)re);
+  const unsigned long long lt = (1ull << l) - 1ull;
+  uint32_t thr_w = thr;
+  asm volatile("" : "+s"(thr_w));  // (as above: the masks of the counting pass are formed again)
+  if (!ties) {
+    each([&](uint32_t k32, int j) {
+      const bool keep = k32 <= thr_w;
+      const unsigned long long m = __ballot(keep);
+      if (keep) list[rb + (uint32_t)__popcll(m & lt)] = a + j;
+      rb += (uint32_t)__popcll(m);
+    });
+  } else {
+    each([&](uint32_t k32, int j) {
+      const bool better = k32 < thr_w, equal = k32 == thr_w;
+      const unsigned long long bm = __ballot(better), em = __ballot(equal);
+      const uint32_t eq_before = re + (uint32_t)__popcll(em & lt);  // equal keys with a lower index
+      const uint32_t pos = rb + (uint32_t)__popcll(bm & lt) + min(eq_before, need_eq);
+      if (better || (equal && eq_before < need_eq)) list[pos] = a + j;
+      rb += (uint32_t)__popcll(bm);
+      re += (uint32_t)__popcll(em);
+    });
+  }
+}
+
 __global__ void decode_zero_kernel(uint32_t* p, size_t n) {
   const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;
@@ -318,6 +563,8 @@ __global__ __launch_bounds__(256) void decode_update_kernel(const float* __restr
 
 // Keys per workgroup of the attention pass.
 constexpr int DEC_CHUNK = 256;
+// Longest sequence that one workgroup per head selects alone: 16 waves x 64 lanes x 64 registers.
+constexpr int DEC_SELECT_MAX = 1 << 16;
 
 // (3) single-row attention over one chunk of DEC_CHUNK kept keys: a key row is held by D / 8
 // lanes; every lane group keeps its own running (m, l, o) over the keys it visits, the groups are
@@ -518,12 +765,22 @@ int launch_decode(const dma_shape& s, float scale, const void* q, const void* K,
   if (incremental) {
     decode_update_kernel<<<nbh, 256, 0, st>>>(z, cu, lens, kept, s.T, s.H_q, s.k);
   } else {
-    const size_t nz = 4 * (size_t)nbh * 256;
-    decode_zero_kernel<<<(unsigned)((nz + 255) / 256), 256, 0, st>>>(ds.hist, nz);
-    const dim3 sgrid(nbh, ds.nsl);
-    for (int pass = 3; pass >= 0; pass--) decode_hist_kernel<<<sgrid, 256, 0, st>>>(ds, pass);
-    decode_count_kernel<<<sgrid, 256, 0, st>>>(ds);
-    decode_write_kernel<<<sgrid, 256, 0, st>>>(ds);
+    // One workgroup per (sequence, head) selects alone while its keys fit its registers; the host sees only the
+    // caches' total, so a batch is taken at twice its average length.
+    const long longest = s.max_seqlen > 0 && s.max_seqlen < s.T ? s.max_seqlen : s.T;
+    const long typical = std::min(longest, (2l * s.T + s.n_docs - 1) / s.n_docs);
+    if (typical > DEC_SELECT_MAX && ds.nsl > 1) {
+      const size_t nz = 4 * (size_t)nbh * 256;
+      decode_zero_kernel<<<(unsigned)((nz + 255) / 256), 256, 0, st>>>(ds.hist, nz);
+      const dim3 sgrid(nbh, ds.nsl);
+      for (int pass = 3; pass >= 0; pass--) decode_hist_kernel<<<sgrid, 256, 0, st>>>(ds, pass);
+      decode_count_kernel<<<sgrid, 256, 0, st>>>(ds);
+      decode_write_kernel<<<sgrid, 256, 0, st>>>(ds);
+    } else if (typical > 16 * 1024) {
+      decode_select_kernel<64><<<nbh, 1024, 0, st>>>(ds);
+    } else {
+      decode_select_kernel<16><<<nbh, 1024, 0, st>>>(ds);
+    }
   }
   if (s.dtype == DMA_BF16) {
     if (s.d == 256) launch_decode_t<__bf16, 256>(s, c2, q, K, V, z, cu, lens, o, lse, kept, part, nsplit, st);
