@@ -6,8 +6,13 @@
 #include "common.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace dma {
+
+struct float8 {
+  float4 a, b;
+};
 
 __device__ __forceinline__ uint32_t desc_key_u32(float z) {
   // ascending unsigned order == descending float order (-0 and +0 compare equal)
@@ -569,73 +574,95 @@ constexpr int DEC_SELECT_MAX = 1 << 16;
 // (3) single-row attention over one chunk of DEC_CHUNK kept keys: a key row is held by D / 8
 // lanes; every lane group keeps its own running (m, l, o) over the keys it visits, the groups are
 // merged through LDS, and the chunk's (o, m, l) goes to `part` for decode_merge_kernel.
+// HBM-bound: the chunk's key indices and scores are requested in one go and wait in LDS, then U rows of K and
+// of V are in flight per lane group.  The G heads of a kv-group have the same chunk of their lists, which covers
+// about the same rows, on one XCD at the same time, so rows that several of them keep come from its L2
+// (workgroups are dealt to the 8 XCDs in turn; 24 caches of 5461 keys, 32 / 8 heads, k = 2048:
+// step of 65536 cached tokens in 8 caches 58 -> 44 us, 24 caches of 5461 keys 154 -> 133 us a call).
 template <typename TV, int D>
 __global__ __launch_bounds__(256) void decode_attend_kernel(const TV* __restrict__ q, const TV* __restrict__ K,
                                                             const TV* __restrict__ V, const float* __restrict__ z,
                                                             const int32_t* __restrict__ cu,
                                                             const int32_t* __restrict__ lens,
                                                             const int32_t* __restrict__ kept, float* part, int T,
-                                                            int H_q, int H_kv, int k, int nsplit, float c2) {
-  const int bh = blockIdx.x, b = bh / H_q, h = bh % H_q, sp = blockIdx.y;
+                                                            int n_docs, int H_q, int H_kv, int k, int nsplit, float c2) {
+  const unsigned wg = blockIdx.y * gridDim.x + blockIdx.x;  // (a second grid dimension only past 2^22 workgroups)
+  const int G = H_q / H_kv, x = wg & 7, idx = (int)(wg >> 3);
+  const int unit = (idx / G) * 8 + x, sp = unit / (n_docs * H_kv), bg = unit - sp * (n_docs * H_kv);
+  if (sp >= nsplit) return;
+  const int b = bg / H_kv, g = bg - b * H_kv, h = g * G + idx % G, bh = b * H_q + h;
   const int n = dec_len(cu, lens, b);
   const int kcap = k < T ? k : T, kk = k < n ? k : n;
   const int32_t* list = kept + (size_t)bh * kcap;
-  const int i0 = sp * DEC_CHUNK, i1 = min(i0 + DEC_CHUNK, kk);
+  const int i0 = sp * DEC_CHUNK, cnt = min(DEC_CHUNK, kk - i0);
+  if (cnt <= 0) return;  // (decode_merge_kernel reads the chunks that hold keys)
   constexpr int LPR = D / 8, NG = 256 / LPR;
+  constexpr int U = sizeof(TV) == 2 ? 8 : 4;  // keys in flight per lane group
   const int tid = threadIdx.x, sub = tid % LPR, grp = tid / LPR;
-  const int g = h / (H_q / H_kv);
   float* out = part + ((size_t)bh * nsplit + sp) * (D + 2);
-  auto load8 = [&](const TV* p, float* o8) {
+  __shared__ int ids[DEC_CHUNK];
+  __shared__ float zs[DEC_CHUNK];  // exp2-domain bias of the key; -inf past the end of the list
+  {
+    const int id = list[i0 + min(tid, cnt - 1)];
+    ids[tid] = id;
+    zs[tid] = tid < cnt ? z[(size_t)h * T + id] * LOG2E : -INFINITY;
+  }
+  using Raw = typename std::conditional<sizeof(TV) == 2, uint4, float8>::type;
+  auto unpack = [&](const Raw& r, float* o8) {
     if constexpr (sizeof(TV) == 2) {
-      const uint4 raw = *reinterpret_cast<const uint4*>(p);
-      const uint32_t u[4] = {raw.x, raw.y, raw.z, raw.w};
+      const uint32_t u[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
       for (int e = 0; e < 4; e++) {
         o8[2 * e] = __uint_as_float(u[e] << 16);
         o8[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
       }
     } else {
-      const float4 x0 = *reinterpret_cast<const float4*>(p);
-      const float4 x1 = *reinterpret_cast<const float4*>(p + 4);
-      o8[0] = x0.x; o8[1] = x0.y; o8[2] = x0.z; o8[3] = x0.w;
-      o8[4] = x1.x; o8[5] = x1.y; o8[6] = x1.z; o8[7] = x1.w;
+      o8[0] = r.a.x; o8[1] = r.a.y; o8[2] = r.a.z; o8[3] = r.a.w;
+      o8[4] = r.b.x; o8[5] = r.b.y; o8[6] = r.b.z; o8[7] = r.b.w;
     }
   };
   float qv[8];
-  load8(q + ((size_t)b * H_q + h) * D + 8 * sub, qv);
+  unpack(*reinterpret_cast<const Raw*>(q + ((size_t)b * H_q + h) * D + 8 * sub), qv);
   float m = -INFINITY, lsum = 0.f, acc[8];
 #pragma unroll
   for (int e = 0; e < 8; e++) acc[e] = 0.f;
-  constexpr int U = 4;  // keys in flight per lane group
-  for (int i = i0 + grp; i < i1; i += NG * U) {
-    float kv[U][8], vv[U][8], zz[U];
-    bool ok[U];
+  __syncthreads();
+  for (int i = grp; i < cnt; i += NG * U) {
+    Raw kr[U], vr[U];
+    float s2[U];
 #pragma unroll
     for (int u = 0; u < U; u++) {
-      const int ii = i + u * NG;
-      ok[u] = ii < i1;
-      const int id = ok[u] ? list[ii] : list[i];
-      const size_t off = ((size_t)id * H_kv + g) * D + 8 * sub;
-      load8(K + off, kv[u]);
-      load8(V + off, vv[u]);
-      zz[u] = z[(size_t)h * T + id];
+      const int ii = min(i + u * NG, DEC_CHUNK - 1);  // (past the end of the list: its last key, with bias -inf)
+      const size_t off = ((size_t)ids[ii] * H_kv + g) * D + 8 * sub;
+      kr[u] = *reinterpret_cast<const Raw*>(K + off);
+      vr[u] = *reinterpret_cast<const Raw*>(V + off);
     }
+    float m_new = m;
 #pragma unroll
     for (int u = 0; u < U; u++) {
-      float s = 0.f;
+      float kv[8], s = 0.f;
+      unpack(kr[u], kv);
 #pragma unroll
-      for (int e = 0; e < 8; e++) s = fmaf(qv[e], kv[u][e], s);
+      for (int e = 0; e < 8; e++) s = fmaf(qv[e], kv[e], s);
 #pragma unroll
       for (int sft = LPR / 2; sft > 0; sft >>= 1) s += __shfl_xor(s, sft);
-      if (ok[u]) {
-        const float s2 = fmaf(s, c2, zz[u] * LOG2E);  // exp2 domain
-        const float m_new = fmaxf(m, s2);
-        const float alpha = fast_exp2(m - m_new), pv = fast_exp2(s2 - m_new);
-        m = m_new;
-        lsum = lsum * alpha + pv;
+      s2[u] = i + u * NG < cnt ? fmaf(s, c2, zs[i + u * NG]) : -INFINITY;  // exp2 domain
+      m_new = fmaxf(m_new, s2[u]);
+    }
+    const float ref = m_new == -INFINITY ? 0.f : m_new;  // (every score of this group so far is -inf)
+    const float alpha = fast_exp2(m - ref);
+    m = m_new;
+    lsum *= alpha;
 #pragma unroll
-        for (int e = 0; e < 8; e++) acc[e] = fmaf(acc[e], alpha, pv * vv[u][e]);
-      }
+    for (int e = 0; e < 8; e++) acc[e] *= alpha;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      float vv[8];
+      unpack(vr[u], vv);
+      const float pv = fast_exp2(s2[u] - ref);
+      lsum += pv;
+#pragma unroll
+      for (int e = 0; e < 8; e++) acc[e] = fmaf(pv, vv[e], acc[e]);
     }
   }
   __shared__ float mo[NG][D + 2];
@@ -663,7 +690,8 @@ __global__ __launch_bounds__(256) void decode_attend_kernel(const TV* __restrict
   }
 }
 
-// (4) merge the chunks of one (sequence, head): o = sum_c o_c 2^(M_c - M) / sum_c l_c 2^(M_c - M).
+// (4) merge the chunks of one (sequence, head): o = sum_c o_c 2^(M_c - M) / sum_c l_c 2^(M_c - M).  Eight chunks
+// are requested at a time: the kernel is the latency of its dependent loads.
 template <typename TV, int D>
 __global__ __launch_bounds__(D) void decode_merge_kernel(const float* __restrict__ part, const int32_t* __restrict__ cu,
                                                          const int32_t* __restrict__ lens, TV* o, float* lse, int H_q,
@@ -678,13 +706,29 @@ __global__ __launch_bounds__(D) void decode_merge_kernel(const float* __restrict
   }
   const int kk = k < n ? k : n, ns = (kk + DEC_CHUNK - 1) / DEC_CHUNK;
   const float* p = part + (size_t)bh * nsplit * (D + 2);
-  float M = -INFINITY;
-  for (int s = 0; s < ns; s++) M = fmaxf(M, p[s * (D + 2) + D]);
-  float num = 0.f, den = 0.f;
-  for (int s = 0; s < ns; s++) {
-    const float w8 = fast_exp2(p[s * (D + 2) + D] - M);
-    num = fmaf(p[s * (D + 2) + c], w8, num);
-    den = fmaf(p[s * (D + 2) + D + 1], w8, den);
+  float M = -INFINITY, num = 0.f, den = 0.f;
+  for (int s0 = 0; s0 < ns; s0 += 8) {
+    float Ms[8], ls[8], os[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+      const float* ps = p + (size_t)min(s0 + u, ns - 1) * (D + 2);
+      Ms[u] = ps[D];
+      ls[u] = ps[D + 1];
+      os[u] = ps[c];
+    }
+    float Mn = M;
+#pragma unroll
+    for (int u = 0; u < 8; u++) Mn = fmaxf(Mn, Ms[u]);
+    const float ref = Mn == -INFINITY ? 0.f : Mn, alpha = fast_exp2(M - ref);
+    M = Mn;
+    num *= alpha;
+    den *= alpha;
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+      const float w8 = s0 + u < ns ? fast_exp2(Ms[u] - ref) : 0.f;
+      num = fmaf(os[u], w8, num);
+      den = fmaf(ls[u], w8, den);
+    }
   }
   orow[c] = TV(num / den);
   if (c == 0) lse[(size_t)h * n_docs + b] = (M + __builtin_amdgcn_logf(den)) * LN2;
@@ -718,8 +762,9 @@ static void launch_decode_t(const dma_shape& s, float c2, const void* q, const v
                             const int32_t* cu, const int32_t* lens, void* o, float* lse, int32_t* kept, float* part,
                             int nsplit, hipStream_t st) {
   const int nbh = s.n_docs * s.H_q;
-  decode_attend_kernel<TV, D><<<dim3(nbh, nsplit), 256, 0, st>>>((const TV*)q, (const TV*)K, (const TV*)V, z, cu, lens,
-                                                                  kept, part, s.T, s.H_q, s.H_kv, s.k, nsplit, c2);
+  const long wgs = ((long)s.n_docs * s.H_kv * nsplit + 7) / 8 * 8 * (s.H_q / s.H_kv), gx = wgs < (1l << 22) ? wgs : 1l << 22;
+  decode_attend_kernel<TV, D><<<dim3((unsigned)gx, (unsigned)((wgs + gx - 1) / gx)), 256, 0, st>>>(
+      (const TV*)q, (const TV*)K, (const TV*)V, z, cu, lens, kept, part, s.T, s.n_docs, s.H_q, s.H_kv, s.k, nsplit, c2);
   decode_merge_kernel<TV, D><<<nbh, D, 0, st>>>(part, cu, lens, (TV*)o, lse, s.H_q, s.k, nsplit);
 }
 
