@@ -317,38 +317,42 @@ __global__ __launch_bounds__(NW * 64, (NW == 8 || D == 256) ? 1 : (D == 64 ? 3 :
 }
 
 // ------------------------------------------------------------------ dK, dV, dz
-constexpr int MAXSWEEP = 320;  // most query blocks one key-stationary work item sweeps
+constexpr int DKV_NW = SG / 32;  // waves of a key-stationary workgroup
+constexpr int MAXSWEEP = 64;     // most query blocks one key-stationary work item sweeps
 
-// Eight waves.  Wave w serves columns 32 * (w % 4) .. +31 of the workgroup's SG columns in one of two
-// roles (w / 4); the two waves of a column block share a SIMD and overlap each other's MFMA and
-// element-wise work, and each wave's state fits the register budget of two waves per SIMD:
-//   role 0 ("P"):  S = Q K^T + z / scale, P = exp2(S c2 - LSE2) (masked in partial mode), dV^T += dO^T P;
-//                  holds K fragments and dV^T; hands P (fp32) to its partner through LDS.
-//   role 1 ("dS"): dP = dO V^T in the same period as role 0's S, then, one period later (so that
-//                  its element-wise work overlaps role 0's MFMAs and vice versa),
-//                  dS = P o (dP - D), dz += colsum(dS), dK^T += Q^T dS; holds V fragments and dK^T.
-// Lane (n, hh) owns column 32 * (w % 4) + n; its accumulator holds channels 32cb + 8gq + 4hh + u.
+// Four waves; wave w serves columns 32 w .. + 31 of the workgroup's SG columns and carries a column through
+// the whole step:
+//   S = Q K^T + z / scale, dP = dO V^T - D, P = exp2(S c2 - LSE2) (masked in partial mode), dV^T += dO^T P,
+//   dS = P o dP, dz += colsum(dS), dK^T += Q^T dS.
+// Lane (n, hh) owns column 32 w + n; its accumulators hold channels 32cb + 8gq + 4hh + u.
+// What bounds it: the chain of one step (two products, exponentials, two products) at two waves per SIMD, and
+// the work at a block's first step (rows of new keys, flush of finished ones); the matrix pipe is busy 40 % of
+// the time.  An earlier form split the chain over two waves that handed P through LDS and met at one barrier for
+// 128 columns and 8 waves; here two workgroups of 4 waves share a compute unit and drift apart in phase, so one
+// computes while the other waits (slot sweep / partial launch, us, before -> after: 65536 packed tokens, 16 heads,
+// d = 64, window 512: 680 / 248 -> 510 / 180; 16384 tokens, 32 heads, d = 128, window 2048: 1563 / 179 -> 1380 / 196;
+// 16 heads, d = 256: 1885 / 460 -> 1945 / 276).  A register reload inside a step costs more than it looks: it waits
+// for the copies requested just before it.  So nothing may spill there: part of the K fragments waits in LDS, and
+// small lane-dependent values are formed where they are used (fresh_lane).
 template <int D, bool PARTIAL>
-__global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
+__global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : 2) void dkv_kernel(BwdArgs p) {
   using TL = TileLayout<D>;
   constexpr int KS = D / 16, CB = D / 32, CPR = D / 8, RPL = 64 / CPR;
   constexpr int SUB = 32;                 // query rows per pipeline step
   constexpr int NSUB = BQ / SUB;          // steps per query block
   constexpr int NWL = 2 * (SUB / RPL);    // 16-byte wave copies per step (Q rows, then dO rows)
-  constexpr int NS = D == 256 ? 3 : 5;    // ring stages (a stage of 512-byte rows is 32 KiB)
+  constexpr int NS = D == 64 ? 4 : 3;     // ring stages
   constexpr int STILE = SUB * D;
-  constexpr int LDS_ST = 32 + 4;          // staging row: the 32 channels of one flush pass, padded
-  constexpr bool ENTER = D != 256;        // a key's first block belongs to its column (at 256 channels the mask costs more
-                                          // spilled registers than the listing: 1.78 -> 1.92 ms against 0.45 -> 0.39)
-  constexpr int NCH = D == 256 ? 2 : 1;   // column halves of a flush pass (LDS is short at 256 channels)
-  constexpr int STC = 32 / NCH;           // columns staged at a time
+  constexpr int KL = D == 64 ? 0 : D == 128 ? 6 : 8;  // contraction steps whose K fragments wait in LDS
+  constexpr int STR = D == 128 ? 8 : 16, STC = D == 64 ? 64 : 32;  // flush staging: columns, channels
+  constexpr int LDS_ST = STC + 4;         // padded staging row
   __shared__ __align__(16) uint16_t ringQ[NS * STILE];
   __shared__ __align__(16) uint16_t ringdO[NS * STILE];
   __shared__ __align__(16) float meta[NS][64];   // per stage: [0,32) LSE * log2 e, [32,64) -D
   __shared__ __align__(16) int idbuf[2][SG];     // column ids of the current / next block
   __shared__ __align__(16) int4 binfo[MAXSWEEP + 1];  // block table of this work item's sweep
-  __shared__ __align__(16) float stage_all[8 * STC * LDS_ST];  // per wave: [STC columns][32 channels] fp32, flush staging
-  __shared__ __align__(16) f32x4 pbuf[2][4][4][64];  // P hand-off (fp32): [step parity][column block][row group][lane]
+  __shared__ __align__(16) float stage_all[DKV_NW * STR * LDS_ST];  // per wave: [STR columns][STC channels] fp32, flush staging
+  __shared__ __align__(16) bf16x8 klds[KL ? DKV_NW * KL * 64 : 1];  // [wave][ks][lane]: K fragments of the first KL steps
 
   const int ngrp = PARTIAL ? MAXPART / SG : p.kpad / SG;
   const int nchunk = (p.nblk_cap + (PARTIAL ? p.seg_part : p.seg) - 1) / (PARTIAL ? p.seg_part : p.seg);
@@ -360,7 +364,12 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
   const int chunk = PARTIAL ? item % nchunk : item / ngrp, grp = PARTIAL ? item / nchunk : item - chunk * ngrp;
   const int g = h / (p.H_q / p.H_kv);
   const int tid = thread_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, n = l & 31, hh = l >> 5;
-  const int kb4 = w & 3, role = w >> 2;
+  // The lane number for values that are formed where they are used: kept over the loop they would spill.
+  auto fresh_lane = [&] {
+    int ln = l;
+    asm volatile("" : "+v"(ln));
+    return ln;
+  };
   const float* zqh = p.zq + (size_t)h * p.T;
   const float* Dh = p.Dws + (size_t)h * p.T;
   const float* L2h = p.L2ws + (size_t)h * p.T;
@@ -377,7 +386,7 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
   // the group has at least one column (clean mode: slots in use at the block's end, x = the document's
   // first row; partial mode: listed keys, x = first list entry).
   __shared__ int nblocks_s;
-  for (int i = tid; i < MAXSWEEP + 1; i += 512) binfo[i] = make_int4(-1, 0, 0, 0);
+  for (int i = tid; i < MAXSWEEP + 1; i += DKV_NW * 64) binfo[i] = make_int4(-1, 0, 0, 0);
   __syncthreads();
   if (w == 0) {
     int cnt = 0;
@@ -390,11 +399,11 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
         if (info.x >= 0) {
           int total;
           if (PARTIAL) {
-            const int first = ENTER ? p.pent[(size_t)h * p.nblk_cap + bi] : 0;  // the slot sweep has the keys before it
+            const int first = p.pent[(size_t)h * p.nblk_cap + bi];  // the slot sweep has the keys before it
             total = p.pcnt[(size_t)h * p.nblk_cap + bi] - first;
             info.w = first;
           } else {
-            total = min(p.k, (ENTER && p.causal ? info.z : info.y) - info.w);
+            total = min(p.k, (p.causal ? info.z : info.y) - info.w);
           }
           nc = max(0, min(SG, total - grp * SG));
         }
@@ -429,24 +438,22 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
   };
 
   // ---- producer: copies of step v (32 query rows of Q and dO, their LSE/D, and at a block's first
-  // step the block's column ids).  Only the four role-0 waves issue copies: the role-1 waves carry
-  // the longer chain of a step (they run the dS / dK^T part of the previous step before their dP),
-  // while the role-0 waves have idle time at every barrier.  Every issuing wave issues the same
-  // number of copies for every step.  Rows past the end of the block (or every row of a block without
+  // step the block's column ids).  Every wave issues the same number of copies for every step.  Rows past the end of the block (or every row of a block without
   // columns) re-read a valid row: their LSE is +inf and their D is 0, so whatever Q / dO they hold
   // contributes exactly 0.
-  constexpr int WLW0 = NWL / 4;   // copies per issuing wave and step: first half Q rows, second half dO rows
+  constexpr int WLW0 = NWL / DKV_NW;   // copies per issuing wave and step: first half Q rows, second half dO rows
   constexpr int NLO = WLW0 / 2;   // distinct row positions among them
   static_assert(WLW0 == 2 * NLO && NLO >= 1, "copy layout of the key-stationary kernel");
   const uint32_t row_stride = (uint32_t)p.H_q * D * 2;  // bytes between consecutive rows of Q / dO
-  int lane_r[NLO];          // tile row this lane copies (copy j takes rows (kb4 + 4 (j mod NLO)) * RPL ...)
-  uint32_t lane_c[NLO];     // byte offset of its 16-byte chunk within the row
-  uint32_t lane_off[NLO];   // ... from the step's first row, for a full step
+  // Copy u of a wave takes rows (w + 4 u) * RPL + l / CPR.  Where 4 RPL is a multiple of the swizzle's period of
+  // 16 rows, its lane offset is that of copy 0 and the rows between them go into the scalar base.
+  constexpr int NOFF = NLO == 1 || DKV_NW * RPL % 16 == 0 ? 1 : NLO;
+  auto lane_row = [&](int ln, int u) { return (w + DKV_NW * u) * RPL + ln / CPR; };
+  auto lane_chunk = [&](int ln, int u) { return (uint32_t)(((ln % CPR) ^ TL::swz(lane_row(ln, u))) * 16); };
+  uint32_t lane_off[NOFF];  // byte offset from the step's first row, for a full step
 #pragma unroll
-  for (int u = 0; u < NLO; u++) {
-    lane_r[u] = (kb4 + 4 * u) * RPL + l / CPR;
-    lane_c[u] = (uint32_t)(((l % CPR) ^ TL::swz(lane_r[u])) * 16);
-    lane_off[u] = (uint32_t)lane_r[u] * row_stride + lane_c[u];
+  for (int u = 0; u < NOFF; u++) {
+    lane_off[u] = (uint32_t)lane_row(l, u) * row_stride + lane_chunk(l, u);
     settle(lane_off[u]);
   }
   const char* Qh = (const char*)uniform_ptr(reinterpret_cast<const char*>(p.Q) + (size_t)h * D * 2);   // row 0 of this head
@@ -454,7 +461,6 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
   Cursor pc = {-1, 0, 0, 0, 0};
   int issue_st = 0;   // ring stage of the next step to issue (steps are issued in order: v mod NS without a division)
   auto issue = [&](int v) {
-    if (role != 0) return;
     const int qs = v % NSUB;
     if (qs == 0) pc = load_cursor(v / NSUB);
     const int st = issue_st;
@@ -468,33 +474,40 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
 #pragma unroll
       for (int j = 0; j < WLW0; j++) {
         const int u = j % NLO;
-        dma16s((j >= NLO ? dOh : Qh) + boff, lane_off[u], (j >= NLO ? dstdO : dstQ) + (kb4 + 4 * u) * RPL * D);
+        const uint32_t skip = u < NOFF ? 0u : (uint32_t)(DKV_NW * u * RPL) * row_stride;
+        dma16s((j >= NLO ? dOh : Qh) + (boff + skip), lane_off[u < NOFF ? u : 0],
+               (j >= NLO ? dstdO : dstQ) + (w + DKV_NW * u) * RPL * D);
       }
-      if (w == 0) dma4(hh == 0 ? L2h + rowb + n : Dh + rowb + n, &meta[st][0]);
+      if (w == 0) {
+        const int ln = fresh_lane(), n = ln & 31;
+        dma4(ln < 32 ? L2h + rowb + n : Dh + rowb + n, &meta[st][0]);
+      }
     } else {  // the ragged last step of a block, or a block without columns: rows past the end repeat a valid one
       const int nvalid = max(left, 0);
+      const int ln = fresh_lane();
       const uint32_t boff = (uint32_t)(nvalid > 0 ? rowb : 0) * row_stride;
 #pragma unroll
       for (int j = 0; j < WLW0; j++) {
         const int u = j % NLO;
-        const uint32_t off = (uint32_t)min(lane_r[u], max(nvalid - 1, 0)) * row_stride + lane_c[u];
-        dma16s((j >= NLO ? dOh : Qh) + boff, off, (j >= NLO ? dstdO : dstQ) + (kb4 + 4 * u) * RPL * D);
+        const uint32_t off = (uint32_t)min(lane_row(ln, u), max(nvalid - 1, 0)) * row_stride + lane_chunk(ln, u);
+        dma16s((j >= NLO ? dOh : Qh) + boff, off, (j >= NLO ? dstdO : dstQ) + (w + DKV_NW * u) * RPL * D);
       }
       if (w == 0) {
+        const int n = ln & 31;
         const bool ok = n < nvalid;
-        const float* src = hh == 0 ? (ok ? L2h + rowb + n : c_pinf) : (ok ? Dh + rowb + n : c_zero_f);
+        const float* src = ln < 32 ? (ok ? L2h + rowb + n : c_pinf) : (ok ? Dh + rowb + n : c_zero_f);
         dma4(src, &meta[st][0]);
       }
     }
-    if (qs == 0 && (w == 1 || w == 2)) {
+    if (qs == 0 && w < SG / 64) {
       const int bi = pc.bi;
-      const int cl = (w - 1) * 64 + l;
+      const int cl = w * 64 + fresh_lane();
       const int32_t* src = c_m1;
       if (cl < pc.ncols) {
         src = PARTIAL ? p.plist + ((size_t)h * p.nblk_cap + bi) * MAXPART + pc.x + grp * SG + cl
                       : p.slot_tab + ((size_t)h * p.nblk_cap + bi) * p.kpad + grp * SG + cl;
       }
-      dma4(src, &idbuf[(v / NSUB) & 1][(w - 1) * 64]);
+      dma4(src, &idbuf[(v / NSUB) & 1][w * 64]);
     }
   };
 
@@ -504,139 +517,119 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
   int curid = -1, kj = KJ_NONE, ke = 0;
   bool entering = false;
   float zq = -INFINITY;  // z / scale of this lane's key: the start value of its S accumulator
-  bf16x8 breg[KS];  // B-operand fragments of this lane's key: K rows (role 0) or V rows (role 1)
+  bf16x8 kreg[KS > KL ? KS - KL : 1], vreg[KS];  // B-operand fragments of this lane's key: its K row and its V row
+  const bf16x8 zero8 = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
+  bf16x8* kl = klds + w * KL * 64 + l;
 #pragma unroll
-  for (int ks = 0; ks < KS; ks++) breg[ks] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
-  f32x16 acc[CB];   // dV^T (role 0) or dK^T (role 1) of this lane's column
+  for (int ks = 0; ks < KS; ks++) {
+    vreg[ks] = zero8;
+    if (ks < KL) kl[64 * ks] = zero8;
+    else kreg[ks < KL ? 0 : ks - KL] = zero8;
+  }
+  f32x16 dvacc[CB], dkacc[CB];  // dV^T and dK^T of this lane's column
 #pragma unroll
   for (int cb = 0; cb < CB; cb++)
 #pragma unroll
-    for (int v = 0; v < 16; v++) acc[cb][v] = 0.f;
+    for (int v = 0; v < 16; v++) dvacc[cb][v] = dkacc[cb][v] = 0.f;
   float dzacc = 0.f;
 
-  float* stage = stage_all + w * STC * LDS_ST;
-  // Flush the columns whose lanes pass doit = true (wave-uniform call).  The accumulator is
-  // transposed through the wave's LDS staging area, 32 channels at a time, so that
-  // each atomic instruction adds consecutive channels of one key.
-  auto flush = [&](bool doit) {
-    const float dzt = dzacc + __shfl_xor(dzacc, 32);
-    doit = doit && curid >= 0;
-    const unsigned fm = (unsigned)(__ballot(doit) & 0xffffffffull);
-    if (fm == 0) return;
-    if (role == 1 && doit && hh == 0) atomicAdd(p.dz + (size_t)h * p.T + curid, dzt);
-    const float mul = role == 1 ? scale : 1.f;
-    float* dst = role == 1 ? p.dK32 : p.dV32;
-    const bool dense = __popc(fm) > 6;  // many columns (a partial-mode block change, the end of a sweep)
-    int* stage_id = reinterpret_cast<int*>(stage);
-    if (NCH == 1 && dense && hh == 0) stage_id[n * LDS_ST + 32] = doit ? curid : -1;
+  float* stage = stage_all + w * STR * LDS_ST;
+  // Flush the columns whose lanes pass doit = true (wave-uniform call).  The accumulators of up to STR columns at
+  // a time are transposed through the wave's LDS staging area, STC channels at a time, so that each atomic
+  // instruction adds consecutive channels of one or two keys.
+  // Lanes of a wave hand values to each other through LDS (in order, no barrier needed): the compiler must not
+  // carry a lane's view of the staging area across.
+  auto lanes_exchange = [] { asm volatile("" ::: "memory"); };
+  auto flush_one = [&](const f32x16 (&acc)[CB], float* dst, float mul, bool mine, int row, int cnt, int idrow,
+                       int ln) __attribute__((always_inline)) {
+    const int n = ln & 31, hh = ln >> 5;
 #pragma unroll
-    for (int cb = 0; cb < CB; cb++) {
+    for (int c0 = 0; c0 < CB; c0 += STC / 32) {
+      if (mine) {
 #pragma unroll
-      for (int ch = 0; ch < NCH; ch++) {  // columns STC * ch .. + STC - 1 of the wave's 32
-        const bool mine = NCH == 1 || (n >> 4) == ch;
-        const int sr = n & (STC - 1);     // staging row of this lane's column
-        if (NCH > 1 && dense && hh == 0 && mine) stage_id[sr * LDS_ST + 32] = doit ? curid : -1;
-        if (doit && mine) {
+        for (int cb = c0; cb < c0 + STC / 32; cb++)
 #pragma unroll
           for (int gq = 0; gq < 4; gq++) {
             f32x4 v4;
 #pragma unroll
-            for (int u = 0; u < 4; u++) v4[u] = acc[cb][4 * gq + u] * mul;
-            *reinterpret_cast<f32x4*>(&stage[sr * LDS_ST + 8 * gq + 4 * hh]) = v4;
+            for (int u = 0; u < 4; u++) v4[u] = acc[cb][4 * gq + u];
+            *reinterpret_cast<f32x4*>(&stage[row * LDS_ST + 32 * (cb - c0) + 8 * gq + 4 * hh]) = v4;
           }
-        }
-        if (dense) {
-          // every pass handles the column pair (2i, 2i+1): the ids sit in the padding of the staging
-          // rows, so the passes are independent of each other and pipeline
+      }
+      lanes_exchange();
+      constexpr int RPI = 64 / STC, U = 4;  // keys per atomic instruction, instructions in flight
+      for (int i0 = 0; i0 < cnt; i0 += RPI * U) {
+        float x[U];
 #pragma unroll
-          for (int i = 0; i < STC / 2; i++) {
-            const int c = 2 * i + hh;
-            const int id = stage_id[c * LDS_ST + 32];
-            if (id >= 0) atomicAdd(dst + ((size_t)id * p.H_kv + g) * D + 32 * cb + n, stage[c * LDS_ST + n]);
-          }
-        } else {
-          unsigned m = NCH == 1 ? fm : fm & (0xffffu << (16 * ch));
-          while (m) {  // two flushed columns per pass: lanes 0-31 and 32-63 take one column each
-            const int c0 = __ffs(m) - 1;
-            m &= m - 1;
-            int c1 = c0;
-            if (m) {
-              c1 = __ffs(m) - 1;
-              m &= m - 1;
+        for (int u = 0; u < U; u++) x[u] = stage[(i0 + RPI * u + (RPI == 2 ? hh : 0)) * LDS_ST + (ln & (STC - 1))] * mul;
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          const int i = i0 + RPI * u;
+          if (i < cnt) {
+            const int id0 = __builtin_amdgcn_readlane(idrow, i);
+            if (RPI == 1) {
+              atomicAdd(dst + ((size_t)id0 * p.H_kv + g) * D + 32 * c0 + ln, x[u]);
+            } else {
+              const int id = hh == 0 ? id0 : __builtin_amdgcn_readlane(idrow, i + 1);
+              if (hh == 0 || i + 1 < cnt) atomicAdd(dst + ((size_t)id * p.H_kv + g) * D + 32 * c0 + n, x[u]);
             }
-            const int c = hh == 0 ? c0 : c1;
-            const int id = __shfl(curid, c);
-            if (hh == 0 || c1 != c0)
-              atomicAdd(dst + ((size_t)id * p.H_kv + g) * D + 32 * cb + n, stage[(c & (STC - 1)) * LDS_ST + n]);
           }
         }
       }
+      lanes_exchange();
+    }
+  };
+  auto flush = [&](bool doit) __attribute__((always_inline)) {
+    const int ln = fresh_lane();
+    const int n = ln & 31, hh = ln >> 5;
+    const float dzt = dzacc + __shfl_xor(dzacc, 32);
+    doit = doit && curid >= 0;
+    const unsigned fm = (unsigned)__builtin_amdgcn_readfirstlane((int)(__ballot(doit) & 0xffffffffull));
+    if (fm == 0) return;
+    if (doit && hh == 0) atomicAdd(p.dz + (size_t)h * p.T + curid, dzt);
+    int* stage_id = reinterpret_cast<int*>(stage);
+    const int nf = __popc(fm), rank = __popc(fm & ((1u << n) - 1u));
+    for (int r0 = 0; r0 < nf; r0 += STR) {
+      const int row = rank - r0, cnt = min(STR, nf - r0);
+      const bool mine = doit && row >= 0 && row < STR;
+      if (mine && hh == 0) stage_id[row * LDS_ST + STC] = curid;  // (in the padding)
+      lanes_exchange();
+      const int idrow = stage_id[(ln & (STR - 1)) * LDS_ST + STC];  // lane r: the key of staging row r
+      flush_one(dvacc, p.dV32, 1.f, mine, row, cnt, idrow, ln);
+      flush_one(dkacc, p.dK32, scale, mine, row, cnt, idrow, ln);
     }
   };
 
   FragOffsets<D> fo;
   fo.init(l);
   Cursor cc = {-1, 0, 0, 0, 0};
-  f32x16 sacc;        // role 0: S of the current step; role 1: dP of the step it has in flight
-  bool pend = false;  // role 1: step pstep has its dP computed; dS, dz and dK^T are still due
-  int pstep = 0;
-#pragma unroll
-  for (int vv = 0; vv < 16; vv++) sacc[vv] = 0.f;
-  for (int v = 0; v < NS - 2; v++) issue(v);
+  for (int v = 0; v < NS - 1; v++) issue(v);
 
-  for (int it = 0; it <= nsteps; it++) {
-    // copies of step `it` must have landed: at most NS-3 later steps' worth may still be in flight
+  for (int v = 0; v < nsteps; v++) {
+    // copies of step v must have landed: at most NS-2 later steps' worth may still be in flight
     // (the occasional id copies and the flush traffic only make this wait more conservative)
-    if (w == 0) wait_vmcnt<(NS - 3) * (WLW0 + 1)>();
-    else wait_vmcnt<(NS - 3) * WLW0>();
-    lds_barrier();
+    if (w == 0) wait_vmcnt<(NS - 2) * (WLW0 + 1)>();
+    else wait_vmcnt<(NS - 2) * WLW0>();
+    lds_barrier();  // (and every wave is done with step v - 1, whose stage the next copies take)
     fo.pin();
-    issue(it + NS - 2);
+    issue(v + NS - 1);
 
-    // role 1 first finishes the step whose dP it computed at the end of the previous period
-    // (dS, dz, dK^T): its element-wise work then runs while role 0 is in its S = Q K^T MFMAs, and
-    // its dK^T MFMAs while role 0 computes P.
-    if (role == 1 && pend) {
-      const int st = pstep % NS;
-      const f32x4* ph = &pbuf[pstep & 1][kb4][0][l];  // row group gq at ph[64 * gq]
-      bf16x8 bb[2];
-#pragma unroll
-      for (int gq = 0; gq < 4; gq++) {
-        const f32x4 pq = ph[64 * gq];
-#pragma unroll
-        for (int u = 0; u < 4; u++) {
-          const int vv = 4 * gq + u;
-          const float ds = pq[u] * sacc[vv];  // sacc = dP - D (the accumulator started at -D_i)
-          dzacc += ds;
-          bb[vv >> 3][vv & 7] = (__bf16)ds;
-        }
-      }
-      const uint16_t* Qs = ringQ + st * STILE;
-#pragma unroll
-      for (int c = 0; c < 2; c++)
-#pragma unroll
-        for (int cb = 0; cb < CB; cb++) acc[cb] = mfma32(fo.tr_frag(Qs, 16 * c, cb), bb[c], acc[cb]);
-    }
-    pend = false;
-
-    const int v = it;
-    if (v >= nsteps) continue;
     const int qs = v % NSUB;
     if (qs == 0) cc = load_cursor(v / NSUB);
     const int ncols = cc.ncols, row0 = cc.row0, row1 = cc.row1;
     if (qs == 0) {
-      const int cl = 32 * kb4 + n;
+      const int cl = 32 * w + n;
       int newid = (cl < ncols) ? idbuf[(v / NSUB) & 1][cl] : -1;
       if (!PARTIAL) {
-        if (newid < -1) newid = ENTER ? -2 - newid : -1;  // enters inside this block
+        if (newid < -1) newid = -2 - newid;  // enters inside this block
         // Columns that are new in this block (the first k rows of a document) are not in the table: column
         // c takes the document's key c, unless that key is gone again before the block ends.
         const int col = grp * SG + cl, old = row0 - cc.x;
-        if (ENTER && p.causal && grp * SG + 32 * kb4 + 31 >= old && cl < ncols && col >= old) {
+        if (p.causal && grp * SG + 32 * w + 31 >= old && cl < ncols && col >= old) {
           const int key = cc.x + col;
           if (p.expiry[(size_t)h * p.T + key] >= row1) newid = key;
         }
-        entering = ENTER && p.causal && __any(newid > row0);
+        entering = p.causal && __any(newid > row0);
         if (newid != curid) kj = newid >= 0 ? newid : KJ_NONE;
       }
       const bool changed = newid != curid;
@@ -645,10 +638,14 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
         // (the flush reads the accumulators and the old ids only).
         if (changed) {
           if (newid >= 0) {
-            const uint16_t* src = (role == 0 ? p.K : p.V) + ((size_t)newid * p.H_kv + g) * D + 8 * hh;
+            const size_t off = ((size_t)newid * p.H_kv + g) * D + 8 * hh;
 #pragma unroll
-            for (int ks = 0; ks < KS; ks++)
-              breg[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(src + 16 * ks));
+            for (int ks = 0; ks < KS; ks++) {
+              const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p.K + off + 16 * ks));
+              if (ks < KL) kl[64 * ks] = kf;
+              else kreg[ks < KL ? 0 : ks - KL] = kf;
+              vreg[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p.V + off + 16 * ks));
+            }
             zq = zqh[newid];
             if (PARTIAL) {
               kj = newid;
@@ -656,7 +653,11 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
             }
           } else {
 #pragma unroll
-            for (int ks = 0; ks < KS; ks++) breg[ks] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
+            for (int ks = 0; ks < KS; ks++) {
+              vreg[ks] = zero8;
+              if (ks < KL) kl[64 * ks] = zero8;
+              else kreg[ks < KL ? 0 : ks - KL] = zero8;
+            }
             zq = -INFINITY;
             if (PARTIAL) {
               kj = KJ_NONE;
@@ -669,20 +670,23 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
 #pragma unroll
           for (int cb = 0; cb < CB; cb++)
 #pragma unroll
-            for (int vv = 0; vv < 16; vv++) acc[cb][vv] = 0.f;
+            for (int vv = 0; vv < 16; vv++) dvacc[cb][vv] = dkacc[cb][vv] = 0.f;
           dzacc = 0.f;
           curid = newid;
         }
         if (PARTIAL) settle(ke);
         settle(zq);
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++) settle(breg[ks]);
+        for (int ks = 0; ks < KS; ks++) {
+          if (ks >= KL) settle(kreg[ks < KL ? 0 : ks - KL]);
+          settle(vreg[ks]);
+        }
       }
     }
-    if (ncols == 0 || row0 + SUB * qs >= row1) continue;  // nothing to do this step (same for both roles)
+    if (ncols == 0 || row0 + SUB * qs >= row1) continue;  // nothing to do this step
     if (PARTIAL) {
       // none of this wave's keys is active on these rows (entering keys are listed by ascending
-      // first row, expiring ones by ascending end row); both roles of a column block agree
+      // first row, expiring ones by ascending end row)
       const int rf = row0 + SUB * qs;
       if (!__any((kj < rf + SUB) & (ke > rf))) continue;
     } else if (entering && !__any((curid >= 0) & (kj < row0 + SUB * qs + SUB))) {
@@ -693,65 +697,63 @@ __global__ __launch_bounds__(512, 1) void dkv_kernel(BwdArgs p) {
     const uint16_t* Qs = ringQ + st * STILE;
     const uint16_t* dOs = ringdO + st * STILE;
 
-    // role 0: S = Q K^T ; role 1: dP = dO V^T   (this lane's key column against the step's 32 rows)
-    const uint16_t* As = role == 0 ? Qs : dOs;
-    if (role == 0) {  // S starts at z / scale, so that scale * S is the biased score
-      // (a key that enters in a later step: all of its rows stay at -inf, so P = 0 and dS = 0 exactly; in
-      // the step it enters in, the rows before it do)
-      const int rf = row0 + SUB * qs;
-      float z0 = zq;
-      if (!PARTIAL && entering) z0 = kj >= rf + SUB ? -INFINITY : zq;
-      if (!PARTIAL && entering && __any((kj > rf) & (kj < rf + SUB))) {
-        const int first = kj - rf - 4 * hh;
+    // S starts at z / scale, so that scale * S is the biased score (a key that enters in a later step: all of
+    // its rows stay at -inf, so P = 0 and dS = 0 exactly; in the step it enters in, the rows before it do)
+    f32x16 sacc, dpacc;
+    const int rf = row0 + SUB * qs;
+    float z0 = zq;
+    if (!PARTIAL && entering) z0 = kj >= rf + SUB ? -INFINITY : zq;
+    if (!PARTIAL && entering && __any((kj > rf) & (kj < rf + SUB))) {
+      const int first = kj - rf - 4 * hh;
 #pragma unroll
-        for (int vv = 0; vv < 16; vv++) sacc[vv] = 8 * (vv >> 2) + (vv & 3) >= first ? z0 : -INFINITY;
-      } else {
+      for (int vv = 0; vv < 16; vv++) sacc[vv] = 8 * (vv >> 2) + (vv & 3) >= first ? z0 : -INFINITY;
+    } else {
 #pragma unroll
-        for (int vv = 0; vv < 16; vv++) sacc[vv] = z0;
-      }
-    } else {  // dP starts at -D_i of the accumulator's rows: the products then leave dP - D, what dS needs
-      const float* Dss = meta[st] + 32;
-#pragma unroll
-      for (int gq = 0; gq < 4; gq++) {
-        const f32x4 dd = *reinterpret_cast<const f32x4*>(&Dss[8 * gq + 4 * hh]);
-#pragma unroll
-        for (int u = 0; u < 4; u++) sacc[4 * gq + u] = dd[u];
-      }
+      for (int vv = 0; vv < 16; vv++) sacc[vv] = z0;
     }
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      sacc = mfma32(fo.row_frag(As, 0, ks), breg[ks], sacc);
+    for (int ks = 0; ks < KS; ks++) sacc = mfma32(fo.row_frag(Qs, 0, ks), ks < KL ? kl[64 * ks] : kreg[ks < KL ? 0 : ks - KL], sacc);
+    // dP starts at -D_i of the accumulator's rows: the products then leave dP - D, what dS needs
+    const float* row_meta = meta[st] + 4 * (fresh_lane() >> 5);
+#pragma unroll
+    for (int gq = 0; gq < 4; gq++) {
+      const f32x4 dd = *reinterpret_cast<const f32x4*>(&row_meta[32 + 8 * gq]);
+#pragma unroll
+      for (int u = 0; u < 4; u++) dpacc[4 * gq + u] = dd[u];
     }
-    if (role == 1) {  // the rest of this step follows the next barrier
-      pend = true;
-      pstep = v;
-      continue;
-    }
-    f32x4* ph = &pbuf[v & 1][kb4][0][l];
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) dpacc = mfma32(fo.row_frag(dOs, 0, ks), vreg[ks], dpacc);
     bf16x8 bb[2];  // P: the B operand of the dV^T accumulation
-    const float* lses = meta[st];
 #pragma unroll
     for (int gq = 0; gq < 4; gq++) {
       const int r = 8 * gq + 4 * hh;
-      const f32x4 ls = *reinterpret_cast<const f32x4*>(&lses[r]);
-      f32x4 pq;
+      const f32x4 ls = *reinterpret_cast<const f32x4*>(&row_meta[8 * gq]);
 #pragma unroll
       for (int u = 0; u < 4; u++) {
         const int vv = 4 * gq + u;
         float pv = fast_exp2(fmaf(sacc[vv], c2, -ls[u]));
         if (PARTIAL) {
-          const int row = row0 + SUB * qs + r + u;
+          const int row = rf + r + u;
           pv = ((row >= kj) & (row < ke)) ? pv : 0.f;
         }
-        pq[u] = pv;
+        sacc[vv] = pv;
         bb[vv >> 3][vv & 7] = (__bf16)pv;
       }
-      ph[64 * gq] = pq;
     }
 #pragma unroll
     for (int c = 0; c < 2; c++)
 #pragma unroll
-      for (int cb = 0; cb < CB; cb++) acc[cb] = mfma32(fo.tr_frag(dOs, 16 * c, cb), bb[c], acc[cb]);
+      for (int cb = 0; cb < CB; cb++) dvacc[cb] = mfma32(fo.tr_frag(dOs, 16 * c, cb), bb[c], dvacc[cb]);
+#pragma unroll
+    for (int vv = 0; vv < 16; vv++) {  // dS: the B operand of the dK^T accumulation
+      const float ds = sacc[vv] * dpacc[vv];
+      dzacc += ds;
+      bb[vv >> 3][vv & 7] = (__bf16)ds;
+    }
+#pragma unroll
+    for (int c = 0; c < 2; c++)
+#pragma unroll
+      for (int cb = 0; cb < CB; cb++) dkacc[cb] = mfma32(fo.tr_frag(Qs, 16 * c, cb), bb[c], dkacc[cb]);
   }
   wait_vmcnt<0>();
   flush(true);
@@ -807,11 +809,10 @@ int launch_bwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
     if (seg > L.nblk_cap) seg = L.nblk_cap;
     if (seg > MAXSWEEP) seg = MAXSWEEP;
     a.seg = (int)seg;
-    // Blocks per partial-mode work item: up to 8, which amortises the pipeline fill, but at least about 256
-    // items with keys in them (most blocks list at most one group of them), else the launch is one long
-    // chain on an idle chip: 2 x 4096 tokens x 16 heads 0.135 ms at 8 blocks, 0.070 at 2; 10007 tokens x 8
-    // heads, window 333: 0.110 at 8, 0.052 at 1; 16384 x 32 heads: 0.194 at 2, 0.166 at 8.
-    long sp = (long)L.nblk_cap * s.H_q / 256;
+    // Blocks per partial-mode work item: up to 8, which amortises the pipeline fill, but at least about 1024
+    // items (most blocks list at most one group of columns, so about as many workgroups have work; 512 fit the
+    // chip at once): 16384 tokens x 32 heads 312 us with 256 items, 196 with 1024; 65536 x 16 heads, d = 64: 184 and 180.
+    long sp = (long)L.nblk_cap * s.H_q / 1024;
     a.seg_part = sp < 1 ? 1 : sp > 8 ? 8 : (int)sp;
   }
 
@@ -832,14 +833,14 @@ int launch_bwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
   else dq_kernel<64, 4><<<gq, 256, 0, st>>>(a);  // half blocks, three workgroups per compute unit (three waves per SIMD)
   prof_end(DMA_STAGE_BWD_DQ, st);
   prof_begin(DMA_STAGE_BWD_DKV, st);
-  if (s.d == 256) dkv_kernel<256, false><<<gclean, 512, 0, st>>>(a);
-  else if (s.d == 128) dkv_kernel<128, false><<<gclean, 512, 0, st>>>(a);
-  else dkv_kernel<64, false><<<gclean, 512, 0, st>>>(a);
+  if (s.d == 256) dkv_kernel<256, false><<<gclean, DKV_NW * 64, 0, st>>>(a);
+  else if (s.d == 128) dkv_kernel<128, false><<<gclean, DKV_NW * 64, 0, st>>>(a);
+  else dkv_kernel<64, false><<<gclean, DKV_NW * 64, 0, st>>>(a);
   prof_end(DMA_STAGE_BWD_DKV, st);
   prof_begin(DMA_STAGE_BWD_PART, st);
-  if (s.d == 256) dkv_kernel<256, true><<<gpart, 512, 0, st>>>(a);
-  else if (s.d == 128) dkv_kernel<128, true><<<gpart, 512, 0, st>>>(a);
-  else dkv_kernel<64, true><<<gpart, 512, 0, st>>>(a);
+  if (s.d == 256) dkv_kernel<256, true><<<gpart, DKV_NW * 64, 0, st>>>(a);
+  else if (s.d == 128) dkv_kernel<128, true><<<gpart, DKV_NW * 64, 0, st>>>(a);
+  else dkv_kernel<64, true><<<gpart, DKV_NW * 64, 0, st>>>(a);
   prof_end(DMA_STAGE_BWD_PART, st);
   prof_begin(DMA_STAGE_BWD_CVT, st);
   const unsigned gcvt = grid_for(nkv / 4, 1024);
