@@ -802,9 +802,13 @@ int launch_bwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
   a.plist = (const int32_t*)(p.plan + L.off_plist);
   a.consts = p.plan + L.off_consts;
   a.T = s.T; a.H_q = s.H_q; a.H_kv = s.H_kv; a.k = s.k; a.nblk_cap = L.nblk_cap; a.kpad = L.kpad; a.causal = s.causal;
-  {  // sweep length of a clean-mode work item: as long as possible while keeping >= 512 work items
-    const long groups = (long)(L.kpad / SG) * s.H_q;
-    long seg = (long)L.nblk_cap * groups / 512;
+  {  // Sweep length of a clean-mode work item: as long as possible with an item for every workgroup that fits the
+    // chip at once (three per compute unit at 64 channels, two at 128, one at 256) and no second round of a few
+    // items.  us of a training step, about 512 items but rather more -> this rule: 65536 packed tokens, d = 64
+    // 1740 -> 1690; 16384 tokens x 32 heads, d = 64 1770 -> 1680; 40000 tokens x 8 heads, d = 128, window 100
+    // 721 -> 693; 9000 tokens x 16 heads, d = 256 1437 -> 1314.
+    const long groups = (long)(L.kpad / SG) * s.H_q, resident = s.d == 64 ? 768 : s.d == 128 ? 512 : 256;
+    long seg = ((long)((s.T + BQ - 1) / BQ) * groups + resident - 1) / resident;
     if (seg < 2) seg = 2;
     if (seg > L.nblk_cap) seg = L.nblk_cap;
     if (seg > MAXSWEEP) seg = MAXSWEEP;
