@@ -6,6 +6,8 @@
 // HBM-bound: one pass over V (read) and dV (write, plus a read when accumulating), dz read once.
 #include "common.h"
 
+#include <algorithm>
+
 namespace dma {
 
 // One workgroup per (TT-token tile, kv-head); TT = 64, or 32 at 256 channels (the V tile is kept in LDS).  (1) every row is held by D / 8 lanes, which reduce
@@ -158,6 +160,145 @@ __global__ __launch_bounds__(256) void mask_bwd_kernel(const TV* __restrict__ V,
   for (int hh = tid; hh < G; hh += 256) atomicAdd(dA + g * G + hh, dap[hh]);
 }
 
+// The same for bf16 values and groups of 1, 2, 4 or 8 q-heads, without LDS tiles or barriers: a value row is held
+// by D / 8 lanes with the group's weights and dW sums in registers, a wave walks its rows U per lane group at a
+// time, and the V, dV and dz of the next rows are requested before the current ones are worked on.  The tile
+// kernel above was bound by three dependent round trips to memory and five barriers per tile.  The
+// transcendental work of the U * G (row, q-head) pairs of a lane group is dealt out to its lanes.  us, tile
+// kernel -> this one: 16384 tokens, 32 / 8 heads, d = 128 65 -> 30 (3.4 TB/s); 65536 tokens, 16 heads, d = 64
+// 111 -> 71; 16384 tokens, 16 / 4 heads, d = 256 100 -> 32; 8192 tokens, 16 / 4 heads, d = 128 25 -> 19.
+template <int D, int G>
+__global__ __launch_bounds__(256) void mask_bwd_rows_kernel(const uint16_t* __restrict__ V, const float* __restrict__ W,
+                                                            const float* __restrict__ A, const float* __restrict__ dz,
+                                                            float* dW, float* dA, uint16_t* dV, int accumulate, int T,
+                                                            int H_kv, int rows_per_wg) {
+  constexpr int LPR = D / 8, RPW = 64 / LPR, U = 2, STEP = 4 * RPW * U, NR = (U * G + LPR - 1) / LPR;
+  static_assert(LPR % G == 0, "a lane's pairs belong to one q-head");
+  const int g = blockIdx.y, tid = threadIdx.x, w = tid >> 6, l = tid & 63, sub = l % LPR, rg = l / LPR;
+  const int t_begin = blockIdx.x * rows_per_wg, t_end = min(T, t_begin + rows_per_wg);
+  const int hi = sub % G;  // q-head of this lane's pairs
+  float wr[G][8], dw[G][8], da = 0.f;
+#pragma unroll
+  for (int h = 0; h < G; h++) {
+    const float4* w4 = reinterpret_cast<const float4*>(W + (size_t)(g * G + h) * D + 8 * sub);
+    const float4 x0 = w4[0], x1 = w4[1];
+    wr[h][0] = x0.x; wr[h][1] = x0.y; wr[h][2] = x0.z; wr[h][3] = x0.w;
+    wr[h][4] = x1.x; wr[h][5] = x1.y; wr[h][6] = x1.z; wr[h][7] = x1.w;
+#pragma unroll
+    for (int e = 0; e < 8; e++) dw[h][e] = 0.f;
+  }
+  const float a = A[g * G + hi];
+  const float* dzh = dz + (size_t)(g * G + hi) * T;
+  auto row = [&](int t0, int u) { return t0 + (w * U + u) * RPW + rg; };
+  auto offset = [&](int t) { return ((size_t)min(t, t_end - 1) * H_kv + g) * D + 8 * sub; };
+  uint4 vn[U], dn[U];
+  float zn[NR];
+  auto request = [&](int t0) {
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      vn[u] = *reinterpret_cast<const uint4*>(V + offset(row(t0, u)));
+      dn[u] = accumulate ? *reinterpret_cast<const uint4*>(dV + offset(row(t0, u))) : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < NR; r++) {
+      const int pair = sub + r * LPR, t = row(t0, pair / G);
+      zn[r] = pair < U * G && t < t_end ? dzh[t] : 0.f;
+    }
+  };
+  auto unpack = [](const uint4& raw, float* o) {
+    const uint32_t u[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      o[2 * e] = __uint_as_float(u[e] << 16);
+      o[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
+    }
+  };
+  request(t_begin);
+  for (int t0 = t_begin; t0 < t_end; t0 += STEP) {
+    uint4 vc[U], dc[U];
+    float zc[NR], x[U][G], dx[NR];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      vc[u] = vn[u];
+      dc[u] = dn[u];
+    }
+#pragma unroll
+    for (int r = 0; r < NR; r++) zc[r] = zn[r];
+    if (t0 + STEP < t_end) request(t0 + STEP);
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      float v[8];
+      unpack(vc[u], v);
+#pragma unroll
+      for (int h = 0; h < G; h++) {
+        float s = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; e++) s = fmaf(v[e], wr[h][e], s);
+#pragma unroll
+        for (int off = LPR / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
+        x[u][h] = s;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < NR; r++) {
+      const int pair = sub + r * LPR;
+      const bool in = pair < U * G && row(t0, pair / G) < t_end;
+      float xi = 0.f;
+#pragma unroll
+      for (int i = r * LPR; i < U * G && i < (r + 1) * LPR; i++) xi = sub == i - r * LPR ? x[i / G][i % G] : xi;
+      const float sp = fmaxf(xi, 0.f) + log1pf(expf(-fabsf(xi)));
+      const float zv = expf(a * sp);
+      const float sig = 1.f / (1.f + expf(-xi));
+      const float dzz = zc[r] * zv;
+      dx[r] = in ? dzz * a * sig : 0.f;
+      da += in ? dzz * sp : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      float v[8], dv[8], old[8];
+      unpack(vc[u], v);
+      unpack(dc[u], old);
+#pragma unroll
+      for (int e = 0; e < 8; e++) dv[e] = 0.f;
+#pragma unroll
+      for (int h = 0; h < G; h++) {
+        const int i = u * G + h;
+        const float d = __shfl(dx[i / LPR], rg * LPR + i % LPR);
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+          dv[e] = fmaf(d, wr[h][e], dv[e]);
+          dw[h][e] = fmaf(d, v[e], dw[h][e]);
+        }
+      }
+      bf16x8 o;
+#pragma unroll
+      for (int e = 0; e < 8; e++) o[e] = (__bf16)(dv[e] + old[e]);
+      if (row(t0, u) < t_end) *reinterpret_cast<uint4*>(dV + offset(row(t0, u))) = __builtin_bit_cast(uint4, o);
+    }
+  }
+  // sums of the workgroup, then one set of atomics
+  __shared__ float sdw[4][G * D];
+  __shared__ float sda[256];
+#pragma unroll
+  for (int h = 0; h < G; h++)
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      float s = dw[h][e];
+#pragma unroll
+      for (int off = LPR; off < 64; off <<= 1) s += __shfl_xor(s, off);
+      if (rg == 0) sdw[w][h * D + 8 * sub + e] = s;
+    }
+  sda[tid] = da;
+  __syncthreads();
+  for (int i = tid; i < G * D; i += 256)
+    atomicAdd(dW + (size_t)g * G * D + i, (sdw[0][i] + sdw[1][i]) + (sdw[2][i] + sdw[3][i]));
+  if (tid < G) {
+    float s = 0.f;
+    for (int i = tid; i < 256; i += G) s += sda[i];  // (256 and the lane groups are multiples of G)
+    atomicAdd(dA + g * G + tid, s);
+  }
+}
+
 __global__ void fill_zero_kernel(float* a, size_t na, float* b, size_t nb) {
   const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
   if (i < na) a[i] = 0.f;
@@ -175,6 +316,26 @@ int launch_mask_bwd(const dma_shape& s, const void* V, const float* W, const flo
   if (mask_bwd_lds_bytes(s) > 64 * 1024) return DMA_EUNSUPPORTED;  // (before the first launch)
   const size_t nw = (size_t)s.H_q * s.d;
   fill_zero_kernel<<<(unsigned)((nw + 255) / 256), 256, 0, st>>>(dW, nw, dA, (size_t)s.H_q);
+  const int G = s.H_q / s.H_kv;
+  if (s.dtype == DMA_BF16 && (G == 1 || G == 2 || G == 4 || G == 8)) {
+    const int step = 4 * (64 / (s.d / 8)) * 2;  // rows of one trip of a workgroup
+    // Two workgroups per compute unit: every one ends with contended atomics on dW (1024 instead of 512: 29 us instead of
+    // 19 at 8192 tokens x 4 kv-heads), and with rows in flight ahead two are enough.  Up to 512 rows each: beyond
+    // that the atomics are few and shorter workgroups even out the end (65536 x 16: 84 us at 2048 rows, 71 at 512).
+    long rows = std::min(((long)s.T * s.H_kv + 511) / 512, 512l);
+    rows = (rows + step - 1) / step * step;
+    const dim3 rgrid((unsigned)((s.T + rows - 1) / rows), s.H_kv);
+#define DMA_MR(DD, GG) \
+  mask_bwd_rows_kernel<DD, GG><<<rgrid, 256, 0, st>>>((const uint16_t*)V, W, A, dz, dW, dA, (uint16_t*)dV, accumulate, s.T, s.H_kv, (int)rows)
+#define DMA_MRG(DD) \
+  do { if (G == 1) DMA_MR(DD, 1); else if (G == 2) DMA_MR(DD, 2); else if (G == 4) DMA_MR(DD, 4); else DMA_MR(DD, 8); } while (0)
+    if (s.d == 256) DMA_MRG(256);
+    else if (s.d == 128) DMA_MRG(128);
+    else DMA_MRG(64);
+#undef DMA_MRG
+#undef DMA_MR
+    return hipGetLastError() == hipSuccess ? DMA_OK : DMA_EHIP;
+  }
   const int TT = s.d == 256 ? 32 : 64;  // tokens per tile
   const int ntiles = (s.T + TT - 1) / TT;
   // enough workgroups to fill the chip (about four per CU), as few contended atomics as possible
