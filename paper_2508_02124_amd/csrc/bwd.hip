@@ -10,11 +10,11 @@
 //  * dkv_kernel, key-stationary: a workgroup owns SG slot columns of one head and sweeps query
 //    blocks in steps of 32 rows, fed by a ring of asynchronous Q / dO copies.  A slot column always
 //    holds one resident key, so its tiles are dense and need no mask; K and V fragments of the
-//    resident stay in registers together with the dK^T, dV^T and dz accumulators.  When the
+//    resident stay in registers (part of K's in LDS) together with the dK^T, dV^T and dz accumulators.  When the
 //    resident of a column changes, the finished key is flushed with a handful of fp32 atomics (dK
 //    and dV are shared by the q-heads of a group) and the column is re-armed.  The same kernel, in
-//    "partial" mode, handles the keys that enter or expire inside a block: columns come from the
-//    blocks' partial lists, elements are masked with j <= i < e_j, and every column changes at
+//    "partial" mode, handles the keys that expire inside a block or enter it without staying: columns
+//    come from the blocks' partial lists, elements are masked with j <= i < e_j, and every column changes at
 //    every block of the (short) sweep.
 //
 // The dS / P blocks are produced in the accumulator layout of S = Q K^T (dkv) or S^T = K Q^T (dq),
