@@ -655,6 +655,11 @@ __global__ __launch_bounds__(256) void decode_attend_kernel(const TV* __restrict
     lsum *= alpha;
 #pragma unroll
     for (int e = 0; e < 8; e++) acc[e] *= alpha;
+    if (i - grp + NG * U > cnt) {  // (workgroup-uniform) past the list's end not even an infinite value may count: 0 * inf
+#pragma unroll
+      for (int u = 0; u < U; u++)
+        if (i + u * NG >= cnt) vr[u] = Raw{};
+    }
 #pragma unroll
     for (int u = 0; u < U; u++) {
       float vv[8];
@@ -725,8 +730,9 @@ __global__ __launch_bounds__(D) void decode_merge_kernel(const float* __restrict
     den *= alpha;
 #pragma unroll
     for (int u = 0; u < 8; u++) {
-      const float w8 = s0 + u < ns ? fast_exp2(Ms[u] - ref) : 0.f;
-      num = fmaf(os[u], w8, num);
+      const bool in = s0 + u < ns;  // (past the end the last chunk is read again and counts for nothing, whatever it holds)
+      const float w8 = in ? fast_exp2(Ms[u] - ref) : 0.f;
+      num = fmaf(in ? os[u] : 0.f, w8, num);
       den = fmaf(ls[u], w8, den);
     }
   }

@@ -81,3 +81,33 @@ def test_gather_of_any_group_count(gpu, H_q, H_kv, d, lens, k):
     fin = np.isfinite(rl)
     assert (np.isneginf(lse) == ~fin).all()
     check_close("lse", lse[fin], rl[fin], **tol(True))
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("bf16", 256), ("f32", 128)])
+@pytest.mark.parametrize("lens,k", [((1, 5, 63), 64), ((255, 257, 300), 300), ((700, 2049, 2500), 4096), ((900, 40), 300)])
+def test_infinite_value_of_the_last_key(gpu, dtype, d, lens, k):
+    """An infinite value in a sequence's newest key gives an infinity where that key is kept, as the sum of
+    Eq. 6 does, and nothing where it is not: the rows past the end of a list or of its chunks do not count."""
+    print(f"[case] infinite value {dtype} d={d} {lens} k={k}", flush=True)
+    T, n_docs, H_q, H_kv = sum(lens), len(lens), 4, 2
+    r = np.random.default_rng(29)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    dev = lambda *s: torch.from_numpy(r.standard_normal(s).astype(np.float32)).to(gpu).to(dt)
+    q, K, V = dev(n_docs, H_q, d), dev(T, H_kv, d), dev(T, H_kv, d)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    for b in range(n_docs):
+        V[int(cu[b + 1]) - 1, 1, 3 + b] = float("inf")
+    z = torch.from_numpy(scores("ordinary", H_q, T, r)).to(gpu)
+    shape = B.make_shape(T=T, n_docs=n_docs, H_q=H_q, H_kv=H_kv, d=d, k=k, dtype=B.DMA_BF16 if dtype == "bf16" else B.DMA_F32)
+    nb, kcap = B.dma_decode_kept_bytes(shape), min(k, T)
+    kept = torch.full((nb // 4,), -7, dtype=torch.int32, device=gpu)
+    o, lse = torch.zeros((n_docs, H_q, d), dtype=dt, device=gpu), torch.zeros((H_q, n_docs), device=gpu)
+    B.dma_decode(shape, q, K, V, z, torch.from_numpy(cu).to(gpu), o, lse, kept, nb)
+    lists, out = kept.cpu()[: n_docs * H_q * kcap].view(n_docs, H_q, kcap), o.float().cpu()
+    assert torch.isfinite(lse).all() and not torch.isnan(out).any()
+    for b, n in enumerate(lens):
+        for h in range(H_q):
+            want = torch.zeros(d, dtype=torch.bool)
+            want[3 + b] = h // 2 == 1 and int(cu[b + 1]) - 1 in lists[b, h, : min(k, n)].tolist()
+            assert torch.equal(torch.isposinf(out[b, h]), want), (b, h)
+            assert torch.isfinite(out[b, h][~want]).all(), (b, h)
