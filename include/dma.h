@@ -56,7 +56,10 @@ typedef enum { DMA_BF16 = 0, DMA_F32 = 1 } dma_dtype;
 typedef struct {
   int32_t T;            /* total packed tokens                                        */
   int32_t n_docs;       /* number of documents (sequences) packed into T              */
-  int32_t max_seqlen;   /* upper bound on the longest document (0 => T)               */
+  int32_t max_seqlen;   /* upper bound on the longest document (0 => T).  It chooses between
+                           equal ways of working; a bound that is too small costs time
+                           but changes no result.  (dma_mask_gen_bias: also the length
+                           of a bias row that the documents share, which must hold)    */
   int32_t H_q;          /* query heads                                                */
   int32_t H_kv;         /* key/value heads, divides H_q                               */
   int32_t d;            /* head dimension: 64, 128 or 256 (256: not for the cross-head

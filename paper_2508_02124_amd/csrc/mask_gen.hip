@@ -732,17 +732,121 @@ __global__ __launch_bounds__(BQ) void partial_list_kernel(const int4* __restrict
   }
 }
 
+// The plan of one block of a document that is longer than the window after all: the caller's length bound, which
+// sent the call to plan_all_kept_kernel, was too small.  No result depends on that bound, so the block's part of
+// expiry, table and lists is worked out here by itself, from the scores of the whole document: O(n) per key and 64
+// passes over the scores for the two kept sets, far slower than the selection, but only a wrong bound leads here
+// (dma_mask_gen with window 2048, us, right bound -> a bound of 2048: documents of 9000, 200 and 3000 keys, 8 heads
+// 98 -> 1090; one of 16384 keys, 32 heads 130 -> 3225).  The residents stand in the table by ascending index instead
+// of in a column of their own from block to block.
+__device__ __forceinline__ void plan_longer_document(const int4 info, int end, const float* __restrict__ zh, int32_t* ex,
+                                                     int32_t* row, int32_t* list, int32_t* pcnt, int32_t* pent, int k,
+                                                     int kpad) {
+  __shared__ uint32_t ks[BQ];
+  __shared__ int wsum[BQ / 64];
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  const int r0 = info.y, r1 = info.z, a = info.w, j = r0 + tid;
+  // e = max(j, k-th smallest index among the keys ranked ahead of j)
+  const uint32_t kj = desc_key(zh[min(j, r1 - 1)]);
+  int ahead = 0, kth = -1;
+  for (int t0 = a; t0 < end; t0 += BQ) {
+    __syncthreads();
+    ks[tid] = desc_key(zh[min(t0 + tid, end - 1)]);
+    __syncthreads();
+    const int m = min(BQ, end - t0);
+    for (int i = 0; i < m; i++) {
+      const bool before = ks[i] < kj || (ks[i] == kj && t0 + i < j);
+      ahead += before;
+      if (before && ahead == k) kth = t0 + i;
+    }
+  }
+  const int e = kth < 0 ? end : max(j, kth);
+  if (j < r1) ex[j] = e;
+  // position of this thread among those with p, counted on from `total`, which moves on behind the last of them
+  auto place = [&](bool p, int& total) {
+    const unsigned long long m = __ballot(p);
+    __syncthreads();
+    if (l == 0) wsum[w] = __popcll(m);
+    __syncthreads();
+    int pos = total + __popcll(m & ((1ull << l) - 1ull));
+#pragma unroll
+    for (int i = 0; i < BQ / 64; i++) {
+      if (i < w) pos += wsum[i];
+      total += wsum[i];
+    }
+    return pos;
+  };
+  // the kept set of row `last`: the keys up to it before `v`, and the first need_eq of those equal to v
+  auto kept_set = [&](int last, int& need_eq) {
+    const int kk = min(k, last + 1 - a);
+    uint32_t v = 0;
+    int less = 0;
+    for (int bit = 31; bit >= 0; bit--) {
+      const uint32_t cand = v | (1u << bit);
+      int c = 0;
+      for (int t = a + tid; t <= last; t += BQ) c += desc_key(zh[t]) < cand;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+      __syncthreads();
+      if (l == 0) wsum[w] = c;
+      __syncthreads();
+      c = 0;
+#pragma unroll
+      for (int i = 0; i < BQ / 64; i++) c += wsum[i];
+      if (c < kk) {
+        v = cand;
+        less = c;
+      }
+    }
+    need_eq = kk - less;
+    return v;
+  };
+  // the block's own keys: those that stay in a new column of their own (the document's first k keys), then the others
+  const bool ent = j < r1 && e > j, stays = ent && e >= r1 && j - a < k;
+  int n_list = 0;
+  const int ps = place(stays, n_list);
+  const int n_stay = n_list;
+  const int pe = place(ent && !stays, n_list);
+  if (ent) list[stays ? ps : pe] = j;
+  // older keys: resident to the block's end (table), or kept by its first row and evicted inside it (list)
+  int need0, need1, eq0 = 0, eq1 = 0, n_row = 0;
+  const uint32_t v0 = kept_set(r0, need0), v1 = kept_set(r1 - 1, need1);
+  for (int t0 = a; t0 < r0; t0 += BQ) {
+    const int t = t0 + tid;
+    const bool in = t < r0;
+    const uint32_t kt = desc_key(zh[min(t, r0 - 1)]);
+    const int q0 = place(in && kt == v0, eq0), q1 = place(in && kt == v1, eq1);
+    const bool at_first = in && (kt < v0 || (kt == v0 && q0 < need0));
+    const bool at_end = in && (kt < v1 || (kt == v1 && q1 < need1));
+    const int pr = place(at_end, n_row), px = place(at_first && !at_end, n_list);
+    if (at_end) row[pr] = t;
+    else if (at_first) list[px] = t;
+  }
+  for (int c = n_row + tid; c < kpad; c += BQ) row[c] = -1;
+  if (tid == 0) {
+    *pcnt = n_list;
+    *pent = n_stay;
+  }
+}
+
 // Documents no longer than the window: every key enters at its own row and stays.  Expiry, the slot table's
 // rows (column c = the document's key c, once it is older than the block) and the partial lists (the block's
 // own keys, all of them to its end) follow from the block table alone, in one launch instead of the six of a
 // selection.  One workgroup per (block, head).  Forward of a 1019-token prompt, 32 heads: 52.6 -> 40.8 us.
 __global__ __launch_bounds__(BQ) void plan_all_kept_kernel(const int4* __restrict__ blk, const int32_t* __restrict__ cu,
-                                                           int32_t* expiry, int32_t* slot_tab, int32_t* pcnt,
-                                                           int32_t* pent, int32_t* plist, int T, int nblk_cap, int kpad) {
+                                                           const float* __restrict__ z, int32_t* expiry,
+                                                           int32_t* slot_tab, int32_t* pcnt, int32_t* pent,
+                                                           int32_t* plist, int T, int nblk_cap, int kpad, int k) {
   const int bi = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
   const int4 info = blk[bi];
   const size_t hb = (size_t)h * nblk_cap + bi;
   const bool used = info.x >= 0;
+  const int end = used ? cu[info.x + 1] : 0;
+  if (used && end - info.w > k) {  // (workgroup-uniform)
+    plan_longer_document(info, end, z + (size_t)h * T, expiry + (size_t)h * T, slot_tab + hb * kpad,
+                         plist + hb * MAXPART, pcnt + hb, pent + hb, k, kpad);
+    return;
+  }
   const int rows = used ? info.z - info.y : 0, older = used ? info.y - info.w : 0;
   int4* row = reinterpret_cast<int4*>(slot_tab + hb * kpad);
   for (int c = 4 * tid; c < kpad; c += 4 * BQ)
@@ -751,7 +855,7 @@ __global__ __launch_bounds__(BQ) void plan_all_kept_kernel(const int4* __restric
   if (tid == 0) pcnt[hb] = pent[hb] = rows;
   if (tid < rows) {
     plist[hb * MAXPART + tid] = info.y + tid;
-    expiry[(size_t)h * T + info.y + tid] = cu[info.x + 1];
+    expiry[(size_t)h * T + info.y + tid] = end;
   }
 }
 
@@ -896,14 +1000,14 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
   }
   prof_end(DMA_STAGE_Z, st);
   const bool all_kept = s.causal && (s.max_seqlen > 0 && s.max_seqlen < s.T ? s.max_seqlen : s.T) <= s.k;
-  if (all_kept) {  // (the caller's bound says that no document is longer than the window: nothing to select)
+  if (all_kept) {  // (the caller's bound says that no document is longer than the window: nothing to select, or very little)
     for (int stage : {DMA_STAGE_SORT, DMA_STAGE_EXPIRY}) {
       prof_begin(stage, st);
       prof_end(stage, st);
     }
     prof_begin(DMA_STAGE_PLAN, st);
-    plan_all_kept_kernel<<<dim3(L.nblk_cap, s.H_q), BQ, 0, st>>>(blk, cu, expiry, slot_tab, pcnt, pent, plist, s.T,
-                                                                L.nblk_cap, L.kpad);
+    plan_all_kept_kernel<<<dim3(L.nblk_cap, s.H_q), BQ, 0, st>>>(blk, cu, z, expiry, slot_tab, pcnt, pent, plist, s.T,
+                                                                L.nblk_cap, L.kpad, s.k);
     if (topk_idx) topk_idx_kernel<<<dim3(s.T, s.H_q), 64, 0, st>>>(cu, s.n_docs, s.causal, expiry, topk_idx, s.T, s.k);
     prof_end(DMA_STAGE_PLAN, st);
     return hipGetLastError() == hipSuccess ? DMA_OK : DMA_EHIP;

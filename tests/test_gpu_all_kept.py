@@ -1,11 +1,16 @@
 """Plans of documents no longer than the window, which are written without a selection, against the general path:
-the same shape without the caller's length bound (max_seqlen = 0) selects as usual."""
+the same shape without the caller's length bound (max_seqlen = 0) selects as usual.  And the same call with a bound
+that is too small for some of its documents: no result depends on the bound."""
 from __future__ import annotations
 
+import numpy as np
 import pytest
 import torch
 
 from paper_2508_02124_amd import binding as B
+from paper_2508_02124_amd import workloads as wlmod
+from paper_2508_02124_amd.device_case import DeviceCase
+from test_gpu_parity import check_gradients, check_mask
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +65,25 @@ def test_all_kept_plan_equals_the_selected_one(gpu, lens, k):
             assert short[4][h * nb_s + b] == full[4][h * nb_f + b]
     kp = min(short[5].shape[2], full[5].shape[2])
     assert torch.equal(short[5][:, :nblk, :kp], full[5][:, :nblk, :kp])
+
+
+@pytest.mark.parametrize("pattern", ["random", "levels", "rising", "falling"])
+@pytest.mark.parametrize("lens,k,bound", [((900, 40, 600), 300, 300), ((257, 1), 256, 200), ((700, 3), 40, 40),
+                                          ((30,) * 300 + (70, 513), 64, 64)])
+def test_results_do_not_depend_on_the_length_bound(gpu, pattern, lens, k, bound):
+    wl = wlmod.small_workload(f"bound_{pattern}_{bound}_below_{max(lens)}", 37, 2, 1, 64, k, lens)
+    print(f"[case] {wl.name} k={k}", flush=True)
+    inp = wlmod.make_inputs(wl)
+    rng = np.random.default_rng(k)
+    z = {"random": np.exp(-np.log1p(np.exp(rng.standard_normal((2, inp.T))))),
+         "levels": np.round(rng.random((2, inp.T)) * 12) / 12,
+         "rising": np.tile(np.linspace(0.1, 1.5, inp.T), (2, 1)),
+         "falling": np.tile(np.linspace(1.5, 0.1, inp.T), (2, 1))}[pattern].astype(np.float32)
+    case = DeviceCase(inp, gpu, z_override=z, topk=True)
+    case.shape.max_seqlen = bound          # (below the longest document; the plan's layout stays the same)
+    assert B.dma_mask_bytes(case.shape) == case.mask.numel()
+    case.mask_gen()
+    check_mask(case, wl.name)
+    case.fwd()
+    case.bwd()
+    check_gradients(case, z.astype(np.float64), "bf16")
