@@ -35,6 +35,7 @@ struct DecSel {
   uint32_t* hist;  // [4][n_docs * H_q][256], zeroed before the first pass
   uint32_t* cnt;   // [n_docs * H_q][nsl][4 waves][2]: keys better than / equal to the threshold
   int T, H_q, k, nsl;
+  int split;       // the sliced launches select for sequences longer than this, decode_select_kernel for the others
 };
 
 // Wave 0: the digit of `h256` at which the running count reaches `remaining`; updates prefix / remaining.
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(256) void decode_hist_kernel(DecSel p, int pass) {
   const int bh = blockIdx.x, b = bh / p.H_q, h = bh % p.H_q, sl = blockIdx.y, nbh = gridDim.x;
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const DecSlice s = dec_slice(p, b, sl, w);
-  if (s.n <= 0 || s.kk == s.n) return;  // (workgroup-uniform)
+  if (s.n <= p.split || s.kk == s.n) return;  // (workgroup-uniform)
   // every digit has 32 sub-counters (one per lane pair), so that the lanes of a wave that hit the
   // same digit (scores share their leading bits) do not serialise on one LDS address
   __shared__ uint32_t hist[256 * 32];
@@ -140,7 +141,8 @@ __global__ __launch_bounds__(256) void decode_count_kernel(DecSel p) {
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const DecSlice s = dec_slice(p, b, sl, w);
   uint32_t* out = p.cnt + (((size_t)bh * p.nsl + sl) * 4 + w) * 2;
-  if (s.n <= 0 || s.kk == s.n) {  // everything is kept
+  if (s.n <= p.split) return;
+  if (s.kk == s.n) {  // everything is kept
     if (l == 0) {
       out[0] = (uint32_t)(s.j1 - s.j0);
       out[1] = 0;
@@ -176,7 +178,7 @@ __global__ __launch_bounds__(256) void decode_write_kernel(DecSel p) {
   const int bh = blockIdx.x, b = bh / p.H_q, h = bh % p.H_q, sl = blockIdx.y, nbh = gridDim.x;
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const DecSlice s = dec_slice(p, b, sl, w);
-  if (s.n <= 0) return;
+  if (s.n <= p.split) return;
   const int kcap = p.k < p.T ? p.k : p.T;
   int32_t* list = p.kept + (size_t)bh * kcap;
   __shared__ uint32_t st[2];
@@ -228,12 +230,13 @@ __global__ __launch_bounds__(256) void decode_write_kernel(DecSel p) {
 // histogram of 2048 equal bins between the sequence's smallest and largest key finds the bin of the kk-th
 // best; that bin's keys (few, unless scores are tied) move to LDS, where they are ranked against each other
 // -- or, if they are many, counted digit by digit -- for the exact threshold; the kept keys are then
-// counted and written in index order.  What bounds it is instruction issue on one compute unit (five passes
+// counted and written in index order.  (SPLIT: sequences longer than p.split are not this kernel's.)  What bounds it is instruction issue on one compute unit (five passes
 // over the registers) and, for short sequences, the chain of barriers between the passes.  The sliced launches
 // above pay a launch and a pass over z for every one of those links: whole call, us, sliced -> this, k = 2048,
 // 32 heads: one cache of 65536 keys 59 -> 45, 24 caches of 5461 keys on average 213 -> 154.  Past the registers
-// the passes read L2 at one compute unit's rate (131072 keys: 140 us of selection against 50 sliced).
-template <int R>
+// every pass reads the scores again, 0.11 us per 1000 keys: still issue, not the loads (32 of them in flight
+// instead of 8: 93 -> 89 us for 130000 keys).
+template <int R, bool SPLIT>
 __global__ __launch_bounds__(1024, 4) void decode_select_kernel(DecSel p) {
   constexpr int NW = 16, REP = 4, BITS = 11, NDIG = 1 << BITS, CAND = 8192, RANK = 512, STEP = 4;
   constexpr uint32_t NONE = 0xffffffffu;  // behind every key
@@ -241,6 +244,11 @@ __global__ __launch_bounds__(1024, 4) void decode_select_kernel(DecSel p) {
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
   const int a = p.cu[b], n = dec_len(p.cu, p.lens, b);
   if (n <= 0) return;
+  if (SPLIT && n > p.split) {  // left to the sliced launches behind this one: their histograms start at zero
+    for (int pass = 0; pass < 4; pass++)
+      if (tid < 256) p.hist[((size_t)pass * gridDim.x + bh) * 256 + tid] = 0;
+    return;
+  }
   const int kk = p.k < n ? p.k : n, kcap = p.k < p.T ? p.k : p.T;
   int32_t* list = p.kept + (size_t)bh * kcap;
   if (kk == n) {  // everything is kept
@@ -568,7 +576,7 @@ __global__ __launch_bounds__(256) void decode_update_kernel(const float* __restr
 
 // Keys per workgroup of the attention pass.
 constexpr int DEC_CHUNK = 256;
-// Longest sequence that one workgroup per head selects alone: 16 waves x 64 lanes x 64 registers.
+// Keys that the registers of one selecting workgroup hold: 16 waves x 64 lanes x 64.
 constexpr int DEC_SELECT_MAX = 1 << 16;
 
 // (3) single-row attention over one chunk of DEC_CHUNK kept keys: a key row is held by D / 8
@@ -817,20 +825,32 @@ int launch_decode(const dma_shape& s, float scale, const void* q, const void* K,
     decode_update_kernel<<<nbh, 256, 0, st>>>(z, cu, lens, kept, s.T, s.H_q, s.k);
   } else {
     // One workgroup per (sequence, head) selects alone while its keys fit its registers; the host sees only the
-    // caches' total, so a batch is taken at twice its average length.
+    // caches' total, so a batch is taken at twice its average length.  A sequence that is longer than the registers
+    // all the same (where the caller's bound, or without one the total, allows it) is left to the sliced launches if
+    // each head has many slices there, 12 or more: at 8 they are slower than one workgroup that reads L2 again (whole
+    // call, us, k = 2048, one workgroup / sliced: 130000 and three times 300 keys, 32 heads 98 / 135, 16 heads 94 / 88,
+    // 2 heads 90 / 47; 290000 and nine times 500 keys, 8 heads 182 / 149).  Without a bound, an even batch of few heads
+    // pays for launches that find nothing to do: eight times 16000 keys, 8 heads 28 -> 38 us (all sliced: 59).
     const long longest = s.max_seqlen > 0 && s.max_seqlen < s.T ? s.max_seqlen : s.T;
     const long typical = std::min(longest, (2l * s.T + s.n_docs - 1) / s.n_docs);
-    if (typical > DEC_SELECT_MAX && ds.nsl > 1) {
+    const bool all_sliced = typical > DEC_SELECT_MAX && ds.nsl > 1;
+    const bool long_sliced = !all_sliced && longest > DEC_SELECT_MAX && ds.nsl >= 12;
+    ds.split = all_sliced ? 0 : DEC_SELECT_MAX;
+    if (all_sliced) {
       const size_t nz = 4 * (size_t)nbh * 256;
       decode_zero_kernel<<<(unsigned)((nz + 255) / 256), 256, 0, st>>>(ds.hist, nz);
+    } else if (long_sliced) {
+      if (typical > 16 * 1024) decode_select_kernel<64, true><<<nbh, 1024, 0, st>>>(ds);
+      else decode_select_kernel<16, true><<<nbh, 1024, 0, st>>>(ds);
+    } else {
+      if (typical > 16 * 1024) decode_select_kernel<64, false><<<nbh, 1024, 0, st>>>(ds);
+      else decode_select_kernel<16, false><<<nbh, 1024, 0, st>>>(ds);
+    }
+    if (all_sliced || long_sliced) {
       const dim3 sgrid(nbh, ds.nsl);
       for (int pass = 3; pass >= 0; pass--) decode_hist_kernel<<<sgrid, 256, 0, st>>>(ds, pass);
       decode_count_kernel<<<sgrid, 256, 0, st>>>(ds);
       decode_write_kernel<<<sgrid, 256, 0, st>>>(ds);
-    } else if (typical > 16 * 1024) {
-      decode_select_kernel<64><<<nbh, 1024, 0, st>>>(ds);
-    } else {
-      decode_select_kernel<16><<<nbh, 1024, 0, st>>>(ds);
     }
   }
   if (s.dtype == DMA_BF16) {

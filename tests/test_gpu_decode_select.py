@@ -67,6 +67,29 @@ def test_selection_is_exact(gpu, pattern, lens, k):
             assert (got[b, h, : min(k, n)] == want).all(), (b, h)
 
 
+# One sequence far above the average: read again in every pass because the form for shorter ones was chosen (16
+# registers: 20001 keys; 64: 66001 keys of 24 heads), or left to the sliced launches (66001 keys of two heads, the
+# last time with a window that keeps all of them), with and without the caller's bound.
+@pytest.mark.parametrize("pattern", ["ordinary", "equal", "levels", "outlier", "signed", "rising"])
+@pytest.mark.parametrize("H_q,lens,k", [(2, (20001, 1, 700, 900), 9000), (24, (66001, 300, 5, 1000), 700),
+                                        (2, (300, 66001, 0, 1000), 700), (2, (66001, 5, 900), 67000)])
+def test_selection_of_a_skewed_batch(gpu, pattern, H_q, lens, k):
+    print(f"[case] select skewed {pattern} {H_q} heads {lens} k={k}", flush=True)
+    rng = np.random.default_rng(19)
+    z = scores(pattern, H_q, sum(lens), rng)
+    lists = []
+    for bound in (0, max(lens)):
+        _, _, _, cu, got, o, _ = decode(gpu, lens, H_q, 1, 64, k, z, np.random.default_rng(5), max_seqlen=bound)
+        lists.append(got)
+        assert np.isfinite(o).all()
+    for b, n in enumerate(lens):
+        for h in range(H_q):
+            zs = z[h, cu[b]:cu[b + 1]] + np.float32(0.0)
+            want = np.sort(np.argsort(-zs, kind="stable")[: min(k, n)]) + cu[b]
+            for got in lists:
+                assert (got[b, h, : min(k, n)] == want).all(), (b, h)
+
+
 @pytest.mark.parametrize("H_q,H_kv,d,lens,k", [(3, 1, 128, (700, 5, 0, 257, 1300), 513), (6, 3, 64, (1030,), 256),
                                                (5, 5, 256, (300, 600, 255), 257), (8, 1, 128, (2000, 1), 1025)])
 def test_gather_of_any_group_count(gpu, H_q, H_kv, d, lens, k):
