@@ -317,12 +317,20 @@ int launch_mask_bwd(const dma_shape& s, const void* V, const float* W, const flo
   const size_t nw = (size_t)s.H_q * s.d;
   fill_zero_kernel<<<(unsigned)((nw + 255) / 256), 256, 0, st>>>(dW, nw, dA, (size_t)s.H_q);
   const int G = s.H_q / s.H_kv;
-  if (s.dtype == DMA_BF16 && (G == 1 || G == 2 || G == 4 || G == 8)) {
+  // The rows kernel's end (sums over its lane groups, then atomics) outweighs its shorter trips while there are few rows
+  // and these are short (us at 64 channels, rows / tile kernel: 256 tokens, 2 / 1 heads 10.5 / 7.2; 8192 tokens, 16 / 4
+  // heads 17.8 / 16.1; 16384 tokens, 16 / 4 heads 20.1 / 24.8).
+  const bool few_rows = s.d == 64 && G > 1 && (long)s.T * s.H_kv <= 32768;
+  if (s.dtype == DMA_BF16 && !few_rows && (G == 1 || G == 2 || G == 4 || G == 8)) {
     const int step = 4 * (64 / (s.d / 8)) * 2;  // rows of one trip of a workgroup
     // Two workgroups per compute unit: every one ends with contended atomics on dW (1024 instead of 512: 29 us instead of
     // 19 at 8192 tokens x 4 kv-heads), and with rows in flight ahead two are enough.  Up to 512 rows each: beyond
     // that the atomics are few and shorter workgroups even out the end (65536 x 16: 84 us at 2048 rows, 71 at 512).
-    long rows = std::min(((long)s.T * s.H_kv + 511) / 512, 512l);
+    // Below 64 rows each the atomics weigh more than idle compute units: one workgroup per unit, half of one where a
+    // row is for at most two q-heads (us, 16 or 32 rows -> this: 16384 tokens, one head, d = 128 19.1 -> 13.7; 8192
+    // tokens, one head, d = 256 19.1 -> 12.7; 4096 tokens, 16 / 4 heads, d = 128 16.9 -> 14.5).
+    const long all_rows = (long)s.T * s.H_kv, wgs = G <= 2 ? 128 : 256;
+    long rows = std::max(std::min((all_rows + 511) / 512, 512l), std::min((all_rows + wgs - 1) / wgs, 64l));
     rows = (rows + step - 1) / step * step;
     const dim3 rgrid((unsigned)((s.T + rows - 1) / rows), s.H_kv);
 #define DMA_MR(DD, GG) \

@@ -13,8 +13,13 @@ from paper_2508_02124_amd import workloads as wlmod
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T", [1, 15, 64, 65, 4099])
-@pytest.mark.parametrize("H_q,H_kv,d", [(2, 2, 64), (8, 1, 64), (4, 2, 128), (3, 1, 128), (8, 2, 128), (8, 1, 256), (2, 1, 256)])
+EDGES = [(T, *heads) for T in (1, 15, 64, 65, 4099)
+         for heads in ((2, 2, 64), (8, 1, 64), (4, 2, 128), (3, 1, 128), (8, 2, 128), (8, 1, 256), (2, 1, 256))]
+# 64 channels and a group: on both sides of the row count from which the rows kernel is taken
+EDGES += [(T, *heads) for T in (16384, 16385) for heads in ((4, 2, 64), (8, 2, 64), (16, 2, 64))]
+
+
+@pytest.mark.parametrize("T,H_q,H_kv,d", EDGES)
 def test_score_gradient_edges(gpu, T, H_q, H_kv, d):
     print(f"[case] score gradient T={T} {H_q}/{H_kv} d={d}", flush=True)
     r = np.random.default_rng(T + 10 * H_q + d)
