@@ -97,26 +97,22 @@ def measured_traffic(kernel):
     return None
 
 
-def clean_pair_count(inp, eg, BQ=256):
-    """Kept (row, key) pairs whose key is resident for ALL rows of the pair's 256-row block (the pairs
-    dkv_kernel<clean> works on), summed over heads; counted on the host from the expiry array."""
+def clean_pair_count(case, k):
+    """Kept (row, key) pairs that dkv_kernel<clean> works on, summed over heads, counted on the host from the
+    (causal) plan: per block and head all rows of the keys resident for the whole block, and the rows from its own on of
+    every key that enters inside the block and stays to its end in a slot column (named -2 - key in the table; a key among
+    its document's first k has a new column of its own)."""
     import numpy as np
-    clean_pairs = 0
-    for a, b in zip(inp.cu_seqlens[:-1], inp.cu_seqlens[1:]):
-        a, b = int(a), int(b)
-        n = b - a
-        if n == 0:
-            continue
-        j = np.arange(n)[None, :]
-        e = eg[:, a:b] - a
-        first = j // BQ + 1                                   # first block a key can be clean in
-        # block bl is clean for the key iff bl >= first and e > min((bl + 1) BQ, n) - 1
-        last_full = np.where(e >= n, (n - 1) // BQ, e // BQ - 1)    # last block with e > its last row
-        nb = np.clip(last_full - first + 1, 0, None) * (e > j)
-        rows_last = n - ((n - 1) // BQ) * BQ                  # rows of the (possibly ragged) last block
-        pairs = nb * BQ - np.where((nb > 0) & (last_full == (n - 1) // BQ), BQ - rows_last, 0)
-        clean_pairs += int(pairs.sum())
-    return clean_pairs
+    eg, pv = case.host("expiry").astype(np.int64), case.plan_views()
+    pairs = 0
+    for b in range(pv["nblk"]):
+        _, r0, r1, doc0 = (int(x) for x in pv["blk"][b])
+        row = pv["slot"][:, b]
+        named = row[row < -1]
+        pairs += int((row >= 0).sum()) * (r1 - r0) + int((r1 + 2 + named.astype(np.int64)).sum())
+        j = np.arange(r0, min(r1, doc0 + k))
+        pairs += int(((eg[:, j] >= r1) * (r1 - j)).sum())
+    return pairs
 
 
 def time_workload(wl, steps, warmup, dev, structured_z=False, calibration_copy=False):
@@ -204,9 +200,8 @@ def roofline_objects(wl, inp, case, rec, with_traffic):
     nact = rec["nact"]
     stage_flops = {"fwd": 4.0 * wl.d * nact * wl.H_q}
     if wl.backward:
-        eg = case.host("expiry").astype(np.int64)
         stage_flops["bwd_dq"] = 6.0 * wl.d * nact * wl.H_q
-        stage_flops["bwd_dkv"] = 8.0 * wl.d * clean_pair_count(inp, eg)
+        stage_flops["bwd_dkv"] = 8.0 * wl.d * clean_pair_count(case, wl.k)
     kernel_names = {"fwd": "fwd_kernel", "bwd_dq": "dq_kernel", "bwd_dkv": "dkv_kernel<clean>"}
     objs = {}
     for st, fl in stage_flops.items():
