@@ -76,8 +76,8 @@ typedef struct {
  * per-block key lists and scratch of the selection), and of the scratch
  * workspace dma_fwd / dma_bwd need.  0 if the shape is invalid.
  * The plan is not linear in T: its slot table holds one int32 per (q-head, block of
- * 256 query rows, slot), slots = min(k, max_seqlen) rounded up to 128, i.e. about
- * H_q * T * min(k, max_seqlen) / 64 bytes, on top of about 40 bytes per (q-head, token)
+ * 256 query rows, slot), slots = min(k, T) rounded up to 128, i.e. about
+ * H_q * T * min(k, T) / 64 bytes, on top of about 40 bytes per (q-head, token)
  * (scores, expiry, key lists, scratch of the selection).  Examples with H_q = 32: 36 MiB
  * at T = 16384, k = 2048; 111 MiB at T = 65536, k = 1024; 0.58 GiB at k = 16384; 2.1 GiB
  * at T = k = 65536 (every key kept: the quadratic corner).  There is no cap: a caller
@@ -93,7 +93,8 @@ size_t dma_workspace_bytes(const dma_shape* shape);
  * mask buffer.  Returns DMA_OK or the error of an invalid shape.
  *   blocks         int32[nblk_cap][4]: {document, first row, end row, document start}; document -1 past the end
  *   slot_table     int32[H_q][nblk_cap][kpad]: resident key of each slot column; below 0 = none for the whole
- *                  block (-2 - key: that key enters inside the block and stays to its end; -1 otherwise)
+ *                  block (-2 - key: that key enters inside the block and stays to its end; -1 otherwise.
+ *                  dma_version() < 141 does not say whether a plan has such entries)
  *   partial_count  int32[H_q][nblk_cap];  partial_list int32[H_q][nblk_cap][max_partial]
  *   header         int32[16], [0] = number of blocks;  zq float[H_q][T] = z / softmax_scale
  */

@@ -261,6 +261,6 @@ const char* dma_strerror(int status) {
   }
 }
 
-int dma_version(void) { return 140; }
+int dma_version(void) { return 141; }
 
 }  // extern "C"

@@ -332,8 +332,11 @@ constexpr int MAXSWEEP = 64;     // most query blocks one key-stationary work it
 // computes while the other waits (slot sweep / partial launch, us, before -> after: 65536 packed tokens, 16 heads,
 // d = 64, window 512: 680 / 248 -> 510 / 180; 16384 tokens, 32 heads, d = 128, window 2048: 1563 / 179 -> 1380 / 196;
 // 16 heads, d = 256: 1885 / 460 -> 1945 / 276).  A register reload inside a step costs more than it looks: it waits
-// for the copies requested just before it.  So nothing may spill there: part of the K fragments waits in LDS, and
-// small lane-dependent values are formed where they are used (fresh_lane).
+// for the copies requested just before it.  So part of the K fragments waits in LDS, and small lane-dependent values
+// are formed where they are used (fresh_lane).  As built: nothing spills at d = 64; 15 registers (sweep) and 6
+// (partial) at d = 128, reloaded at the issue of id copies and at block changes; at d = 256 27 and 48, and there the
+// step itself reloads (sweep: nine dwords at its end, so that the next step's S waits for the copies issued at its
+// head; partial: three times between its products), which is what keeps the sweep above its former 1885 us.
 template <int D, bool PARTIAL>
 __global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : 2) void dkv_kernel(BwdArgs p) {
   using TL = TileLayout<D>;
@@ -685,8 +688,8 @@ __global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : 2) void dkv_kernel(BwdA
     }
     if (ncols == 0 || row0 + SUB * qs >= row1) continue;  // nothing to do this step
     if (PARTIAL) {
-      // none of this wave's keys is active on these rows (entering keys are listed by ascending
-      // first row, expiring ones by ascending end row)
+      // none of this wave's keys is active on these rows (the entering keys that do not stay are listed by
+      // ascending first row, the expiring ones behind them by ascending end row)
       const int rf = row0 + SUB * qs;
       if (!__any((kj < rf + SUB) & (ke > rf))) continue;
     } else if (entering && !__any((curid >= 0) & (kj < row0 + SUB * qs + SUB))) {

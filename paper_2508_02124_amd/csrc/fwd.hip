@@ -197,8 +197,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || D == 256) ? 1 :
     issue_kv(t + NS - 1, (ST + NS - 1) % NS);
     const int ist = t % (2 * NS);  // stage of the tile's ids
     if (t >= nc) {
-      // partial tile: skip it if none of its keys is active on any of this wave's 32 rows (the
-      // lists are ordered by first / last active row, so about half of the wave-tiles drop out)
+      // partial tile: skip it if none of its keys is active on any of this wave's 32 rows (a list is three runs:
+      // entering keys that stay, other entering keys, each by first active row, then expiring ones by last)
       const int jl = ids_ring[ist][l], el = e_ring[ST][l];
       const int rfirst = row0 + 32 * w;
       if (!__any((jl >= 0) & (jl <= rfirst + 31) & (el > rfirst))) return;
