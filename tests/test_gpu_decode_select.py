@@ -1,6 +1,6 @@
 """The one-launch selection of a decode and the grouped gather behind it, at the sizes where they change path:
 keys per wave (multiples of 1024), the register capacities (16384 and 65536 keys), the candidate limits
-(512 ranked, 8192 listed, more = from registers), ties across the threshold, scores of every sign, and
+(512 ranked, 8192 listed, more = counted from all keys), ties across the threshold, scores of every sign, and
 numbers of (sequence, kv-head) pairs that 8 does not divide."""
 from __future__ import annotations
 
