@@ -9,7 +9,8 @@ namespace dma {
 
 // ------------------------------------------------------------------ tiling constants
 constexpr int BQ = 256;        // query rows per block (one workgroup of the query-stationary kernels: 8 waves x 32 rows)
-constexpr int KT = 64;         // keys per tile of the query-stationary kernels
+constexpr int KT = 64;         // keys per tile of dq_kernel
+constexpr int CUS = 256;       // compute units of the chip
 constexpr int MAXPART = 2 * BQ;  // a block has at most BQ entering + BQ expiring keys
 constexpr int SG = 128;        // slot columns per workgroup of the key-stationary backward
 constexpr int SEG_MIN = 4096;  // keys per segment of the selection (what one workgroup sorts in LDS): 4096 when
@@ -243,6 +244,12 @@ __device__ __forceinline__ void dma16s_pair(const void* base_a, const void* base
       : "=&s"(keep)
       : "v"(lane_off), "s"(base_a), "s"(base_b), "s"(lds_a), "s"(lds_b)
       : "memory");
+}
+// One copy of the same kind with the base already in scalar registers (uniform_ptr).
+__device__ __forceinline__ void dma16u(const void* base, uint32_t lane_off, uint32_t lds) {
+  uint32_t keep;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b32 m0, %0"
+               : "=&s"(keep) : "v"(lane_off), "s"(base), "s"(lds));
 }
 // a * b for a, b < 2^24 (one full-rate instruction; the masks fold away)
 __device__ __forceinline__ uint32_t mul24(uint32_t a, uint32_t b) { return (a & 0xffffffu) * (b & 0xffffffu); }

@@ -1,20 +1,27 @@
 // Forward pass (Eq. 5-6; online softmax of Alg. 1, query-stationary so O, l, m stay in registers).
 //
-// One workgroup (8 waves) = one block of BQ = 256 query rows of one head; wave w owns rows
-// 32w .. 32w+31, and the two waves that share a SIMD overlap each other's MFMA and softmax work.
-// The keys a block needs are gathered, KT at a time, into a ring of LDS stages by asynchronous
-// global->LDS copies issued NS-1 tiles ahead (no staging registers): first the slot table row of
+// One workgroup = one block of BQ = 256 query rows of one head (8 waves) or half of one (4 waves); wave w owns 32 of
+// its rows.  The keys a block needs are gathered a tile at a time (64 keys, or 32) into rings of four LDS stages by
+// asynchronous global->LDS copies issued two to three tiles ahead (no staging registers): first the slot table row of
 // the block (residents active for every row of the block: no mask needed, empty slots carry
 // z = -inf), then the block's partial list (keys entering or expiring inside the block: pairs
-// outside j <= i < e_j start their score at -inf).  The key ids of a tile are themselves copied
-// into an LDS ring NS-1 tiles before the tile's K/V copies are issued, so no register ever waits
-// on a load.
+// outside j <= i < e_j get a score of -inf).  The key ids of a tile are themselves copied
+// into an LDS ring two tiles before the tile's K copies are issued, so no register ever waits on a load.
 //
-// Per tile the wave computes S^T = K Q^T (keys x queries) so that each lane holds one query column
-// per block: the softmax statistics are per lane, and the exponentiated block is already laid out
+// Work is done in units of 32 keys.  The wave computes S^T = K Q^T (keys x queries) so that each lane holds one query
+// column: the softmax statistics are per lane, and the exponentiated block is already laid out
 // as the B operand of O^T += V^T P^T.  The bias z is not added after the product: the accumulator
-// starts at z / scale, so scale * acc is the biased score and one FMA gives the exp2 argument.
+// starts at z / scale, so scale * acc is the biased score and one FMA gives the exp2 argument.  The step of a unit also
+// holds the next unit's S product and the previous unit's PV product, interleaved with its exponentials instruction by
+// instruction.
+//
+// What bounds it: at 64K tokens, 32 heads, d = 128, window 16384 a tile of 64 keys takes 3100 cycles against 2048 of the
+// matrix pipe, at a clock that the power limit holds at 1.8 to 1.9 GHz: fewer instructions and fewer bytes moved give
+// more than a tighter schedule (leaving out the copies alone raises the clock by 15 %).  Each wave doing the whole
+// chain of a tile at a time took 15.1 ms there, this form 13.9; 16384 tokens, window 2048: 592 -> 548 us; 16 heads of
+// 256 channels, where no second wave of a SIMD fills the gaps: 882 -> 628 us.
 #include "common.h"
+#include <cmath>
 #include <type_traits>
 
 namespace dma {
@@ -33,36 +40,49 @@ struct FwdArgs {
   int T, H_q, H_kv, k, nblk_cap, kpad;
 };
 
-constexpr float MSLACK = 8.f;  // log2 slack of the lazily updated softmax reference maximum
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>)
+template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
+// Largest sum of a lane's sixteen weights of one unit that the fast path accepts, as the bits of a float: every weight
+// is then at most 2^8.  Infinities and NaNs (nothing kept so far: reference maximum -inf) compare above it.
+constexpr uint32_t SUM_LIMIT = 0x43800000u;
 
 // (second launch bound = waves per SIMD: at D = 64 the kernel is held to 128 registers so that two
 // workgroups share a compute unit -- four waves per SIMD hide the element-wise work, which weighs
 // twice as much per MFMA there; at D = 128 the accumulators alone need more than that)
-// NW waves per workgroup: 8 (one 256-row block per workgroup, four ring stages) or 4 (half a block,
-// two ring stages, two workgroups per compute unit: the two waves of a SIMD then belong to different
-// workgroups and do not meet at the same barriers).
-template <int D, int NW>
-__global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || D == 256) ? 1 : 2)) void fwd_kernel(FwdArgs p) {
+// NW waves per workgroup: 8 (one 256-row block per workgroup) or 4 (half a block); UT 32-key units per tile.  Four waves
+// with tiles of 32 keys leave room for a second workgroup on the compute unit: the two waves of a SIMD then belong to
+// different workgroups and do not meet at the same barriers.
+template <int D, int NW, int UT>
+__global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D == 256) ? 1 : 2)) void fwd_kernel(FwdArgs p) {
   using TL = TileLayout<D>;
   constexpr int KS = D / 16;          // contraction steps of K Q^T
   constexpr int CB = D / 32;          // 32-channel blocks of O^T
   constexpr int CPR = D / 8;          // 16-byte chunks per row
   constexpr int RPL = 64 / CPR;       // rows covered by one wave-wide 16-byte copy
+  constexpr int KT = 32 * UT;         // keys per tile
   constexpr int WL = KT / RPL / NW;   // such copies per wave per K (or V) tile
-  constexpr int NS = NW == 8 ? 4 : 2; // ring stages
+  constexpr int NS = 4;               // ring stages
   constexpr int NT = NW * 64;         // threads
   constexpr int HALVES = 8 / NW;      // workgroups per 256-row block
   constexpr int TILE = KT * D;        // elements of one K or V tile
   __shared__ __align__(16) uint16_t ringK[NS * TILE];
   __shared__ __align__(16) uint16_t ringV[NS * TILE];
-  __shared__ __align__(16) int ids_ring[2 * NS][KT];
-  __shared__ __align__(16) float z_ring[NS][KT];
-  __shared__ __align__(16) int e_ring[NS][KT];
+  __shared__ __align__(16) int ids_ring[2 * NS][64];  // (rows of 64: what one wave-wide copy writes)
+  __shared__ __align__(16) float z_ring[NS][64];
+  __shared__ __align__(16) int e_ring[NS][64];
 
   int h, item;
   if (!xcd_map(wg_id(), p.H_q, p.nblk_cap * HALVES, h, item)) return;
   const int bi = p.nblk_cap - 1 - item / HALVES;  // long blocks first
   const int4 info = p.blk[bi];
+  const int np_keys = p.pcnt[(size_t)h * p.nblk_cap + bi];
+  const float c2 = *reinterpret_cast<const float*>(p.consts + PLAN_C2_OFF);  // softmax scale * log2(e)
   if (info.x < 0) return;
   const int blk_row0 = info.y, row1 = info.z, doc0 = info.w;
   const int row0 = blk_row0 + (item % HALVES) * (NW * 32);  // first row of this workgroup's part of the block
@@ -71,7 +91,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || D == 256) ? 1 :
   const int tid = thread_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, n = l & 31, hh = l >> 5;
   const int ncol = min(p.k, blk_row0 - doc0);
   const int nc = (ncol + KT - 1) / KT;
-  const int np_keys = p.pcnt[(size_t)h * p.nblk_cap + bi];
+  const int shift = (NS - nc % NS) % NS;  // ring stage of tile 0: tile t takes stage (t + shift) % NS
   const int nt = nc + (np_keys + KT - 1) / KT;
   const int32_t* slot_row = p.slot_tab + ((size_t)h * p.nblk_cap + bi) * p.kpad;
   const int32_t* plist_row = p.plist + ((size_t)h * p.nblk_cap + bi) * MAXPART;
@@ -80,7 +100,6 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || D == 256) ? 1 :
   const float* c_ninf = reinterpret_cast<const float*>(p.consts + 256);
   const int32_t* c_zero = reinterpret_cast<const int32_t*>(p.consts + 260);
   const int32_t* c_m1 = reinterpret_cast<const int32_t*>(p.consts + 264);
-  const float c2 = *reinterpret_cast<const float*>(p.consts + PLAN_C2_OFF);  // softmax scale * log2(e)
 
   // ---- asynchronous producers (every wave issues the same number of copies for every tile index,
   // real or past the end, so the outstanding-copy counts below are constants).  A gathered row is
@@ -102,48 +121,53 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || D == 256) ? 1 :
   auto issue_ids = [&](int tt) {
     if (w == 0) {
       const int32_t* src = c_m1;
+      const int ll = l & (KT - 1);
       if (tt < nc) {
-        src = slot_row + tt * KT + l;
+        src = slot_row + tt * KT + ll;
       } else if (tt < nt) {
-        const int q = (tt - nc) * KT + l;
+        const int q = (tt - nc) * KT + ll;
         if (q < np_keys) src = plist_row + q;
       }
       dma4(src, &ids_ring[tt % (2 * NS)][0]);
     }
   };
-  auto issue_kv = [&](int tt, int st) {  // st = tt % NS (a constant in the main loop)
+  // rows of tile tt: the key ids first (an LDS read), the copies once they are there
+  auto row_ids = [&](int tt, int (&idv)[WL]) __attribute__((always_inline)) {
     const int* idr = ids_ring[tt % (2 * NS)];
-    int idv[WL];
 #pragma unroll
     for (int j = 0; j < WL; j++) idv[j] = idr[lane_row[j]];
-    int idl = 0;
-    if (w == 1) idl = idr[l];
+  };
+  auto copy_rows = [&](const void* base, uint32_t lds, int stage, const int (&idv)[WL]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < WL; j++) {
-      const uint32_t off = mul24((uint32_t)max(idv[j], 0), row_pitch) + lane_chunk[j];
-      const uint32_t dst = (uint32_t)((st * TILE + j * RPL * D) * 2);
-      dma16s_pair(Kg, Vg, off, ldsK + dst, ldsV + dst);
-    }
+    for (int j = 0; j < WL; j++)
+      dma16u(base, mul24((uint32_t)max(idv[j], 0), row_pitch) + lane_chunk[j],
+             lds + (uint32_t)((stage * TILE + j * RPL * D) * 2));
+  };
+  auto issue_rows = [&](const void* base, uint32_t lds, int tt) __attribute__((always_inline)) {
+    int idv[WL];
+    row_ids(tt, idv);
+    copy_rows(base, lds, (tt + shift) % NS, idv);
+  };
+  auto issue_scalars = [&](int tt) {
     if (w == 1) {
-      dma4(idl >= 0 ? zqh + idl : c_ninf, &z_ring[st][0]);
-      dma4(idl >= 0 ? (const void*)(eh + idl) : (const void*)c_zero, &e_ring[st][0]);
+      const int idl = ids_ring[tt % (2 * NS)][l];
+      dma4(idl >= 0 ? zqh + idl : c_ninf, &z_ring[(tt + shift) % NS][0]);
+      dma4(idl >= 0 ? (const void*)(eh + idl) : (const void*)c_zero, &e_ring[(tt + shift) % NS][0]);
     }
   };
-  // copies a wave issues per tile step, and how many may still be in flight when tile t is needed
+  // Iteration t of the tile loops requests the ids of tile t + 5, K rows and scalars of tile t + 3 and V rows of tile
+  // t + 2, and starts when everything requested before iteration t - 1 has landed: K up to tile t + 1, V up to tile t.
+  auto issue_small = [&](int t) __attribute__((always_inline)) {
+    issue_ids(t + 5);
+    issue_scalars(t + 3);
+  };
   auto wait_tile = [&]() {
-    if (w == 0) wait_vmcnt<(NS - 2) * (2 * WL + 1)>();
-    else if (w == 1) wait_vmcnt<(NS - 2) * (2 * WL + 2)>();
-    else wait_vmcnt<(NS - 2) * (2 * WL)>();
+    if (w == 0) wait_vmcnt<2 * WL + 1>();
+    else if (w == 1) wait_vmcnt<2 * WL + 2>();
+    else wait_vmcnt<2 * WL>();
   };
 
-  for (int tt = 0; tt < NS - 1; tt++) issue_ids(tt);
-  wait_vmcnt<0>();
-  lds_barrier();
-  for (int i = 0; i < NS - 1; i++) {
-    issue_ids(NS - 1 + i);
-    issue_kv(i, i);
-  }
-
+  for (int tt = 0; tt < 5; tt++) issue_ids(tt);
   // query fragments (B operand of K Q^T): lane holds row qi, channels 16*ks + 8*hh .. +8
   const int qi = row0 + 32 * w + n;
   bf16x8 qreg[KS];
@@ -155,9 +179,21 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || D == 256) ? 1 :
       if (qi < row1) raw = *reinterpret_cast<const uint4*>(qrow + 16 * ks);
       qreg[ks] = __builtin_bit_cast(bf16x8, raw);
     }
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) settle(qreg[ks]);
   }
+  // The pipelined loop's first step multiplies the (zero) weights before the first unit with the last unit of the ring
+  // stage before it: those rows have to hold numbers.
+  for (int c = tid; c < 32 * CPR; c += NT)
+    reinterpret_cast<uint4*>(ringV + (shift + NS - 1) % NS * TILE + TILE - 32 * D)[c] = make_uint4(0, 0, 0, 0);
+  wait_vmcnt<0>();
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) settle(qreg[ks]);
+  lds_barrier();
+  for (int i = 0; i < 3; i++) {
+    issue_rows(Kg, ldsK, i);
+    issue_scalars(i);
+    if (i < 2) issue_rows(Vg, ldsV, i);
+  }
+
   // The lane's fragment addresses with the ring bases folded in: inside the (stage-unrolled) main
   // loop every LDS read is one of these registers plus an immediate.
   FragOffsets<D> fo;
@@ -184,113 +220,231 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || D == 256) ? 1 :
 #pragma unroll
     for (int v = 0; v < 16; v++) oacc[cb][v] = 0.f;
   float m_run = -INFINITY, lsum = 0.f;
-  // the query loads above are ordinary loads issued after the prologue copies; wait for them here so
-  // that the per-tile counts below only ever see copies
-  wait_vmcnt<0>();
 
-  // one key tile; ST = t % NS is a compile-time constant (the loop below is unrolled over the ring)
-  auto tile = [&](auto stc, const int t) {
-    constexpr int ST = decltype(stc)::value;
-    if (t > 0) wait_tile();  // (t == 0: the wait above already drained everything)
-    lds_barrier();
-    issue_ids(t + 2 * NS - 2);
-    issue_kv(t + NS - 1, (ST + NS - 1) % NS);
-    const int ist = t % (2 * NS);  // stage of the tile's ids
-    if (t >= nc) {
-      // partial tile: skip it if none of its keys is active on any of this wave's 32 rows (a list is three runs:
-      // entering keys that stay, other entering keys, each by first active row, then expiring ones by last)
-      const int jl = ids_ring[ist][l], el = e_ring[ST][l];
-      const int rfirst = row0 + 32 * w;
-      if (!__any((jl >= 0) & (jl <= rfirst + 31) & (el > rfirst))) return;
+  // S^T of one unit; its accumulator starts at z / scale, so that scale * acc is the biased score.  so, zo: byte offsets
+  // of the unit in the K ring and in the ring of the scalars.
+  auto start_scores = [&](uint32_t zo) __attribute__((always_inline)) {
+    f32x16 s;
+#pragma unroll
+    for (int gq = 0; gq < 4; gq++) {
+      const f32x4 zz = lds_load<f32x4>(zlane + zo + 32 * gq);
+#pragma unroll
+      for (int u = 0; u < 4; u++) s[4 * gq + u] = zz[u];
     }
-
-    // The accumulator of S^T = K Q^T starts at z / scale, so that scale * acc is the biased score;
-    // in a partial tile, pairs outside [j, e_j) start (and stay) at -inf.
-    f32x16 sacc[2];
+    return s;
+  };
+  auto scores = [&](f32x16& s, uint32_t so) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kb = 0; kb < 2; kb++)
+    for (int ks = 0; ks < KS; ks++) s = mfma32(lds_load<bf16x8>(kfrag[ks] + so), qreg[ks], s);
+  };
+  // Weights of one unit from its scores, and the statistics.  The reference maximum m_run of a row moves only when a
+  // weight would get large: the exponentials are formed with the old one and summed, and only if a lane's sum shows a
+  // weight that could exceed 2^8 is the unit's maximum looked for, O and l rescaled and the unit's weights formed
+  // again.  Same softmax; no maximum in the common case.
+  auto exponentials = [&](const f32x16& s, bf16x8 (&pb)[2], float nm) __attribute__((always_inline)) {
+    float l0 = 0.f, l1 = 0.f;
 #pragma unroll
-      for (int gq = 0; gq < 4; gq++) {
-        const f32x4 zz = lds_load<f32x4>(zlane + 4 * (ST * KT + 32 * kb + 8 * gq));
-#pragma unroll
-        for (int u = 0; u < 4; u++) sacc[kb][4 * gq + u] = zz[u];
-      }
-    if (t >= nc) {
-      const uint32_t js = jlane + 4 * ist * KT;
-#pragma unroll
-      for (int kb = 0; kb < 2; kb++)
-#pragma unroll
-        for (int gq = 0; gq < 4; gq++) {
-          const i32x4 jj = lds_load<i32x4>(js + 4 * (32 * kb + 8 * gq));
-          const i32x4 ee = lds_load<i32x4>(elane + 4 * (ST * KT + 32 * kb + 8 * gq));
-#pragma unroll
-          for (int u = 0; u < 4; u++) {
-            const bool ok = (jj[u] >= 0) & (qi >= jj[u]) & (qi < ee[u]);
-            sacc[kb][4 * gq + u] = ok ? sacc[kb][4 * gq + u] : -INFINITY;
-          }
-        }
+    for (int v = 0; v < 16; v++) {
+      const float pv = fast_exp2(fmaf(s[v], c2, nm));
+      if (v & 1) l1 += pv; else l0 += pv;
+      pb[v >> 3][v & 7] = (__bf16)pv;
     }
-    // two independent accumulation chains (the tile's two 32-key halves), interleaved
+    return l0 + l1;
+  };
+  auto take_sum = [&](const f32x16& s, bf16x8 (&pb)[2], float sum) __attribute__((always_inline)) {
+    if (__builtin_expect(__any(__builtin_bit_cast(uint32_t, sum) > SUM_LIMIT), 0)) {
+      float mx = fmaxf(s[0], s[1]);
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++)
-#pragma unroll
-      for (int kb = 0; kb < 2; kb++) {
-        const bf16x8 kf = lds_load<bf16x8>(kfrag[ks] + 2 * (ST * TILE + 32 * kb * D));
-        sacc[kb] = mfma32(kf, qreg[ks], sacc[kb]);
-      }
-    // Online softmax in the exp2 domain with a lazily updated reference maximum: m_run moves only
-    // when the tile's maximum exceeds it by more than MSLACK, so that the rescaling of O and l is
-    // rare; until then the exponentials are at most 2^MSLACK, which fp32 accumulation absorbs.
-    float mx = fmaxf(sacc[0][0], sacc[1][0]);
-#pragma unroll
-    for (int v = 1; v < 16; v++) mx = fmaxf(fmaxf(mx, sacc[0][v]), sacc[1][v]);  // one three-input maximum each
-    mx = half_swap_max(mx) * c2;
-    const bool grow = mx > m_run + MSLACK;
-    if (__any(grow)) {
-      const float m_new = grow ? mx : m_run;
-      const float alpha = grow ? fast_exp2(m_run - m_new) : 1.f;  // m_run = -inf: 0, nothing accumulated yet
-      m_run = m_new;
+      for (int v = 2; v < 16; v++) mx = fmaxf(mx, s[v]);
+      mx = half_swap_max(mx) * c2;
+      const bool grow = mx > m_run;
+      const float alpha = grow ? fast_exp2(m_run - mx) : 1.f;  // m_run = -inf: 0, nothing accumulated yet
+      m_run = grow ? mx : m_run;
       lsum *= alpha;
 #pragma unroll
       for (int cb = 0; cb < CB; cb++)
 #pragma unroll
         for (int v = 0; v < 16; v++) oacc[cb][v] *= alpha;
+      sum = exponentials(s, pb, m_run == -INFINITY ? 0.f : -m_run);  // nothing kept so far: exp2(-inf - 0) = 0
     }
-    const float msub = (m_run == -INFINITY) ? 0.f : m_run;  // row with nothing kept so far: exp2(-inf - 0) = 0
-    bf16x8 pb[4];  // the four 16-key quarters
-    float ls2 = 0.f;  // (two chains: the sums stay fp32-exact in the weights, LSE feeds the backward)
-#pragma unroll
-    for (int kb = 0; kb < 2; kb++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) {
-        const float pv = fast_exp2(fmaf(sacc[kb][v], c2, -msub));
-        if (kb == 0) lsum += pv; else ls2 += pv;
-        pb[2 * kb + (v >> 3)][v & 7] = (__bf16)pv;
-      }
-    lsum += ls2;
-    // O^T += V^T P^T
-#pragma unroll
-    for (int c = 0; c < 4; c++)
-#pragma unroll
-      for (int cb = 0; cb < CB; cb++) {
-        const s16x4 lo = lds_read_tr_at(vfrag[cb][0] + 2 * (ST * TILE + 16 * c * D));
-        const s16x4 hi = lds_read_tr_at(vfrag[cb][1] + 2 * (ST * TILE + 16 * c * D));
-        const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-        oacc[cb] = mfma32(vf, pb[c], oacc[cb]);
-      }
+    lsum += sum;
   };
-  for (int t = 0; t < nt; t += NS) {
-    tile(std::integral_constant<int, 0>{}, t);
-    if (t + 1 >= nt) break;
-    tile(std::integral_constant<int, 1>{}, t + 1);
-    if constexpr (NS == 4) {
-      if (t + 2 >= nt) break;
-      tile(std::integral_constant<int, 2>{}, t + 2);
-      if (t + 3 >= nt) break;
-      tile(std::integral_constant<int, 3>{}, t + 3);
+  auto value_frag = [&](int i, uint32_t so) __attribute__((always_inline)) {  // A operand of the i-th product of O^T += V^T P^T
+    const int c = i / CB, cb = i % CB;
+    const s16x4 lo = lds_read_tr_at(vfrag[cb][0] + so + 2 * 16 * c * D);
+    const s16x4 hi = lds_read_tr_at(vfrag[cb][1] + so + 2 * 16 * c * D);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  // O^T += V^T P^T of one unit
+  auto accumulate = [&](const bf16x8 (&pb)[2], uint32_t so) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 2 * CB; i++) oacc[i % CB] = mfma32(value_frag(i, so), pb[i / CB], oacc[i % CB]);
+  };
+  constexpr uint32_t UB = 2 * 32 * D;  // bytes of one unit in a ring
+
+  int t = 0;
+  wait_vmcnt<0>();
+  lds_barrier();
+  // ---- tiles, software-pipelined: the step of unit i holds the products S(i + 1) and O += V P(i - 1) and the
+  // exponentials of unit i, which depend on none of them, so that the matrix pipe has work while the wave issues the
+  // element-wise instructions.  The order is fixed where one or two waves share a SIMD: a product, the LDS read of the
+  // fragment LEAD products ahead, and a share of the element-wise work.
+  bf16x8 pn0[2];  // weights of the unit before
+  pn0[0] = pn0[1] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
+  f32x16 sc = start_scores(4 * 64 * shift);
+  scores(sc, shift * (2 * TILE));
+  bool act0 = true, act1 = true;  // partial tiles: the unit before, this unit has a key that is active on a row of the wave
+  constexpr int NM = KS + 2 * CB;  // products of a step: KS of the next unit's scores, then 2 CB of the previous unit's output
+  // (64 channels: four waves share a SIMD and overlap by themselves; their 128 registers do not hold fragments read
+  // ahead, nor the masks of a pipelined partial step: there the order is the compiler's and partial units run one by one)
+  constexpr bool FIXED = D != 64;
+  constexpr int LEAD = D == 256 ? 6 : D == 128 ? 4 : 0;
+  auto tile = [&](auto stc, auto maskedc) __attribute__((always_inline)) {
+    constexpr int ST = decltype(stc)::value;  // (t + shift) % NS
+    constexpr bool MASKED = decltype(maskedc)::value;
+    if (t > 0) {
+      wait_tile();
+      lds_barrier();
     }
+    issue_small(t);
+    static_for<UT>([&](auto uc) __attribute__((always_inline)) {
+      constexpr int u = decltype(uc)::value;
+      constexpr int ss = u + 1 < UT ? ST : (ST + 1) % NS, su = u + 1 < UT ? u + 1 : 0;
+      constexpr int vs = u > 0 ? ST : (ST + NS - 1) % NS, vu = u > 0 ? u - 1 : UT - 1;
+      constexpr uint32_t ko = ss * (2 * TILE) + su * UB, vo = vs * (2 * TILE) + vu * UB;
+      int idv[WL];
+      if constexpr (MASKED) {
+        // Skip the step if no key of its three units is active on any of this wave's 32 rows (a list is three runs:
+        // entering keys that stay, other entering keys, each by first active row, then expiring ones by last).
+        const int rfirst = row0 + 32 * w, tn = u + 1 < UT ? t : t + 1;
+        const int jl = ids_ring[tn % (2 * NS)][32 * su + n], el = e_ring[ss][32 * su + n];
+        const bool act2 = __any((jl <= rfirst + 31) & (el > rfirst));  // (an empty entry has el = 0)
+        const bool run = act0 | act1 | act2;
+        act0 = act1;
+        act1 = act2;
+        if (!run) {
+#pragma unroll
+          for (int v = 0; v < 16; v++) sc[v] = -INFINITY;
+          pn0[0] = pn0[1] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
+          if constexpr (u == 0) {
+            row_ids(t + 3, idv);
+            copy_rows(Kg, ldsK, (ST + 3) % NS, idv);
+          }
+          if constexpr (u == UT - 1) {
+            row_ids(t + 2, idv);
+            copy_rows(Vg, ldsV, (ST + 2) % NS, idv);
+          }
+          return;
+        }
+        // pairs outside [j, e_j) get no weight
+        const uint32_t js = jlane + 4 * ((t % (2 * NS)) * 64 + 32 * u);
+#pragma unroll
+        for (int gq = 0; gq < 4; gq++) {
+          const i32x4 jj = lds_load<i32x4>(js + 32 * gq);
+          const i32x4 ee = lds_load<i32x4>(elane + 4 * (ST * 64 + 32 * u) + 32 * gq);
+#pragma unroll
+          for (int v = 0; v < 4; v++) sc[4 * gq + v] = ((qi >= jj[v]) & (qi < ee[v])) ? sc[4 * gq + v] : -INFINITY;
+        }
+      }
+      f32x16 sn = start_scores(4 * (ss * 64 + 32 * su));
+      bf16x8 fr[LEAD + 1], pn[2];
+      float pv[16], l0 = 0.f, l1 = 0.f;
+      const float nm = -m_run;
+      auto frag = [&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value;
+        if constexpr (m < KS) fr[m % (LEAD + 1)] = lds_load<bf16x8>(kfrag[m] + ko);
+        else if constexpr (m < NM) fr[m % (LEAD + 1)] = value_frag(m - KS, vo);
+      };
+      static_for<LEAD>(frag);
+      if constexpr (FIXED) __builtin_amdgcn_sched_barrier(0);
+      static_for<NM>([&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value;
+        if constexpr (u == 0 && m == 0) row_ids(t + 3, idv);
+        if constexpr (u == UT - 1 && m == NM / 2) row_ids(t + 2, idv);
+        frag(std::integral_constant<int, m + LEAD>{});
+        if constexpr (m < KS) sn = mfma32(fr[m % (LEAD + 1)], qreg[m], sn);
+        else oacc[(m - KS) % CB] = mfma32(fr[m % (LEAD + 1)], pn0[(m - KS) / CB], oacc[(m - KS) % CB]);
+        // element-wise work of unit i: the exponentials of some scores, sum and rounding of those before
+        constexpr int e0 = m * 16 / (NM - 2) < 16 ? m * 16 / (NM - 2) : 16;
+        constexpr int e1 = (m + 1) * 16 / (NM - 2) < 16 ? (m + 1) * 16 / (NM - 2) : 16;
+        constexpr int f0 = m > 0 ? (m - 1) * 16 / (NM - 2) : 0;
+#pragma unroll
+        for (int v = e0; v < e1; v++) pv[v] = fast_exp2(fmaf(sc[v], c2, nm));
+#pragma unroll
+        for (int v = f0; v < e0; v++) {
+          if (v & 1) l1 += pv[v]; else l0 += pv[v];
+          pn[v >> 3][v & 7] = (__bf16)pv[v];
+        }
+        if constexpr (u == 0 && m == NM / 2 - 2) copy_rows(Kg, ldsK, (ST + 3) % NS, idv);
+        if constexpr (u == UT - 1 && m == NM - 2) copy_rows(Vg, ldsV, (ST + 2) % NS, idv);
+        if constexpr (FIXED) __builtin_amdgcn_sched_barrier(0);
+      });
+      if constexpr (FIXED) {
+        settle(pn[0]);
+        settle(pn[1]);
+      }
+      take_sum(sc, pn, l0 + l1);
+      sc = sn;
+      pn0[0] = pn[0];
+      pn0[1] = pn[1];
+    });
+    t++;
+  };
+  // (Ring stages are shifted so that the last clean tile takes the last stage and the first partial one stage 0: one
+  // way in and one way out of each loop, and no register moves at their ends.)
+  constexpr std::integral_constant<int, 0> s0{};
+  constexpr std::integral_constant<int, 1> s1{};
+  constexpr std::integral_constant<int, 2> s2{};
+  constexpr std::integral_constant<int, 3> s3{};
+  for (int base = -shift; base < nc; base += NS) {
+    if (base >= 0) tile(s0, std::false_type{});
+    if (base + 1 >= 0) tile(s1, std::false_type{});
+    if (base + 2 >= 0) tile(s2, std::false_type{});
+    tile(s3, std::false_type{});
   }
-  static_assert(NS == 4 || NS == 2, "the main loop is unrolled over the ring stages");
+  if constexpr (!FIXED) {
+    if (nc > 0) accumulate(pn0, (NS - 1) * (2 * TILE) + (UT - 1) * UB);
+    for (; t < nt; t++) {
+      if (t > 0) {
+        wait_tile();
+        lds_barrier();
+      }
+      issue_small(t);
+      issue_rows(Kg, ldsK, t + 3);
+      issue_rows(Vg, ldsV, t + 2);
+      const int st = (t + shift) % NS, ist = t % (2 * NS);
+      const int rfirst = row0 + 32 * w;
+#pragma unroll 1
+      for (int u = 0; u < UT; u++) {
+        const int jl = ids_ring[ist][32 * u + n], el = e_ring[st][32 * u + n];
+        if (!__any((jl <= rfirst + 31) & (el > rfirst))) continue;  // (an empty entry has el = 0)
+        const uint32_t zo = 4 * (st * 64 + 32 * u), so = st * (2 * TILE) + u * UB;
+        f32x16 s = start_scores(zo);
+        const uint32_t js = jlane + 4 * (ist * 64 + 32 * u);
+#pragma unroll
+        for (int gq = 0; gq < 4; gq++) {
+          const i32x4 jj = lds_load<i32x4>(js + 32 * gq);
+          const i32x4 ee = lds_load<i32x4>(elane + zo + 32 * gq);
+#pragma unroll
+          for (int v = 0; v < 4; v++) s[4 * gq + v] = ((qi >= jj[v]) & (qi < ee[v])) ? s[4 * gq + v] : -INFINITY;
+        }
+        scores(s, so);
+        bf16x8 pb[2];
+        const float sum = exponentials(s, pb, -m_run);
+        take_sum(s, pb, sum);
+        accumulate(pb, so);
+      }
+    }
+  } else {
+    for (int base = nc; base < nt; base += NS) {
+      tile(s0, std::true_type{});
+      if (base + 1 < nt) tile(s1, std::true_type{});
+      if (base + 2 < nt) tile(s2, std::true_type{});
+      if (base + 3 < nt) tile(s3, std::true_type{});
+    }
+    static_assert(NS == 4, "the loops are unrolled over the ring stages");
+    accumulate(pn0, ((nt + shift + NS - 1) % NS) * (2 * TILE) + (UT - 1) * UB);
+  }
 
   // epilogue: drain the (dummy) copies still in flight, normalise, stage O through LDS for
   // coalesced rows, write LSE
@@ -338,16 +492,23 @@ int launch_fwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
   a.consts = p.plan + L.off_consts;
   a.T = s.T; a.H_q = s.H_q; a.H_kv = s.H_kv; a.k = s.k; a.nblk_cap = L.nblk_cap; a.kpad = L.kpad;
   prof_begin(DMA_STAGE_FWD, st);
-  // Small problems (fewer than four 256-row blocks per compute unit, e.g. 2 x 4096 tokens x 16 heads) run
-  // the half-block variant: twice as many, shorter work items balance better over the chip (-7 % there);
-  // at the headline size the two variants measure the same and the whole-block one gathers half as much.
-  const bool half_blocks = s.d == 128 && (long)s.H_q * L.nblk_cap < 1024;
+  // 128 channels: whole blocks of eight waves, unless they would leave the chip idle.  One half block of four waves per
+  // compute unit, with tiles of 64 keys, where all half blocks fit the chip at once (us, whole / half blocks: 1024 tokens
+  // x 32 heads 34.7 / 30.6, 2048 x 16 48.6 / 42.3; twice as many items 53 / 68).  Otherwise half blocks with tiles of 32
+  // keys, two per compute unit, where whole blocks would keep less than 4/5 of it busy: the last round of blocks is not
+  // full, or, in a single round, documents are not much longer than the window, so that blocks differ in length
+  // (2048 x 32 53.6 / 51.7, 7 documents in 10007 x 8 window 333 49.4 / 46.9; above the line 8192 x 8 53.2 / 57.7,
+  // 2 x 4096 x 16 92 / 98).
+  const double blocks = (double)s.H_q * ((s.T + BQ - 1) / BQ), rounds = std::ceil(blocks / CUS);
+  const double len = (double)s.T / s.n_docs, window = s.k < len ? s.k : len;
+  const double busy = blocks / (CUS * rounds) * (1. - window / (2. * len) / rounds);
   // 256 channels: half blocks of four waves, one per SIMD with the whole register file (the output
   // accumulators alone are 128 registers per wave).
-  if (s.d == 256) fwd_kernel<256, 4><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 256, 0, st>>>(a);
-  else if (half_blocks) fwd_kernel<128, 4><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 256, 0, st>>>(a);
-  else if (s.d == 128) fwd_kernel<128, 8><<<xcd_grid(s.H_q, L.nblk_cap), 512, 0, st>>>(a);
-  else fwd_kernel<64, 8><<<xcd_grid(s.H_q, L.nblk_cap), 512, 0, st>>>(a);
+  if (s.d == 256) fwd_kernel<256, 4, 1><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 256, 0, st>>>(a);
+  else if (s.d == 64) fwd_kernel<64, 8, 2><<<xcd_grid(s.H_q, L.nblk_cap), 512, 0, st>>>(a);
+  else if (2 * blocks <= CUS) fwd_kernel<128, 4, 2><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 256, 0, st>>>(a);
+  else if (busy < 0.8) fwd_kernel<128, 4, 1><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 256, 0, st>>>(a);
+  else fwd_kernel<128, 8, 2><<<xcd_grid(s.H_q, L.nblk_cap), 512, 0, st>>>(a);
   prof_end(DMA_STAGE_FWD, st);
   return hipGetLastError() == hipSuccess ? DMA_OK : DMA_EHIP;
 }

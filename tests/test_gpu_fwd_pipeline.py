@@ -1,0 +1,49 @@
+"""The pipelined forward at the edges of its tiles: clean tile counts of every remainder of the ring, documents that end
+inside a block, each form that the dispatch chooses, and rows whose reference maximum moves again and again."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle as orc
+from paper_2508_02124_amd import workloads as wlmod
+from gpu_harness import DeviceCase, check_close, tol
+
+pytestmark = pytest.mark.gpu
+
+# q-heads, kv-heads, head dimension, documents, windows.  At 128 channels: half blocks with 64-key tiles (few blocks),
+# half blocks with 32-key tiles (160 blocks on 256 compute units), whole blocks (256 blocks and a short window).
+FORMS = {
+    "d128_half64": (2, 1, 128, (700, 33, 515), (1, 31, 33, 64, 65, 129, 193, 256, 300)),
+    "d128_half32": (32, 8, 128, (1280,), (33, 100, 200)),
+    "d128_whole": (32, 8, 128, (1025, 1023), (65, 130, 200)),
+    "d256": (2, 1, 256, (700, 33, 515), (1, 31, 33, 64, 65, 97, 129, 300)),
+    "d64": (2, 1, 64, (700, 33, 515), (1, 31, 33, 64, 65, 129, 193, 300)),
+}
+
+
+def forward(gpu, name, k, grow):
+    H_q, H_kv, d, lens, _ = FORMS[name]
+    inp = wlmod.make_inputs(wlmod.small_workload(f"{name}_k{k}", 900 + k, H_q, H_kv, d, k, lens))
+    if grow:  # scores that climb along the keys by far more than 2^8 in the weights, with steps up and down on the way
+        j = np.arange(inp.T, dtype=np.float32)
+        slope = (j / 40 + 8 * np.sin(j / 9)) / np.sqrt(d)
+        inp.Q[:] = wlmod.bf16_bits_to_f32(wlmod.f32_to_bf16_bits(0.25 * inp.Q + 1))
+        inp.K[:] = wlmod.bf16_bits_to_f32(wlmod.f32_to_bf16_bits(0.25 * inp.K + slope[:, None, None]))
+        for x in ("Q", "K"):
+            inp.bits[x] = wlmod.f32_to_bf16_bits(getattr(inp, x))
+    case = DeviceCase(inp, gpu)
+    case.mask_gen()
+    case.fwd()
+    heads = sorted({0, H_q - 1})
+    O, LSE = orc.dma_forward(inp.Q, inp.K, inp.V, case.host("z"), inp.cu_seqlens, k, heads=heads)[:2]
+    check_close(f"O {name} k={k}", case.host("O")[:, heads], np.asarray(O)[:, heads], **tol(True))
+    check_close(f"LSE {name} k={k}", case.host("LSE")[heads], np.asarray(LSE)[heads], **tol(True))
+
+
+@pytest.mark.parametrize("grow", [False, True], ids=["plain", "climbing"])
+@pytest.mark.parametrize("name", FORMS)
+def test_forward_forms(gpu, name, grow):
+    for k in FORMS[name][4]:
+        print(f"[case] forward {name} k={k} climbing={grow}", flush=True)
+        forward(gpu, name, k, grow)
