@@ -21,7 +21,6 @@
 // which is exactly the B-operand layout of the products that consume them; the other operand of
 // those products is read from row-major LDS tiles with transposing LDS reads.
 #include "common.h"
-#include <type_traits>
 
 namespace dma {
 
@@ -46,18 +45,25 @@ struct BwdArgs {
 };
 
 // ------------------------------------------------------------------ dQ (and D, LSE * log2 e)
-// NW waves per workgroup: 8 (a whole 256-row block, four ring stages) or 4 (half a block, two ring
-// stages, two workgroups per compute unit), as in the forward kernel.
-template <int D, int NW>
-__global__ __launch_bounds__(NW * 64, (NW == 8 || D == 256) ? 1 : (D == 64 ? 3 : 2)) void dq_kernel(BwdArgs p) {
+// NW waves per workgroup: 8 (a whole 256-row block) or 4 (half a block); UT 32-key units per tile, as in the forward
+// kernel.  Software-pipelined like it: the step of unit i holds the products dP(i), S(i + 1) and dQ += K dS(i), and its
+// element-wise work runs under the products that do not need it: P(i) under dP(i), dS(i) under S(i + 1).  What bounds it
+// is what bounds the forward: the power limit's clock, then the matrix pipe.  Against the whole chain of a tile at a time
+// (us): 16384 tokens x 32 heads 872 -> 798; 16 heads of 256 channels, one wave per SIMD, 1172 -> 890; 2 x 4096 x 16
+// heads 141 -> 126; packed 65536 x 16 heads of 64 channels, not pipelined (three waves per SIMD; pipelined 426 there),
+// but with its rows addressed by immediates and dP started at -D: 425 -> 402.
+template <int D, int NW, int UT>
+__global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p) {
   using TL = TileLayout<D>;
+  constexpr int KT = 32 * UT;
   constexpr int KS = D / 16, CB = D / 32, CPR = D / 8, RPL = 64 / CPR, WL = KT / RPL / NW;
-  constexpr int NS = NW == 8 ? 4 : 2, TILE = KT * D, NT = NW * 64, HALVES = 8 / NW;
-  __shared__ __align__(16) uint16_t ringK[NS * TILE];
-  __shared__ __align__(16) uint16_t ringV[NS * TILE];
-  __shared__ __align__(16) int ids_ring[2 * NS][KT];
-  __shared__ __align__(16) float z_ring[NS][KT];
-  __shared__ __align__(16) int e_ring[NS][KT];
+  constexpr bool PIPED = D != 64;
+  constexpr int NS = PIPED ? 4 : 2, AHEAD = NS - 1;  // ring stages; tiles between a copy's request and its use
+  constexpr int TILE = KT * D, NT = NW * 64, HALVES = 8 / NW;
+  __shared__ __align__(16) uint16_t ring[2 * NS * TILE];  // K stages, then V stages
+  __shared__ __align__(16) int ids_ring[2 * NS][64];  // (rows of 64: what one wave-wide copy writes)
+  __shared__ __align__(16) float z_ring[NS][64];
+  __shared__ __align__(16) int e_ring[NS][64];
 
   // This launch also clears what the key-stationary launches behind it accumulate into with atomics
   // (the fp32 dK / dV buffers and dz): every workgroup, also one without a block, takes its share of
@@ -72,6 +78,9 @@ __global__ __launch_bounds__(NW * 64, (NW == 8 || D == 256) ? 1 : (D == 64 ? 3 :
   if (!xcd_map(wg_id(), p.H_q, p.nblk_cap * HALVES, h, item)) return;
   const int bi = p.nblk_cap - 1 - item / HALVES;  // long blocks first
   const int4 info = p.blk[bi];
+  const int np_keys = p.pcnt[(size_t)h * p.nblk_cap + bi];
+  const float scale = *reinterpret_cast<const float*>(p.consts + PLAN_SCALE_OFF);
+  const float c2 = *reinterpret_cast<const float*>(p.consts + PLAN_C2_OFF);
   if (info.x < 0) return;
   const int blk_row0 = info.y, row1 = info.z, doc0 = info.w;
   const int row0 = blk_row0 + (item % HALVES) * (NW * 32);  // first row of this workgroup's part of the block
@@ -80,8 +89,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 8 || D == 256) ? 1 : (D == 64 ? 3 :
   const int tid = thread_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, n = l & 31, hh = l >> 5;
   const int ncol = min(p.k, blk_row0 - doc0);
   const int nc = (ncol + KT - 1) / KT;
-  const int np_keys = p.pcnt[(size_t)h * p.nblk_cap + bi];
   const int nt = nc + (np_keys + KT - 1) / KT;
+  const int shift = (NS - nc % NS) % NS;  // ring stage of tile 0: tile t takes stage (t + shift) % NS
   const int32_t* slot_row = p.slot_tab + ((size_t)h * p.nblk_cap + bi) * p.kpad;
   const int32_t* plist_row = p.plist + ((size_t)h * p.nblk_cap + bi) * MAXPART;
   const float* zqh = p.zq + (size_t)h * p.T;
@@ -89,11 +98,10 @@ __global__ __launch_bounds__(NW * 64, (NW == 8 || D == 256) ? 1 : (D == 64 ? 3 :
   const float* c_ninf = reinterpret_cast<const float*>(p.consts + 256);
   const int32_t* c_zero = reinterpret_cast<const int32_t*>(p.consts + 260);
   const int32_t* c_m1 = reinterpret_cast<const int32_t*>(p.consts + 264);
-  const float scale = *reinterpret_cast<const float*>(p.consts + PLAN_SCALE_OFF);
-  const float c2 = *reinterpret_cast<const float*>(p.consts + PLAN_C2_OFF);
 
   // gathered rows: wave-uniform base of the kv-head plus a 32-bit byte offset (id * row pitch + the
   // lane's chunk); an empty slot (id < 0) copies row 0, which its score of -inf keeps out of every sum
+  constexpr uint32_t VOFF = 2 * NS * TILE;  // bytes from a K row to the V row of the same key
   const void* Kg = uniform_ptr(p.K + (size_t)g * D);
   const void* Vg = uniform_ptr(p.V + (size_t)g * D);
   const uint32_t row_pitch = (uint32_t)p.H_kv * D * 2;
@@ -104,50 +112,60 @@ __global__ __launch_bounds__(NW * 64, (NW == 8 || D == 256) ? 1 : (D == 64 ? 3 :
     lane_row[j] = (w * WL + j) * RPL + l / CPR;
     lane_chunk[j] = (uint32_t)(((l % CPR) ^ TL::swz(lane_row[j])) * 16);
   }
-  const uint32_t ldsK = lds_addr(ringK) + (uint32_t)(w * WL * RPL * D * 2);
-  const uint32_t ldsV = lds_addr(ringV) + (uint32_t)(w * WL * RPL * D * 2);
+  const uint32_t ldsK = lds_addr(ring) + (uint32_t)(w * WL * RPL * D * 2);
+  const uint32_t ldsV = ldsK + VOFF;
   auto issue_ids = [&](int tt) {
     if (w == 0) {
       const int32_t* src = c_m1;
+      const int ll = l & (KT - 1);
       if (tt < nc) {
-        src = slot_row + tt * KT + l;
+        src = slot_row + tt * KT + ll;
       } else if (tt < nt) {
-        const int q = (tt - nc) * KT + l;
+        const int q = (tt - nc) * KT + ll;
         if (q < np_keys) src = plist_row + q;
       }
       dma4(src, &ids_ring[tt % (2 * NS)][0]);
     }
   };
-  auto issue_kv = [&](int tt, int st) {  // st = tt % NS (a constant in the main loop)
+  auto row_ids = [&](int tt, int (&idv)[WL]) __attribute__((always_inline)) {
     const int* idr = ids_ring[tt % (2 * NS)];
-    int idv[WL];
 #pragma unroll
     for (int j = 0; j < WL; j++) idv[j] = idr[lane_row[j]];
-    int idl = 0;
-    if (w == 1) idl = idr[l];
+  };
+  auto copy_rows = [&](int stage, const int (&idv)[WL]) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < WL; j++) {
       const uint32_t off = mul24((uint32_t)max(idv[j], 0), row_pitch) + lane_chunk[j];
-      const uint32_t dst = (uint32_t)((st * TILE + j * RPL * D) * 2);
-      dma16s_pair(Kg, Vg, off, ldsK + dst, ldsV + dst);
-    }
-    if (w == 1) {
-      dma4(idl >= 0 ? zqh + idl : c_ninf, &z_ring[st][0]);
-      dma4(idl >= 0 ? (const void*)(eh + idl) : (const void*)c_zero, &e_ring[st][0]);
+      const uint32_t dst = (uint32_t)((stage * TILE + j * RPL * D) * 2);
+      dma16u(Kg, off, ldsK + dst);
+      dma16u(Vg, off, ldsV + dst);
     }
   };
+  auto issue_scalars = [&](int tt) {
+    if (w == 1) {
+      const int idl = ids_ring[tt % (2 * NS)][l];
+      dma4(idl >= 0 ? zqh + idl : c_ninf, &z_ring[(tt + shift) % NS][0]);
+      dma4(idl >= 0 ? (const void*)(eh + idl) : (const void*)c_zero, &e_ring[(tt + shift) % NS][0]);
+    }
+  };
+  // Iteration t of the tile loops requests the ids of tile t + AHEAD + 2 and the rows and scalars of tile t + AHEAD.  It
+  // starts when everything requested before iteration t - 1 has landed (tiles up to t + 1), or, without pipelining,
+  // everything (tile t).
   auto wait_tile = [&]() {
-    if (w == 0) wait_vmcnt<(NS - 2) * (2 * WL + 1)>();
-    else if (w == 1) wait_vmcnt<(NS - 2) * (2 * WL + 2)>();
-    else wait_vmcnt<(NS - 2) * (2 * WL)>();
+    if (!PIPED) wait_vmcnt<0>();
+    else if (w == 0) wait_vmcnt<2 * WL + 1>();
+    else if (w == 1) wait_vmcnt<2 * WL + 2>();
+    else wait_vmcnt<2 * WL>();
   };
 
-  for (int tt = 0; tt < NS - 1; tt++) issue_ids(tt);
+  for (int tt = 0; tt < AHEAD + 2; tt++) issue_ids(tt);
   wait_vmcnt<0>();
   lds_barrier();
-  for (int i = 0; i < NS - 1; i++) {
-    issue_ids(NS - 1 + i);
-    issue_kv(i, i);
+  for (int i = 0; i < AHEAD; i++) {
+    int idv[WL];
+    row_ids(i, idv);
+    copy_rows((i + shift) % NS, idv);
+    issue_scalars(i);
   }
 
   const int qi = row0 + 32 * w + n;
@@ -187,19 +205,17 @@ __global__ __launch_bounds__(NW * 64, (NW == 8 || D == 256) ? 1 : (D == 64 ? 3 :
   // read is one of these registers plus an immediate
   FragOffsets<D> fo;
   fo.init(l);
-  uint32_t kfrag[KS], vfrag[KS], ktr[CB][2];
+  uint32_t kfrag[KS], ktr[CB][2];
 #pragma unroll
   for (int ks = 0; ks < KS; ks++) {
-    kfrag[ks] = lds_addr(ringK) + 2 * fo.row(ks);
-    vfrag[ks] = lds_addr(ringV) + 2 * fo.row(ks);
+    kfrag[ks] = lds_addr(ring) + 2 * fo.row(ks);
     settle(kfrag[ks]);
-    settle(vfrag[ks]);
   }
 #pragma unroll
   for (int cb = 0; cb < CB; cb++)
 #pragma unroll
     for (int q = 0; q < 2; q++) {
-      ktr[cb][q] = lds_addr(ringK) + 2 * fo.tr(cb, q);
+      ktr[cb][q] = lds_addr(ring) + 2 * fo.tr(cb, q);
       settle(ktr[cb][q]);
     }
   uint32_t zlane = lds_addr(&z_ring[0][4 * hh]);
@@ -210,92 +226,182 @@ __global__ __launch_bounds__(NW * 64, (NW == 8 || D == 256) ? 1 : (D == 64 ? 3 :
   for (int cb = 0; cb < CB; cb++)
 #pragma unroll
     for (int v = 0; v < 16; v++) dqacc[cb][v] = 0.f;
-  wait_vmcnt<0>();  // the ordinary loads and stores above; from here on only copies are in flight
 
-  // one key tile; ST = t % NS is a compile-time constant (the loop below is unrolled over the ring)
-  auto tile = [&](auto stc, const int t) {
-    constexpr int ST = decltype(stc)::value;
-    if (t > 0) wait_tile();
-    lds_barrier();
-    issue_ids(t + 2 * NS - 2);
-    issue_kv(t + NS - 1, (ST + NS - 1) % NS);
-    const int ist = t % (2 * NS);
-    const bool masked = t >= nc;
-    if (masked) {
-      // partial tile: skip it if none of its keys is active on any of this wave's 32 rows
-      const int jl = ids_ring[ist][l], el = e_ring[ST][l];
-      const int rfirst = row0 + 32 * w;
-      if (!__any((jl >= 0) & (jl <= rfirst + 31) & (el > rfirst))) return;
+  // S^T of a unit starts at z / scale, so that scale * acc is the biased score; its dP^T starts at -D_i
+  auto start_scores = [&](uint32_t zo) __attribute__((always_inline)) {
+    f32x16 s;
+#pragma unroll
+    for (int gq = 0; gq < 4; gq++) {
+      const f32x4 zz = lds_load<f32x4>(zlane + zo + 32 * gq);
+#pragma unroll
+      for (int u = 0; u < 4; u++) s[4 * gq + u] = zz[u];
     }
-
+    return s;
+  };
+  f32x16 dpacc;
+  auto start_dp = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int kb = 0; kb < 2; kb++) {
-      bf16x8 dsb[2];  // the two 16-key halves
-      {
-        // S^T starts at z / scale (so that scale * acc is the biased score) and, in a partial
-        // tile, at -inf for pairs outside [j, e_j): those get P = 0 and dS = 0 exactly.
-        f32x16 sacc, dpacc;
-#pragma unroll
-        for (int gq = 0; gq < 4; gq++) {
-          const f32x4 zz = lds_load<f32x4>(zlane + 4 * (ST * KT + 32 * kb + 8 * gq));
-#pragma unroll
-          for (int u = 0; u < 4; u++) {
-            sacc[4 * gq + u] = zz[u];
-            dpacc[4 * gq + u] = 0.f;
-          }
-        }
-        if (masked) {
-#pragma unroll
-          for (int gq = 0; gq < 4; gq++) {
-            const i32x4 jj = lds_load<i32x4>(jlane + 4 * (ist * KT + 32 * kb + 8 * gq));
-            const i32x4 ee = lds_load<i32x4>(elane + 4 * (ST * KT + 32 * kb + 8 * gq));
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-              const bool ok = (jj[u] >= 0) & (qi >= jj[u]) & (qi < ee[u]);
-              sacc[4 * gq + u] = ok ? sacc[4 * gq + u] : -INFINITY;
-            }
-          }
-        }
-#pragma unroll
-        for (int ks = 0; ks < KS; ks++) {
-          sacc = mfma32(lds_load<bf16x8>(kfrag[ks] + 2 * (ST * TILE + 32 * kb * D)), qreg[ks], sacc);
-          dpacc = mfma32(lds_load<bf16x8>(vfrag[ks] + 2 * (ST * TILE + 32 * kb * D)), doreg[ks], dpacc);
-        }
-#pragma unroll
-        for (int v = 0; v < 16; v++) {
-          const float pv = fast_exp2(fmaf(sacc[v], c2, -lse2));
-          const float ds = pv * (dpacc[v] - Dsum);
-          dsb[v >> 3][v & 7] = (__bf16)ds;
-        }
-      }
-      // dQ^T += K^T dS^T for this half of the tile
-#pragma unroll
-      for (int c = 0; c < 2; c++)
-#pragma unroll
-        for (int cb = 0; cb < CB; cb++) {
-          const s16x4 lo = lds_read_tr_at(ktr[cb][0] + 2 * (ST * TILE + (32 * kb + 16 * c) * D));
-          const s16x4 hi = lds_read_tr_at(ktr[cb][1] + 2 * (ST * TILE + (32 * kb + 16 * c) * D));
-          const bf16x8 kf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-          dqacc[cb] = mfma32(kf, dsb[c], dqacc[cb]);
-        }
+    for (int v = 0; v < 16; v++) dpacc[v] = -Dsum;
+  };
+  constexpr uint32_t UB = 2 * 32 * D;  // bytes of one unit in a ring
+  constexpr int NM = 2 * KS + 2 * CB;  // products of a step: dP(i), S(i + 1), dQ(i)
+  constexpr int LEAD = D == 256 ? 5 : D == 128 ? 3 : 1;  // fragments read ahead of their product
+  static_assert(NM % (LEAD + 1) == 0, "the fragments read ahead for the next step keep their registers");
+  bf16x8 fr[LEAD + 1];
+  // A operand of product m of the step of unit (stage vs, u), whose next unit is (stage ss, su): byte offsets vo, ko
+  auto frag = [&](auto mc, uint32_t vo, uint32_t ko) __attribute__((always_inline)) {
+    constexpr int m = decltype(mc)::value;
+    if constexpr (m < KS) {
+      // (VOFF is beyond an instruction's offset at 128 channels and more: one addition, formed where it is used -- eight
+      // more address registers would spill)
+      uint32_t a = kfrag[m];
+      asm volatile("v_add_u32 %0, %1, %2" : "=v"(a) : "n"(VOFF), "v"(kfrag[m]));
+      fr[m % (LEAD + 1)] = lds_load<bf16x8>(a + vo);
+    } else if constexpr (m < 2 * KS) {
+      fr[m % (LEAD + 1)] = lds_load<bf16x8>(kfrag[m - KS] + ko);
+    } else {
+      constexpr int c = (m - 2 * KS) / CB, cb = (m - 2 * KS) % CB;
+      const s16x4 lo = lds_read_tr_at(ktr[cb][0] + vo + 2 * 16 * c * D);
+      const s16x4 hi = lds_read_tr_at(ktr[cb][1] + vo + 2 * 16 * c * D);
+      fr[m % (LEAD + 1)] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     }
   };
-  for (int t = 0; t < nt; t += NS) {
-    tile(std::integral_constant<int, 0>{}, t);
-    if (t + 1 >= nt) break;
-    tile(std::integral_constant<int, 1>{}, t + 1);
+
+  int t = 0;
+  wait_vmcnt<0>();  // the copies of the first tiles, and the ordinary loads and stores above: from here on only copies are in flight
+  lds_barrier();
+  f32x16 sc;
+  if constexpr (PIPED) {
+    sc = start_scores(4 * 64 * shift);
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) sc = mfma32(lds_load<bf16x8>(kfrag[ks] + shift * (2 * TILE)), qreg[ks], sc);
+    start_dp();
+    static_for<LEAD>([&](auto mc) __attribute__((always_inline)) { frag(mc, shift * (2 * TILE), 0); });
+  }
+  bool act0 = true;  // partial tiles: this unit has a key that is active on a row of the wave
+  auto tile = [&](auto stc, auto maskedc) __attribute__((always_inline)) {
+    constexpr int ST = decltype(stc)::value;  // (t + shift) % NS
+    constexpr bool MASKED = decltype(maskedc)::value;
+    if (t > 0) {
+      wait_tile();
+      lds_barrier();
+    }
+    issue_ids(t + AHEAD + 2);
+    issue_scalars(t + AHEAD);
+    static_for<UT>([&](auto uc) __attribute__((always_inline)) {
+      constexpr int u = decltype(uc)::value;
+      constexpr int ss = u + 1 < UT ? ST : (ST + 1) % NS, su = u + 1 < UT ? u + 1 : 0;
+      constexpr uint32_t ko = ss * (2 * TILE) + su * UB, vo = ST * (2 * TILE) + u * UB;
+      int idv[WL];
+      auto mask = [&]() __attribute__((always_inline)) {
+        // pairs outside [j, e_j) get P = 0 and dS = 0 exactly
+        const uint32_t js = jlane + 4 * ((t % (2 * NS)) * 64 + 32 * u);
+#pragma unroll
+        for (int gq = 0; gq < 4; gq++) {
+          const i32x4 jj = lds_load<i32x4>(js + 32 * gq);
+          const i32x4 ee = lds_load<i32x4>(elane + 4 * (ST * 64 + 32 * u) + 32 * gq);
+#pragma unroll
+          for (int v = 0; v < 4; v++) sc[4 * gq + v] = ((qi >= jj[v]) & (qi < ee[v])) ? sc[4 * gq + v] : -INFINITY;
+        }
+      };
+      if constexpr (MASKED) {
+        // Skip the step if no key of its units is active on any of this wave's 32 rows
+        const int rfirst = row0 + 32 * w, tn = !PIPED || u + 1 < UT ? t : t + 1;
+        const int jl = ids_ring[tn % (2 * NS)][PIPED ? 32 * su + n : 32 * u + n], el = e_ring[PIPED ? ss : ST][PIPED ? 32 * su + n : 32 * u + n];
+        const bool act1 = __any((jl <= rfirst + 31) & (el > rfirst));  // (an empty entry has el = 0)
+        const bool run = (PIPED && act0) | act1;
+        act0 = act1;
+        if (!run) {
+          if constexpr (PIPED) {
+#pragma unroll
+            for (int v = 0; v < 16; v++) sc[v] = -INFINITY;
+            static_for<LEAD>([&](auto mc) __attribute__((always_inline)) { frag(mc, ko, 0); });
+          }
+          if constexpr (u == 0) {
+            row_ids(t + AHEAD, idv);
+            copy_rows((ST + AHEAD) % NS, idv);
+          }
+          return;
+        }
+        if constexpr (PIPED) mask();
+      }
+      bf16x8 dsb[2];
+      if constexpr (!PIPED) {
+        if constexpr (u == 0) row_ids(t + AHEAD, idv);
+        sc = start_scores(4 * (ST * 64 + 32 * u));
+        start_dp();
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) {
+          sc = mfma32(lds_load<bf16x8>(kfrag[ks] + vo), qreg[ks], sc);
+          dpacc = mfma32(lds_load<bf16x8>(kfrag[ks] + (VOFF + vo)), doreg[ks], dpacc);
+        }
+        if constexpr (u == 0) copy_rows((ST + AHEAD) % NS, idv);
+        if constexpr (MASKED) mask();
+#pragma unroll
+        for (int v = 0; v < 16; v++) dsb[v >> 3][v & 7] = (__bf16)(fast_exp2(fmaf(sc[v], c2, -lse2)) * dpacc[v]);
+        static_for<2 * CB>([&](auto ic) __attribute__((always_inline)) {
+          constexpr int i = decltype(ic)::value;
+          frag(std::integral_constant<int, 2 * KS + i>{}, vo, 0);
+          dqacc[i % CB] = mfma32(fr[i % (LEAD + 1)], dsb[i / CB], dqacc[i % CB]);
+        });
+        return;
+      }
+      f32x16 sn;
+      float pv[16];
+      static_for<NM>([&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value;
+        if constexpr (u == 0 && m == 0) row_ids(t + AHEAD, idv);
+        if constexpr (m == KS / 2) sn = start_scores(4 * (ss * 64 + 32 * su));
+        if constexpr (m + LEAD < NM) frag(std::integral_constant<int, m + LEAD>{}, vo, ko);
+        else frag(std::integral_constant<int, m + LEAD - NM>{}, ko, 0);
+        if constexpr (m < KS) dpacc = mfma32(fr[m % (LEAD + 1)], doreg[m], dpacc);
+        else if constexpr (m < 2 * KS) sn = mfma32(fr[m % (LEAD + 1)], qreg[m - KS], sn);
+        else dqacc[(m - 2 * KS) % CB] = mfma32(fr[m % (LEAD + 1)], dsb[(m - 2 * KS) / CB], dqacc[(m - 2 * KS) % CB]);
+        if constexpr (m < KS) {  // P(i)
+#pragma unroll
+          for (int v = m * 16 / KS; v < (m + 1) * 16 / KS; v++) pv[v] = fast_exp2(fmaf(sc[v], c2, -lse2));
+        }
+        // dS(i): its first half before the first products with it, the second under those
+        constexpr int f0 = KS + KS / 4, fn = KS - KS / 4;
+        if constexpr (m >= f0 && m < 2 * KS) {
+#pragma unroll
+          for (int v = (m - f0) * 8 / fn; v < (m + 1 - f0) * 8 / fn; v++) dsb[0][v] = (__bf16)(pv[v] * dpacc[v]);
+        }
+        if constexpr (m >= 2 * KS && m < 2 * KS + CB) {
+#pragma unroll
+          for (int v = (m - 2 * KS) * 8 / CB; v < (m + 1 - 2 * KS) * 8 / CB; v++) dsb[1][v] = (__bf16)(pv[8 + v] * dpacc[8 + v]);
+        }
+        if constexpr (m == NM - 2) start_dp();
+        if constexpr (u == 0 && m == KS + 1) copy_rows((ST + AHEAD) % NS, idv);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      sc = sn;
+    });
+    t++;
+  };
+  constexpr std::integral_constant<int, 0> s0{};
+  constexpr std::integral_constant<int, 1> s1{};
+  for (int base = -shift; base < nc; base += NS) {
+    if (base >= 0) tile(s0, std::false_type{});
     if constexpr (NS == 4) {
-      if (t + 2 >= nt) break;
-      tile(std::integral_constant<int, 2>{}, t + 2);
-      if (t + 3 >= nt) break;
-      tile(std::integral_constant<int, 3>{}, t + 3);
+      if (base + 1 >= 0) tile(s1, std::false_type{});
+      if (base + 2 >= 0) tile(std::integral_constant<int, 2 % NS>{}, std::false_type{});
+    }
+    tile(std::integral_constant<int, NS - 1>{}, std::false_type{});
+  }
+  for (int base = nc; base < nt; base += NS) {
+    tile(s0, std::true_type{});
+    if (base + 1 < nt) tile(s1, std::true_type{});
+    if constexpr (NS == 4) {
+      if (base + 2 < nt) tile(std::integral_constant<int, 2 % NS>{}, std::true_type{});
+      if (base + 3 < nt) tile(std::integral_constant<int, 3 % NS>{}, std::true_type{});
     }
   }
-  static_assert(NS == 4 || NS == 2, "the main loop is unrolled over the ring stages");
+  static_assert(NS == 4 || NS == 2, "the loops are unrolled over the ring stages");
 
   wait_vmcnt<0>();
   lds_barrier();
-  uint16_t* Os = ringK;  // [NW * 32][D] staging with the tile swizzle
+  uint16_t* Os = ring;  // [NW * 32][D] staging with the tile swizzle
   static_assert(NS * KT >= NW * 32, "dQ staging aliases the K ring");
 #pragma unroll
   for (int cb = 0; cb < CB; cb++)
@@ -828,16 +934,19 @@ int launch_bwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
   a.dz_n = (size_t)s.H_q * s.T;
   prof_begin(DMA_STAGE_BWD_ZERO, st);  // (an empty stage: dq_kernel clears the accumulators)
   prof_end(DMA_STAGE_BWD_ZERO, st);
-  // (at 256 channels the query-stationary kernels run as half blocks: four waves with the whole register file each)
-  const unsigned gq = s.d != 128 ? xcd_grid(s.H_q, 2l * L.nblk_cap) : xcd_grid(s.H_q, L.nblk_cap);
+  // dq_kernel: half blocks at 64 channels (three per compute unit), at 256 (four waves with the whole register file each)
+  // and, at 128, where every one of them finds a compute unit of its own (us, whole / half blocks: 300 tokens x 2 heads
+  // 19.5 / 16.5, 1024 x 32 45 / 38, 4096 x 4 57 / 47; with more of them than compute units 5 x 800 x 8 36 / 45).
+  const bool halves = s.d != 128 || 2 * most_blocks(s) <= CUS;
+  const unsigned gq = halves ? xcd_grid(s.H_q, 2l * L.nblk_cap) : xcd_grid(s.H_q, L.nblk_cap);
   a.grid_dq = gq;
   const unsigned gclean = xcd_grid(s.H_q, (long)((L.nblk_cap + a.seg - 1) / a.seg) * (L.kpad / SG));
   const unsigned gpart = xcd_grid(s.H_q, (long)((L.nblk_cap + a.seg_part - 1) / a.seg_part) * (MAXPART / SG));
   prof_begin(DMA_STAGE_BWD_DQ, st);
-  // (the half-block variant, NW = 4, measured the same or slower at every benchmark shape)
-  if (s.d == 256) dq_kernel<256, 4><<<gq, 256, 0, st>>>(a);
-  else if (s.d == 128) dq_kernel<128, 8><<<gq, 512, 0, st>>>(a);
-  else dq_kernel<64, 4><<<gq, 256, 0, st>>>(a);  // half blocks, three workgroups per compute unit (three waves per SIMD)
+  if (s.d == 256) dq_kernel<256, 4, 1><<<gq, 256, 0, st>>>(a);
+  else if (s.d == 128 && halves) dq_kernel<128, 4, 2><<<gq, 256, 0, st>>>(a);
+  else if (s.d == 128) dq_kernel<128, 8, 2><<<gq, 512, 0, st>>>(a);
+  else dq_kernel<64, 4, 2><<<gq, 256, 0, st>>>(a);
   prof_end(DMA_STAGE_BWD_DQ, st);
   prof_begin(DMA_STAGE_BWD_DKV, st);
   if (s.d == 256) dkv_kernel<256, false><<<gclean, DKV_NW * 64, 0, st>>>(a);

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <type_traits>
 #include "../../include/dma.h"
 
 namespace dma {
@@ -121,6 +122,12 @@ static inline WsLayout ws_layout(const dma_shape& s) {
   return w;
 }
 
+// Query blocks of all heads: the most there can be, and about how many there are (a document's last block is half full).
+static inline double most_blocks(const dma_shape& s) { return (double)s.H_q * (double)(((long)s.T + (long)s.n_docs * (BQ - 1)) / BQ); }
+static inline double typical_blocks(const dma_shape& s) {
+  return s.n_docs == 1 ? most_blocks(s) : s.H_q * ((double)s.T / BQ + 0.5 * s.n_docs);
+}
+
 // ------------------------------------------------------------------ launch entry points (defined in the .hip files)
 struct Ptrs {  // everything the kernels need, resolved by the host API
   dma_shape s;
@@ -167,6 +174,14 @@ void prof_end(int stage, hipStream_t st);
 
 #ifdef __HIPCC__
 // ------------------------------------------------------------------ device helpers
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>)
+template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   // D[32x32] += A[32x16] B[16x32].  Lane l holds A[l%32][8*(l/32) .. +8), B[8*(l/32) .. +8)[l%32],
   // and D[8*(v/4) + 4*(l/32) + v%4][l%32] in register v.

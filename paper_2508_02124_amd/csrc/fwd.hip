@@ -22,7 +22,6 @@
 // 256 channels, where no second wave of a SIMD fills the gaps: 882 -> 628 us.
 #include "common.h"
 #include <cmath>
-#include <type_traits>
 
 namespace dma {
 
@@ -39,14 +38,6 @@ struct FwdArgs {
   const char* consts;   // [0,256) zeros; +256: float -inf; +260: int 0; +264: int -1; +272: softmax scale, scale * log2(e)
   int T, H_q, H_kv, k, nblk_cap, kpad;
 };
-
-// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>)
-template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<N, I + 1>(f);
-  }
-}
 
 // Largest sum of a lane's sixteen weights of one unit that the fast path accepts, as the bits of a float: every weight
 // is then at most 2^8.  Infinities and NaNs (nothing kept so far: reference maximum -inf) compare above it.
@@ -499,14 +490,14 @@ int launch_fwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
   // full, or, in a single round, documents are not much longer than the window, so that blocks differ in length
   // (2048 x 32 53.6 / 51.7, 7 documents in 10007 x 8 window 333 49.4 / 46.9; above the line 8192 x 8 53.2 / 57.7,
   // 2 x 4096 x 16 92 / 98).
-  const double blocks = (double)s.H_q * ((s.T + BQ - 1) / BQ), rounds = std::ceil(blocks / CUS);
+  const double blocks = typical_blocks(s), rounds = std::ceil(blocks / CUS);
   const double len = (double)s.T / s.n_docs, window = s.k < len ? s.k : len;
   const double busy = blocks / (CUS * rounds) * (1. - window / (2. * len) / rounds);
   // 256 channels: half blocks of four waves, one per SIMD with the whole register file (the output
   // accumulators alone are 128 registers per wave).
   if (s.d == 256) fwd_kernel<256, 4, 1><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 256, 0, st>>>(a);
   else if (s.d == 64) fwd_kernel<64, 8, 2><<<xcd_grid(s.H_q, L.nblk_cap), 512, 0, st>>>(a);
-  else if (2 * blocks <= CUS) fwd_kernel<128, 4, 2><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 256, 0, st>>>(a);
+  else if (2 * most_blocks(s) <= CUS) fwd_kernel<128, 4, 2><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 256, 0, st>>>(a);
   else if (busy < 0.8) fwd_kernel<128, 4, 1><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 256, 0, st>>>(a);
   else fwd_kernel<128, 8, 2><<<xcd_grid(s.H_q, L.nblk_cap), 512, 0, st>>>(a);
   prof_end(DMA_STAGE_FWD, st);
