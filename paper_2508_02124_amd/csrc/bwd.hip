@@ -10,7 +10,7 @@
 //  * dkv_kernel, key-stationary: a workgroup owns SG slot columns of one head and sweeps query
 //    blocks in steps of 32 rows, fed by a ring of asynchronous Q / dO copies.  A slot column always
 //    holds one resident key, so its tiles are dense and need no mask; K and V fragments of the
-//    resident stay in registers (part of K's in LDS) together with the dK^T, dV^T and dz accumulators.  When the
+//    resident stay in registers and LDS together with the dK^T, dV^T and dz accumulators.  When the
 //    resident of a column changes, the finished key is flushed with a handful of fp32 atomics (dK
 //    and dV are shared by the q-heads of a group) and the column is re-armed.  The same kernel, in
 //    "partial" mode, handles the keys that expire inside a block or enter it without staying: columns
@@ -431,29 +431,29 @@ constexpr int MAXSWEEP = 64;     // most query blocks one key-stationary work it
 //   S = Q K^T + z / scale, dP = dO V^T - D, P = exp2(S c2 - LSE2) (masked in partial mode), dV^T += dO^T P,
 //   dS = P o dP, dz += colsum(dS), dK^T += Q^T dS.
 // Lane (n, hh) owns column 32 w + n; its accumulators hold channels 32cb + 8gq + 4hh + u.
-// What bounds it: the chain of one step (two products, exponentials, two products) at two waves per SIMD, and
-// the work at a block's first step (rows of new keys, flush of finished ones); the matrix pipe is busy 40 % of
-// the time.  An earlier form split the chain over two waves that handed P through LDS and met at one barrier for
-// 128 columns and 8 waves; here two workgroups of 4 waves share a compute unit and drift apart in phase, so one
-// computes while the other waits (slot sweep / partial launch, us, before -> after: 65536 packed tokens, 16 heads,
-// d = 64, window 512: 680 / 248 -> 510 / 180; 16384 tokens, 32 heads, d = 128, window 2048: 1563 / 179 -> 1380 / 196;
-// 16 heads, d = 256: 1885 / 460 -> 1945 / 276).  A register reload inside a step costs more than it looks: it waits
-// for the copies requested just before it.  So part of the K fragments waits in LDS, and small lane-dependent values
-// are formed where they are used (fresh_lane).  As built: nothing spills at d = 64; 15 registers (sweep) and 6
-// (partial) at d = 128, reloaded at the issue of id copies and at block changes; at d = 256 27 and 48, and there the
-// step itself reloads (sweep: nine dwords at its end, so that the next step's S waits for the copies issued at its
-// head; partial: three times between its products), which is what keeps the sweep above its former 1885 us.
+// Two workgroups of 4 waves share a compute unit at 128 channels (three at 64, one at 256) and drift apart in phase, so
+// one computes while the other waits.  What bounds it at 128 channels: of 4140 cycles per 32-row step of a wave (2050 are
+// the matrix pipe's for its two waves) 2440 are the products and what they wait for, 580 the change of keys at block
+// starts, 460 the issue of copies, 450 the barrier, 220 the copies' arrival -- at a clock that the power limit holds at 1.9
+// to 2.1 GHz.  At 256 channels, one wave per SIMD at 2.4 GHz, the products' own latencies count: 3600 of 5800 cycles.
+// Registers decide the rest: the accumulators take D, so all of the K fragments and some of V's wait in LDS at 128
+// channels (two ring stages instead of three make room) and half of K's at 256; small lane-dependent
+// values are formed where they are used (fresh_lane).  Slot sweep / partial launch, us, with the products in the
+// compiler's order, the keys' rows through registers and a wait in every pass of a flush -> now: 16384 tokens x 32 heads
+// 1160 / 186 -> 1060 / 168; 2 x 4096 x 16 heads 193 / 81 -> 167 / 66; 16 heads of 256 channels 1775 / 278 -> 1290 / 246;
+// packed 65536 x 16 heads of 64 channels 371 / 169 -> 363 / 167.
 template <int D, bool PARTIAL>
-__global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : 2) void dkv_kernel(BwdArgs p) {
+__global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : D == 64 ? 3 : 2) void dkv_kernel(BwdArgs p) {
   using TL = TileLayout<D>;
   constexpr int KS = D / 16, CB = D / 32, CPR = D / 8, RPL = 64 / CPR;
   constexpr int SUB = 32;                 // query rows per pipeline step
   constexpr int NSUB = BQ / SUB;          // steps per query block
   constexpr int NWL = 2 * (SUB / RPL);    // 16-byte wave copies per step (Q rows, then dO rows)
-  constexpr int NS = D == 64 ? 4 : 3;     // ring stages
+  constexpr int NS = D == 64 ? 4 : D == 128 ? 2 : 3;  // ring stages
   constexpr int STILE = SUB * D;
-  constexpr int KL = D == 64 ? 0 : D == 128 ? 6 : 8;  // contraction steps whose K fragments wait in LDS
-  constexpr int STR = D == 128 ? 8 : 16, STC = D == 64 ? 64 : 32;  // flush staging: columns, channels
+  constexpr int KL = D == 64 ? 0 : 8;  // contraction steps whose K fragments wait in LDS
+  constexpr int VL = D == 128 ? 2 : 0; // ... and V fragments
+  constexpr int STR = 8, STC = D == 64 ? 64 : 32;  // flush staging: columns, channels
   constexpr int LDS_ST = STC + 4;         // padded staging row
   __shared__ __align__(16) uint16_t ringQ[NS * STILE];
   __shared__ __align__(16) uint16_t ringdO[NS * STILE];
@@ -461,6 +461,7 @@ __global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : 2) void dkv_kernel(BwdA
   __shared__ __align__(16) int idbuf[2][SG];     // column ids of the current / next block
   __shared__ __align__(16) int4 binfo[MAXSWEEP + 1];  // block table of this work item's sweep
   __shared__ __align__(16) float stage_all[DKV_NW * STR * LDS_ST];  // per wave: [STR columns][STC channels] fp32, flush staging
+  __shared__ __align__(16) bf16x8 vlds[VL ? DKV_NW * VL * 64 : 1];
   __shared__ __align__(16) bf16x8 klds[KL ? DKV_NW * KL * 64 : 1];  // [wave][ks][lane]: K fragments of the first KL steps
 
   const int ngrp = PARTIAL ? MAXPART / SG : p.kpad / SG;
@@ -626,12 +627,14 @@ __global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : 2) void dkv_kernel(BwdA
   int curid = -1, kj = KJ_NONE, ke = 0;
   bool entering = false;
   float zq = -INFINITY;  // z / scale of this lane's key: the start value of its S accumulator
-  bf16x8 kreg[KS > KL ? KS - KL : 1], vreg[KS];  // B-operand fragments of this lane's key: its K row and its V row
+  bf16x8 kreg[KS > KL ? KS - KL : 1], vreg[KS - VL];  // B-operand fragments of this lane's key: its K row and its V row
   const bf16x8 zero8 = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
   bf16x8* kl = klds + w * KL * 64 + l;
+  bf16x8* vl = vlds + w * VL * 64 + l;
 #pragma unroll
   for (int ks = 0; ks < KS; ks++) {
-    vreg[ks] = zero8;
+    if (ks < VL) vl[64 * ks] = zero8;
+    else vreg[ks < VL ? 0 : ks - VL] = zero8;
     if (ks < KL) kl[64 * ks] = zero8;
     else kreg[ks < KL ? 0 : ks - KL] = zero8;
   }
@@ -649,45 +652,6 @@ __global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : 2) void dkv_kernel(BwdA
   // Lanes of a wave hand values to each other through LDS (in order, no barrier needed): the compiler must not
   // carry a lane's view of the staging area across.
   auto lanes_exchange = [] { asm volatile("" ::: "memory"); };
-  auto flush_one = [&](const f32x16 (&acc)[CB], float* dst, float mul, bool mine, int row, int cnt, int idrow,
-                       int ln) __attribute__((always_inline)) {
-    const int n = ln & 31, hh = ln >> 5;
-#pragma unroll
-    for (int c0 = 0; c0 < CB; c0 += STC / 32) {
-      if (mine) {
-#pragma unroll
-        for (int cb = c0; cb < c0 + STC / 32; cb++)
-#pragma unroll
-          for (int gq = 0; gq < 4; gq++) {
-            f32x4 v4;
-#pragma unroll
-            for (int u = 0; u < 4; u++) v4[u] = acc[cb][4 * gq + u];
-            *reinterpret_cast<f32x4*>(&stage[row * LDS_ST + 32 * (cb - c0) + 8 * gq + 4 * hh]) = v4;
-          }
-      }
-      lanes_exchange();
-      constexpr int RPI = 64 / STC, U = 4;  // keys per atomic instruction, instructions in flight
-      for (int i0 = 0; i0 < cnt; i0 += RPI * U) {
-        float x[U];
-#pragma unroll
-        for (int u = 0; u < U; u++) x[u] = stage[(i0 + RPI * u + (RPI == 2 ? hh : 0)) * LDS_ST + (ln & (STC - 1))] * mul;
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-          const int i = i0 + RPI * u;
-          if (i < cnt) {
-            const int id0 = __builtin_amdgcn_readlane(idrow, i);
-            if (RPI == 1) {
-              atomicAdd(dst + ((size_t)id0 * p.H_kv + g) * D + 32 * c0 + ln, x[u]);
-            } else {
-              const int id = hh == 0 ? id0 : __builtin_amdgcn_readlane(idrow, i + 1);
-              if (hh == 0 || i + 1 < cnt) atomicAdd(dst + ((size_t)id * p.H_kv + g) * D + 32 * c0 + n, x[u]);
-            }
-          }
-        }
-      }
-      lanes_exchange();
-    }
-  };
   auto flush = [&](bool doit) __attribute__((always_inline)) {
     const int ln = fresh_lane();
     const int n = ln & 31, hh = ln >> 5;
@@ -698,14 +662,51 @@ __global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : 2) void dkv_kernel(BwdA
     if (doit && hh == 0) atomicAdd(p.dz + (size_t)h * p.T + curid, dzt);
     int* stage_id = reinterpret_cast<int*>(stage);
     const int nf = __popc(fm), rank = __popc(fm & ((1u << n) - 1u));
+    constexpr int NP = 2 * D / STC, CPP = STC / 32;  // passes (dV, then dK), 32-channel blocks per pass
+    constexpr int RPI = 64 / STC, U = STR / RPI;     // keys per atomic instruction, instructions per pass
     for (int r0 = 0; r0 < nf; r0 += STR) {
       const int row = rank - r0, cnt = min(STR, nf - r0);
       const bool mine = doit && row >= 0 && row < STR;
       if (mine && hh == 0) stage_id[row * LDS_ST + STC] = curid;  // (in the padding)
       lanes_exchange();
-      const int idrow = stage_id[(ln & (STR - 1)) * LDS_ST + STC];  // lane r: the key of staging row r
-      flush_one(dvacc, p.dV32, 1.f, mine, row, cnt, idrow, ln);
-      flush_one(dkacc, p.dK32, scale, mine, row, cnt, idrow, ln);
+      const int sub = RPI == 2 ? hh : 0;
+      size_t off[U];  // element of staging row RPI u + sub this lane adds to, of the first pass of dV and of dK
+#pragma unroll
+      for (int u = 0; u < U; u++)
+        off[u] = ((size_t)stage_id[(RPI * u + (RPI * u + sub < cnt ? sub : 0)) * LDS_ST + STC] * p.H_kv + g) * D + (ln & (STC - 1));
+      // A wave's LDS accesses take effect in order: the next pass is written as soon as the reads of the one before it
+      // are on their way, and the atomics of a pass follow the reads of the next.
+      float x[2][U];
+      auto add = [&](int ps) __attribute__((always_inline)) {
+        float* dst = ps < NP / 2 ? p.dV32 : p.dK32;
+        const int c0 = ps % (NP / 2) * STC;
+#pragma unroll
+        for (int u = 0; u < U; u++)
+          if (RPI * u < cnt) {
+            if (RPI * u + sub < cnt) atomicAdd(dst + off[u] + c0, ps < NP / 2 ? x[ps & 1][u] : x[ps & 1][u] * scale);
+          }
+      };
+#pragma unroll
+      for (int ps = 0; ps < NP; ps++) {
+        if (mine) {
+#pragma unroll
+          for (int cb = 0; cb < CPP; cb++)
+#pragma unroll
+            for (int gq = 0; gq < 4; gq++) {
+              const f32x16& acc = ps < NP / 2 ? dvacc[ps % (NP / 2) * CPP + cb] : dkacc[ps % (NP / 2) * CPP + cb];
+              f32x4 v4;
+#pragma unroll
+              for (int u = 0; u < 4; u++) v4[u] = acc[4 * gq + u];
+              *reinterpret_cast<f32x4*>(&stage[row * LDS_ST + 32 * cb + 8 * gq + 4 * hh]) = v4;
+            }
+        }
+        lanes_exchange();
+#pragma unroll
+        for (int u = 0; u < U; u++) x[ps & 1][u] = stage[(RPI * u + sub) * LDS_ST + (ln & (STC - 1))];
+        lanes_exchange();
+        if (ps > 0) add(ps - 1);
+      }
+      add(NP - 1);
     }
   };
 
@@ -750,10 +751,10 @@ __global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : 2) void dkv_kernel(BwdA
             const size_t off = ((size_t)newid * p.H_kv + g) * D + 8 * hh;
 #pragma unroll
             for (int ks = 0; ks < KS; ks++) {
-              const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p.K + off + 16 * ks));
-              if (ks < KL) kl[64 * ks] = kf;
-              else kreg[ks < KL ? 0 : ks - KL] = kf;
-              vreg[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p.V + off + 16 * ks));
+              if (ks < KL) dma16(p.K + off + 16 * ks, klds + (w * KL + ks) * 64);
+              else kreg[ks < KL ? 0 : ks - KL] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p.K + off + 16 * ks));
+              if (ks < VL) dma16(p.V + off + 16 * ks, vlds + (w * VL + ks) * 64);
+              else vreg[ks < VL ? 0 : ks - VL] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p.V + off + 16 * ks));
             }
             zq = zqh[newid];
             if (PARTIAL) {
@@ -763,7 +764,8 @@ __global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : 2) void dkv_kernel(BwdA
           } else {
 #pragma unroll
             for (int ks = 0; ks < KS; ks++) {
-              vreg[ks] = zero8;
+              if (ks < VL) vl[64 * ks] = zero8;
+              else vreg[ks < VL ? 0 : ks - VL] = zero8;
               if (ks < KL) kl[64 * ks] = zero8;
               else kreg[ks < KL ? 0 : ks - KL] = zero8;
             }
@@ -783,12 +785,13 @@ __global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : 2) void dkv_kernel(BwdA
           dzacc = 0.f;
           curid = newid;
         }
+        wait_vmcnt<0>();  // the rows that go to LDS (the other loads and the atomics too)
         if (PARTIAL) settle(ke);
         settle(zq);
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) {
           if (ks >= KL) settle(kreg[ks < KL ? 0 : ks - KL]);
-          settle(vreg[ks]);
+          if (ks >= VL) settle(vreg[ks < VL ? 0 : ks - VL]);
         }
       }
     }
@@ -820,49 +823,80 @@ __global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : 2) void dkv_kernel(BwdA
 #pragma unroll
       for (int vv = 0; vv < 16; vv++) sacc[vv] = z0;
     }
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) sacc = mfma32(fo.row_frag(Qs, 0, ks), ks < KL ? kl[64 * ks] : kreg[ks < KL ? 0 : ks - KL], sacc);
-    // dP starts at -D_i of the accumulator's rows: the products then leave dP - D, what dS needs
+    // The products in a fixed order (S, dP, dV^T, dK^T), each with the LDS reads of the fragments LEAD products ahead and
+    // a share of the element-wise work: P under dP and the first products with P, dS under dV and the first with dS.
+    // (64 channels: the order is the compiler's; three waves share a SIMD there, and fragments read ahead would spill)
     const float* row_meta = meta[st] + 4 * (fresh_lane() >> 5);
-#pragma unroll
-    for (int gq = 0; gq < 4; gq++) {
-      const f32x4 dd = *reinterpret_cast<const f32x4*>(&row_meta[32 + 8 * gq]);
-#pragma unroll
-      for (int u = 0; u < 4; u++) dpacc[4 * gq + u] = dd[u];
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) dpacc = mfma32(fo.row_frag(dOs, 0, ks), vreg[ks], dpacc);
-    bf16x8 bb[2];  // P: the B operand of the dV^T accumulation
-#pragma unroll
-    for (int gq = 0; gq < 4; gq++) {
-      const int r = 8 * gq + 4 * hh;
-      const f32x4 ls = *reinterpret_cast<const f32x4*>(&row_meta[8 * gq]);
-#pragma unroll
-      for (int u = 0; u < 4; u++) {
-        const int vv = 4 * gq + u;
-        float pv = fast_exp2(fmaf(sacc[vv], c2, -ls[u]));
-        if (PARTIAL) {
-          const int row = rf + r + u;
-          pv = ((row >= kj) & (row < ke)) ? pv : 0.f;
-        }
-        sacc[vv] = pv;
-        bb[vv >> 3][vv & 7] = (__bf16)pv;
+    constexpr int NM = 2 * KS + 4 * CB, LEAD = D == 256 ? 4 : D == 128 ? 2 : 0, EPS = 16 / KS;
+    bf16x8 fr[LEAD + 1], fk[KL || VL ? LEAD + 1 : 1], bb[2], db[2];
+    f32x4 ls[2];
+    auto frag = [&](auto mc) __attribute__((always_inline)) {
+      constexpr int m = decltype(mc)::value;
+      if constexpr (m < KS) {
+        fr[m % (LEAD + 1)] = fo.row_frag(Qs, 0, m);
+        if constexpr (m < KL) fk[m % (LEAD + 1)] = kl[64 * m];
+      } else if constexpr (m < 2 * KS) {
+        fr[m % (LEAD + 1)] = fo.row_frag(dOs, 0, m - KS);
+        if constexpr (m - KS < VL) fk[m % (LEAD + 1)] = vl[64 * (m - KS)];
+      } else if constexpr (m < 2 * KS + 2 * CB) {
+        fr[m % (LEAD + 1)] = fo.tr_frag(dOs, 16 * ((m - 2 * KS) / CB), (m - 2 * KS) % CB);
+      } else if constexpr (m < NM) {
+        fr[m % (LEAD + 1)] = fo.tr_frag(Qs, 16 * ((m - 2 * KS - 2 * CB) / CB), (m - 2 * KS - 2 * CB) % CB);
       }
-    }
+    };
+    static_for<LEAD>(frag);
+    if constexpr (D != 64) __builtin_amdgcn_sched_barrier(0);
+    static_for<NM>([&](auto mc) __attribute__((always_inline)) {
+      constexpr int m = decltype(mc)::value;
+      frag(std::integral_constant<int, m + LEAD>{});
+      // dP starts at -D_i of the accumulator's rows: the products then leave dP - D, what dS needs
+      if constexpr (m >= KS - 4 && m < KS) {
+        constexpr int gq = m - (KS - 4);
+        const f32x4 dd = *reinterpret_cast<const f32x4*>(&row_meta[32 + 8 * gq]);
 #pragma unroll
-    for (int c = 0; c < 2; c++)
+        for (int u = 0; u < 4; u++) dpacc[4 * gq + u] = dd[u];
+      }
+      if constexpr (m < KS) {
+        if constexpr (m < KL) sacc = mfma32(fr[m % (LEAD + 1)], fk[m % (LEAD + 1)], sacc);
+        else sacc = mfma32(fr[m % (LEAD + 1)], kreg[m - KL], sacc);
+      } else if constexpr (m < 2 * KS) {
+        if constexpr (m - KS < VL) dpacc = mfma32(fr[m % (LEAD + 1)], fk[m % (LEAD + 1)], dpacc);
+        else dpacc = mfma32(fr[m % (LEAD + 1)], vreg[m - KS - VL], dpacc);
+      } else if constexpr (m < 2 * KS + 2 * CB) {
+        constexpr int i = m - 2 * KS;
+        dvacc[i % CB] = mfma32(fr[m % (LEAD + 1)], bb[i / CB], dvacc[i % CB]);
+      } else {
+        constexpr int i = m - 2 * KS - 2 * CB;
+        dkacc[i % CB] = mfma32(fr[m % (LEAD + 1)], db[i / CB], dkacc[i % CB]);
+      }
+      constexpr int p0 = KS + 1, d0 = 2 * KS + 2;  // first products that P and dS form under
+      constexpr int PQ = 4 / EPS;  // products per four elements of P: their LSE is read PQ products ahead
+      if constexpr (m >= p0 - PQ && m < p0 + KS - PQ && (m - p0 + PQ) % PQ == 0) {
+        constexpr int gq = (m - p0 + PQ) / PQ;
+        ls[gq & 1] = *reinterpret_cast<const f32x4*>(&row_meta[8 * gq]);
+      }
+      if constexpr (m >= p0 && m < p0 + KS) {
 #pragma unroll
-      for (int cb = 0; cb < CB; cb++) dvacc[cb] = mfma32(fo.tr_frag(dOs, 16 * c, cb), bb[c], dvacc[cb]);
+        for (int vv = (m - p0) * EPS; vv < (m - p0 + 1) * EPS; vv++) {
+          float pv = fast_exp2(fmaf(sacc[vv], c2, -ls[(vv >> 2) & 1][vv & 3]));
+          if (PARTIAL) {
+            const int row = rf + 8 * (vv >> 2) + 4 * hh + (vv & 3);
+            pv = ((row >= kj) & (row < ke)) ? pv : 0.f;
+          }
+          sacc[vv] = pv;
+          bb[vv >> 3][vv & 7] = (__bf16)pv;
+        }
+      }
+      if constexpr (m >= d0 && m < d0 + KS) {
 #pragma unroll
-    for (int vv = 0; vv < 16; vv++) {  // dS: the B operand of the dK^T accumulation
-      const float ds = sacc[vv] * dpacc[vv];
-      dzacc += ds;
-      bb[vv >> 3][vv & 7] = (__bf16)ds;
-    }
-#pragma unroll
-    for (int c = 0; c < 2; c++)
-#pragma unroll
-      for (int cb = 0; cb < CB; cb++) dkacc[cb] = mfma32(fo.tr_frag(Qs, 16 * c, cb), bb[c], dkacc[cb]);
+        for (int vv = (m - d0) * EPS; vv < (m - d0 + 1) * EPS; vv++) {
+          const float ds = sacc[vv] * dpacc[vv];
+          dzacc += ds;
+          db[vv >> 3][vv & 7] = (__bf16)ds;
+        }
+      }
+      if constexpr (D != 64) __builtin_amdgcn_sched_barrier(0);
+    });
   }
   wait_vmcnt<0>();
   flush(true);
