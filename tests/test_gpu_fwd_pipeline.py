@@ -73,3 +73,18 @@ def test_gradient_forms(gpu, name):
         case.fwd()
         case.bwd()
         check_gradients(case, case.host("z").astype(np.float64), "bf16", label=f"{name} k={k} ")
+
+
+def test_gradients_of_rows_that_are_never_kept(gpu):
+    """Enough rows, few enough of them kept, for the conversion that does not read the others: every row is written."""
+    print("[case] sparse conversion", flush=True)
+    k, lens = 100, (1000,) * 20 + (1,)
+    inp = wlmod.make_inputs(wlmod.small_workload("sparse_rows", 990, 4, 2, 128, k, lens))
+    case = DeviceCase(inp, gpu)   # (outputs start as NaN)
+    case.mask_gen()
+    case.fwd()
+    case.bwd()
+    check_gradients(case, case.host("z").astype(np.float64), "bf16", label="sparse rows ")
+    never = (case.host("expiry") == np.arange(inp.T)[None, :]).reshape(2, 2, inp.T).all(axis=1)  # [kv-head, token]
+    assert 0.3 < never.mean() < 0.9
+    assert (case.host("dK").transpose(1, 0, 2)[never] == 0).all() and (case.host("dV").transpose(1, 0, 2)[never] == 0).all()
