@@ -40,9 +40,23 @@ __device__ __forceinline__ void plan_consts(uint32_t* consts, size_t i, float sc
 // blk[i] = {document, first row, end row, w}: the attention kernels take min(k, first row - w) as the
 // number of resident slot columns of the block.  Causal: w = first row of the document (the keys
 // before the block); otherwise every block of a document has min(k, n) columns.
-__global__ void blkinfo_kernel(const int32_t* __restrict__ cu, int n_docs, int nblk_cap, int k, int causal, int4* blk,
-                               int32_t* docblk, int32_t* hdr, uint32_t* consts, float scale) {
+// It is made by one workgroup of the score launch (a launch of its own took 2 to 4 us and as much of the host).
+struct BlkArgs {
+  const int32_t* cu;
+  int n_docs, nblk_cap, k, causal;
+  int4* blk;
+  int32_t *docblk, *hdr;
+  uint32_t* consts;
+  float scale;
+};
+__device__ __forceinline__ void block_table(const BlkArgs& p) {  // 256 threads
   __shared__ int s_total, s_scan[4];
+  const int32_t* __restrict__ cu = p.cu;
+  const int n_docs = p.n_docs, nblk_cap = p.nblk_cap, k = p.k, causal = p.causal;
+  int4* blk = p.blk;
+  int32_t *docblk = p.docblk, *hdr = p.hdr;
+  uint32_t* consts = p.consts;
+  const float scale = p.scale;
   plan_consts(consts, threadIdx.x, scale);
   // docblk = exclusive prefix sum of the documents' block counts: 256 documents per round, scanned in the
   // waves' registers (a call of a few documents is all latency: 3.2 -> 2.3 us), the running total carried between rounds
@@ -102,12 +116,17 @@ __global__ void fill_i32_kernel(int32_t* p, size_t n, int32_t v) {
 template <typename TV, int D, int GMAX>
 __global__ __launch_bounds__(256) void z_kernel(const TV* __restrict__ V, const float* __restrict__ W,
                                                 const float* __restrict__ A, float* __restrict__ z,
-                                                float* __restrict__ zq, float inv_scale, int T, int H_q, int H_kv) {
+                                                float* __restrict__ zq, float inv_scale, int T, int H_q, int H_kv,
+                                                BlkArgs blocks) {
+  if (blockIdx.x == 0) {  // (the first column of the grid: its first workgroup makes the block table)
+    if (blockIdx.y == 0) block_table(blocks);
+    return;
+  }
   extern __shared__ float zs[];  // [G][64]
   constexpr int LPR = D / 8;     // lanes per value row (8 elements per lane)
   constexpr int RPP = 256 / LPR; // rows per pass
   constexpr int NP = 64 / RPP;
-  const int g = blockIdx.y, G = H_q / H_kv, t0 = blockIdx.x * 64;
+  const int g = blockIdx.y, G = H_q / H_kv, t0 = (blockIdx.x - 1) * 64;
   const int tid = threadIdx.x, sub = tid % LPR, rl = tid / LPR;
   float v[NP][8];
 #pragma unroll
@@ -173,9 +192,13 @@ __global__ __launch_bounds__(256) void z_kernel(const TV* __restrict__ V, const 
 // zq = z / softmax_scale for scores supplied by the caller (the attention kernels start their
 // Q K^T accumulators at it, so that scale * accumulator is the biased score).
 __global__ __launch_bounds__(256) void zq_kernel(const float* __restrict__ z, float* __restrict__ zq,
-                                                 float inv_scale, size_t n) {
-  size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  const size_t st = (size_t)gridDim.x * blockDim.x;
+                                                 float inv_scale, size_t n, BlkArgs blocks) {
+  if (blockIdx.x == 0) {
+    block_table(blocks);
+    return;
+  }
+  size_t i = (blockIdx.x - 1) * (size_t)blockDim.x + threadIdx.x;
+  const size_t st = (size_t)(gridDim.x - 1) * blockDim.x;
   for (; i < n; i += st) zq[i] = z[i] * inv_scale;
 }
 
@@ -217,7 +240,7 @@ __device__ __forceinline__ int seg_woff(int seg, int a, int d, int p) {
 // positions the mask of zero bits and the number of zeros before the word; the array is stably
 // partitioned, zeros first, for the next level).  A document of one segment leaves its rank order in
 // si0 for expiry_kernel; the segments of a longer document leave their sorted keys and local
-// indices in sk1 / si1 for merge_expiry_kernel.
+// indices in sk1 / si1 for expiry_kernel.
 template <int NB>  // chunks of 64 keys per wave: a segment is 16 waves x NB chunks = 1024 NB keys
 __global__ __launch_bounds__(1024) void sort_wavelet_kernel(SortArgs p) {
   constexpr int SEG = 1024 * NB;
@@ -426,23 +449,6 @@ __device__ __forceinline__ uint32_t wavelet_kth(const SortArgs& p, int h, int sl
   return val;
 }
 
-// Documents of one segment.  One thread per (head, rank position): expiry of the key at that rank,
-// e_j = max(j, k-th smallest index among the keys ranked ahead of j).
-__global__ __launch_bounds__(256) void expiry_kernel(SortArgs p) {
-  const int t = blockIdx.x * 256 + threadIdx.x, h = blockIdx.y;
-  if (t >= p.T) return;
-  const int d = find_doc(p.cu, p.n_docs, t);
-  const int a = p.cu[d], b = p.cu[d + 1], n = b - a;
-  if (n <= p.k || n > p.seg) return;
-  const int r = t - a;
-  const int j = (int)p.si0[(size_t)h * p.T + t];
-  int e = b;
-  if (r >= p.k)
-    e = a + max(j, (int)wavelet_kth(p, h, seg_slot(p.seg, a, d, 0), seg_woff(p.seg, a, d, 0), dev_ceil_log2(n), (uint32_t)r,
-                                    (uint32_t)p.k - 1u));
-  p.expiry[(size_t)h * p.T + a + j] = e;
-}
-
 // Longer documents.  One thread per (head, key), visited in the sorted order of its segment.  Its
 // rank in the whole document is its rank in the segment plus, for every other segment, the number
 // of keys there that come before it -- a binary search in that segment's sorted keys (ties go to
@@ -454,14 +460,28 @@ __global__ __launch_bounds__(256) void expiry_kernel(SortArgs p) {
 // at the one that holds the k-th earlier-ranked key -- for most keys of a long document the first
 // segment already holds k better keys, and an answer in an earlier segment needs no quantile query
 // (every index there is below the key's own, so the key is never kept).
-template <bool RANK>
-__global__ __launch_bounds__(256) void merge_expiry_kernel(SortArgs p) {
+// A document of one segment needs no search: the thread takes the key at rank r = its position and asks the segment's
+// wavelet matrix for e_j = max(j, k-th smallest index among the keys ranked ahead of j).  LONG: some document may have
+// several segments (one launch serves both kinds: a second one took 4 to 5 us).
+template <bool RANK, bool LONG>
+__global__ __launch_bounds__(256) void expiry_kernel(SortArgs p) {
   const int t = blockIdx.x * 256 + threadIdx.x, h = blockIdx.y;
   if (t >= p.T) return;
   const int d = find_doc(p.cu, p.n_docs, t);
   const int a = p.cu[d], b = p.cu[d + 1], n = b - a;
   const int SEG = p.seg;
-  if (n <= p.k || n <= SEG) return;
+  if (n <= p.k) return;
+  if (!LONG || n <= SEG) {
+    if (RANK) return;  // (one segment: its rank order is the document's)
+    const int r = t - a;
+    const int j = (int)p.si0[(size_t)h * p.T + t];
+    int e = b;
+    if (r >= p.k)
+      e = a + max(j, (int)wavelet_kth(p, h, seg_slot(SEG, a, d, 0), seg_woff(SEG, a, d, 0), dev_ceil_log2(n), (uint32_t)r,
+                                      (uint32_t)p.k - 1u));
+    p.expiry[(size_t)h * p.T + a + j] = e;
+    return;
+  }
   const int nseg = (n + SEG - 1) / SEG;
   const int ps = (t - a) / SEG, r = (t - a) - ps * SEG;
   const size_t hd = (size_t)h * p.T + a;
@@ -605,6 +625,57 @@ __global__ __launch_bounds__(256) void slot_table_kernel(const int32_t* __restri
   if (slot < b0 * BQ && e >= min(b0 * BQ + BQ, n)) slot_tab[((size_t)h * nblk_cap + blk0 + b0) * kpad + slot] = -2 - t;
 }
 
+// The partial lists of two blocks (BQ threads each; b: this half's block, or -1): keys that enter inside the block and stay
+// to its end in a slot column of their own (ascending; pent counts them: the key-stationary backward takes them in
+// its slot sweep), then the other keys that enter inside the block (ascending), then keys that were
+// resident at the block's first row and are evicted inside it (by ascending evictor).
+struct ListArgs {
+  const int32_t* parent;
+  int32_t *pcnt, *pent, *plist;
+};
+__device__ __forceinline__ void partial_lists(const int4* __restrict__ blk, const int32_t* __restrict__ expiry,
+                                              const int32_t* __restrict__ slotid, const ListArgs& p, int b, int h, int T,
+                                              int nblk_cap) {
+  __shared__ int cnt[2][3][BQ / 64];
+  const int half = threadIdx.x / BQ, tid = threadIdx.x % BQ, w = tid >> 6, l = tid & 63;
+  const int4 info = b >= 0 ? blk[b] : make_int4(-1, 0, 0, 0);
+  const int i = info.y + tid;
+  const int e = info.x >= 0 && i < info.z ? expiry[(size_t)h * T + i] : 0;
+  const bool ent = info.x >= 0 && i < info.z && e > i;
+  int m = -1;
+  bool stays = false;  // its slot column belongs to it alone from here to the block's end: an older column, or its own new one
+  if (ent) {
+    m = p.parent[(size_t)h * T + i];
+    const int col = slotid[(size_t)h * T + i];
+    stays = e >= info.z && (col < info.y - info.w || col == i - info.w);  // (causal plan: w = first row of the document)
+  }
+  const bool exq = ent && m >= 0 && m < info.y && i > info.y;  // evicted at the block's first row: not active here
+  const unsigned long long sm = __ballot(ent && stays), em = __ballot(ent && !stays), xm = __ballot(exq);
+  const unsigned long long lt = (1ull << l) - 1ull;
+  __syncthreads();  // (the counts of the blocks before have been read)
+  if (l == 0) {
+    cnt[half][0][w] = __popcll(sm);
+    cnt[half][1][w] = __popcll(em);
+    cnt[half][2][w] = __popcll(xm);
+  }
+  __syncthreads();
+  if (b < 0) return;
+  int sbase = 0, ebase = 0, xbase = 0, stot = 0, etot = 0, xtot = 0;
+  for (int i2 = 0; i2 < BQ / 64; i2++) {
+    if (i2 < w) { sbase += cnt[half][0][i2]; ebase += cnt[half][1][i2]; xbase += cnt[half][2][i2]; }
+    stot += cnt[half][0][i2];
+    etot += cnt[half][1][i2];
+    xtot += cnt[half][2][i2];
+  }
+  int32_t* out = p.plist + ((size_t)h * nblk_cap + b) * MAXPART;
+  if (ent) out[stays ? sbase + __popcll(sm & lt) : stot + ebase + __popcll(em & lt)] = i;
+  if (exq) out[stot + etot + xbase + __popcll(xm & lt)] = m;
+  if (tid == 0) {
+    p.pcnt[(size_t)h * nblk_cap + b] = stot + etot + xtot;
+    p.pent[(size_t)h * nblk_cap + b] = stot;
+  }
+}
+
 // The same table, row by row, in tiles of SLOT_TILE columns.  One workgroup per (chunk of
 // consecutive blocks, head, column tile) keeps in LDS, per slot, the latest key of the slot's chain, with its
 // expiry; a block's own keys are taken in and its row is then one coalesced pass (the key if it
@@ -613,15 +684,23 @@ __global__ __launch_bounds__(256) void slot_table_kernel(const int32_t* __restri
 // earlier keys (exactly one key per chain is still kept at a given row; every column tile repeats
 // the scan, so this kernel serves windows of up to SLOT_TILES_MAX tiles).  The scattered 4-byte
 // stores of the kernel above cost a 64-byte write each; these rows are written whole.
+// The last layer of the grid makes the chunks' partial lists (a launch of its own took 4 to 9 us).
 constexpr int SLOT_TILE = 4096;
 constexpr int SLOT_TILES_MAX = 4;
 __global__ __launch_bounds__(512) void slot_rows_kernel(const int4* __restrict__ blk, const int32_t* __restrict__ expiry,
                                                         const int32_t* __restrict__ slotid, int32_t* slot_tab, int T,
-                                                        int nblk_cap, int kpad, int blocks_per_chunk) {
+                                                        int nblk_cap, int kpad, int blocks_per_chunk, ListArgs lists) {
   __shared__ unsigned long long cur[SLOT_TILE];  // (key + 1) << 32 | expiry; 0 = no key yet
   const int h = blockIdx.y, tid = threadIdx.x;
-  const int c0 = blockIdx.z * SLOT_TILE, nc = min(SLOT_TILE, kpad - c0);  // this workgroup's columns
   const int b_begin = blockIdx.x * blocks_per_chunk, b_end = min(b_begin + blocks_per_chunk, nblk_cap);
+  if (blockIdx.z + 1 == gridDim.z) {
+    for (int b0 = b_begin; b0 < b_end; b0 += 2) {
+      const int b = b0 + tid / BQ;
+      partial_lists(blk, expiry, slotid, lists, b < b_end ? b : -1, h, T, nblk_cap);
+    }
+    return;
+  }
+  const int c0 = blockIdx.z * SLOT_TILE, nc = min(SLOT_TILE, kpad - c0);  // this workgroup's columns
   const int32_t* ex = expiry + (size_t)h * T;
   const int32_t* sid = slotid + (size_t)h * T;
   int doc = -1;
@@ -677,58 +756,6 @@ __global__ __launch_bounds__(512) void slot_rows_kernel(const int4* __restrict__
       row[c] = entry;
     }
     __syncthreads();
-  }
-}
-
-// One workgroup (BQ threads) per (block, head): keys that enter inside the block and stay to its end
-// in a slot column of their own (ascending; pent counts them: the key-stationary backward takes them in
-// its slot sweep), then the other keys that enter inside the block (ascending), then keys that were
-// resident at the block's first row and are evicted inside it (by ascending evictor).
-__global__ __launch_bounds__(BQ) void partial_list_kernel(const int4* __restrict__ blk,
-                                                          const int32_t* __restrict__ expiry,
-                                                          const int32_t* __restrict__ parent,
-                                                          const int32_t* __restrict__ slotid, int32_t* pcnt,
-                                                          int32_t* pent, int32_t* plist, int T, int nblk_cap) {
-  const int bi = blockIdx.x, h = blockIdx.y;
-  const int4 info = blk[bi];
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
-  if (info.x < 0) {
-    if (tid == 0) pcnt[(size_t)h * nblk_cap + bi] = pent[(size_t)h * nblk_cap + bi] = 0;
-    return;
-  }
-  const int i = info.y + tid;
-  const int e = i < info.z ? expiry[(size_t)h * T + i] : 0;
-  const bool ent = (i < info.z) && e > i;
-  int m = -1;
-  bool stays = false;  // its slot column belongs to it alone from here to the block's end: an older column, or its own new one
-  if (ent) {
-    m = parent[(size_t)h * T + i];
-    const int col = slotid[(size_t)h * T + i];
-    stays = e >= info.z && (col < info.y - info.w || col == i - info.w);  // (causal plan: w = first row of the document)
-  }
-  const bool exq = ent && m >= 0 && m < info.y && i > info.y;  // evicted at the block's first row: not active here
-  __shared__ int cnt[3][BQ / 64];
-  const unsigned long long sm = __ballot(ent && stays), em = __ballot(ent && !stays), xm = __ballot(exq);
-  const unsigned long long lt = (1ull << l) - 1ull;
-  if (l == 0) {
-    cnt[0][w] = __popcll(sm);
-    cnt[1][w] = __popcll(em);
-    cnt[2][w] = __popcll(xm);
-  }
-  __syncthreads();
-  int sbase = 0, ebase = 0, xbase = 0, stot = 0, etot = 0, xtot = 0;
-  for (int i2 = 0; i2 < BQ / 64; i2++) {
-    if (i2 < w) { sbase += cnt[0][i2]; ebase += cnt[1][i2]; xbase += cnt[2][i2]; }
-    stot += cnt[0][i2];
-    etot += cnt[1][i2];
-    xtot += cnt[2][i2];
-  }
-  int32_t* out = plist + ((size_t)h * nblk_cap + bi) * MAXPART;
-  if (ent) out[stays ? sbase + __popcll(sm & lt) : stot + ebase + __popcll(em & lt)] = i;
-  if (exq) out[stot + etot + xbase + __popcll(xm & lt)] = m;
-  if (tid == 0) {
-    pcnt[(size_t)h * nblk_cap + bi] = stot + etot + xtot;
-    pent[(size_t)h * nblk_cap + bi] = stot;
   }
 }
 
@@ -971,16 +998,15 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
   int32_t* slotid = (int32_t*)(base + L.off_slotid);
 
   prof_begin(DMA_STAGE_Z, st);
-  blkinfo_kernel<<<1, 256, 0, st>>>(cu, s.n_docs, L.nblk_cap, s.k, s.causal, blk, docblk, hdr,
-                                   (uint32_t*)(base + L.off_consts), p.scale);
+  const BlkArgs blocks = {cu, s.n_docs, L.nblk_cap, s.k, s.causal, blk, docblk, hdr, (uint32_t*)(base + L.off_consts), p.scale};
   float* zq = (float*)(base + L.off_zq);
   const float inv_scale = 1.0f / p.scale;
   if (W) {
     const int G = s.H_q / s.H_kv;
-    dim3 grid((s.T + 63) / 64, s.H_kv);
+    dim3 grid(1 + (s.T + 63) / 64, s.H_kv);
     const size_t sh = (size_t)G * 64 * sizeof(float);
 #define DMA_Z(TV, DD, GM) \
-  z_kernel<TV, DD, GM><<<grid, 256, sh, st>>>((const TV*)V, W, A, z, zq, inv_scale, s.T, s.H_q, s.H_kv)
+  z_kernel<TV, DD, GM><<<grid, 256, sh, st>>>((const TV*)V, W, A, z, zq, inv_scale, s.T, s.H_q, s.H_kv, blocks)
     if (s.dtype == DMA_BF16) {
       if (s.d == 256) { if (G <= 4) DMA_Z(uint16_t, 256, 4); else DMA_Z(uint16_t, 256, 8); }
       else if (s.d == 128) { if (G <= 4) DMA_Z(uint16_t, 128, 4); else DMA_Z(uint16_t, 128, 8); }
@@ -996,7 +1022,7 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
     const size_t n = (size_t)s.H_q * s.T;
     size_t grid = (n + 1023) / 1024;
     if (grid > (1u << 20)) grid = 1u << 20;
-    zq_kernel<<<(unsigned)grid, 256, 0, st>>>(z, zq, inv_scale, n);
+    zq_kernel<<<1 + (unsigned)grid, 256, 0, st>>>(z, zq, inv_scale, n, blocks);
   }
   prof_end(DMA_STAGE_Z, st);
   const bool all_kept = s.causal && (s.max_seqlen > 0 && s.max_seqlen < s.T ? s.max_seqlen : s.T) <= s.k;
@@ -1038,27 +1064,27 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
     fill(slot_tab, (size_t)s.H_q * L.nblk_cap * L.kpad, -1);
     fill(pcnt, (L.off_plist - L.off_pcnt) / 4, 0);  // pcnt and pent
     // (documents of several segments get their whole-document rank order from the merge kernel)
-    if (s.T > L.seg) merge_expiry_kernel<true><<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
+    if (s.T > L.seg) expiry_kernel<true, true><<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
     noncausal_plan_kernel<<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(cu, s.n_docs, sa.si0, docblk, expiry, slot_tab,
                                                                         s.T, s.k, L.nblk_cap, L.kpad);
   } else {
     prof_begin(DMA_STAGE_EXPIRY, st);
-    // (documents of one segment / of several segments; a single document is one or the other)
-    if (s.n_docs > 1 || s.T <= L.seg) expiry_kernel<<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
-    if (s.T > L.seg) merge_expiry_kernel<false><<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
+    if (s.T > L.seg) expiry_kernel<false, true><<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
+    else expiry_kernel<false, false><<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
     prof_end(DMA_STAGE_EXPIRY, st);
     prof_begin(DMA_STAGE_PLAN, st);
     slot_kernel<<<dim3(s.n_docs, s.H_q), 1024, 0, st>>>(cu, expiry, parent, slotid, s.T, s.k);
-    if (L.kpad <= SLOT_TILES_MAX * SLOT_TILE) {
-      const int per = L.nblk_cap / 16 > 4 ? L.nblk_cap / 16 : 4;  // about 16 chunks per head
-      slot_rows_kernel<<<dim3((L.nblk_cap + per - 1) / per, s.H_q, (L.kpad + SLOT_TILE - 1) / SLOT_TILE), 512, 0, st>>>(blk, expiry, slotid, slot_tab, s.T,
-                                                                               L.nblk_cap, L.kpad, per);
-    } else {
+    const int per = L.nblk_cap / 16 > 4 ? L.nblk_cap / 16 : 4;  // about 16 chunks per head
+    int tiles = (L.kpad + SLOT_TILE - 1) / SLOT_TILE;
+    if (tiles > SLOT_TILES_MAX) {
+      tiles = 0;  // (the launch below is left with the partial lists)
       fill(slot_tab, (size_t)s.H_q * L.nblk_cap * L.kpad, -1);
       slot_table_kernel<<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(cu, s.n_docs, expiry, slotid, docblk, slot_tab,
                                                                       s.T, L.nblk_cap, L.kpad);
     }
-    partial_list_kernel<<<dim3(L.nblk_cap, s.H_q), BQ, 0, st>>>(blk, expiry, parent, slotid, pcnt, pent, plist, s.T, L.nblk_cap);
+    const ListArgs lists = {parent, pcnt, pent, plist};
+    slot_rows_kernel<<<dim3((L.nblk_cap + per - 1) / per, s.H_q, tiles + 1), 512, 0, st>>>(blk, expiry, slotid, slot_tab, s.T,
+                                                                                         L.nblk_cap, L.kpad, per, lists);
   }
   if (topk_idx) topk_idx_kernel<<<dim3(s.T, s.H_q), 64, 0, st>>>(cu, s.n_docs, s.causal, expiry, topk_idx, s.T, s.k);
   prof_end(DMA_STAGE_PLAN, st);
