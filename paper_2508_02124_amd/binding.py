@@ -98,20 +98,30 @@ def lib():
 
 
 def _ptr(x):
-    if x is None:
-        return None
-    if isinstance(x, int):
-        return ctypes.c_void_p(x)
-    return ctypes.c_void_p(x.data_ptr())
+    # (an address as a plain int: the c_void_p parameters take it as it is)
+    if x is None or isinstance(x, int):
+        return x
+    return x.data_ptr()
+
+
+_raw_stream = None
 
 
 def _stream(stream):
+    """The stream's handle; None = torch's current stream of the current device, asked for without the Stream object
+    that torch.cuda.current_stream() makes (2.8 -> 0.3 us of every call)."""
+    global _raw_stream
     if stream is None:
         import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        if _raw_stream is None:
+            get = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+            if get is None or not torch.cuda.is_initialized():
+                return torch.cuda.current_stream().cuda_stream
+            _raw_stream = (get, torch._C._cuda_getDevice)
+        return _raw_stream[0](_raw_stream[1]())
     if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 def make_shape(T, n_docs, H_q, H_kv, d, k, causal=True, dtype=DMA_BF16, softmax_scale=0.0, max_seqlen=0):
