@@ -97,24 +97,6 @@ def measured_traffic(kernel):
     return None
 
 
-def clean_pair_count(case, k):
-    """Kept (row, key) pairs that dkv_kernel<clean> works on, summed over heads, counted on the host from the
-    (causal) plan: per block and head all rows of the keys resident for the whole block, and the rows from its own on of
-    every key that enters inside the block and stays to its end in a slot column (named -2 - key in the table; a key among
-    its document's first k has a new column of its own)."""
-    import numpy as np
-    eg, pv = case.host("expiry").astype(np.int64), case.plan_views()
-    pairs = 0
-    for b in range(pv["nblk"]):
-        _, r0, r1, doc0 = (int(x) for x in pv["blk"][b])
-        row = pv["slot"][:, b]
-        named = row[row < -1]
-        pairs += int((row >= 0).sum()) * (r1 - r0) + int((r1 + 2 + named.astype(np.int64)).sum())
-        j = np.arange(r0, min(r1, doc0 + k))
-        pairs += int(((eg[:, j] >= r1) * (r1 - j)).sum())
-    return pairs
-
-
 def time_workload(wl, steps, warmup, dev, structured_z=False, calibration_copy=False):
     """Times `steps` steps (mask_gen + fwd [+ bwd]) of one workload.  Returns the timing record and the
     device case.  Stage events are recorded inside the timed region on every fourth step (an armed
@@ -192,16 +174,14 @@ def time_workload(wl, steps, warmup, dev, structured_z=False, calibration_copy=F
 def roofline_objects(wl, inp, case, rec, with_traffic):
     """Roofline records of the kernels of the step.  MFMA kernels: algorithmic FLOPs of the launch
     (per kept pair: forward 4d = S and PV; dQ kernel 6d = S, dP, dQ; key-stationary kernel 8d = S, dP,
-    dV, dK on the pairs of its launch) / mean launch duration / 2.5 PFLOP/s.  The score kernel of
-    mask generation is HBM-bound: bytes of V read once + z and z / scale written, / duration / 8 TB/s
-    (its stage also holds the block-table launch, a few microseconds)."""
-    import numpy as np
+    dV, dK) / mean launch duration / 2.5 PFLOP/s.  The score kernel of
+    mask generation is HBM-bound: bytes of V read once + z and z / scale written, / duration / 8 TB/s."""
     stage_ms = rec["stage_ms"]
     nact = rec["nact"]
     stage_flops = {"fwd": 4.0 * wl.d * nact * wl.H_q}
     if wl.backward:
         stage_flops["bwd_dq"] = 6.0 * wl.d * nact * wl.H_q
-        stage_flops["bwd_dkv"] = 8.0 * wl.d * clean_pair_count(case, wl.k)
+        stage_flops["bwd_dkv"] = 8.0 * wl.d * nact * wl.H_q  # (slot sweeps and partial lists are one launch)
     kernel_names = {"fwd": "fwd_kernel", "bwd_dq": "dq_kernel", "bwd_dkv": "dkv_kernel<clean>"}
     objs = {}
     for st, fl in stage_flops.items():

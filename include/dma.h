@@ -298,8 +298,8 @@ typedef enum {
   DMA_STAGE_FWD = 4,        /* fwd: the attention kernel                                  */
   DMA_STAGE_BWD_ZERO = 5,   /* bwd: (empty: the dQ stage clears the fp32 accumulators)   */
   DMA_STAGE_BWD_DQ = 6,     /* bwd: D and dQ (query-stationary)                           */
-  DMA_STAGE_BWD_DKV = 7,    /* bwd: dK, dV, dz on the slot columns (key-stationary)       */
-  DMA_STAGE_BWD_PART = 8,   /* bwd: dK, dV, dz of keys entering / expiring inside a block */
+  DMA_STAGE_BWD_DKV = 7,    /* bwd: dK, dV, dz (key-stationary)                           */
+  DMA_STAGE_BWD_PART = 8,   /* bwd: (empty: the DKV stage has the partial lists too)      */
   DMA_STAGE_BWD_CVT = 9,    /* bwd: fp32 accumulators -> output dtype                     */
   DMA_N_STAGES = 10
 } dma_stage;

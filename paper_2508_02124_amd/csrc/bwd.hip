@@ -43,6 +43,7 @@ struct BwdArgs {
   size_t zero_n4;  // float4 elements from dK32 to the end of dV32 (cleared by dq_kernel)
   size_t dz_n;     // elements of dz (cleared by dq_kernel)
   unsigned grid_dq;  // workgroups of the dq_kernel launch
+  unsigned grid_clean;  // workgroups of the slot sweeps in the dkv_kernel launch (a multiple of 8)
 };
 
 // ------------------------------------------------------------------ dQ (and D, LSE * log2 e)
@@ -439,36 +440,53 @@ constexpr int MAXSWEEP = 64;     // most query blocks one key-stationary work it
 // to 2.1 GHz.  At 256 channels, one wave per SIMD at 2.4 GHz, the products' own latencies count: 3600 of 5800 cycles.
 // Registers decide the rest: the accumulators take D, so all of the K fragments and some of V's wait in LDS at 128
 // channels (two ring stages instead of three make room) and half of K's at 256; small lane-dependent
-// values are formed where they are used (fresh_lane).  Slot sweep / partial launch, us, with the products in the
+// values are formed where they are used (fresh_lane).  Slot sweep / partial lists (as launches of their own), us, with the products in the
 // compiler's order, the keys' rows through registers and a wait in every pass of a flush -> now: 16384 tokens x 32 heads
 // 1160 / 186 -> 1060 / 168; 2 x 4096 x 16 heads 193 / 81 -> 167 / 66; 16 heads of 256 channels 1775 / 278 -> 1290 / 246;
 // packed 65536 x 16 heads of 64 channels 371 / 169 -> 363 / 167.
+template <int D> struct DkvShape {
+  static constexpr int KS = D / 16, CB = D / 32;
+  static constexpr int SUB = 32;                       // query rows per pipeline step
+  static constexpr int NS = D == 64 ? 4 : D == 128 ? 2 : 3;  // ring stages
+  static constexpr int STILE = SUB * D;
+  static constexpr int KL = D == 64 ? 0 : 8;           // contraction steps whose K fragments wait in LDS
+  static constexpr int VL = D == 128 ? 2 : 0;          // ... and V fragments
+  static constexpr int STR = 8, STC = D == 64 ? 64 : 32;  // flush staging: columns, channels
+  static constexpr int LDS_ST = STC + 4;               // padded staging row
+};
+template <int D> struct DkvShared {
+  using S = DkvShape<D>;
+  __align__(16) uint16_t ringQ[S::NS * S::STILE];
+  __align__(16) uint16_t ringdO[S::NS * S::STILE];
+  __align__(16) float meta[S::NS][64];   // per stage: [0,32) LSE * log2 e, [32,64) -D
+  __align__(16) int idbuf[2][SG];        // column ids of the current / next block
+  __align__(16) int4 binfo[MAXSWEEP + 1];  // block table of this work item's sweep
+  __align__(16) float stage_all[DKV_NW * S::STR * S::LDS_ST];  // per wave: [STR columns][STC channels] fp32, flush staging
+  __align__(16) bf16x8 vlds[S::VL ? DKV_NW * S::VL * 64 : 1];
+  __align__(16) bf16x8 klds[S::KL ? DKV_NW * S::KL * 64 : 1];  // [wave][ks][lane]: K fragments of the first KL steps
+  int nblocks;
+};
 template <int D, bool PARTIAL>
-__global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : D == 64 ? 3 : 2) void dkv_kernel(BwdArgs p) {
+__device__ __forceinline__ void dkv_sweep(const BwdArgs& p, const int wg, DkvShared<D>& sm) {
   using TL = TileLayout<D>;
-  constexpr int KS = D / 16, CB = D / 32, CPR = D / 8, RPL = 64 / CPR;
-  constexpr int SUB = 32;                 // query rows per pipeline step
+  using S = DkvShape<D>;
+  constexpr int KS = S::KS, CB = S::CB, CPR = D / 8, RPL = 64 / CPR;
+  constexpr int SUB = S::SUB, NS = S::NS, STILE = S::STILE, KL = S::KL, VL = S::VL, STR = S::STR, STC = S::STC, LDS_ST = S::LDS_ST;
   constexpr int NSUB = BQ / SUB;          // steps per query block
   constexpr int NWL = 2 * (SUB / RPL);    // 16-byte wave copies per step (Q rows, then dO rows)
-  constexpr int NS = D == 64 ? 4 : D == 128 ? 2 : 3;  // ring stages
-  constexpr int STILE = SUB * D;
-  constexpr int KL = D == 64 ? 0 : 8;  // contraction steps whose K fragments wait in LDS
-  constexpr int VL = D == 128 ? 2 : 0; // ... and V fragments
-  constexpr int STR = 8, STC = D == 64 ? 64 : 32;  // flush staging: columns, channels
-  constexpr int LDS_ST = STC + 4;         // padded staging row
-  __shared__ __align__(16) uint16_t ringQ[NS * STILE];
-  __shared__ __align__(16) uint16_t ringdO[NS * STILE];
-  __shared__ __align__(16) float meta[NS][64];   // per stage: [0,32) LSE * log2 e, [32,64) -D
-  __shared__ __align__(16) int idbuf[2][SG];     // column ids of the current / next block
-  __shared__ __align__(16) int4 binfo[MAXSWEEP + 1];  // block table of this work item's sweep
-  __shared__ __align__(16) float stage_all[DKV_NW * STR * LDS_ST];  // per wave: [STR columns][STC channels] fp32, flush staging
-  __shared__ __align__(16) bf16x8 vlds[VL ? DKV_NW * VL * 64 : 1];
-  __shared__ __align__(16) bf16x8 klds[KL ? DKV_NW * KL * 64 : 1];  // [wave][ks][lane]: K fragments of the first KL steps
+  auto& ringQ = sm.ringQ;
+  auto& ringdO = sm.ringdO;
+  auto& meta = sm.meta;
+  auto& idbuf = sm.idbuf;
+  auto& binfo = sm.binfo;
+  auto& stage_all = sm.stage_all;
+  auto& vlds = sm.vlds;
+  auto& klds = sm.klds;
 
   const int ngrp = PARTIAL ? MAXPART / SG : p.kpad / SG;
   const int nchunk = (p.nblk_cap + (PARTIAL ? p.seg_part : p.seg) - 1) / (PARTIAL ? p.seg_part : p.seg);
   int h, item;
-  if (!xcd_map(wg_id(), p.H_q, ngrp * nchunk, h, item)) return;
+  if (!xcd_map(wg, p.H_q, ngrp * nchunk, h, item)) return;
   // Clean mode: the groups of a chunk are neighbours.  Partial mode: group-major, because the high
   // groups of most chunks are empty and workgroups go to the shader engines in turn: with the
   // groups as the fast index all the work would land on the engines that get groups 0 and 1.
@@ -496,7 +514,7 @@ __global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : D == 64 ? 3 : 2) void d
   // {block index, first row, rows | columns of this group << 16, x} of every block of the chunk in which
   // the group has at least one column (clean mode: slots in use at the block's end, x = the document's
   // first row; partial mode: listed keys, x = first list entry).
-  __shared__ int nblocks_s;
+  int& nblocks_s = sm.nblocks;
   for (int i = tid; i < MAXSWEEP + 1; i += DKV_NW * 64) binfo[i] = make_int4(-1, 0, 0, 0);
   __syncthreads();
   if (w == 0) {
@@ -903,6 +921,18 @@ __global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : D == 64 ? 3 : 2) void d
   flush(true);
 }
 
+// The slot sweeps' workgroups first, one for every place on the chip, then those of the partial lists: these are short
+// and start where sweeps end early (a sweep of 16384 tokens x 32 heads ends between 917 and 1146 us).  One launch against
+// two, us: 16384 x 32 heads 1260 -> 1155, 2 x 4096 x 16 heads 238 -> 217, packed 65536 x 16 heads of 64 channels 538 -> 495,
+// 16 heads of 256 channels 1523 -> 1443, 300 tokens x 2 heads 53 -> 28.
+template <int D>
+__global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : D == 64 ? 3 : 2) void dkv_kernel(BwdArgs p) {
+  __shared__ DkvShared<D> sm;
+  const int wg = wg_id();
+  if (wg < (int)p.grid_clean) dkv_sweep<D, false>(p, wg, sm);
+  else dkv_sweep<D, true>(p, wg - (int)p.grid_clean, sm);
+}
+
 // dK, dV: fp32 accumulators -> bf16 outputs.  HBM-bound (5.8 TB/s).  SPARSE: a row that no q-head of its group ever keeps
 // has a zero gradient, and its accumulators are not read (packed 65536 x 16 heads, d = 64, window 512, no groups, where
 // 37 % of the rows are kept: 141 -> 98 us).  Looking at the expiries costs 30 % where most rows are kept (16384 tokens,
@@ -1019,15 +1049,13 @@ int launch_bwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
   else if (s.d == 128) dq_kernel<128, 8, 2><<<gq, 512, 0, st>>>(a);
   else dq_kernel<64, 4, 2><<<gq, 256, 0, st>>>(a);
   prof_end(DMA_STAGE_BWD_DQ, st);
+  a.grid_clean = gclean;
   prof_begin(DMA_STAGE_BWD_DKV, st);
-  if (s.d == 256) dkv_kernel<256, false><<<gclean, DKV_NW * 64, 0, st>>>(a);
-  else if (s.d == 128) dkv_kernel<128, false><<<gclean, DKV_NW * 64, 0, st>>>(a);
-  else dkv_kernel<64, false><<<gclean, DKV_NW * 64, 0, st>>>(a);
+  if (s.d == 256) dkv_kernel<256><<<gclean + gpart, DKV_NW * 64, 0, st>>>(a);
+  else if (s.d == 128) dkv_kernel<128><<<gclean + gpart, DKV_NW * 64, 0, st>>>(a);
+  else dkv_kernel<64><<<gclean + gpart, DKV_NW * 64, 0, st>>>(a);
   prof_end(DMA_STAGE_BWD_DKV, st);
-  prof_begin(DMA_STAGE_BWD_PART, st);
-  if (s.d == 256) dkv_kernel<256, true><<<gpart, DKV_NW * 64, 0, st>>>(a);
-  else if (s.d == 128) dkv_kernel<128, true><<<gpart, DKV_NW * 64, 0, st>>>(a);
-  else dkv_kernel<64, true><<<gpart, DKV_NW * 64, 0, st>>>(a);
+  prof_begin(DMA_STAGE_BWD_PART, st);  // (an empty stage: the launch above has the partial lists too)
   prof_end(DMA_STAGE_BWD_PART, st);
   prof_begin(DMA_STAGE_BWD_CVT, st);
   const unsigned gcvt = grid_for(nkv / 4, 1024);
