@@ -122,10 +122,10 @@ static inline WsLayout ws_layout(const dma_shape& s) {
   return w;
 }
 
-// Query blocks of all heads: the most there can be, and about how many there are (a document's last block is half full).
+// Query blocks of all heads: the most there can be, and about how many there are (documents of the average length).
 static inline double most_blocks(const dma_shape& s) { return (double)s.H_q * (double)(((long)s.T + (long)s.n_docs * (BQ - 1)) / BQ); }
 static inline double typical_blocks(const dma_shape& s) {
-  return s.n_docs == 1 ? most_blocks(s) : s.H_q * ((double)s.T / BQ + 0.5 * s.n_docs);
+  return (double)s.H_q * s.n_docs * (double)(((s.T + s.n_docs - 1) / s.n_docs + BQ - 1) / BQ);
 }
 
 // ------------------------------------------------------------------ launch entry points (defined in the .hip files)

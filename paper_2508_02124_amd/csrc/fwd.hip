@@ -71,26 +71,45 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
   int h, item;
   if (!xcd_map(wg_id(), p.H_q, p.nblk_cap * HALVES, h, item)) return;
   const int bi = p.nblk_cap - 1 - item / HALVES;  // long blocks first
+  const int tid = thread_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, n = l & 31, hh = l >> 5;
+  const int32_t* slot_row = p.slot_tab + ((size_t)h * p.nblk_cap + bi) * p.kpad;
+  const int32_t* c_m1 = reinterpret_cast<const int32_t*>(p.consts + 264);
+  // The key ids of the first tiles are requested with the block's table entry, as if all of these were slot columns: one
+  // memory latency less before the first rows (where there are fewer, the others are requested again below).  65536
+  // tokens, window 1024: 1320 -> 1275 us.  (64 channels: two workgroups per compute unit hide that latency, and the
+  // registers do not: 253 -> 275.)
+  constexpr int FIRST = 5;
+  constexpr bool EARLY = D != 64;
+  if (EARLY && w == 0) {
+#pragma unroll
+    for (int tt = 0; tt < FIRST; tt++) {
+      const int c = tt * KT + (l & (KT - 1));
+      dma4(c < p.kpad ? slot_row + c : c_m1, &ids_ring[tt % (2 * NS)][0]);
+    }
+  }
   const int4 info = p.blk[bi];
   const int np_keys = p.pcnt[(size_t)h * p.nblk_cap + bi];
   const float c2 = *reinterpret_cast<const float*>(p.consts + PLAN_C2_OFF);  // softmax scale * log2(e)
-  if (info.x < 0) return;
+  if (info.x < 0) {
+    wait_vmcnt<0>();  // (no copy may outlive the workgroup)
+    return;
+  }
   const int blk_row0 = info.y, row1 = info.z, doc0 = info.w;
   const int row0 = blk_row0 + (item % HALVES) * (NW * 32);  // first row of this workgroup's part of the block
-  if (row0 >= row1) return;
+  if (row0 >= row1) {
+    wait_vmcnt<0>();
+    return;
+  }
   const int g = h / (p.H_q / p.H_kv);
-  const int tid = thread_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, n = l & 31, hh = l >> 5;
   const int ncol = min(p.k, blk_row0 - doc0);
   const int nc = (ncol + KT - 1) / KT;
   const int shift = (NS - nc % NS) % NS;  // ring stage of tile 0: tile t takes stage (t + shift) % NS
   const int nt = nc + (np_keys + KT - 1) / KT;
-  const int32_t* slot_row = p.slot_tab + ((size_t)h * p.nblk_cap + bi) * p.kpad;
   const int32_t* plist_row = p.plist + ((size_t)h * p.nblk_cap + bi) * MAXPART;
   const float* zqh = p.zq + (size_t)h * p.T;
   const int32_t* eh = p.expiry + (size_t)h * p.T;
   const float* c_ninf = reinterpret_cast<const float*>(p.consts + 256);
   const int32_t* c_zero = reinterpret_cast<const int32_t*>(p.consts + 260);
-  const int32_t* c_m1 = reinterpret_cast<const int32_t*>(p.consts + 264);
 
   // ---- asynchronous producers (every wave issues the same number of copies for every tile index,
   // real or past the end, so the outstanding-copy counts below are constants).  A gathered row is
@@ -158,16 +177,24 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
     else wait_vmcnt<2 * WL>();
   };
 
-  for (int tt = 0; tt < 5; tt++) issue_ids(tt);
+  if (EARLY) {
+    if (w == 0 && nc < FIRST) {
+      wait_vmcnt<0>();
+      for (int tt = nc; tt < FIRST; tt++) issue_ids(tt);
+    }
+  } else {
+    for (int tt = 0; tt < FIRST; tt++) issue_ids(tt);
+  }
   // query fragments (B operand of K Q^T): lane holds row qi, channels 16*ks + 8*hh .. +8
   const int qi = row0 + 32 * w + n;
   bf16x8 qreg[KS];
   {
-    const uint16_t* qrow = p.Q + ((size_t)qi * p.H_q + h) * D + 8 * hh;
+    // (EARLY: rows past the end repeat the last one: the same number of loads for every wave, and results that nothing stores)
+    const uint16_t* qrow = p.Q + ((size_t)(EARLY ? min(qi, row1 - 1) : qi) * p.H_q + h) * D + 8 * hh;
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
       uint4 raw = make_uint4(0, 0, 0, 0);
-      if (qi < row1) raw = *reinterpret_cast<const uint4*>(qrow + 16 * ks);
+      if (EARLY || qi < row1) raw = *reinterpret_cast<const uint4*>(qrow + 16 * ks);
       qreg[ks] = __builtin_bit_cast(bf16x8, raw);
     }
   }
@@ -175,14 +202,22 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
   // stage before it: those rows have to hold numbers.
   for (int c = tid; c < 32 * CPR; c += NT)
     reinterpret_cast<uint4*>(ringV + (shift + NS - 1) % NS * TILE + TILE - 32 * D)[c] = make_uint4(0, 0, 0, 0);
-  wait_vmcnt<0>();
+  if (EARLY) {
+    wait_vmcnt<KS>();  // the ids; the loads of Q may still be on their way
+  } else {
+    wait_vmcnt<0>();
 #pragma unroll
-  for (int ks = 0; ks < KS; ks++) settle(qreg[ks]);
+    for (int ks = 0; ks < KS; ks++) settle(qreg[ks]);
+  }
   lds_barrier();
   for (int i = 0; i < 3; i++) {
     issue_rows(Kg, ldsK, i);
     issue_scalars(i);
     if (i < 2) issue_rows(Vg, ldsV, i);
+  }
+  if (EARLY) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) settle(qreg[ks]);
   }
 
   // The lane's fragment addresses with the ring bases folded in: inside the (stage-unrolled) main
