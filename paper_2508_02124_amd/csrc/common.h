@@ -10,7 +10,6 @@ namespace dma {
 
 // ------------------------------------------------------------------ tiling constants
 constexpr int BQ = 256;        // query rows per block (one workgroup of the query-stationary kernels: 8 waves x 32 rows)
-constexpr int KT = 64;         // keys per tile of dq_kernel
 constexpr int CUS = 256;       // compute units of the chip
 constexpr int MAXPART = 2 * BQ;  // a block has at most BQ entering + BQ expiring keys
 constexpr int SG = 128;        // slot columns per workgroup of the key-stationary backward
@@ -247,18 +246,6 @@ __device__ __forceinline__ void dma16s(const void* uniform_base, uint32_t lane_o
   uint32_t keep;
   asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b32 m0, %0"
                : "=&s"(keep) : "v"(lane_off), "s"(sb), "s"(lds) : "memory");
-}
-// Two copies with one scalar base each and a shared per-lane 32-bit byte offset (the K and the V row
-// piece of one gathered key): M0 is saved and restored once around the pair.
-__device__ __forceinline__ void dma16s_pair(const void* base_a, const void* base_b, uint32_t lane_off,
-                                            uint32_t lds_a, uint32_t lds_b) {
-  uint32_t keep;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\t"
-      "s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\ts_mov_b32 m0, %0"
-      : "=&s"(keep)
-      : "v"(lane_off), "s"(base_a), "s"(base_b), "s"(lds_a), "s"(lds_b)
-      : "memory");
 }
 // One copy of the same kind with the base already in scalar registers (uniform_ptr).
 __device__ __forceinline__ void dma16u(const void* base, uint32_t lane_off, uint32_t lds) {

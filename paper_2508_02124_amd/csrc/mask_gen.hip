@@ -1063,7 +1063,7 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
     prof_begin(DMA_STAGE_PLAN, st);
     fill(slot_tab, (size_t)s.H_q * L.nblk_cap * L.kpad, -1);
     fill(pcnt, (L.off_plist - L.off_pcnt) / 4, 0);  // pcnt and pent
-    // (documents of several segments get their whole-document rank order from the merge kernel)
+    // (documents of several segments get their whole-document rank order from expiry_kernel's RANK form)
     if (s.T > L.seg) expiry_kernel<true, true><<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
     noncausal_plan_kernel<<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(cu, s.n_docs, sa.si0, docblk, expiry, slot_tab,
                                                                         s.T, s.k, L.nblk_cap, L.kpad);
