@@ -21,6 +21,7 @@
 // chain of a tile at a time took 15.1 ms there, this form 13.9; 16384 tokens, window 2048: 592 -> 548 us; 16 heads of
 // 256 channels, where no second wave of a SIMD fills the gaps: 882 -> 628 us.
 #include "common.h"
+#include "softmax_ref.h"
 #include <cmath>
 
 namespace dma {
@@ -284,7 +285,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
       float mx = fmaxf(s[0], s[1]);
 #pragma unroll
       for (int v = 2; v < 16; v++) mx = fmaxf(mx, s[v]);
-      mx = half_swap_max(mx) * c2;
+      mx = reference_of(half_swap_max(mx), c2);
       const bool grow = mx > m_run;
       const float alpha = grow ? fast_exp2(m_run - mx) : 1.f;  // m_run = -inf: 0, nothing accumulated yet
       m_run = grow ? mx : m_run;

@@ -131,3 +131,44 @@ def test_bias_at_the_cfg2_shape_dense(gpu):
     B.dma_bias_bwd(case.shape, case.dz, case.cu, 1, False, dbias)
     ref_db = orc.bias_backward(dz, 1, inp.cu_seqlens, False, n_max=inp.max_seqlen)
     print("  dbias", check_close("dbias", dbias.cpu().numpy(), ref_db, **t), flush=True)
+
+
+# heads, head dimension, documents, windows: every form of the forward that the dispatch chooses
+MASKED_FORMS = {
+    "d128_half64": (2, 1, 128, (700, 33, 515), (65, 300)),
+    "d128_half32": (32, 8, 128, (1280,), (200,)),
+    "d128_whole": (32, 8, 128, (1025, 1023), (200,)),
+    "d256": (2, 1, 256, (700, 33, 515), (129,)),
+    "d64": (2, 1, 64, (700, 33, 515), (129,)),
+}
+
+
+@pytest.mark.parametrize("name", MASKED_FORMS)
+def test_bias_masks_the_first_keys(gpu, name):
+    """The first keys of every document masked by a finite bias whose last place is worth thousands of powers of two:
+    they carry no weight in a row that keeps an unmasked key, however many of them come first."""
+    H_q, H_kv, d, lens, windows = MASKED_FORMS[name]
+    for k in windows:
+        inp = wlmod.make_inputs(wlmod.small_workload(f"masked_{name}", 75 + k, H_q, H_kv, d, k, lens))
+        case = DeviceCase(inp, gpu)
+        heads = sorted({0, H_q - 1})
+        for n_masked in (20, 40, 70, 150):
+            ref = None
+            for value in (-1.3e10, -3e12, -7e20, -1e30, -9e30, -3e37):
+                print(f"[case] {name} k={k}: first {n_masked} keys at {value}", flush=True)
+                braw = np.zeros((H_q, inp.T), dtype=np.float32)
+                for a, b in zip(inp.cu_seqlens[:-1], inp.cu_seqlens[1:]):
+                    braw[:, a:min(b, a + n_masked)] = value
+                B.dma_mask_gen_bias(case.shape, case.V, case.W, case.A, case.cu, to_dev(braw, gpu), H_q, True, case.z,
+                                    case.expiry, None, case.mask)
+                case.fwd()
+                if ref is None:  # (the same for every value)
+                    i, j = np.arange(inp.T)[:, None], np.arange(inp.T)[None, :]
+                    kept = (i >= j) & (i < case.host("expiry")[heads][:, None, :])
+                    real = (kept & (braw[heads] == 0)[:, None, :]).any(axis=2)   # [head, row]
+                    ref = orc.dma_forward(inp.Q, inp.K, inp.V, case.host("z").astype(np.float64), inp.cu_seqlens, k,
+                                          heads=heads, bias=braw.astype(np.float64))[:2]
+                O, LSE = np.asarray(ref[0])[:, heads], np.asarray(ref[1])[heads]
+                assert 0.5 < real.mean() < 1
+                check_close("O", case.host("O")[:, heads][real.T], O[real.T], **tol(True))
+                check_close("LSE", case.host("LSE")[heads][real], LSE[real], **tol(True))
