@@ -12,8 +12,9 @@ LIB = os.path.join(HERE, "libdma_hip.so")
 PROBE_LIB = os.path.join(HERE, "libdma_probe.so")   # the benchmark's yardsticks: a library of their own
 SOURCES = ["api.hip", "mask_gen.hip", "fwd.hip", "bwd.hip", "mask_bwd.hip", "xhead.hip", "decode.hip", "debug_f32.hip"]
 PROBE_SOURCES = ["probe.hip"]
-# The attention kernels never produce a NaN from finite inputs (inf - inf is avoided explicitly), so
-# their max / compare chains may skip NaN canonicalisation; infinities stay honoured (-inf masks).
+# The attention kernels form no NaN from finite inputs (inf - inf is avoided: softmax_ref.h; a row whose keys are all
+# masked beyond the range of fp32 ends as 0 / 0, which nothing compares), so their max / compare chains may
+# skip NaN canonicalisation; infinities stay honoured (-inf masks).
 # With IEEE mode off as well, a maximum is one instruction (no quieting of its inputs first).  The
 # device library's helpers are built with the mode on and would not inline into such kernels: these
 # two files read launch indices through builtins (wg_id, thread_id) and call no library function.

@@ -40,10 +40,6 @@ struct FwdArgs {
   int T, H_q, H_kv, k, nblk_cap, kpad;
 };
 
-// Largest sum of a lane's sixteen weights of one unit that the fast path accepts, as the bits of a float: every weight
-// is then at most 2^8.  Infinities and NaNs (nothing kept so far: reference maximum -inf) compare above it.
-constexpr uint32_t SUM_LIMIT = 0x43800000u;
-
 // (second launch bound = waves per SIMD: at D = 64 the kernel is held to 128 registers so that two
 // workgroups share a compute unit -- four waves per SIMD hide the element-wise work, which weighs
 // twice as much per MFMA there; at D = 128 the accumulators alone need more than that)
@@ -246,7 +242,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
   for (int cb = 0; cb < CB; cb++)
 #pragma unroll
     for (int v = 0; v < 16; v++) oacc[cb][v] = 0.f;
-  float m_run = -INFINITY, lsum = 0.f;
+  float m_run = REF_NONE, lsum = 0.f;
   uint32_t limit = 0;  // largest sum without a look at the maximum: nothing in the first 64 keys, then SUM_LIMIT
 
   // S^T of one unit; its accumulator starts at z / scale, so that scale * acc is the biased score.  so, zo: byte offsets
@@ -270,11 +266,11 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
   // weight that could exceed 2^8 is the unit's maximum looked for, O and l rescaled and the unit's weights formed
   // again.  Same softmax; no maximum in the common case.  The first 64 keys always go that way: the largest weight of a
   // row is then mostly 1, which bf16 holds exactly (rows of a few hundred keys: error of O 2.01e-3 -> 1.97e-3).
-  auto exponentials = [&](const f32x16& s, bf16x8 (&pb)[2], float nm) __attribute__((always_inline)) {
+  auto exponentials = [&](const f32x16& s, bf16x8 (&pb)[2]) __attribute__((always_inline)) {
     float l0 = 0.f, l1 = 0.f;
 #pragma unroll
     for (int v = 0; v < 16; v++) {
-      const float pv = fast_exp2(fmaf(s[v], c2, nm));
+      const float pv = fast_exp2(weight_exponent(s[v], c2, m_run));
       if (v & 1) l1 += pv; else l0 += pv;
       pb[v >> 3][v & 7] = (__bf16)pv;
     }
@@ -287,14 +283,14 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
       for (int v = 2; v < 16; v++) mx = fmaxf(mx, s[v]);
       mx = reference_of(half_swap_max(mx), c2);
       const bool grow = mx > m_run;
-      const float alpha = grow ? fast_exp2(m_run - mx) : 1.f;  // m_run = -inf: 0, nothing accumulated yet
+      const float alpha = grow ? fast_exp2(m_run - mx) : 1.f;  // (nothing kept so far: O and l are 0)
       m_run = grow ? mx : m_run;
       lsum *= alpha;
 #pragma unroll
       for (int cb = 0; cb < CB; cb++)
 #pragma unroll
         for (int v = 0; v < 16; v++) oacc[cb][v] *= alpha;
-      sum = exponentials(s, pb, m_run == -INFINITY ? 0.f : -m_run);  // nothing kept so far: exp2(-inf - 0) = 0
+      sum = exponentials(s, pb);
     }
     lsum += sum;
   };
@@ -378,7 +374,6 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
       f32x16 sn = start_scores(4 * (ss * 64 + 32 * su));
       bf16x8 fr[LEAD + 1], pn[2];
       float pv[16], l0 = 0.f, l1 = 0.f;
-      const float nm = -m_run;
       auto frag = [&](auto mc) __attribute__((always_inline)) {
         constexpr int m = decltype(mc)::value;
         if constexpr (m < KS) fr[m % (LEAD + 1)] = lds_load<bf16x8>(kfrag[m] + ko);
@@ -398,7 +393,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
         constexpr int e1 = (m + 1) * 16 / (NM - 2) < 16 ? (m + 1) * 16 / (NM - 2) : 16;
         constexpr int f0 = m > 0 ? (m - 1) * 16 / (NM - 2) : 0;
 #pragma unroll
-        for (int v = e0; v < e1; v++) pv[v] = fast_exp2(fmaf(sc[v], c2, nm));
+        for (int v = e0; v < e1; v++) pv[v] = fast_exp2(weight_exponent(sc[v], c2, m_run));
 #pragma unroll
         for (int v = f0; v < e0; v++) {
           if (v & 1) l1 += pv[v]; else l0 += pv[v];
@@ -460,7 +455,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
         }
         scores(s, so);
         bf16x8 pb[2];
-        const float sum = exponentials(s, pb, -m_run);
+        const float sum = exponentials(s, pb);
         take_sum(s, pb, sum);
         accumulate(pb, so);
       }
