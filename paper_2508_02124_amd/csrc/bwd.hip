@@ -307,16 +307,20 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
         }
       };
       if constexpr (MASKED) {
-        // Skip the step if no key of its units is active on any of this wave's 32 rows
+        // Skip the step if no key of its units is active on any of this wave's 32 rows; if only the next unit's are, its
+        // scores are all there is to do (a P of zero must not meet an infinite value or key)
         const int rfirst = row0 + 32 * w, tn = !PIPED || u + 1 < UT ? t : t + 1;
         const int jl = ids_ring[tn % (2 * NS)][PIPED ? 32 * su + n : 32 * u + n], el = e_ring[PIPED ? ss : ST][PIPED ? 32 * su + n : 32 * u + n];
         const bool act1 = __any((jl <= rfirst + 31) & (el > rfirst));  // (an empty entry has el = 0)
-        const bool run = (PIPED && act0) | act1;
+        const bool run = PIPED ? act0 : act1;
         act0 = act1;
         if (!run) {
           if constexpr (PIPED) {
+            if (act1) {
+              sc = start_scores(4 * (ss * 64 + 32 * su));
 #pragma unroll
-            for (int v = 0; v < 16; v++) sc[v] = -INFINITY;
+              for (int ks = 0; ks < KS; ks++) sc = mfma32(lds_load<bf16x8>(kfrag[ks] + ko), qreg[ks], sc);
+            }
             static_for<LEAD>([&](auto mc) __attribute__((always_inline)) { frag(mc, ko, 0); });
           }
           if constexpr (u == 0) {

@@ -338,76 +338,93 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
       constexpr int vs = u > 0 ? ST : (ST + NS - 1) % NS, vu = u > 0 ? u - 1 : UT - 1;
       constexpr uint32_t ko = ss * (2 * TILE) + su * UB, vo = vs * (2 * TILE) + vu * UB;
       int idv[WL];
+      bool prev = true, cur = true, next = true;
       if constexpr (MASKED) {
-        // Skip the step if no key of its three units is active on any of this wave's 32 rows (a list is three runs:
-        // entering keys that stay, other entering keys, each by first active row, then expiring ones by last).
+        // A unit is active if some key of it is, on any of this wave's 32 rows (a list is three runs: entering keys
+        // that stay, other entering keys, each by first active row, then expiring ones by last).  The step of three
+        // inactive units is skipped.  At the start of a run of active ones there is no output product: a weight of zero
+        // must not meet the infinite value of a key that no row of the wave keeps.  (fwd, us, with those products ->
+        // without: 16 documents of 4096 x 4 heads, window 256, scores that rise along the keys 138 -> 123; random
+        // scores: unchanged.)
         const int rfirst = row0 + 32 * w, tn = u + 1 < UT ? t : t + 1;
         const int jl = ids_ring[tn % (2 * NS)][32 * su + n], el = e_ring[ss][32 * su + n];
-        const bool act2 = __any((jl <= rfirst + 31) & (el > rfirst));  // (an empty entry has el = 0)
-        const bool run = act0 | act1 | act2;
-        act0 = act1;
-        act1 = act2;
-        if (!run) {
+        prev = act0, cur = act1, next = __any((jl <= rfirst + 31) & (el > rfirst));  // (an empty entry has el = 0)
+        act0 = cur;
+        act1 = next;
+        if (prev | cur) {  // pairs outside [j, e_j) get no weight
+          const uint32_t js = jlane + 4 * ((t % (2 * NS)) * 64 + 32 * u);
 #pragma unroll
-          for (int v = 0; v < 16; v++) sc[v] = -INFINITY;
-          pn0[0] = pn0[1] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
-          if constexpr (u == 0) {
-            row_ids(t + 3, idv);
-            copy_rows(Kg, ldsK, (ST + 3) % NS, idv);
+          for (int gq = 0; gq < 4; gq++) {
+            const i32x4 jj = lds_load<i32x4>(js + 32 * gq);
+            const i32x4 ee = lds_load<i32x4>(elane + 4 * (ST * 64 + 32 * u) + 32 * gq);
+#pragma unroll
+            for (int v = 0; v < 4; v++) sc[4 * gq + v] = ((qi >= jj[v]) & (qi < ee[v])) ? sc[4 * gq + v] : -INFINITY;
           }
-          if constexpr (u == UT - 1) {
-            row_ids(t + 2, idv);
-            copy_rows(Vg, ldsV, (ST + 2) % NS, idv);
-          }
-          return;
-        }
-        // pairs outside [j, e_j) get no weight
-        const uint32_t js = jlane + 4 * ((t % (2 * NS)) * 64 + 32 * u);
-#pragma unroll
-        for (int gq = 0; gq < 4; gq++) {
-          const i32x4 jj = lds_load<i32x4>(js + 32 * gq);
-          const i32x4 ee = lds_load<i32x4>(elane + 4 * (ST * 64 + 32 * u) + 32 * gq);
-#pragma unroll
-          for (int v = 0; v < 4; v++) sc[4 * gq + v] = ((qi >= jj[v]) & (qi < ee[v])) ? sc[4 * gq + v] : -INFINITY;
         }
       }
-      f32x16 sn = start_scores(4 * (ss * 64 + 32 * su));
-      bf16x8 fr[LEAD + 1], pn[2];
-      float pv[16], l0 = 0.f, l1 = 0.f;
-      auto frag = [&](auto mc) __attribute__((always_inline)) {
-        constexpr int m = decltype(mc)::value;
-        if constexpr (m < KS) fr[m % (LEAD + 1)] = lds_load<bf16x8>(kfrag[m] + ko);
-        else if constexpr (m < NM) fr[m % (LEAD + 1)] = value_frag(m - KS, vo);
-      };
-      static_for<LEAD>(frag);
-      if constexpr (FIXED) __builtin_amdgcn_sched_barrier(0);
-      static_for<NM>([&](auto mc) __attribute__((always_inline)) {
-        constexpr int m = decltype(mc)::value;
-        if constexpr (u == 0 && m == 0) row_ids(t + 3, idv);
-        if constexpr (u == UT - 1 && m == NM / 2) row_ids(t + 2, idv);
-        frag(std::integral_constant<int, m + LEAD>{});
-        if constexpr (m < KS) sn = mfma32(fr[m % (LEAD + 1)], qreg[m], sn);
-        else oacc[(m - KS) % CB] = mfma32(fr[m % (LEAD + 1)], pn0[(m - KS) / CB], oacc[(m - KS) % CB]);
-        // element-wise work of unit i: the exponentials of some scores, sum and rounding of those before
-        constexpr int e0 = m * 16 / (NM - 2) < 16 ? m * 16 / (NM - 2) : 16;
-        constexpr int e1 = (m + 1) * 16 / (NM - 2) < 16 ? (m + 1) * 16 / (NM - 2) : 16;
-        constexpr int f0 = m > 0 ? (m - 1) * 16 / (NM - 2) : 0;
-#pragma unroll
-        for (int v = e0; v < e1; v++) pv[v] = fast_exp2(weight_exponent(sc[v], c2, m_run));
-#pragma unroll
-        for (int v = f0; v < e0; v++) {
-          if (v & 1) l1 += pv[v]; else l0 += pv[v];
-          pn[v >> 3][v & 7] = (__bf16)pv[v];
-        }
-        if constexpr (u == 0 && m == NM / 2 - 2) copy_rows(Kg, ldsK, (ST + 3) % NS, idv);
-        if constexpr (u == UT - 1 && m == NM - 2) copy_rows(Vg, ldsV, (ST + 2) % NS, idv);
+      f32x16 sn;
+      bf16x8 pn[2];
+      float sum = 0.f;
+      auto step = [&]() __attribute__((always_inline)) {
+        sn = start_scores(4 * (ss * 64 + 32 * su));
+        bf16x8 fr[LEAD + 1];
+        float pv[16], l0 = 0.f, l1 = 0.f;
+        auto frag = [&](auto mc) __attribute__((always_inline)) {
+          constexpr int m = decltype(mc)::value;
+          if constexpr (m < KS) fr[m % (LEAD + 1)] = lds_load<bf16x8>(kfrag[m] + ko);
+          else if constexpr (m < NM) fr[m % (LEAD + 1)] = value_frag(m - KS, vo);
+        };
+        static_for<LEAD>(frag);
         if constexpr (FIXED) __builtin_amdgcn_sched_barrier(0);
-      });
-      if constexpr (FIXED) {
-        settle(pn[0]);
-        settle(pn[1]);
+        static_for<NM>([&](auto mc) __attribute__((always_inline)) {
+          constexpr int m = decltype(mc)::value;
+          if constexpr (u == 0 && m == 0) row_ids(t + 3, idv);
+          if constexpr (u == UT - 1 && m == NM / 2) row_ids(t + 2, idv);
+          frag(std::integral_constant<int, m + LEAD>{});
+          if constexpr (m < KS) sn = mfma32(fr[m % (LEAD + 1)], qreg[m], sn);
+          else oacc[(m - KS) % CB] = mfma32(fr[m % (LEAD + 1)], pn0[(m - KS) / CB], oacc[(m - KS) % CB]);
+          // element-wise work of unit i: the exponentials of some scores, sum and rounding of those before
+          constexpr int e0 = m * 16 / (NM - 2) < 16 ? m * 16 / (NM - 2) : 16;
+          constexpr int e1 = (m + 1) * 16 / (NM - 2) < 16 ? (m + 1) * 16 / (NM - 2) : 16;
+          constexpr int f0 = m > 0 ? (m - 1) * 16 / (NM - 2) : 0;
+#pragma unroll
+          for (int v = e0; v < e1; v++) pv[v] = fast_exp2(weight_exponent(sc[v], c2, m_run));
+#pragma unroll
+          for (int v = f0; v < e0; v++) {
+            if (v & 1) l1 += pv[v]; else l0 += pv[v];
+            pn[v >> 3][v & 7] = (__bf16)pv[v];
+          }
+          if constexpr (u == 0 && m == NM / 2 - 2) copy_rows(Kg, ldsK, (ST + 3) % NS, idv);
+          if constexpr (u == UT - 1 && m == NM - 2) copy_rows(Vg, ldsV, (ST + 2) % NS, idv);
+          if constexpr (FIXED) __builtin_amdgcn_sched_barrier(0);
+        });
+        if constexpr (FIXED) {
+          settle(pn[0]);
+          settle(pn[1]);
+        }
+        sum = l0 + l1;
+      };
+      if (!MASKED || prev) {
+        step();
+      } else {
+        if constexpr (u == 0) {
+          row_ids(t + 3, idv);
+          copy_rows(Kg, ldsK, (ST + 3) % NS, idv);
+        }
+        if constexpr (u == UT - 1) {
+          row_ids(t + 2, idv);
+          copy_rows(Vg, ldsV, (ST + 2) % NS, idv);
+        }
+        sn = sc;  // (what no active unit needs keeps its value)
+        pn[0] = pn0[0];
+        pn[1] = pn0[1];
+        if (next) {
+          sn = start_scores(4 * (ss * 64 + 32 * su));
+          scores(sn, ko);
+        }
+        if (cur) sum = exponentials(sc, pn);
       }
-      take_sum(sc, pn, l0 + l1);
+      take_sum(sc, pn, sum);
       sc = sn;
       pn0[0] = pn[0];
       pn0[1] = pn[1];
@@ -469,7 +486,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
       if (base + 3 < nt) tile(s3, std::true_type{});
     }
     static_assert(NS == 4, "the loops are unrolled over the ring stages");
-    accumulate(pn0, ((nt + shift + NS - 1) % NS) * (2 * TILE) + (UT - 1) * UB);
+    if (act0) accumulate(pn0, ((nt + shift + NS - 1) % NS) * (2 * TILE) + (UT - 1) * UB);
   }
 
   // epilogue: drain the (dummy) copies still in flight, normalise, stage O through LDS for

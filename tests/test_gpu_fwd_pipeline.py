@@ -88,3 +88,42 @@ def test_gradients_of_rows_that_are_never_kept(gpu):
     never = (case.host("expiry") == np.arange(inp.T)[None, :]).reshape(2, 2, inp.T).all(axis=1)  # [kv-head, token]
     assert 0.3 < never.mean() < 0.9
     assert (case.host("dK").transpose(1, 0, 2)[never] == 0).all() and (case.host("dV").transpose(1, 0, 2)[never] == 0).all()
+
+
+@pytest.mark.parametrize("what", ["V", "K"])
+@pytest.mark.parametrize("name", FORMS)
+def test_an_infinite_entry_stays_with_the_rows_of_its_unit(gpu, name, what):
+    """One infinite entry of V or K.  Of the rows that do not keep its key, only those may lose their O or dQ that share a
+    step with it: the 32 rows of a wave on which some key of the same 32 entries of the block's list is active."""
+    H_q, H_kv, d, lens, windows = FORMS[name]
+    k = windows[-1]
+    inp = wlmod.make_inputs(wlmod.small_workload(f"inf_{name}", 970, H_q, H_kv, d, k, lens))
+    case = DeviceCase(inp, gpu)
+    case.mask_gen()
+    z, e, pv = case.host("z").copy(), case.host("expiry").copy(), case.plan_views()
+    rows = np.arange(inp.T)
+    ever = [j for j in range(3, inp.T, 29) if (e[:H_q // H_kv, j] > j).any()][:24]
+    assert len(ever) > 8
+    for j in ever:
+        print(f"[case] {name}: infinite {what} of key {j}", flush=True)
+        case = DeviceCase(inp, gpu, z_override=z)
+        getattr(case, what)[j, 0, 5] = float("inf")
+        case.mask_gen()
+        case.fwd()
+        case.bwd()
+        for h in range(H_q // H_kv):
+            lost = (rows >= j) & (rows < e[h, j])
+            for b in range(pv["nblk"]):
+                r0, r1 = pv["blk"][b][1:3]
+                entries = pv["plist"][h, b, :pv["pcnt"][h, b]]
+                at = np.flatnonzero(entries == j)
+                if at.size:
+                    unit = entries[at[0] // 32 * 32:][:32]
+                    for r in range(r0, r1, 32):
+                        if ((unit <= r + 31) & (e[h, unit] > r)).any():
+                            lost[r:min(r + 32, r1)] = True
+            for out in ("O", "dQ"):
+                bad = ~np.isfinite(case.host(out)[:, h]).all(axis=1)
+                assert not (bad & ~lost).any(), (out, h, np.flatnonzero(bad & ~lost)[:8])
+        for out in ("O", "dQ"):
+            assert np.isfinite(case.host(out)[:, H_q // H_kv:]).all()
