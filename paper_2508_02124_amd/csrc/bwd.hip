@@ -280,7 +280,13 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
     start_dp();
     static_for<LEAD>([&](auto mc) __attribute__((always_inline)) { frag(mc, shift * (2 * TILE), 0); });
   }
-  bool act0 = true;  // partial tiles: this unit has a key that is active on a row of the wave
+  // Partial tiles: a unit is active if some key of it is, on any of this wave's 32 rows.
+  const int rfirst = row0 + 32 * w;
+  auto active = [&](int tt, int st, int u) __attribute__((always_inline)) {  // unit u of tile tt, in ring stage st
+    const int jl = ids_ring[tt % (2 * NS)][32 * u + n], el = e_ring[st][32 * u + n];
+    return (bool)__any((jl <= rfirst + 31) & (el > rfirst));  // (an empty entry has el = 0)
+  };
+  bool act0 = true;  // this unit is active
   auto tile = [&](auto stc, auto maskedc) __attribute__((always_inline)) {
     constexpr int ST = decltype(stc)::value;  // (t + shift) % NS
     constexpr bool MASKED = decltype(maskedc)::value;
@@ -307,11 +313,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
         }
       };
       if constexpr (MASKED) {
-        // Skip the step if no key of its units is active on any of this wave's 32 rows; if only the next unit's are, its
-        // scores are all there is to do (a P of zero must not meet an infinite value or key)
-        const int rfirst = row0 + 32 * w, tn = !PIPED || u + 1 < UT ? t : t + 1;
-        const int jl = ids_ring[tn % (2 * NS)][PIPED ? 32 * su + n : 32 * u + n], el = e_ring[PIPED ? ss : ST][PIPED ? 32 * su + n : 32 * u + n];
-        const bool act1 = __any((jl <= rfirst + 31) & (el > rfirst));  // (an empty entry has el = 0)
+        // Skip the step of an inactive unit; the scores of the next one, if that is active, are all there is to do (a P of
+        // zero must not meet an infinite value or key)
+        const bool act1 = PIPED ? active(u + 1 < UT ? t : t + 1, ss, su) : active(t, ST, u);
         const bool run = PIPED ? act0 : act1;
         act0 = act1;
         if (!run) {
@@ -395,6 +399,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
     }
     tile(std::integral_constant<int, NS - 1>{}, std::false_type{});
   }
+  if constexpr (PIPED) act0 = active(nc, 0, 0);  // (its ids and scalars are there: tile nc - 1 waited for those of one tile more)
   for (int base = nc; base < nt; base += NS) {
     tile(s0, std::true_type{});
     if (base + 1 < nt) tile(s1, std::true_type{});

@@ -318,7 +318,13 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
   pn0[0] = pn0[1] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
   f32x16 sc = start_scores(4 * 64 * shift);
   scores(sc, shift * (2 * TILE));
-  bool act0 = true, act1 = true;  // partial tiles: the unit before, this unit has a key that is active on a row of the wave
+  // Partial tiles: a unit is active if some key of it is, on any of this wave's 32 rows.
+  const int rfirst = row0 + 32 * w;
+  auto active = [&](int tt, int st, int u) __attribute__((always_inline)) {  // unit u of tile tt, in ring stage st
+    const int jl = ids_ring[tt % (2 * NS)][32 * u + n], el = e_ring[st][32 * u + n];
+    return (bool)__any((jl <= rfirst + 31) & (el > rfirst));  // (an empty entry has el = 0)
+  };
+  bool act0 = true, act1 = true;  // the unit before, this unit is active
   constexpr int NM = KS + 2 * CB;  // products of a step: KS of the next unit's scores, then 2 CB of the previous unit's output
   // (64 channels: four waves share a SIMD and overlap by themselves; their 128 registers do not hold fragments read
   // ahead, nor the masks of a pipelined partial step: there the order is the compiler's and partial units run one by one)
@@ -340,15 +346,12 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
       int idv[WL];
       bool prev = true, cur = true, next = true;
       if constexpr (MASKED) {
-        // A unit is active if some key of it is, on any of this wave's 32 rows (a list is three runs: entering keys
-        // that stay, other entering keys, each by first active row, then expiring ones by last).  The step of three
-        // inactive units is skipped.  At the start of a run of active ones there is no output product: a weight of zero
+        // (A list is three runs: entering keys that stay, other entering keys, each by first active row, then expiring
+        // ones by last.)  The step of three inactive units is skipped.  At the start of a run of active ones there is no output product: a weight of zero
         // must not meet the infinite value of a key that no row of the wave keeps.  (fwd, us, with those products ->
         // without: 16 documents of 4096 x 4 heads, window 256, scores that rise along the keys 138 -> 123; random
         // scores: unchanged.)
-        const int rfirst = row0 + 32 * w, tn = u + 1 < UT ? t : t + 1;
-        const int jl = ids_ring[tn % (2 * NS)][32 * su + n], el = e_ring[ss][32 * su + n];
-        prev = act0, cur = act1, next = __any((jl <= rfirst + 31) & (el > rfirst));  // (an empty entry has el = 0)
+        prev = act0, cur = act1, next = active(u + 1 < UT ? t : t + 1, ss, su);
         act0 = cur;
         act1 = next;
         if (prev | cur) {  // pairs outside [j, e_j) get no weight
@@ -455,11 +458,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
       issue_rows(Kg, ldsK, t + 3);
       issue_rows(Vg, ldsV, t + 2);
       const int st = (t + shift) % NS, ist = t % (2 * NS);
-      const int rfirst = row0 + 32 * w;
 #pragma unroll 1
       for (int u = 0; u < UT; u++) {
-        const int jl = ids_ring[ist][32 * u + n], el = e_ring[st][32 * u + n];
-        if (!__any((jl <= rfirst + 31) & (el > rfirst))) continue;  // (an empty entry has el = 0)
+        if (!active(t, st, u)) continue;
         const uint32_t zo = 4 * (st * 64 + 32 * u), so = st * (2 * TILE) + u * UB;
         f32x16 s = start_scores(zo);
         const uint32_t js = jlane + 4 * (ist * 64 + 32 * u);
@@ -479,6 +480,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
       limit = (t + 1) * UT >= 2 ? SUM_LIMIT : 0u;
     }
   } else {
+    act1 = active(nc, 0, 0);  // (its ids and scalars are there: tile nc - 1 waited for those of one tile more)
     for (int base = nc; base < nt; base += NS) {
       tile(s0, std::true_type{});
       if (base + 1 < nt) tile(s1, std::true_type{});

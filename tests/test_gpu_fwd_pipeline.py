@@ -91,14 +91,17 @@ def test_gradients_of_rows_that_are_never_kept(gpu):
 
 
 @pytest.mark.parametrize("what", ["V", "K"])
+@pytest.mark.parametrize("rising", [False, True], ids=["", "rising"])
 @pytest.mark.parametrize("name", FORMS)
-def test_an_infinite_entry_stays_with_the_rows_of_its_unit(gpu, name, what):
+def test_an_infinite_entry_stays_with_the_rows_of_its_unit(gpu, name, rising, what):
     """One infinite entry of V or K.  Of the rows that do not keep its key, only those may lose their O or dQ that share a
-    step with it: the 32 rows of a wave on which some key of the same 32 entries of the block's list is active."""
+    step with it: the 32 rows of a wave on which some key of the same 32 entries of the block's list is active.  Rising
+    scores and a window of 40: a block's list begins with the last 40 keys of the block, which most waves do not keep."""
     H_q, H_kv, d, lens, windows = FORMS[name]
-    k = windows[-1]
+    k = 40 if rising else windows[-1]
     inp = wlmod.make_inputs(wlmod.small_workload(f"inf_{name}", 970, H_q, H_kv, d, k, lens))
-    case = DeviceCase(inp, gpu)
+    z = np.tile(np.linspace(0.1, 1, inp.T, dtype=np.float32), (H_q, 1)) if rising else None
+    case = DeviceCase(inp, gpu, z_override=z)
     case.mask_gen()
     z, e, pv = case.host("z").copy(), case.host("expiry").copy(), case.plan_views()
     rows = np.arange(inp.T)
