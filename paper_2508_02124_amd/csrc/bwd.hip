@@ -943,52 +943,68 @@ __global__ __launch_bounds__(DKV_NW * 64, D == 256 ? 1 : D == 64 ? 3 : 2) void d
 }
 
 // dK, dV: fp32 accumulators -> bf16 outputs.  HBM-bound (5.8 TB/s).  SPARSE: a row that no q-head of its group ever keeps
-// has a zero gradient, and its accumulators are not read (packed 65536 x 16 heads, d = 64, window 512, no groups, where
-// 37 % of the rows are kept: 141 -> 98 us).  Looking at the expiries costs 30 % where most rows are kept (16384 tokens,
-// 32 / 8 heads, window 2048, 86 %: 33 -> 43 us).
+// has a zero gradient, and its accumulators are not read.  A workgroup looks the expiries of its rows up once per row and
+// head, before its first load (once per float4 before): what that costs where every row is kept after all, with scores
+// that rise along the keys, is about one memory latency.  Every row read / random scores / rising scores, us: packed
+// 65536 x 16 heads of 64 channels, window 512, 131 / 73 / 134 (before: 99 / 144), the same of 128 channels 311 / 159 / 284
+// (194 / 315), 32768 x 2 heads of 128 channels 17.3 / 8.8 / 20.1 (24 / 23), 8192 x 8 heads of 256 channels 31.7 / 14.0 /
+// 35.5 (18 / 38).  Workgroups of four times the rows: 78 / 141, 170 / 294, 14.0 / 24.7, 17.7 / 34.6.
 struct CvtArgs {
   const float *a, *b;
   uint16_t *oa, *ob;
   const int32_t* expiry;
   int T, H_kv, G;
-  unsigned row4;  // float4 per row
   size_t n4;
   unsigned nwg;
 };
-template <bool SPARSE>
+constexpr int CVT_U = 4, CVT_N4 = 256 * CVT_U;  // float4 per thread and per workgroup of the sparse form
+__device__ __forceinline__ void cvt_store(uint16_t* out, size_t i, float4 x) {
+  bf16x4 o;
+  o[0] = (__bf16)x.x; o[1] = (__bf16)x.y; o[2] = (__bf16)x.z; o[3] = (__bf16)x.w;
+  reinterpret_cast<bf16x4*>(out)[i] = o;
+}
+template <int D, bool SPARSE>
 __global__ __launch_bounds__(256) void cvt_bf16_kernel(CvtArgs p) {  // (256 threads)
-  constexpr int U = SPARSE ? 4 : 1;
-  const size_t st = (size_t)p.nwg * 256;
-  for (size_t i0 = wg_id() * (size_t)256 + thread_id(); i0 < p.n4; i0 += U * st) {
-    bool kept[U];
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      const size_t i = i0 + u * st;
-      kept[u] = !SPARSE;  // (U = 1: i < n4)
-      if (SPARSE && i < p.n4) {
-        const unsigned row = (unsigned)(i / p.row4), t = row / (unsigned)p.H_kv, g = row - t * (unsigned)p.H_kv;
-        const int32_t* e = p.expiry + (size_t)g * p.G * p.T + t;
-        for (int q = 0; q < p.G; q++) kept[u] = kept[u] || e[(size_t)q * p.T] > (int)t;
-      }
+  const float4 *a = reinterpret_cast<const float4*>(p.a), *b = reinterpret_cast<const float4*>(p.b);
+  if constexpr (!SPARSE) {
+    const size_t st = (size_t)p.nwg * 256;
+    for (size_t i = wg_id() * (size_t)256 + thread_id(); i < p.n4; i += st) {
+      const float4 x = a[i], y = b[i];
+      cvt_store(p.oa, i, x);
+      cvt_store(p.ob, i, y);
     }
-    float4 x[U], y[U];
+  } else {
+    constexpr int ROW4 = D / 4, ROWS = CVT_N4 / ROW4, QP = 256 / ROWS;  // QP threads share the heads of a row's group
+    __shared__ int kept[QP][ROWS];
+    const int tid = thread_id();
+    const size_t base = (size_t)wg_id() * CVT_N4, row = base / ROW4 + tid % ROWS;
+    int any = 0;  // (a row past the end has none)
+    if (row < p.n4 / ROW4) {
+      const unsigned t = (unsigned)row / (unsigned)p.H_kv, g = (unsigned)row - t * (unsigned)p.H_kv;
+      const int32_t* e = p.expiry + (size_t)g * p.G * p.T + t;
+      for (int q = tid / ROWS; q < p.G; q += QP) any |= e[(size_t)q * p.T] > (int)t;
+    }
+    kept[tid / ROWS][tid % ROWS] = any;
+    __syncthreads();
+    float4 x[CVT_U], y[CVT_U];
 #pragma unroll
-    for (int u = 0; u < U; u++) {
+    for (int u = 0; u < CVT_U; u++) {
+      const int j = tid + 256 * u;
       x[u] = y[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (kept[u]) {
-        x[u] = reinterpret_cast<const float4*>(p.a)[i0 + u * st];
-        y[u] = reinterpret_cast<const float4*>(p.b)[i0 + u * st];
+      int read = 0;
+#pragma unroll
+      for (int q = 0; q < QP; q++) read |= kept[q][j / ROW4];
+      if (read) {
+        x[u] = a[base + j];
+        y[u] = b[base + j];
       }
     }
 #pragma unroll
-    for (int u = 0; u < U; u++) {
-      const size_t i = i0 + u * st;
+    for (int u = 0; u < CVT_U; u++) {
+      const size_t i = base + tid + 256 * u;
       if (i < p.n4) {
-        bf16x4 xo, yo;
-        xo[0] = (__bf16)x[u].x; xo[1] = (__bf16)x[u].y; xo[2] = (__bf16)x[u].z; xo[3] = (__bf16)x[u].w;
-        yo[0] = (__bf16)y[u].x; yo[1] = (__bf16)y[u].y; yo[2] = (__bf16)y[u].z; yo[3] = (__bf16)y[u].w;
-        reinterpret_cast<bf16x4*>(p.oa)[i] = xo;
-        reinterpret_cast<bf16x4*>(p.ob)[i] = yo;
+        cvt_store(p.oa, i, x[u]);
+        cvt_store(p.ob, i, y[u]);
       }
     }
   }
@@ -1067,13 +1083,17 @@ int launch_bwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
   prof_begin(DMA_STAGE_BWD_PART, st);  // (an empty stage: the launch above has the partial lists too)
   prof_end(DMA_STAGE_BWD_PART, st);
   prof_begin(DMA_STAGE_BWD_CVT, st);
-  const unsigned gcvt = grid_for(nkv / 4, 1024);
-  const CvtArgs ca = {a.dK32, a.dV32, (uint16_t*)dK, (uint16_t*)dV, expiry, s.T, s.H_kv, s.H_q / s.H_kv, (unsigned)s.d / 4, nkv / 4, gcvt};
   // About how many rows are kept: with random scores a document of n keys keeps k (1 + ln(n / k)) of them at some time.
   const double n = (double)s.T / s.n_docs, share = s.causal && n > s.k ? s.k / n * (1. + std::log(n / s.k)) : 1.;
   // (small calls are all latency: 2048 tokens x 2 heads 6.2 -> 8.1 us)
-  if (nkv >= 1u << 22 && 1. - std::pow(1. - share, ca.G) < 0.6) cvt_bf16_kernel<true><<<gcvt, 256, 0, st>>>(ca);
-  else cvt_bf16_kernel<false><<<gcvt, 256, 0, st>>>(ca);
+  const bool sparse = nkv >= 1u << 22 && 1. - std::pow(1. - share, s.H_q / s.H_kv) < 0.6;
+  const unsigned gcvt = sparse ? (unsigned)((nkv / 4 + CVT_N4 - 1) / CVT_N4) : grid_for(nkv / 4, 1024);
+  const CvtArgs ca = {a.dK32, a.dV32, (uint16_t*)dK, (uint16_t*)dV, expiry, s.T, s.H_kv, s.H_q / s.H_kv, nkv / 4, gcvt};
+#define DMA_CVT(DD) (sparse ? cvt_bf16_kernel<DD, true> : cvt_bf16_kernel<DD, false>)<<<gcvt, 256, 0, st>>>(ca)
+  if (s.d == 256) DMA_CVT(256);
+  else if (s.d == 128) DMA_CVT(128);
+  else DMA_CVT(64);
+#undef DMA_CVT
   prof_end(DMA_STAGE_BWD_CVT, st);
   return hipGetLastError() == hipSuccess ? DMA_OK : DMA_EHIP;
 }

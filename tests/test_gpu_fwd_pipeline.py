@@ -90,6 +90,30 @@ def test_gradients_of_rows_that_are_never_kept(gpu):
     assert (case.host("dK").transpose(1, 0, 2)[never] == 0).all() and (case.host("dV").transpose(1, 0, 2)[never] == 0).all()
 
 
+# q-heads, kv-heads, head dimension, documents: at least 2^22 elements of dK, and rows that do not fill the last workgroup
+SPARSE = {"d64": (4, 4, 64, (1000,) * 17 + (13,)), "d128": (4, 1, 128, (1100,) * 30 + (7,)), "d256": (2, 1, 256, (500,) * 33 + (9,))}
+
+
+@pytest.mark.parametrize("rising", [False, True], ids=["random", "rising"])
+@pytest.mark.parametrize("name", SPARSE)
+def test_sparse_conversion_forms(gpu, name, rising):
+    """The conversion that leaves out rows, of every head dimension, also where scores that rise along the keys keep all."""
+    print(f"[case] sparse conversion {name} rising={rising}", flush=True)
+    H_q, H_kv, d, lens = SPARSE[name]
+    inp = wlmod.make_inputs(wlmod.small_workload(f"sparse_{name}", 991, H_q, H_kv, d, 48, lens))
+    assert inp.T * H_kv * d >= 1 << 22
+    z = np.tile(np.linspace(0.1, 1, inp.T, dtype=np.float32), (H_q, 1)) if rising else None
+    case = DeviceCase(inp, gpu, z_override=z)
+    case.mask_gen()
+    case.fwd()
+    case.bwd()
+    kept = (case.host("expiry") > np.arange(inp.T)[None, :]).reshape(H_kv, H_q // H_kv, inp.T).any(axis=1)
+    assert kept.all() if rising else kept.mean() < 0.6
+    for out in ("dK", "dV"):
+        assert (case.host(out).transpose(1, 0, 2)[~kept] == 0).all()
+    check_gradients(case, case.host("z").astype(np.float64), "bf16", label=f"{name} rising={rising} ")
+
+
 @pytest.mark.parametrize("what", ["V", "K"])
 @pytest.mark.parametrize("rising", [False, True], ids=["", "rising"])
 @pytest.mark.parametrize("name", FORMS)
