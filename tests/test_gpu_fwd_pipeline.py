@@ -18,6 +18,8 @@ pytestmark = pytest.mark.gpu
 FORMS = {
     "d128_half64": (2, 1, 128, (700, 33, 515), (1, 31, 33, 64, 65, 129, 193, 256, 300)),
     "d128_half32": (32, 8, 128, (1280,), (33, 100, 200)),
+    # (192 blocks: documents that end inside a block, second halves that are partial or empty)
+    "d128_half32_ragged": (32, 8, 128, (700, 33, 515), (1, 31, 33, 65, 97, 129)),
     "d128_whole": (32, 8, 128, (1025, 1023), (65, 130, 200)),
     "d256": (2, 1, 256, (700, 33, 515), (1, 31, 33, 64, 65, 97, 129, 300)),
     "d64": (2, 1, 64, (700, 33, 515), (1, 31, 33, 64, 65, 129, 193, 300)),
