@@ -174,7 +174,9 @@ def time_workload(wl, steps, warmup, dev, structured_z=False, calibration_copy=F
 def roofline_objects(wl, inp, case, rec, with_traffic):
     """Roofline records of the kernels of the step.  MFMA kernels: algorithmic FLOPs of the launch
     (per kept pair: forward 4d = S and PV; dQ kernel 6d = S, dP, dQ; key-stationary kernel 8d = S, dP,
-    dV, dK) / mean launch duration / 2.5 PFLOP/s.  The score kernel of
+    dV, dK) / mean launch duration / 2.5 PFLOP/s.  The record "dkv_kernel<clean>" is the launch of dkv_kernel, slot
+    sweeps and partial lists: all kept pairs (it has its name from the time when the sweeps were a launch of their own;
+    records of that time counted the sweeps' pairs and duration only).  The score kernel of
     mask generation is HBM-bound: bytes of V read once + z and z / scale written, / duration / 8 TB/s."""
     stage_ms = rec["stage_ms"]
     nact = rec["nact"]
@@ -192,6 +194,8 @@ def roofline_objects(wl, inp, case, rec, with_traffic):
             "traffic": measured_traffic(kernel_names[st]) if with_traffic else None,
             "launch_ms": stage_ms[st], "launch_ms_median": rec["stage_ms_median"][st],
             "launch_ms_min": rec["stage_ms_min"][st], "flops_per_launch": fl}
+        if st == "bwd_dkv":
+            objs[kernel_names[st]]["launch"] = "dkv_kernel: slot sweeps and partial lists, all kept pairs"
     zbytes = inp.T * wl.H_kv * wl.d * 2 + 2 * 4 * wl.H_q * inp.T
     zach = zbytes / (stage_ms["z"] * 1e-3) / 1e9
     objs["z_kernel"] = {"bound": "hbm", "kernel": "z_kernel (mask generation, Eq. 3)", "achieved": zach,

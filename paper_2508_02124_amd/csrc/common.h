@@ -283,22 +283,10 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// A-operand fragment of the TRANSPOSE of a row-major LDS tile: for lane (n = l % 32, hh = l / 32),
-// element e of the result is tile[rowbase + 4*hh + (e % 4) + 8*(e / 4)][32*cb + n].
-template <int D>
-__device__ __forceinline__ bf16x8 tr_frag(const uint16_t* tile, int rowbase, int cb, int l) {
-  const int l16 = l & 15, b16 = (l >> 4) & 1, hh = l >> 5;
-  const int r = rowbase + 4 * hh + (l16 >> 2);
-  const int c = 4 * cb + 2 * b16 + ((l16 & 3) >> 1);
-  const int sub = 4 * (l16 & 1);
-  const s16x4 lo = lds_read_tr(tile + TileLayout<D>::off(r, c) + sub);
-  const s16x4 hi = lds_read_tr(tile + TileLayout<D>::off(r + 8, c) + sub);
-  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
 // The lane's element offsets of the fragments it reads from a swizzled tile:
 //   row(ks)    row fragment (16 bytes): tile[rowbase + n][16*ks + 8*hh .. +8), rowbase a multiple of 16
-//   tr(cb, q)  the two halves (q) of tr_frag(tile, rowbase, cb), rowbase a multiple of 16
+//   tr(cb, q)  the two halves (q) of the A-operand fragment of the tile's TRANSPOSE: element e of it is
+//              tile[rowbase + 4*hh + (e % 4) + 8*(e / 4)][32*cb + n], rowbase a multiple of 16
 // (the swizzle only looks at the low four row bits, so rowbase adds rowbase * D elements).  The
 // swizzle XORs the chunk index, and the chunk bits that ks / cb select lie above the lane's own, so
 // row(ks) = row(0) ^ (16 ks) and tr(cb, q) = tr(0, q) ^ (32 cb): three registers hold all of them
