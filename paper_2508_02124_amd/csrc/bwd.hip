@@ -446,7 +446,7 @@ constexpr int MAXSWEEP = 64;     // most query blocks one key-stationary work it
 // one computes while the other waits.  What bounds it at 128 channels: of 4140 cycles per 32-row step of a wave (2050 are
 // the matrix pipe's for its two waves) 2440 are the products and what they wait for, 580 the change of keys at block
 // starts, 460 the issue of copies, 450 the barrier, 220 the copies' arrival -- at a clock that the power limit holds at 1.9
-// to 2.1 GHz.  At 256 channels, one wave per SIMD at 2.4 GHz, the products' own latencies count: 3600 of 5800 cycles.
+// to 2.1 GHz.  At 256 channels, one wave per SIMD at 2.2 to 2.3 GHz, the products' own latencies count: 3600 of 5800 cycles.
 // Registers decide the rest: the accumulators take D, so all of the K fragments and some of V's wait in LDS at 128
 // channels (two ring stages instead of three make room) and half of K's at 256; small lane-dependent
 // values are formed where they are used (fresh_lane).  Slot sweep / partial lists (as launches of their own), us, with the products in the
