@@ -198,6 +198,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
   }
   Dsum = half_swap_sum(Dsum);
   float lse2 = qvalid ? p.LSE[(size_t)h * p.T + qi] * LOG2E : INFINITY;
+  // A row whose weights are all 0 (LSE = -inf: it keeps nothing but keys that are masked beyond the range of the
+  // exponents) has P = 0 here too, not infinities that would reach the dV of its keys.
+  if (lse2 == -INFINITY) lse2 = INFINITY;
   settle(lse2);
   if (qvalid && hh == 0) {
     p.Dws[(size_t)h * p.T + qi] = -Dsum;  // (negated: the key-stationary kernel starts its dP accumulators at -D_i)

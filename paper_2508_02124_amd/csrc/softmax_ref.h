@@ -23,12 +23,16 @@ constexpr uint32_t SUM_LIMIT = 0x43800000u;
 // Argument of exp2 of a score's weight.
 DMA_FN float weight_exponent(float score, float c2, float ref) { return __builtin_fmaf(score, c2, -ref); }
 
-// The reference for weights whose largest score is top.  The product is rounded and weight_exponent's is not: where
-// its last place is worth more than a few powers of two (keys masked by a bias of -1e10 or below, and nothing else kept
-// so far), exp2 of the difference alone could be infinite.  Then the next float above is taken, and no weight exceeds 1.
+// Largest exponent of a row's greatest weight: sums of 2^16 such weights times values up to 2^10 are finite.
+constexpr float MAX_EXPONENT = 100.f;
+
+// The reference for weights whose largest score is top.  The product is rounded and weight_exponent's is not, so the
+// largest weight is 2^e with e up to half of the product's last place.  That cancels in the softmax (rows that keep
+// nothing but keys masked by a bias of -1e9: all weights 2^e) until 2^e overflows, from a bias of -1e10 on: then the next float
+// above is taken, the weights are 0, and what the row keeps later counts alone.
 DMA_FN float reference_of(float top, float c2) {
   float ref = __builtin_fmaxf(top * c2, REF_NONE);  // (top = -inf: nothing kept)
-  if (weight_exponent(top, c2, ref) > 1.f) {
+  if (weight_exponent(top, c2, ref) > MAX_EXPONENT) {
     const int32_t b = __builtin_bit_cast(int32_t, ref);
     ref = __builtin_bit_cast(float, b + (b < 0 ? -1 : 1));
   }

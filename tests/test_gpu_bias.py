@@ -172,3 +172,45 @@ def test_bias_masks_the_first_keys(gpu, name):
                 assert 0.5 < real.mean() < 1
                 check_close("O", case.host("O")[:, heads][real.T], O[real.T], **tol(True))
                 check_close("LSE", case.host("LSE")[heads][real], LSE[real], **tol(True))
+
+
+@pytest.mark.parametrize("name", MASKED_FORMS)
+def test_rows_that_keep_only_masked_keys(gpu, name):
+    """The first 150 keys masked by one bias whose last place exceeds their other scores: a row that keeps nothing else weights
+    them alike, as long as the rounding of the reference leaves their weights 2^e in range (e = -100 to 90).  Beyond that the row has no
+    weights, and the dV of its keys stays finite."""
+    H_q, H_kv, d, lens, windows = MASKED_FORMS[name]
+    k = windows[0]
+    inp = wlmod.make_inputs(wlmod.small_workload(f"only_masked_{name}", 83, H_q, H_kv, d, k, lens))
+    case = DeviceCase(inp, gpu)
+    f32 = np.float32
+    scale = f32(1 / np.sqrt(d))
+    c2 = scale * f32(np.log2(np.e))
+
+    def exponent(value):  # of the weights: exact product minus rounded product
+        top = float(f32(f32(value) * (f32(1) / scale)))
+        return top * float(c2) - float(f32(f32(top) * c2))
+
+    candidates = [-1e9 - 7.3e6 * i for i in range(260)]
+    values = [v for v in candidates if 2 < exponent(v) < 90][::30] + [v for v in candidates if -100 < exponent(v) < -2][::60]
+    assert len(values) >= 4 and max(exponent(v) for v in values) > 40
+    for value in values + [-1.1e12, -3e15, -1e30, -7e33]:
+        print(f"[case] {name}: {value}, weights 2^{exponent(value):.1f}", flush=True)
+        braw = np.zeros((H_q, inp.T), dtype=np.float32)
+        for a, b in zip(inp.cu_seqlens[:-1], inp.cu_seqlens[1:]):
+            braw[:, a:min(b, a + 150)] = value
+        B.dma_mask_gen_bias(case.shape, case.V, case.W, case.A, case.cu, to_dev(braw, gpu), H_q, True, case.z,
+                            case.expiry, None, case.mask)
+        case.fwd()
+        case.bwd()
+        if value < -1e12:
+            assert np.isfinite(case.host("dV")).all()
+            continue
+        for h in (0, H_q - 1):
+            i, j = np.arange(inp.T)[:, None], np.arange(inp.T)[None, :]
+            kept = (i >= j) & (i < case.host("expiry")[h][None, :])
+            rows = np.flatnonzero(~(kept & (braw[h] == 0)[None, :]).any(axis=1))
+            assert rows.size >= 150
+            # (the scores' last place is at least 1024: q k and z do not move them)
+            mean = kept[rows].astype(np.float64) @ inp.V[:, h // (H_q // H_kv)] / kept[rows].sum(axis=1)[:, None]
+            check_close("O", case.host("O")[rows, h], mean, **tol(True))
