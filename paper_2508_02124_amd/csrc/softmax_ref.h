@@ -28,8 +28,8 @@ constexpr float MAX_EXPONENT = 100.f;
 
 // The reference for weights whose largest score is top.  The product is rounded and weight_exponent's is not, so the
 // largest weight is 2^e with e up to half of the product's last place.  That cancels in the softmax (rows that keep
-// nothing but keys masked by a bias of -1e9: all weights 2^e) until 2^e overflows, from a bias of -1e10 on: then the next float
-// above is taken, the weights are 0, and what the row keeps later counts alone.
+// nothing but keys masked by a bias of -1e9: all weights 2^e) until 2^e overflows, as it can from a bias of -1.5e9 on: then
+// the next float above is taken, the weights are 0, and what the row keeps later counts alone.
 DMA_FN float reference_of(float top, float c2) {
   float ref = __builtin_fmaxf(top * c2, REF_NONE);  // (top = -inf: nothing kept)
   if (weight_exponent(top, c2, ref) > MAX_EXPONENT) {
