@@ -292,9 +292,9 @@ int dma_decode_step(const dma_shape* shape, const void* q, const void* K, const 
  */
 typedef enum {
   DMA_STAGE_Z = 0,          /* mask_gen: block table + content scores (Eq. 3)            */
-  DMA_STAGE_SORT = 1,       /* mask_gen: stable sort + wavelet matrix per (document, head) */
-  DMA_STAGE_EXPIRY = 2,     /* mask_gen: expiry of every key (Eq. 4)                      */
-  DMA_STAGE_PLAN = 3,       /* mask_gen: slots, slot table, partial lists, topk_idx       */
+  DMA_STAGE_SORT = 1,       /* mask_gen: selection (Eq. 4): evictions by blocks; or a sort  */
+  DMA_STAGE_EXPIRY = 2,     /* mask_gen: expiry of every key, after a sort (else empty)   */
+  DMA_STAGE_PLAN = 3,       /* mask_gen: expiries, slots, slot table, partial lists, topk_idx       */
   DMA_STAGE_FWD = 4,        /* fwd: the attention kernel                                  */
   DMA_STAGE_BWD_ZERO = 5,   /* bwd: (empty: the dQ stage clears the fp32 accumulators)   */
   DMA_STAGE_BWD_DQ = 6,     /* bwd: D and dQ (query-stationary)                           */

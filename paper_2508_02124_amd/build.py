@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdma_hip.so")
 PROBE_LIB = os.path.join(HERE, "libdma_probe.so")   # the benchmark's yardsticks: a library of their own
-SOURCES = ["api.hip", "mask_gen.hip", "fwd.hip", "bwd.hip", "mask_bwd.hip", "xhead.hip", "decode.hip", "debug_f32.hip"]
+SOURCES = ["api.hip", "mask_gen.hip", "select.hip", "fwd.hip", "bwd.hip", "mask_bwd.hip", "xhead.hip", "decode.hip", "debug_f32.hip"]
 PROBE_SOURCES = ["probe.hip"]
 # The attention kernels form no NaN from finite inputs (inf - inf is avoided: softmax_ref.h; a row whose keys are all
 # masked beyond the range of fp32 ends as 0 / 0, which nothing compares), so their max / compare chains may

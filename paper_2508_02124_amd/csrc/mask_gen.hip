@@ -1,8 +1,9 @@
 // Mask generation: content scores (Eq. 3), per-row causal top-k as one expiry per key (Eq. 4),
 // and the slot table / per-block partial key lists the attention kernels walk.
 //
-// Selection.  Row i keeps the min(k, i+1) best keys j <= i under (z descending, index ascending).
-// Sort the keys of a document once under that order (stable radix sort); the keys that rank ahead
+// Selection.  Row i keeps the min(k, i+1) best keys j <= i under (z descending, index ascending).  Causal documents up to
+// SELECT_MAX keys are worked out block by block (select.hip).  Longer ones, and plans without the causal restriction, sort:
+// sort the keys of a document once under that order (stable radix sort); the keys that rank ahead
 // of key j are exactly its "dominators".  Key j stops being kept at the row where the k-th
 // dominator (in index order) appears, so
 //     e_j = max(j, k-th smallest index among the keys ranked ahead of j)
@@ -17,6 +18,7 @@
 // tiles: per query block, the resident of every slot that stays the whole block ("clean"), plus a
 // short list of keys that enter or expire inside the block ("partial").
 #include "common.h"
+#include "select.h"
 
 namespace dma {
 
@@ -203,14 +205,6 @@ __global__ __launch_bounds__(256) void zq_kernel(const float* __restrict__ z, fl
 }
 
 // ------------------------------------------------------------------ sort + wavelet matrix
-// Ascending unsigned order of the result == descending float order of z (-0 and +0 compare equal).
-__device__ __forceinline__ uint32_t desc_key(float z) {
-  z = z + 0.0f;
-  uint32_t u = __float_as_uint(z);
-  u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-  return ~u;
-}
-
 __device__ __forceinline__ int dev_ceil_log2(int n) { return n <= 1 ? 0 : 32 - __clz(n - 1); }
 
 struct SortArgs {
@@ -461,9 +455,8 @@ __device__ __forceinline__ uint32_t wavelet_kth(const SortArgs& p, int h, int sl
 // segment already holds k better keys, and an answer in an earlier segment needs no quantile query
 // (every index there is below the key's own, so the key is never kept).
 // A document of one segment needs no search: the thread takes the key at rank r = its position and asks the segment's
-// wavelet matrix for e_j = max(j, k-th smallest index among the keys ranked ahead of j).  LONG: some document may have
-// several segments (one launch serves both kinds: a second one took 4 to 5 us).
-template <bool RANK, bool LONG>
+// wavelet matrix for e_j = max(j, k-th smallest index among the keys ranked ahead of j).
+template <bool RANK>
 __global__ __launch_bounds__(256) void expiry_kernel(SortArgs p) {
   const int t = blockIdx.x * 256 + threadIdx.x, h = blockIdx.y;
   if (t >= p.T) return;
@@ -471,7 +464,7 @@ __global__ __launch_bounds__(256) void expiry_kernel(SortArgs p) {
   const int a = p.cu[d], b = p.cu[d + 1], n = b - a;
   const int SEG = p.seg;
   if (n <= p.k) return;
-  if (!LONG || n <= SEG) {
+  if (n <= SEG) {
     if (RANK) return;  // (one segment: its rank order is the document's)
     const int r = t - a;
     const int j = (int)p.si0[(size_t)h * p.T + t];
@@ -526,31 +519,64 @@ __global__ __launch_bounds__(256) void expiry_kernel(SortArgs p) {
 // ------------------------------------------------------------------ slots
 // parent[i] = the key evicted when key i entered (global index, -1 if none); slotid[i] = root of
 // i's eviction chain = its slot column (document-local, < k).
-__global__ __launch_bounds__(1024) void slot_kernel(const int32_t* __restrict__ cu, const int32_t* __restrict__ expiry,
-                                                    int32_t* parent, int32_t* slotid, int T, int k) {
+// EVICTIONS: parent is given (-2: the row's own key never enters) and the expiries are made here; otherwise the other way
+// round.
+template <bool EVICTIONS>
+__global__ __launch_bounds__(1024) void slot_kernel(const int32_t* __restrict__ cu, int32_t* expiry, int32_t* parent,
+                                                    int32_t* slotid, int T, int k) {
   const int d = blockIdx.x, h = blockIdx.y;
   const int a = cu[d], b = cu[d + 1], n = b - a;
   if (n <= 0) return;
   const size_t hb = (size_t)h * T + a;
   int32_t* par = parent + hb;
   int32_t* sid = slotid + hb;
-  const int32_t* ex = expiry + hb;
+  int32_t* ex = expiry + hb;
   const int tid = threadIdx.x;
+  if (n <= k) {
+    for (int j = tid; j < n; j += 1024) {
+      if (EVICTIONS) ex[j] = b;
+      else par[j] = -1;
+      sid[j] = j;
+    }
+    return;
+  }
   const int rounds = dev_ceil_log2(n);
   constexpr int LDS_N = 65536;  // local indices fit 16 bits up to this length
   __shared__ uint16_t ls[LDS_N];
-  if (n > k && n <= LDS_N) {
-    // the chain links live in LDS from the start: only parent[] and the final slot ids touch memory
-    for (int j = tid; j < n; j += 1024) {
-      par[j] = -1;
-      ls[j] = (uint16_t)j;
-    }
-    __syncthreads();
-    for (int j = tid; j < n; j += 1024) {
-      const int e = ex[j] - a;
-      if (e > j && e < n) {  // key j is evicted at row e by key e
-        par[e] = a + j;
-        ls[e] = (uint16_t)j;
+  // the chain links: link(j) = the key that j evicted, or j itself
+  auto links = [&](auto* link) {
+    if (EVICTIONS) {
+      constexpr int U = 8;  // rows in flight per thread
+      for (int j0 = tid; j0 < n; j0 += U * 1024) {
+        int q[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) q[u] = par[min(j0 + u * 1024, n - 1)];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          const int j = j0 + u * 1024;
+          if (j < n) {
+            link[j] = q[u] >= 0 ? q[u] - a : j;
+            ex[j] = q[u] == -2 ? a + j : b;
+          }
+        }
+      }
+      __syncthreads();
+      for (int j = tid; j < n; j += 1024) {
+        const int q = link[j];
+        if (q != j) ex[q] = a + j;
+      }
+    } else {
+      for (int j = tid; j < n; j += 1024) {
+        par[j] = -1;
+        link[j] = j;
+      }
+      __syncthreads();
+      for (int j = tid; j < n; j += 1024) {
+        const int e = ex[j] - a;
+        if (e > j && e < n) {  // key j is evicted at row e by key e
+          par[e] = a + j;
+          link[e] = j;
+        }
       }
     }
     __syncthreads();
@@ -559,41 +585,20 @@ __global__ __launch_bounds__(1024) void slot_kernel(const int32_t* __restrict__ 
       // ancestor on the same chain, so the jumping only converges faster)
       int moved = 0;
       for (int j = tid; j < n; j += 1024) {
-        const int q = ls[j];
+        const int q = link[j];
         if (q >= k && q != j) {  // (q == j: a key that never enters; nothing points at it)
-          ls[j] = ls[q];
+          link[j] = link[q];
           moved = 1;
         }
       }
       if (!__syncthreads_or(moved)) break;  // every entry is a root: chains are short (about n / k links)
     }
+  };
+  if (n <= LDS_N) {  // in LDS: only parents, expiries and the final slot ids touch memory
+    links(ls);
     for (int j = tid; j < n; j += 1024) sid[j] = ls[j];
-    return;
-  }
-  for (int j = tid; j < n; j += 1024) {
-    par[j] = -1;
-    sid[j] = j;
-  }
-  __syncthreads();
-  if (n <= k) return;
-  for (int j = tid; j < n; j += 1024) {
-    const int e = ex[j] - a;
-    if (e > j && e < n) {  // key j is evicted at row e by key e
-      par[e] = a + j;
-      sid[e] = j;
-    }
-  }
-  __syncthreads();
-  for (int r = 0; r < rounds; r++) {
-    int moved = 0;
-    for (int j = tid; j < n; j += 1024) {
-      const int q = sid[j];
-      if (q >= k && q != j) {
-        sid[j] = sid[q];
-        moved = 1;
-      }
-    }
-    if (!__syncthreads_or(moved)) break;
+  } else {
+    links(sid);
   }
 }
 
@@ -1038,6 +1043,9 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
     prof_end(DMA_STAGE_PLAN, st);
     return hipGetLastError() == hipSuccess ? DMA_OK : DMA_EHIP;
   }
+  // Causal: evictions by blocks (select.hip), unless a document may be longer than SELECT_MAX.  The other plans sort.
+  const int longest = s.max_seqlen > 0 && s.max_seqlen < s.T ? s.max_seqlen : s.T;
+  const bool by_blocks = s.causal && longest <= SELECT_MAX;
   SortArgs sa;
   sa.z = z; sa.cu = cu; sa.expiry = expiry;
   sa.sk0 = (uint32_t*)(base + L.off_sk0); sa.sk1 = (uint32_t*)(base + L.off_sk1);
@@ -1048,8 +1056,15 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
   sa.T = s.T; sa.n_docs = s.n_docs; sa.k = s.k; sa.nbits_cap = L.nbits_cap; sa.wcap = L.wcap;
   sa.nseg_cap = L.nseg_cap; sa.seg = L.seg;
   prof_begin(DMA_STAGE_SORT, st);
-  if (L.seg == SEG_MIN) sort_wavelet_kernel<SEG_MIN / 1024><<<dim3(L.nseg_cap, s.H_q), 1024, 0, st>>>(sa);
-  else sort_wavelet_kernel<SEG_MAX / 1024><<<dim3(L.nseg_cap, s.H_q), 1024, 0, st>>>(sa);
+  if (by_blocks) {
+    const SelectArgs a = {z, cu, blk, parent, (float*)(base + L.off_sk0), (int32_t*)(base + L.off_si0), s.T, s.n_docs,
+                          L.nblk_cap, s.k, longest > CK_DOC ? CK_DOC : 0x7fffffff};
+    launch_evictions(a, longest, s.H_q, st);
+  } else if (L.seg == SEG_MIN) {
+    sort_wavelet_kernel<SEG_MIN / 1024><<<dim3(L.nseg_cap, s.H_q), 1024, 0, st>>>(sa);
+  } else {
+    sort_wavelet_kernel<SEG_MAX / 1024><<<dim3(L.nseg_cap, s.H_q), 1024, 0, st>>>(sa);
+  }
   prof_end(DMA_STAGE_SORT, st);
   const auto fill = [&](int32_t* dst, size_t n, int32_t v) {
     size_t grid = (n + 2047) / 2048;
@@ -1064,16 +1079,16 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
     fill(slot_tab, (size_t)s.H_q * L.nblk_cap * L.kpad, -1);
     fill(pcnt, (L.off_plist - L.off_pcnt) / 4, 0);  // pcnt and pent
     // (documents of several segments get their whole-document rank order from expiry_kernel's RANK form)
-    if (s.T > L.seg) expiry_kernel<true, true><<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
+    if (s.T > L.seg) expiry_kernel<true><<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
     noncausal_plan_kernel<<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(cu, s.n_docs, sa.si0, docblk, expiry, slot_tab,
                                                                         s.T, s.k, L.nblk_cap, L.kpad);
   } else {
     prof_begin(DMA_STAGE_EXPIRY, st);
-    if (s.T > L.seg) expiry_kernel<false, true><<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
-    else expiry_kernel<false, false><<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
+    if (!by_blocks) expiry_kernel<false><<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
     prof_end(DMA_STAGE_EXPIRY, st);
     prof_begin(DMA_STAGE_PLAN, st);
-    slot_kernel<<<dim3(s.n_docs, s.H_q), 1024, 0, st>>>(cu, expiry, parent, slotid, s.T, s.k);
+    (by_blocks ? slot_kernel<true> : slot_kernel<false>)<<<dim3(s.n_docs, s.H_q), 1024, 0, st>>>(cu, expiry, parent, slotid,
+                                                                                              s.T, s.k);
     const int per = L.nblk_cap / 16 > 4 ? L.nblk_cap / 16 : 4;  // about 16 chunks per head
     int tiles = (L.kpad + SLOT_TILE - 1) / SLOT_TILE;
     if (tiles > SLOT_TILES_MAX) {

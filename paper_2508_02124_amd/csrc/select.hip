@@ -1,0 +1,582 @@
+// Causal top-k selection (Eq. 4): which key each row evicts.
+//
+// While a document has more than k rows, every row admits at most one key and evicts the weakest resident, under
+// (score descending, index ascending).  evict_kernel writes parent[i] = the key that row i evicts (-1: none, -2: row i's
+// own key never enters); slot_kernel turns that into expiries.
+//
+// A block of BQ rows is worked out by itself, from the scores before it: at most BQ residents are evicted inside it, and
+// these are among the weakest of the residents at its first row.  A histogram of the scores before the block
+// (equal bins between the smallest and the largest) gives the bin of the k-th best and with it how many keys of the block
+// can enter (e); the keys between the bins of rank k - e and k, grouped by bin, are ranked against their bin.  A
+// key x then leaves at the row where the c-th of the block's keys ranked ahead of x appears, c = the places left behind the
+// residents ahead of x.  Everything is comparison of (score bits, index), so the result is the exact kept set.
+// Where the bins do not separate the scores (ties, outliers, infinities) the two ranks are found exactly, 11 bits of
+// (score bits, index) at a time.
+//
+// Long documents: reading everything before every block grows with the square of the length, so checkpoint_kernel
+// leaves, every CK_SEG keys, the weakest CK_SEG of the residents (no more can be evicted before the next one), and a
+// block reads these and the keys since.
+#include "select.h"
+
+namespace dma {
+
+constexpr int BINS = 1024, BIN_BITS = 10;
+constexpr int RUN = 4;    // keys compared at a time
+constexpr int CAP = 768;  // keys that the ranking takes: those between two bins
+
+__device__ __forceinline__ float key_value(uint32_t key) {
+  const uint32_t u = ~key;
+  return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
+}
+__device__ __forceinline__ uint64_t ranked(uint32_t key, int i) { return (uint64_t)key << 32 | (uint32_t)i; }
+
+// The scores before a block: m0 of a checkpoint's list (their indices in the document beside them), then nz of the document
+// from index c on, both in whole fours.  Threads take four at a time, the first NQ quads of a thread in registers, the others
+// read again in every pass.
+struct __attribute__((aligned(4))) Quad {  // (16 bytes at 4-byte alignment)
+  float v[4];
+};
+template <int NT, int NQ>
+struct Scores {
+  const float *list, *z;
+  const int32_t* list_idx;
+  int c, nq, list_q;
+  Quad r[NQ ? NQ : 1];
+  __device__ __forceinline__ Quad quad(int t) const {
+    Quad q = {};
+    if (t < nq) q = *reinterpret_cast<const Quad*>(t < list_q ? list + 4 * t : z + 4 * (t - list_q));
+    return q;
+  }
+  __device__ __forceinline__ void load(const float* list_, const int32_t* list_idx_, int m0, const float* z_, int nz, int c_) {
+    list = list_; list_idx = list_idx_; z = z_; c = c_;
+    list_q = m0 / 4;
+    nq = list_q + nz / 4;
+#pragma unroll
+    for (int j = 0; j < NQ; j++) {
+      r[j] = Quad{};
+      if (NT * j < nq) r[j] = quad((int)threadIdx.x + NT * j);
+    }
+  }
+  // index in the document of element e of quad t
+  __device__ __forceinline__ int index(int t, int e) const {
+    return t < list_q ? list_idx[4 * t + e] : c + 4 * (t - list_q) + e;
+  }
+  // f(score, t, e) for every element
+  template <typename F> __device__ __forceinline__ void each(F&& f) const {
+#pragma unroll
+    for (int j = 0; j < NQ; j++)
+      if (NT * j < nq) {
+        const int t = (int)threadIdx.x + NT * j;
+        if (t < nq) {
+#pragma unroll
+          for (int e = 0; e < 4; e++) f(r[j].v[e], t, e);
+        }
+      }
+    each_again(f, NQ);
+  }
+  template <typename F> __device__ __forceinline__ void each_again(F&& f, int j) const {
+    constexpr int U = 4;  // quads in flight
+#pragma unroll 1
+    for (; NT * j < nq; j += U) {
+      Quad q[U];
+#pragma unroll
+      for (int u = 0; u < U; u++) q[u] = quad((int)threadIdx.x + NT * (j + u));
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        const int t = (int)threadIdx.x + NT * (j + u);
+        if (t < nq) {
+#pragma unroll
+          for (int e = 0; e < 4; e++) f(q[u].v[e], t, e);
+        }
+      }
+    }
+  }
+};
+
+template <int NT> struct SelShared {
+  static constexpr int NW = NT / 64;
+  __align__(16) uint64_t cand[CAP + RUN];
+  uint32_t wsum[NW];
+  uint32_t kmin[NW], kmax[NW];
+  uint32_t bin[2], before[2], count[2];
+  int fill;
+  uint64_t found;
+};
+
+// Wave-wide inclusive sum, minimum and maximum in registers (data-parallel moves: a lane shuffle through LDS takes ten times as
+// long).
+template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t dpp(uint32_t identity, uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)x, CTRL, ROWS, 0xf, false);
+}
+template <typename F> __device__ __forceinline__ uint32_t wave_scan(uint32_t x, uint32_t identity, F&& op) {
+  x = op(x, dpp<0x111, 0xf>(identity, x));  // row_shr:1, 2, 4, 8
+  x = op(x, dpp<0x112, 0xf>(identity, x));
+  x = op(x, dpp<0x114, 0xf>(identity, x));
+  x = op(x, dpp<0x118, 0xf>(identity, x));
+  x = op(x, dpp<0x142, 0xa>(identity, x));  // row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3
+  return op(x, dpp<0x143, 0xc>(identity, x));
+}
+template <int LANE> __device__ __forceinline__ void write_lane(int& v, uint32_t x) {
+  asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(x), "n"(LANE));
+}
+__device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
+
+// Exclusive prefix sums of a histogram, in place; seen(bin, count before it, count in it) for every bin.
+template <int NT, typename F>
+__device__ __forceinline__ void scan_bins(SelShared<NT>& sm, uint32_t* hist, F&& seen) {
+  constexpr int PER = BINS / NT, NW = NT / 64;
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  uint32_t v[PER], s = 0;
+#pragma unroll
+  for (int i = 0; i < PER; i++) {
+    v[i] = hist[PER * tid + i];
+    s += v[i];
+  }
+  const uint32_t inc = wave_scan(s, 0, [](uint32_t x, uint32_t y) { return x + y; });
+  if (l == 63) sm.wsum[w] = inc;
+  __syncthreads();
+  uint32_t ex = inc - s;
+#pragma unroll
+  for (int i = 0; i < NW; i++) ex += i < w ? sm.wsum[i] : 0u;
+#pragma unroll
+  for (int i = 0; i < PER; i++) {
+    hist[PER * tid + i] = ex;
+    seen(PER * tid + i, ex, v[i]);
+    ex += v[i];
+  }
+  __syncthreads();
+}
+// The bin that holds a rank, with the counts before and in it, to place `at`.
+template <int NT> __device__ __forceinline__ void note_bin(SelShared<NT>& sm, int at, uint32_t rank, int bin, uint32_t before, uint32_t count) {
+  if (rank - before < count) { sm.bin[at] = bin; sm.before[at] = before; sm.count[at] = count; }
+}
+
+template <int NT> __device__ __forceinline__ void clear_bins(uint32_t* hist) {
+  for (int i = threadIdx.x; i < BINS / 4; i += NT) reinterpret_cast<uint4*>(hist)[i] = make_uint4(0, 0, 0, 0);
+}
+
+// Smallest kmin and largest kmax of all threads.
+template <int NT> __device__ __forceinline__ void reduce_range(SelShared<NT>& sm, uint32_t& kmin, uint32_t& kmax) {
+  kmin = last_lane(wave_scan(kmin, 0xffffffffu, [](uint32_t x, uint32_t y) { return min(x, y); }));
+  kmax = last_lane(wave_scan(kmax, 0u, [](uint32_t x, uint32_t y) { return max(x, y); }));
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    sm.kmin[w] = kmin;
+    sm.kmax[w] = kmax;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NT / 64; i++) {
+    kmin = min(kmin, sm.kmin[i]);
+    kmax = max(kmax, sm.kmax[i]);
+  }
+}
+// Best and worst key; the whole range if a score, or the thread's own one, is infinite or not a number.  (own scores are in
+// the range only if there are no others.)
+template <int NT, int NQ>
+__device__ __forceinline__ void key_range(SelShared<NT>& sm, const Scores<NT, NQ>& s, float own, uint32_t& kmin, uint32_t& kmax) {
+  float top = s.nq ? -__builtin_inff() : own, low = s.nq ? __builtin_inff() : own, bad = own * 0.f;
+  s.each([&](float z, int, int) {
+    top = fmaxf(top, z);
+    low = fminf(low, z);
+    bad = fmaf(z, 0.f, bad);
+  });
+  kmin = bad != bad ? 0u : desc_key(top);
+  kmax = bad != bad ? 0xffffffffu : desc_key(low);
+  reduce_range(sm, kmin, kmax);
+}
+// Equal bins between the best and the worst score.
+struct Bins {
+  float c0, c1;
+  bool ok;  // the scores are finite and not all the same
+  __device__ __forceinline__ void init(uint32_t kmin, uint32_t kmax) {
+    const float top = key_value(kmin), range = top - key_value(kmax);
+    c1 = -(BINS - 1) / range;
+    c0 = -c1 * top;
+    ok = range > 0.f && range < __builtin_inff() && c1 > -__builtin_inff() && fabsf(c0) < __builtin_inff();  // (false for NaN)
+  }
+  // never falls along descending finite scores
+  __device__ __forceinline__ int of(float z) const { return (int)__builtin_amdgcn_fmed3f(fmaf(z, c1, c0), 0.f, BINS - 1); }
+};
+
+// ranked(key, index) of the score with the given rank among those with pick(score), for any scores: BIN_BITS of (key,
+// index) at a time, the indices taken as `ibits` wide.  hist: another one than the bins'.
+template <int NT, int NQ, typename F>
+__device__ __forceinline__ uint64_t exact_rank(SelShared<NT>& sm, uint32_t* hist, const Scores<NT, NQ>& s, int ibits, uint32_t rank, F&& pick) {
+  uint32_t kmin = 0xffffffffu, kmax = 0;
+  __syncthreads();
+  s.each_again([&](float z, int, int) {
+    if (pick(z)) {
+      kmin = min(kmin, desc_key(z));
+      kmax = max(kmax, desc_key(z));
+    }
+  }, 0);
+  reduce_range(sm, kmin, kmax);
+  uint64_t base = (uint64_t)kmin << ibits;
+  const uint64_t width = (((uint64_t)kmax + 1) << ibits) - base;
+  int shift = max(0, 64 - (int)__clzll((long long)(width - 1)) - BIN_BITS);
+  for (;;) {
+    clear_bins<NT>(hist);
+    __syncthreads();
+    s.each_again([&](float z, int t, int e) {
+      if (!pick(z)) return;
+      const uint64_t c = (uint64_t)desc_key(z) << ibits | (uint32_t)s.index(t, e), bin = (c - base) >> shift;
+      if (c >= base && bin < BINS) {
+        // (with ties the lanes mostly agree: one addition for all of them)
+        const uint32_t b = (uint32_t)bin, b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+        const uint64_t same = __ballot(b == b0);
+        if (b != b0) atomicAdd(&hist[b], 1u);
+        else if ((same & ((1ull << (threadIdx.x & 63)) - 1ull)) == 0) atomicAdd(&hist[b], (uint32_t)__popcll(same));
+      }
+    }, 0);
+    __syncthreads();
+    scan_bins(sm, hist, [&](int bin, uint32_t before, uint32_t count) { note_bin(sm, 0, rank, bin, before, count); });
+    base += (uint64_t)sm.bin[0] << shift;
+    rank -= sm.before[0];
+    __syncthreads();
+    if (shift == 0) return ranked((uint32_t)(base >> ibits), (int)(base & ((1ull << ibits) - 1)));
+    shift = max(0, shift - BIN_BITS);
+  }
+}
+
+// ------------------------------------------------------------------ checkpoints
+__device__ __forceinline__ int ck_keys(int k) { return k < CK_SEG ? (k + 3) & ~3 : CK_SEG; }
+__device__ __forceinline__ int ck_slot(int a, int d, int p) { return a / CK_SEG + d + p; }
+
+// One workgroup per (checkpoint, head): document d's checkpoint p stands before its key c = CK_SEG (p + 1) and holds, in
+// any order, the weakest ck_keys(k) of the keys kept by row c - 1 (k < CK_SEG: all of them, and up to three more); it is stored at the place of the CK_SEG keys before c.
+// What bounds it: instruction issue over the N scores, three to four passes of loads of 16 bytes per lane: 65536 tokens x
+// 32 heads 44 us (window 16384: 58).
+constexpr int CK_NT = 1024, CK_NQ = 0;
+__global__ __launch_bounds__(CK_NT, 8) void checkpoint_kernel(SelectArgs p) {
+  __shared__ SelShared<CK_NT> sm;
+  __shared__ __align__(16) uint32_t hist[BINS], exact_hist[BINS];
+  const int slot = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
+  int d = 0;
+  {
+    int lo = 0, hi = p.n_docs;  // largest d with ck_slot(cu[d], d, 0) <= slot
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (ck_slot(p.cu[mid], mid, 0) <= slot) lo = mid; else hi = mid;
+    }
+    d = lo;
+  }
+  const int a = p.cu[d], n = p.cu[d + 1] - a;
+  const int c = CK_SEG * (slot - ck_slot(a, d, 0) + 1);
+  if (n <= p.ck_min || n <= p.k || c >= n) return;
+  Scores<CK_NT, CK_NQ> s;
+  s.load(p.z, p.ck_idx, 0, p.z + (size_t)h * p.T + a, c, 0);
+  const int m0 = ck_keys(p.k), kept = max(m0, min(p.k, c));
+  uint64_t from = 0, to = ~0ull;  // the weakest m0 of the kept: ranks kept - m0 .. kept - 1
+  if (kept < c || m0 < kept) {
+    uint32_t kmin, kmax;
+    clear_bins<CK_NT>(hist);
+    key_range(sm, s, 0.f, kmin, kmax);
+    Bins bins;
+    bins.init(kmin, kmax);
+    const uint32_t rank0 = kept - m0, rank1 = kept - 1;
+    if (bins.ok) {
+      s.each([&](float z, int, int) { atomicAdd(&hist[bins.of(z)], 1u); });
+      __syncthreads();
+      scan_bins(sm, hist, [&](int bin, uint32_t before, uint32_t count) {
+        note_bin(sm, 0, rank0, bin, before, count);
+        note_bin(sm, 1, rank1, bin, before, count);
+      });
+    }
+    const uint32_t bin0 = sm.bin[0], before0 = sm.before[0], count0 = sm.count[0];
+    const uint32_t bin1 = sm.bin[1], before1 = sm.before[1], count1 = sm.count[1];
+    __syncthreads();
+#pragma unroll 1
+    for (int i = 0; i < 2; i++) {
+      if (i == 0 ? rank0 == 0 : kept == c) continue;  // (nothing is left out on this side)
+      const uint32_t rank = i == 0 ? rank0 : rank1;
+      uint64_t found;
+      const uint32_t bin = i == 0 ? bin0 : bin1, before = i == 0 ? before0 : before1, count = i == 0 ? count0 : count1;
+      if (bins.ok && count <= CAP) {
+        if (tid == 0) sm.fill = 0;
+        __syncthreads();
+        s.each([&](float z, int t, int e) {
+          if ((uint32_t)bins.of(z) == bin) sm.cand[atomicAdd(&sm.fill, 1)] = ranked(desc_key(z), s.index(t, e));
+        });
+        __syncthreads();
+        if (tid < (int)count) {
+          const uint64_t mine = sm.cand[tid];
+          uint32_t ahead = 0;
+          for (uint32_t j = 0; j < count; j++) ahead += sm.cand[j] < mine;
+          if (before + ahead == rank) sm.found = mine;
+        }
+        __syncthreads();
+        found = sm.found;
+        __syncthreads();
+      } else {
+        // (the bin's keys, or all of them)
+        found = exact_rank(sm, exact_hist, s, 32 - __clz(n), bins.ok ? rank - before : rank,
+                           [&](float z) { return !bins.ok || (uint32_t)bins.of(z) == bin; });
+      }
+      if (i == 0) from = found; else to = found;
+    }
+  }
+  const size_t out = (size_t)h * p.T + a + (c - CK_SEG);
+  __syncthreads();
+  if (tid == 0) sm.fill = 0;
+  __syncthreads();
+  s.each([&](float z, int t, int e) {
+    const int i = s.index(t, e);
+    const uint64_t r = ranked(desc_key(z), i);
+    if (r >= from && r <= to) {
+      const int at = atomicAdd(&sm.fill, 1);
+      p.ck_z[out + at] = z;
+      p.ck_idx[out + at] = i;
+    }
+  });
+}
+
+// ------------------------------------------------------------------ evictions of one block
+// One workgroup per (block, head).  What bounds it: instruction issue; its twelve short phases between barriers take about 14000
+// cycles with 1024 older scores (what a score costs is 15 instructions in all), so seven workgroups share a compute unit.
+// Whole selection, us, against a radix sort and wavelet matrix per 4096 or 16384 keys and a range query per key: 256
+// tokens x 2 heads 25 -> 7, 2 x 4096 x 16 52 -> 12, 16384 x 32 76 -> 25, packed 65536 x 16 121 -> 33, 65536 x 32 of
+// window 1024 241 -> 95.  (Scores of sixteen different values, whole dma_mask_gen: 16384 x 32 114 -> 176, packed 155 -> 108:
+// the counters of a few bins are fought over, and ranks are found among long runs.)  1024 bins and 256 threads
+// against 2048 and 512: packed 41 -> 33, 65536 tokens 74 -> 50, 8192 x 32 heads 17.5 -> 19.
+template <int NT, int NQ>
+__global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
+  constexpr int NW = NT / 64;
+  constexpr int XT = (CAP + BQ + NT - 1) / NT;  // keys ranked per thread
+  static_assert(NT >= BQ, "one thread per row of the block");
+  __shared__ SelShared<NT> sm;
+  __shared__ __align__(16) uint32_t hists[2 * BINS];  // of the older scores, of those of the block that can enter; then the sets below
+  uint32_t *const hist = hists, *const new_hist = hists + BINS;
+  __shared__ __align__(16) uint64_t newc[BQ];      // the block's keys that can enter, in index order
+  __shared__ __align__(16) uint64_t new_run[BQ + RUN];  // ... grouped by bin
+  __shared__ int new_rank[BQ];                     // ... how many of them are ahead of each
+  __shared__ int out[BQ];
+  const int bi = p.nblk_cap - 1 - (int)blockIdx.x, h = blockIdx.y;  // long prefixes first
+  const int4 info = p.blk[bi];
+  if (info.x < 0) return;
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  const int a = info.w, lo = info.y - a, nb = info.z - info.y, n = p.cu[info.x + 1] - a, k = p.k;
+  int32_t* par = p.parent + (size_t)h * p.T + info.y;
+  if (n <= k || lo + nb <= k) {  // nothing is evicted here
+    if (tid < nb) par[tid] = -1;
+    return;
+  }
+  const float* zd = p.z + (size_t)h * p.T + a;
+  int c = 0, m0 = 0, cap = k;  // list of the last checkpoint, if there is one; places for its keys and those since
+  if (n > p.ck_min && lo >= CK_SEG) {
+    c = lo & ~(CK_SEG - 1);
+    m0 = ck_keys(k);
+    cap = k - max(0, min(k, c) - m0);
+  }
+  const int N = m0 + lo - c, kept = min(cap, N);
+  const size_t ck = m0 ? (size_t)h * p.T + a + (c - CK_SEG) : 0;
+  const float zn = zd[lo + min(tid, nb - 1)];
+  const uint32_t kn = desc_key(zn);
+  Scores<NT, NQ> s;
+  s.load(p.ck_z + ck, p.ck_idx + ck, m0, zd + c, lo - c, c);
+
+  // Which older keys take part (nl of them, in sm.cand), how many residents are ahead of all of these, and which of the
+  // block's keys can enter.
+  int strong = 0, nl = 0;
+  bool enters = tid < nb;
+  int b1 = BINS - 1, b2 = 0, end_before = 0, end = N;  // bins of the last resident and of the first that takes part; keys before and up to the end of b1
+  Bins bins;
+  uint32_t kmin, kmax;
+  clear_bins<NT>(hist);
+  clear_bins<NT>(new_hist);
+  if (tid == 0) sm.bin[1] = sm.before[1] = 0;  // (what is left without older keys)
+  key_range(sm, s, zn, kmin, kmax);
+  bins.init(kmin, kmax);
+  bool by_bin = bins.ok;
+  // the bin of a rank among the older keys, and the count before it
+  auto find_bin = [&](int rank) __attribute__((always_inline)) {
+    constexpr int PER = BINS / NT;
+    int begin[PER + 1];
+#pragma unroll
+    for (int i = 0; i < PER; i++) begin[i] = hist[PER * tid + i];
+    begin[PER] = tid + 1 < NT ? (int)hist[PER * (tid + 1)] : N;
+#pragma unroll
+    for (int i = 0; i < PER; i++)
+      if (begin[i] <= rank && rank < begin[i + 1]) { sm.bin[1] = PER * tid + i; sm.before[1] = begin[i]; }
+    __syncthreads();
+  };
+  if (by_bin) {
+    s.each([&](float z, int, int) { atomicAdd(&hist[bins.of(z)], 1u); });
+    __syncthreads();
+    const int bn = bins.of(zn);
+    scan_bins(sm, hist, [&](int bin, uint32_t before, uint32_t count) {
+      note_bin(sm, 0, (uint32_t)(kept - 1), bin, before, count);
+    });
+    // (kept == N: every older key is still there, whatever its rank; with no place left either, a key has to be ahead of
+    // the last of them to enter)
+    if (kept < N) {
+      b1 = sm.bin[0];
+      end_before = sm.before[0];
+      end = end_before + sm.count[0];
+    }
+    enters = tid < nb && bn <= b1 && (cap > N || kn < kmax);
+    const int e = __syncthreads_count(enters);
+    if (e == 0) {
+      if (tid < nb) par[tid] = -2;
+      return;
+    }
+    if (enters) atomicAdd(&new_hist[bn], 1u);
+    // (a row evicts nothing before the places are taken)
+    find_bin(max(0, kept - min(e, lo + nb - k)));
+    b2 = sm.bin[1];
+    strong = sm.before[1];
+    nl = end - strong;
+    by_bin = nl <= CAP;
+    if (by_bin) {
+      s.each([&](float z, int t, int e2) {
+        const int b = bins.of(z);
+        if (b >= b2 && b <= b1) sm.cand[atomicAdd(&hist[b], 1u) - strong] = ranked(desc_key(z), s.index(t, e2));
+      });
+      scan_bins(sm, new_hist, [](int, uint32_t, uint32_t) {});
+      if (enters) new_run[atomicAdd(&new_hist[bn], 1u)] = ranked(kn, lo + tid);
+    }
+  }
+  if (!by_bin && N > 0) {
+    const int ibits = 32 - __clz(n);
+    const auto in_bin = [&](int b) __attribute__((always_inline)) { return [&, b](float z) { return !bins.ok || bins.of(z) == b; }; };
+    uint64_t to = ~0ull;
+    if (kept < N) to = exact_rank(sm, new_hist, s, ibits, kept - 1 - (bins.ok ? end_before : 0), in_bin(b1));
+    enters = tid < nb && (cap > N || kn < (kept < N ? (uint32_t)(to >> 32) : kmax));
+    const int e = __syncthreads_count(enters);
+    if (e == 0) {
+      if (tid < nb) par[tid] = -2;
+      return;
+    }
+    strong = max(0, kept - min(e, lo + nb - k));
+    nl = kept - strong;
+    int b = 0, before = 0;
+    if (bins.ok) {
+      find_bin(strong);
+      b = sm.bin[1];
+      before = sm.before[1];
+    }
+    const uint64_t from = exact_rank(sm, new_hist, s, ibits, strong - before, in_bin(b));
+    if (tid == 0) sm.fill = 0;
+    __syncthreads();
+    s.each_again([&](float z, int t, int e2) {
+      const uint64_t r = ranked(desc_key(z), s.index(t, e2));
+      if (r >= from && r <= to) sm.cand[atomicAdd(&sm.fill, 1)] = r;
+    }, 0);
+  }
+  const int places = cap - strong;  // for the nl older keys and the new ones
+  const uint64_t em = __ballot(enters);
+  if (l == 0) sm.wsum[w] = __popcll(em);
+  if (tid < BQ) out[tid] = enters ? -1 : -2;
+  __syncthreads();  // (sm.cand is complete too)
+  int ne = 0, nbase = 0;
+#pragma unroll
+  for (int i = 0; i < BQ / 64; i++) {
+    nbase += i < w ? sm.wsum[i] : 0u;
+    ne += sm.wsum[i];
+  }
+  if (enters) {
+    const int i = nbase + __popcll(em & ((1ull << l) - 1ull));
+    newc[i] = ranked(kn, lo + tid);
+    if (!by_bin) new_run[i] = ranked(kn, lo + tid);
+  }
+  __syncthreads();
+  // Key x leaves at the row of the left-th new key (in index order) among those ahead of it: `left` from the older keys
+  // ahead of it, and how many new ones are ahead of it in all, ...
+  uint64_t cx[XT];
+  int left[XT], ahead[XT];
+#pragma unroll
+  for (int u = 0; u < XT; u++) {
+    const int x = tid + NT * u;
+    left[u] = ahead[u] = 0;
+    cx[u] = 0;
+    if (x >= nl + ne) continue;
+    cx[u] = x < nl ? sm.cand[x] : newc[x - nl];
+    int r0 = 0, r1 = nl, n0 = 0, n1 = ne;  // the older and the new keys of its bin, or all of them
+    if (by_bin) {
+      const int b = bins.of(key_value((uint32_t)(cx[u] >> 32)));
+      r0 = b > b2 ? (int)hist[b - 1] - strong : 0;  // (the counters stand at their bins' ends now)
+      r1 = b >= b2 ? (int)hist[b] - strong : 0;
+      n0 = b > 0 ? (int)new_hist[b - 1] : 0;
+      n1 = new_hist[b];
+    }
+    auto rank_in = [&](const uint64_t* run, int i0, int i1) __attribute__((always_inline)) {
+      int r = i0, i = i0;
+#pragma unroll 1
+      for (; i + RUN <= i1; i += RUN) {
+#pragma unroll
+        for (int j = 0; j < RUN; j++) r += run[i + j] < cx[u];
+      }
+#pragma unroll
+      for (int j = 0; j < RUN - 1; j++) r += (i + j < i1) & (run[i + j] < cx[u]);
+      return r;
+    };
+    left[u] = places - rank_in(sm.cand, r0, r1);
+    ahead[u] = rank_in(new_run, n0, n1);
+    if (x >= nl) new_rank[x - nl] = ahead[u];
+  }
+  __syncthreads();
+  // ... then by the set of the first r new keys in rank order, as bits in index order, for every r.
+  uint64_t* sets = reinterpret_cast<uint64_t*>(hists);  // [r - 1][BQ / 64]
+  static_assert(BQ * (BQ / 64) * 8 <= 2 * BINS * 4, "the sets take the histograms' place");
+  {
+    const int words = ne <= 64 ? 1 : ne <= 128 ? 2 : 4, wd = w % words;
+    const int mine = 64 * wd + l < ne ? new_rank[64 * wd + l] : BQ;
+    for (int r0 = w / words * 64; r0 < ne; r0 += NW / words * 64) {
+      int lo32 = 0, hi32 = 0;  // lane i: the set of r0 + i + 1
+      static_for<64>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const uint64_t m = __ballot(mine <= r0 + i);
+        write_lane<i>(lo32, (uint32_t)m);
+        write_lane<i>(hi32, (uint32_t)(m >> 32));
+      });
+      if (r0 + l < ne) sets[(r0 + l) * (BQ / 64) + wd] = (uint64_t)(uint32_t)hi32 << 32 | (uint32_t)lo32;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < XT; u++) {
+    const int x = tid + NT * u;
+    if (x >= nl + ne) continue;
+    const int key = a + (int)(uint32_t)cx[u];
+    int y = -1;  // the new key at whose row it leaves
+    if (left[u] > 0 && left[u] <= ahead[u]) {
+      const uint64_t* set = sets + (ahead[u] - 1) * (BQ / 64);
+      int r = left[u];
+      uint64_t m = 0;
+#pragma unroll
+      for (int i = 0; i < BQ / 64; i++)
+        if (64 * i < ne && y < 0) {
+          m = set[i];
+          const int cnt = __popcll(m);
+          if (r <= cnt) y = 64 * i; else r -= cnt;
+        }
+      uint32_t v = (uint32_t)m;
+      const int low = __popc(v);
+      if (r > low) { r -= low; y += 32; v = (uint32_t)(m >> 32); }
+#pragma unroll
+      for (int b = 16; b > 0; b >>= 1) {
+        const int cnt = __popc(v & ((1u << b) - 1u));
+        if (r > cnt) { r -= cnt; y += b; v >>= b; }
+      }
+    }
+    const int row = y >= 0 ? (int)(uint32_t)newc[y] - lo : -1;
+    if (x < nl) {
+      if (y >= 0) out[row] = key;
+    } else if (left[u] <= 0 || (y >= 0 && y < x - nl)) {
+      out[key - a - lo] = -2;  // it never enters
+    } else if (y >= 0) {
+      out[row] = key;
+    }
+  }
+  __syncthreads();
+  if (tid < nb) par[tid] = out[tid];
+}
+
+int launch_evictions(const SelectArgs& a, int longest, int H_q, hipStream_t st) {
+  if (a.ck_min < longest)
+    checkpoint_kernel<<<dim3(a.T / CK_SEG + a.n_docs, H_q), CK_NT, 0, st>>>(a);
+  evict_kernel<256, 4><<<dim3(a.nblk_cap, H_q), 256, 0, st>>>(a);
+  return hipGetLastError() == hipSuccess ? DMA_OK : DMA_EHIP;
+}
+
+}  // namespace dma
