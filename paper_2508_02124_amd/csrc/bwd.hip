@@ -54,14 +54,17 @@ struct BwdArgs {
 // (us): 16384 tokens x 32 heads 872 -> 798; 16 heads of 256 channels, one wave per SIMD, 1172 -> 890; 2 x 4096 x 16
 // heads 141 -> 126; packed 65536 x 16 heads of 64 channels, not pipelined (three waves per SIMD; pipelined 426 there),
 // but with its rows addressed by immediates and dP started at -D: 425 -> 402.
-template <int D, int NW, int UT>
+// PARTS: waves that share the same 32 rows, each with its own units of every tile, as in the forward kernel; their dQ are
+// added at the end.  Whole backward, one / two of them at 128 channels (us): 1019 tokens x 32 heads 95.3 / 92.4, 2048 x 16
+// of window 1024 138 / 132, 300 x 32 47 / 47 (at 64 channels, three waves per SIMD without: 31.0 / 31.5, 69.3 / 70.3).
+template <int D, int NW, int UT, int PARTS = 1>
 __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p) {
   using TL = TileLayout<D>;
-  constexpr int KT = 32 * UT;
+  constexpr int KT = 32 * UT * PARTS;
   constexpr int KS = D / 16, CB = D / 32, CPR = D / 8, RPL = 64 / CPR, WL = KT / RPL / NW;
   constexpr bool PIPED = D != 64;
   constexpr int NS = PIPED ? 4 : 2, AHEAD = NS - 1;  // ring stages; tiles between a copy's request and its use
-  constexpr int TILE = KT * D, NT = NW * 64, HALVES = 8 / NW;
+  constexpr int TILE = KT * D, NT = NW * 64, RW = NW / PARTS, HALVES = 8 / RW;
   __shared__ __align__(16) uint16_t ring[2 * NS * TILE];  // K stages, then V stages
   __shared__ __align__(16) int ids_ring[2 * NS][64];  // (rows of 64: what one wave-wide copy writes)
   __shared__ __align__(16) float z_ring[NS][64];
@@ -85,10 +88,11 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
   const float c2 = *reinterpret_cast<const float*>(p.consts + PLAN_C2_OFF);
   if (info.x < 0) return;
   const int blk_row0 = info.y, row1 = info.z, doc0 = info.w;
-  const int row0 = blk_row0 + (item % HALVES) * (NW * 32);  // first row of this workgroup's part of the block
+  const int row0 = blk_row0 + (item % HALVES) * (RW * 32);  // first row of this workgroup's part of the block
   if (row0 >= row1) return;
   const int g = h / (p.H_q / p.H_kv);
   const int tid = thread_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, n = l & 31, hh = l >> 5;
+  const int wr = w % RW, part = w / RW;
   const int ncol = min(p.k, blk_row0 - doc0);
   const int nc = (ncol + KT - 1) / KT;
   const int nt = nc + (np_keys + KT - 1) / KT;
@@ -170,7 +174,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
     issue_scalars(i);
   }
 
-  const int qi = row0 + 32 * w + n;
+  const int qi = row0 + 32 * wr + n;
   const bool qvalid = qi < row1;
   bf16x8 qreg[KS], doreg[KS];
   float Dsum = 0.f;
@@ -202,29 +206,30 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
   // exponents) has P = 0 here too, not infinities that would reach the dV of its keys.
   if (lse2 == -INFINITY) lse2 = INFINITY;
   settle(lse2);
-  if (qvalid && hh == 0) {
+  if (qvalid && hh == 0 && part == 0) {
     p.Dws[(size_t)h * p.T + qi] = -Dsum;  // (negated: the key-stationary kernel starts its dP accumulators at -D_i)
     p.L2ws[(size_t)h * p.T + qi] = lse2;
   }
   // fragment addresses with the ring bases folded in: inside the stage-unrolled main loop every LDS
-  // read is one of these registers plus an immediate
+  // read is one of these registers plus an immediate; the part's first unit is folded in too
+  const int unit0 = 32 * UT * part;
   FragOffsets<D> fo;
   fo.init(l);
   uint32_t kfrag[KS], ktr[CB][2];
 #pragma unroll
   for (int ks = 0; ks < KS; ks++) {
-    kfrag[ks] = lds_addr(ring) + 2 * fo.row(ks);
+    kfrag[ks] = lds_addr(ring) + 2 * (fo.row(ks) + unit0 * D);
     settle(kfrag[ks]);
   }
 #pragma unroll
   for (int cb = 0; cb < CB; cb++)
 #pragma unroll
     for (int q = 0; q < 2; q++) {
-      ktr[cb][q] = lds_addr(ring) + 2 * fo.tr(cb, q);
+      ktr[cb][q] = lds_addr(ring) + 2 * (fo.tr(cb, q) + unit0 * D);
       settle(ktr[cb][q]);
     }
-  uint32_t zlane = lds_addr(&z_ring[0][4 * hh]);
-  const uint32_t jlane = lds_addr(&ids_ring[0][4 * hh]), elane = lds_addr(&e_ring[0][4 * hh]);
+  uint32_t zlane = lds_addr(&z_ring[0][unit0 + 4 * hh]);
+  const uint32_t jlane = lds_addr(&ids_ring[0][unit0 + 4 * hh]), elane = lds_addr(&e_ring[0][unit0 + 4 * hh]);
   settle(zlane);
   f32x16 dqacc[CB];
 #pragma unroll
@@ -284,9 +289,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
     static_for<LEAD>([&](auto mc) __attribute__((always_inline)) { frag(mc, shift * (2 * TILE), 0); });
   }
   // Partial tiles: a unit is active if some key of it is, on any of this wave's 32 rows.
-  const int rfirst = row0 + 32 * w;
+  const int rfirst = row0 + 32 * wr;
   auto active = [&](int tt, int st, int u) __attribute__((always_inline)) {  // unit u of tile tt, in ring stage st
-    const int jl = ids_ring[tt % (2 * NS)][32 * u + n], el = e_ring[st][32 * u + n];
+    const int jl = ids_ring[tt % (2 * NS)][unit0 + 32 * u + n], el = e_ring[st][unit0 + 32 * u + n];
     return (bool)__any((jl <= rfirst + 31) & (el > rfirst));  // (an empty entry has el = 0)
   };
   bool act0 = true;  // this unit is active
@@ -415,8 +420,35 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
 
   wait_vmcnt<0>();
   lds_barrier();
-  uint16_t* Os = ring;  // [NW * 32][D] staging with the tile swizzle
-  static_assert(NS * KT >= NW * 32, "dQ staging aliases the K ring");
+  if constexpr (PARTS > 1) {
+    static_assert(PARTS == 2 && NS * TILE * 2 >= RW * D * 128, "the second part's dQ takes the K ring");
+    f32x4* dq2 = reinterpret_cast<f32x4*>(ring) + wr * (4 * CB * 64) + l;
+    if (part == 1) {
+#pragma unroll
+      for (int cb = 0; cb < CB; cb++)
+#pragma unroll
+        for (int gq = 0; gq < 4; gq++) {
+          f32x4 x;
+#pragma unroll
+          for (int u = 0; u < 4; u++) x[u] = dqacc[cb][4 * gq + u];
+          dq2[(4 * cb + gq) * 64] = x;
+        }
+    }
+    lds_barrier();
+    if (part == 0) {
+#pragma unroll
+      for (int cb = 0; cb < CB; cb++)
+#pragma unroll
+        for (int gq = 0; gq < 4; gq++) {
+          const f32x4 x = dq2[(4 * cb + gq) * 64];
+#pragma unroll
+          for (int u = 0; u < 4; u++) dqacc[cb][4 * gq + u] += x[u];
+        }
+    }
+  }
+  uint16_t* Os = PARTS > 1 ? ring + NS * TILE : ring;  // [RW * 32][D] staging with the tile swizzle
+  static_assert(NS * KT >= RW * 32, "dQ staging aliases the K ring, or the V ring");
+  if (part == 0)
 #pragma unroll
   for (int cb = 0; cb < CB; cb++)
 #pragma unroll
@@ -424,11 +456,11 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
       bf16x4 o4;
 #pragma unroll
       for (int u = 0; u < 4; u++) o4[u] = (__bf16)(dqacc[cb][4 * gq + u] * scale);
-      *reinterpret_cast<bf16x4*>(&Os[TL::off(32 * w + n, 4 * cb + gq) + 4 * hh]) = o4;
+      *reinterpret_cast<bf16x4*>(&Os[TL::off(32 * wr + n, 4 * cb + gq) + 4 * hh]) = o4;
     }
   lds_barrier();
 #pragma unroll
-  for (int it = 0; it < NW * 32 * CPR / NT; it++) {
+  for (int it = 0; it < RW * 32 * CPR / NT; it++) {
     const int c = tid + NT * it, r = c / CPR, col = c % CPR;
     if (row0 + r < row1)
       *reinterpret_cast<uint4*>(p.dQ + ((size_t)(row0 + r) * p.H_q + h) * D + 8 * col) =
@@ -1066,14 +1098,14 @@ int launch_bwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
   // dq_kernel: half blocks at 64 channels (three per compute unit), at 256 (four waves with the whole register file each)
   // and, at 128, where every one of them finds a compute unit of its own (us, whole / half blocks: 300 tokens x 2 heads
   // 19.5 / 16.5, 1024 x 32 45 / 38, 4096 x 4 57 / 47; with more of them than compute units 5 x 800 x 8 36 / 45).
-  const bool halves = s.d != 128 || 2 * most_blocks(s) <= CUS;
+  const bool few = 2 * most_blocks(s) <= CUS, halves = s.d != 128 || few;
   const unsigned gq = halves ? xcd_grid(s.H_q, 2l * L.nblk_cap) : xcd_grid(s.H_q, L.nblk_cap);
   a.grid_dq = gq;
   const unsigned gclean = xcd_grid(s.H_q, (long)((L.nblk_cap + a.seg - 1) / a.seg) * (L.kpad / SG));
   const unsigned gpart = xcd_grid(s.H_q, (long)((L.nblk_cap + a.seg_part - 1) / a.seg_part) * (MAXPART / SG));
   prof_begin(DMA_STAGE_BWD_DQ, st);
   if (s.d == 256) dq_kernel<256, 4, 1><<<gq, 256, 0, st>>>(a);
-  else if (s.d == 128 && halves) dq_kernel<128, 4, 2><<<gq, 256, 0, st>>>(a);
+  else if (s.d == 128 && few) dq_kernel<128, 8, 1, 2><<<gq, 512, 0, st>>>(a);
   else if (s.d == 128) dq_kernel<128, 8, 2><<<gq, 512, 0, st>>>(a);
   else dq_kernel<64, 4, 2><<<gq, 256, 0, st>>>(a);
   prof_end(DMA_STAGE_BWD_DQ, st);

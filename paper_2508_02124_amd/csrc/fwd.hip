@@ -46,18 +46,22 @@ struct FwdArgs {
 // NW waves per workgroup: 8 (one 256-row block per workgroup) or 4 (half a block); UT 32-key units per tile.  Four waves
 // with tiles of 32 keys leave room for a second workgroup on the compute unit: the two waves of a SIMD then belong to
 // different workgroups and do not meet at the same barriers.
-template <int D, int NW, int UT>
-__global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D == 256) ? 1 : 2)) void fwd_kernel(FwdArgs p) {
+// PARTS: waves that share the same 32 rows.  Each takes its own units of every tile, with statistics of its own; at the
+// end the first one takes in the others' (all are the same softmax).  For calls of so few blocks that a wave would else
+// walk its keys alone on its SIMD, with nothing to fill the gaps between the products' results and their uses.
+template <int D, int NW, int UT, int PARTS = 1>
+__global__ __launch_bounds__(NW * 64, D == 64 && PARTS == 1 ? 4 : ((NW == 8 || UT == 2 || D == 256) ? 1 : 2)) void fwd_kernel(FwdArgs p) {
   using TL = TileLayout<D>;
   constexpr int KS = D / 16;          // contraction steps of K Q^T
   constexpr int CB = D / 32;          // 32-channel blocks of O^T
   constexpr int CPR = D / 8;          // 16-byte chunks per row
   constexpr int RPL = 64 / CPR;       // rows covered by one wave-wide 16-byte copy
-  constexpr int KT = 32 * UT;         // keys per tile
+  constexpr int KT = 32 * UT * PARTS; // keys per tile
   constexpr int WL = KT / RPL / NW;   // such copies per wave per K (or V) tile
   constexpr int NS = 4;               // ring stages
   constexpr int NT = NW * 64;         // threads
-  constexpr int HALVES = 8 / NW;      // workgroups per 256-row block
+  constexpr int RW = NW / PARTS;      // 32-row groups
+  constexpr int HALVES = 8 / RW;      // workgroups per 256-row block
   constexpr int TILE = KT * D;        // elements of one K or V tile
   __shared__ __align__(16) uint16_t ringK[NS * TILE];
   __shared__ __align__(16) uint16_t ringV[NS * TILE];
@@ -69,6 +73,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
   if (!xcd_map(wg_id(), p.H_q, p.nblk_cap * HALVES, h, item)) return;
   const int bi = p.nblk_cap - 1 - item / HALVES;  // long blocks first
   const int tid = thread_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, n = l & 31, hh = l >> 5;
+  const int wr = w % RW, part = w / RW;
   const int32_t* slot_row = p.slot_tab + ((size_t)h * p.nblk_cap + bi) * p.kpad;
   const int32_t* c_m1 = reinterpret_cast<const int32_t*>(p.consts + 264);
   // The key ids of the first tiles are requested with the block's table entry, as if all of these were slot columns: one
@@ -76,7 +81,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
   // tokens, window 1024: 1320 -> 1275 us.  (64 channels: two workgroups per compute unit hide that latency, and the
   // registers do not: 253 -> 275.)
   constexpr int FIRST = 5;
-  constexpr bool EARLY = D != 64;
+  constexpr bool EARLY = D != 64 || PARTS > 1;
   if (EARLY && w == 0) {
 #pragma unroll
     for (int tt = 0; tt < FIRST; tt++) {
@@ -92,7 +97,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
     return;
   }
   const int blk_row0 = info.y, row1 = info.z, doc0 = info.w;
-  const int row0 = blk_row0 + (item % HALVES) * (NW * 32);  // first row of this workgroup's part of the block
+  const int row0 = blk_row0 + (item % HALVES) * (RW * 32);  // first row of this workgroup's part of the block
   if (row0 >= row1) {
     wait_vmcnt<0>();
     return;
@@ -183,7 +188,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
     for (int tt = 0; tt < FIRST; tt++) issue_ids(tt);
   }
   // query fragments (B operand of K Q^T): lane holds row qi, channels 16*ks + 8*hh .. +8
-  const int qi = row0 + 32 * w + n;
+  const int qi = row0 + 32 * wr + n;
   bf16x8 qreg[KS];
   {
     // (EARLY: rows past the end repeat the last one: the same number of loads for every wave, and results that nothing stores)
@@ -196,9 +201,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
     }
   }
   // The pipelined loop's first step multiplies the (zero) weights before the first unit with the last unit of the ring
-  // stage before it: those rows have to hold numbers.
-  for (int c = tid; c < 32 * CPR; c += NT)
-    reinterpret_cast<uint4*>(ringV + (shift + NS - 1) % NS * TILE + TILE - 32 * D)[c] = make_uint4(0, 0, 0, 0);
+  // stage before it (of their part): those rows have to hold numbers.
+  for (int c = tid; c < PARTS * 32 * CPR; c += NT)
+    reinterpret_cast<uint4*>(ringV + (shift + NS - 1) % NS * TILE + (c / (32 * CPR) * UT + UT - 1) * 32 * D)[c % (32 * CPR)] =
+        make_uint4(0, 0, 0, 0);
   if (EARLY) {
     wait_vmcnt<KS>();  // the ids; the loads of Q may still be on their way
   } else {
@@ -218,24 +224,25 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
   }
 
   // The lane's fragment addresses with the ring bases folded in: inside the (stage-unrolled) main
-  // loop every LDS read is one of these registers plus an immediate.
+  // loop every LDS read is one of these registers plus an immediate.  The part's first unit is folded in too.
+  const int unit0 = 32 * UT * part;
   FragOffsets<D> fo;
   fo.init(l);
   uint32_t kfrag[KS], vfrag[CB][2];
 #pragma unroll
   for (int ks = 0; ks < KS; ks++) {
-    kfrag[ks] = lds_addr(ringK) + 2 * fo.row(ks);
+    kfrag[ks] = lds_addr(ringK) + 2 * (fo.row(ks) + unit0 * D);
     settle(kfrag[ks]);
   }
 #pragma unroll
   for (int cb = 0; cb < CB; cb++)
 #pragma unroll
     for (int q = 0; q < 2; q++) {
-      vfrag[cb][q] = lds_addr(ringV) + 2 * fo.tr(cb, q);
+      vfrag[cb][q] = lds_addr(ringV) + 2 * (fo.tr(cb, q) + unit0 * D);
       settle(vfrag[cb][q]);
     }
-  uint32_t zlane = lds_addr(&z_ring[0][4 * hh]);
-  const uint32_t jlane = lds_addr(&ids_ring[0][4 * hh]), elane = lds_addr(&e_ring[0][4 * hh]);
+  uint32_t zlane = lds_addr(&z_ring[0][unit0 + 4 * hh]);
+  const uint32_t jlane = lds_addr(&ids_ring[0][unit0 + 4 * hh]), elane = lds_addr(&e_ring[0][unit0 + 4 * hh]);
   settle(zlane);
   f32x16 oacc[CB];
 #pragma unroll
@@ -319,17 +326,17 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
   f32x16 sc = start_scores(4 * 64 * shift);
   scores(sc, shift * (2 * TILE));
   // Partial tiles: a unit is active if some key of it is, on any of this wave's 32 rows.
-  const int rfirst = row0 + 32 * w;
+  const int rfirst = row0 + 32 * wr;
   auto active = [&](int tt, int st, int u) __attribute__((always_inline)) {  // unit u of tile tt, in ring stage st
-    const int jl = ids_ring[tt % (2 * NS)][32 * u + n], el = e_ring[st][32 * u + n];
+    const int jl = ids_ring[tt % (2 * NS)][unit0 + 32 * u + n], el = e_ring[st][unit0 + 32 * u + n];
     return (bool)__any((jl <= rfirst + 31) & (el > rfirst));  // (an empty entry has el = 0)
   };
   bool act0 = true, act1 = true;  // the unit before, this unit is active
   constexpr int NM = KS + 2 * CB;  // products of a step: KS of the next unit's scores, then 2 CB of the previous unit's output
   // (64 channels: four waves share a SIMD and overlap by themselves; their 128 registers do not hold fragments read
   // ahead, nor the masks of a pipelined partial step: there the order is the compiler's and partial units run one by one)
-  constexpr bool FIXED = D != 64;
-  constexpr int LEAD = D == 256 ? 6 : D == 128 ? 4 : 0;
+  constexpr bool FIXED = D != 64 || PARTS > 1;
+  constexpr int LEAD = D == 256 ? 6 : D == 128 ? 4 : FIXED ? 2 : 0;
   auto tile = [&](auto stc, auto maskedc) __attribute__((always_inline)) {
     constexpr int ST = decltype(stc)::value;  // (t + shift) % NS
     constexpr bool MASKED = decltype(maskedc)::value;
@@ -495,9 +502,42 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
   // coalesced rows, write LSE
   wait_vmcnt<0>();
   lds_barrier();
-  uint16_t* Os = ringK;  // [NW * 32][D] with the tile swizzle
-  static_assert(NS * KT >= NW * 32, "O staging aliases the K ring");
-  {
+  if constexpr (PARTS > 1) {
+    // (a part that kept nothing has l = 0, O = 0 and the lowest reference)
+    static_assert(PARTS == 2 && NS * TILE * 2 >= RW * D * 128 && RW <= NS, "the second part's O takes the K ring");
+    f32x4* o2 = reinterpret_cast<f32x4*>(ringK) + wr * (4 * CB * 64) + l;
+    float *m2 = &z_ring[wr][l], *l2 = reinterpret_cast<float*>(&e_ring[wr][l]);
+    if (part == 1) {
+#pragma unroll
+      for (int cb = 0; cb < CB; cb++)
+#pragma unroll
+        for (int gq = 0; gq < 4; gq++) {
+          f32x4 x;
+#pragma unroll
+          for (int u = 0; u < 4; u++) x[u] = oacc[cb][4 * gq + u];
+          o2[(4 * cb + gq) * 64] = x;
+        }
+      *m2 = m_run;
+      *l2 = lsum;
+    }
+    lds_barrier();
+    if (part == 0) {
+      const float mo = *m2, m = fmaxf(m_run, mo), f0 = fast_exp2(m_run - m), f1 = fast_exp2(mo - m);
+      m_run = m;
+      lsum = lsum * f0 + *l2 * f1;
+#pragma unroll
+      for (int cb = 0; cb < CB; cb++)
+#pragma unroll
+        for (int gq = 0; gq < 4; gq++) {
+          const f32x4 x = o2[(4 * cb + gq) * 64];
+#pragma unroll
+          for (int u = 0; u < 4; u++) oacc[cb][4 * gq + u] = oacc[cb][4 * gq + u] * f0 + x[u] * f1;
+        }
+    }
+  }
+  uint16_t* Os = PARTS > 1 ? ringV : ringK;  // [RW * 32][D] with the tile swizzle
+  static_assert(NS * KT >= RW * 32, "O staging aliases a ring");
+  if (part == 0) {
     const float ltot = half_swap_sum(lsum);
     const float inv = 1.f / ltot;
     if (hh == 0 && qi < row1) p.LSE[(size_t)h * p.T + qi] = (m_run + __builtin_amdgcn_logf(ltot)) * LN2;
@@ -508,12 +548,12 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : ((NW == 8 || UT == 2 || D ==
         bf16x4 o4;
 #pragma unroll
         for (int u = 0; u < 4; u++) o4[u] = (__bf16)(oacc[cb][4 * gq + u] * inv);
-        *reinterpret_cast<bf16x4*>(&Os[TL::off(32 * w + n, 4 * cb + gq) + 4 * hh]) = o4;
+        *reinterpret_cast<bf16x4*>(&Os[TL::off(32 * wr + n, 4 * cb + gq) + 4 * hh]) = o4;
       }
   }
   lds_barrier();
 #pragma unroll
-  for (int it = 0; it < NW * 32 * CPR / NT; it++) {
+  for (int it = 0; it < RW * 32 * CPR / NT; it++) {
     const int c = tid + NT * it, r = c / CPR, col = c % CPR;
     if (row0 + r < row1)
       *reinterpret_cast<uint4*>(p.O + ((size_t)(row0 + r) * p.H_q + h) * D + 8 * col) =
@@ -537,9 +577,12 @@ int launch_fwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
   a.consts = p.plan + L.off_consts;
   a.T = s.T; a.H_q = s.H_q; a.H_kv = s.H_kv; a.k = s.k; a.nblk_cap = L.nblk_cap; a.kpad = L.kpad;
   prof_begin(DMA_STAGE_FWD, st);
-  // 128 channels: whole blocks of eight waves, unless they would leave the chip idle.  One half block of four waves per
-  // compute unit, with tiles of 64 keys, where all half blocks fit the chip at once (us, whole / half blocks: 1024 tokens
-  // x 32 heads 34.7 / 30.6, 2048 x 16 48.6 / 42.3; twice as many items 53 / 68).  Otherwise half blocks with tiles of 32
+  // 64 and 128 channels, all half blocks fit the chip at once: half blocks of eight waves, two of them for the same rows
+  // (the call alone, us; whole blocks at 64 channels / this: 256 tokens x 2 heads 10.8 / 8.8, 1000 x 16 27.4 / 18.8,
+  // 2048 x 16 27.9 / 20.3, 2 x 1500 x 16, too many, 29.0 / 31.0; half blocks of four waves at 128 channels / this: 512 x 32
+  // 19.3 / 17.7, 1019 x 32 29.3 / 26.1, 2048 x 16 of window 1024 40.8 / 33.9, 16000 x 2 41.2 / 35.5; too many: 5 x 800 x 8
+  // of window 256 28.3 / 31.7, 1300 x 32 37.3 / 35.6).
+  // 128 channels otherwise: whole blocks of eight waves, unless they would leave the chip idle: half blocks with tiles of 32
   // keys, two per compute unit, where whole blocks would keep less than 4/5 of it busy: the last round of blocks is not
   // full, or, in a single round, documents are not much longer than the window, so that blocks differ in length
   // (2048 x 32 53.6 / 51.7, 7 documents in 10007 x 8 window 333 49.4 / 46.9; above the line 8192 x 8 53.2 / 57.7,
@@ -547,11 +590,13 @@ int launch_fwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
   const double blocks = typical_blocks(s), rounds = std::ceil(blocks / CUS);
   const double len = (double)s.T / s.n_docs, window = s.k < len ? s.k : len;
   const double busy = blocks / (CUS * rounds) * (1. - window / (2. * len) / rounds);
+  const bool few = 2 * most_blocks(s) <= CUS;
   // 256 channels: half blocks of four waves, one per SIMD with the whole register file (the output
   // accumulators alone are 128 registers per wave).
   if (s.d == 256) fwd_kernel<256, 4, 1><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 256, 0, st>>>(a);
+  else if (s.d == 64 && few) fwd_kernel<64, 8, 1, 2><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 512, 0, st>>>(a);
   else if (s.d == 64) fwd_kernel<64, 8, 2><<<xcd_grid(s.H_q, L.nblk_cap), 512, 0, st>>>(a);
-  else if (2 * most_blocks(s) <= CUS) fwd_kernel<128, 4, 2><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 256, 0, st>>>(a);
+  else if (few) fwd_kernel<128, 8, 1, 2><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 512, 0, st>>>(a);
   else if (busy < 0.8) fwd_kernel<128, 4, 1><<<xcd_grid(s.H_q, 2l * L.nblk_cap), 256, 0, st>>>(a);
   else fwd_kernel<128, 8, 2><<<xcd_grid(s.H_q, L.nblk_cap), 512, 0, st>>>(a);
   prof_end(DMA_STAGE_FWD, st);
