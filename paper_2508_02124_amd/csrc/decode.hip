@@ -4,6 +4,7 @@
 // index ascending) (Eq. 4), and attends to them with the bias z (Eq. 5-6).  HBM-bound: z is read a
 // few times for the selection, then min(k, n) rows of K and V are gathered.
 #include "common.h"
+#include "select.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -13,14 +14,6 @@ namespace dma {
 struct float8 {
   float4 a, b;
 };
-
-__device__ __forceinline__ uint32_t desc_key_u32(float z) {
-  // ascending unsigned order == descending float order (-0 and +0 compare equal)
-  z = z + 0.0f;
-  uint32_t u = __float_as_uint(z);
-  u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-  return ~u;
-}
 
 // ---- selection of the kept set of one very long sequence, spread over nsl slices of every (sequence,
 // q-head) so that it uses the whole chip: four histogram launches (radix select of the kk-th best score, most
@@ -123,7 +116,7 @@ __global__ __launch_bounds__(256) void decode_hist_kernel(DecSel p, int pass) {
     for (int u = 0; u < 8; u++) zv[u] = j0 + u * 64 + l < s.j1 ? zh[j0 + u * 64 + l] : 0.f;
 #pragma unroll
     for (int u = 0; u < 8; u++) {
-      const uint32_t key = desc_key_u32(zv[u]);
+      const uint32_t key = desc_key(zv[u]);
       if (j0 + u * 64 + l < s.j1 && (pass == 3 || (key >> (sh + 8)) == prefix))
         atomicAdd(&hist[((key >> sh) & 255u) * 32 + (l & 31)], 1u);
     }
@@ -161,7 +154,7 @@ __global__ __launch_bounds__(256) void decode_count_kernel(DecSel p) {
 #pragma unroll
     for (int u = 0; u < 8; u++) {
       const bool in = j0 + u * 64 + l < s.j1;
-      const uint32_t key = desc_key_u32(zv[u]);
+      const uint32_t key = desc_key(zv[u]);
       cb += (uint32_t)__popcll(__ballot(in && key < thr));
       ce += (uint32_t)__popcll(__ballot(in && key == thr));
     }
@@ -212,7 +205,7 @@ __global__ __launch_bounds__(256) void decode_write_kernel(DecSel p) {
 #pragma unroll
     for (int u = 0; u < 8; u++) {
       const int j = j0 + u * 64 + l;
-      const uint32_t key = desc_key_u32(zv[u]);
+      const uint32_t key = desc_key(zv[u]);
       const bool in = j < s.j1;
       const bool better = in && (s.kk == s.n || key < thr), equal = in && s.kk < s.n && key == thr;
       const unsigned long long bm = __ballot(better), em = __ballot(equal);
@@ -236,9 +229,14 @@ __global__ __launch_bounds__(256) void decode_write_kernel(DecSel p) {
 // 32 heads: one cache of 65536 keys 59 -> 45, 24 caches of 5461 keys on average 213 -> 154.  Past the registers
 // every pass reads the scores again, 0.11 us per 1000 keys: still issue, not the loads (32 of them in flight
 // instead of 8: 93 -> 89 us for 130000 keys).
+// Two workgroups share a compute unit where 64 registers hold what they need (R = 16: 79 without the bound, one workgroup,
+// and three rounds of 24 x 32 heads), and sums over a wave run in registers.  Whole call, us, 32 heads: 24 caches of 5461 keys
+// 128.2 -> 122.4, 24 of 1000 keys, window 500, 41.1 -> 36.1, 16 of 8192, window 4096, 145.7 -> 141.4; one of 65536 38.7 ->
+// 38.3.  (Workgroups of 256 or 512 threads: 30 for 24 of 1000 keys, but 8 of 8192 45 -> 52 / 48, and a sequence far
+// above the batch's average, which the host does not see, takes two to four times as long.)
 template <int R, bool SPLIT>
-__global__ __launch_bounds__(1024, 4) void decode_select_kernel(DecSel p) {
-  constexpr int NW = 16, REP = 4, BITS = 11, NDIG = 1 << BITS, CAND = 8192, RANK = 512, STEP = 4;
+__global__ __launch_bounds__(1024, R == 16 ? 8 : 4) void decode_select_kernel(DecSel p) {
+  constexpr int NT = 1024, NW = NT / 64, REP = 4, BITS = 11, NDIG = 1 << BITS, DPT = NDIG / NT, CAND = 8192, RANK = 512, STEP = 4;
   constexpr uint32_t NONE = 0xffffffffu;  // behind every key
   const int bh = blockIdx.x, b = bh / p.H_q, h = bh % p.H_q;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
@@ -252,7 +250,7 @@ __global__ __launch_bounds__(1024, 4) void decode_select_kernel(DecSel p) {
   const int kk = p.k < n ? p.k : n, kcap = p.k < p.T ? p.k : p.T;
   int32_t* list = p.kept + (size_t)bh * kcap;
   if (kk == n) {  // everything is kept
-    for (int j = tid; j < n; j += 1024) list[j] = a + j;
+    for (int j = tid; j < n; j += NT) list[j] = a + j;
     return;
   }
   __shared__ __align__(16) uint32_t hist[NDIG * REP];
@@ -263,7 +261,7 @@ __global__ __launch_bounds__(1024, 4) void decode_select_kernel(DecSel p) {
   const int wlen = (n + NW * 64 - 1) / (NW * 64) * 64;  // keys per wave
   const int jw = w * wlen, chunks = wlen / 64, own = min(wlen, n - jw);  // (own <= 0: a wave without keys)
   const bool in_regs = chunks <= R;  // (workgroup-uniform)
-  auto sort_key = [](float z) { return min(desc_key_u32(z), NONE - 1); };  // (never NONE, whatever z holds)
+  auto sort_key = [](float z) { return min(desc_key(z), NONE - 1); };  // (never NONE, whatever z holds)
   uint32_t key[R];
   // f(key, index) for every key of this wave, 64 consecutive ones at a time, ascending; lanes without a key
   // get NONE (in the first pass: another key of the sequence)
@@ -297,8 +295,8 @@ __global__ __launch_bounds__(1024, 4) void decode_select_kernel(DecSel p) {
     for (int u = 0; u < R; u++)
       if (u / STEP * STEP < chunks) key[u] = __float_as_uint(zh[jw + min(u * 64 + l, own - 1)]);
   }
-  hist4[2 * tid] = make_uint4(0, 0, 0, 0);
-  hist4[2 * tid + 1] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+  for (int i = 0; i < DPT; i++) hist4[NT * i + tid] = make_uint4(0, 0, 0, 0);
   if (tid == 0) st[3] = 0;
   if (in_regs) {
 #pragma unroll
@@ -319,11 +317,8 @@ __global__ __launch_bounds__(1024, 4) void decode_select_kernel(DecSel p) {
       kmax = max(kmax, k32 == NONE ? 0u : k32);
     });
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, off));
-    kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off));
-  }
+  kmin = last_lane(wave_scan(kmin, NONE, [](uint32_t x, uint32_t y) { return min(x, y); }));
+  kmax = last_lane(wave_scan(kmax, 0u, [](uint32_t x, uint32_t y) { return max(x, y); }));
   if (l == 0) {
     wsum[w][0] = kmin;
     wsum[w][1] = kmax;
@@ -340,26 +335,28 @@ __global__ __launch_bounds__(1024, 4) void decode_select_kernel(DecSel p) {
   // The digit at which the running count of the histogram reaches `remaining` (st[0..2]); leaves it cleared.
   auto pick = [&](uint32_t remaining) {
     __syncthreads();
-    const uint4 x = hist4[2 * tid], y = hist4[2 * tid + 1];  // this thread's two digits
-    hist4[2 * tid] = make_uint4(0, 0, 0, 0);
-    hist4[2 * tid + 1] = make_uint4(0, 0, 0, 0);
-    const uint32_t cx = x.x + x.y + x.z + x.w, cy = y.x + y.y + y.z + y.w;
-    uint32_t inc = cx + cy;
+    uint32_t c[DPT], sum = 0;  // this thread's digits
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t t = __shfl_up(inc, off);
-      if (l >= off) inc += t;
+    for (int i = 0; i < DPT; i++) {
+      const uint4 x = hist4[DPT * tid + i];
+      hist4[DPT * tid + i] = make_uint4(0, 0, 0, 0);
+      c[i] = x.x + x.y + x.z + x.w;
+      sum += c[i];
     }
+    const uint32_t inc = wave_scan(sum, 0u, [](uint32_t x, uint32_t y) { return x + y; });
     if (l == 63) wsum[w][0] = inc;
     __syncthreads();
-    uint32_t run = inc - cx - cy;
+    uint32_t run = inc - sum;
 #pragma unroll
     for (int i = 0; i < NW; i++) run += i < w ? wsum[i][0] : 0u;
-    if (run < remaining && remaining <= run + cx + cy) {  // exactly one thread
-      const bool second = remaining > run + cx;
-      st[0] = 2u * tid + (second ? 1u : 0u);
-      st[1] = remaining - run - (second ? cx : 0u);
-      st[2] = second ? cy : cx;
+#pragma unroll
+    for (int i = 0; i < DPT; i++) {
+      if (run < remaining && remaining <= run + c[i]) {  // exactly one digit of one thread
+        st[0] = (uint32_t)(DPT * tid + i);
+        st[1] = remaining - run;
+        st[2] = c[i];
+      }
+      run += c[i];
     }
     __syncthreads();
   };
@@ -411,7 +408,7 @@ __global__ __launch_bounds__(1024, 4) void decode_select_kernel(DecSel p) {
           if ((x >> sh) == sub) atomicAdd(&hist[((x >> s2) & ((1u << bits) - 1u)) * REP + (l & (REP - 1))], 1u);
         };
         if (listed) {
-          for (uint32_t i = tid; i < ncand; i += 1024) count(cand[i]);
+          for (uint32_t i = tid; i < ncand; i += NT) count(cand[i]);
         } else {
           uint32_t from = base;
           asm volatile("" : "+v"(from));
@@ -513,7 +510,7 @@ __global__ __launch_bounds__(256) void decode_update_kernel(const float* __restr
     for (int j = 0; j < UPD_R; j++) zz[j] = ids[j] >= 0 ? zh[ids[j]] : 0.f;
 #pragma unroll
     for (int j = 0; j < UPD_R; j++) {
-      const unsigned long long c = ((unsigned long long)desc_key_u32(zz[j]) << 32) | (uint32_t)ids[j];
+      const unsigned long long c = ((unsigned long long)desc_key(zz[j]) << 32) | (uint32_t)ids[j];
       if (ids[j] >= 0 && (wpos < 0 || c > worst)) {
         worst = c;
         wpos = tid + 256 * j;
@@ -522,7 +519,7 @@ __global__ __launch_bounds__(256) void decode_update_kernel(const float* __restr
   } else {
     for (int i = tid; i < kprev; i += 256) {
       const int id = list[i];
-      const unsigned long long c = ((unsigned long long)desc_key_u32(zh[id]) << 32) | (uint32_t)id;
+      const unsigned long long c = ((unsigned long long)desc_key(zh[id]) << 32) | (uint32_t)id;
       if (wpos < 0 || c > worst) {
         worst = c;
         wpos = i;
@@ -550,7 +547,7 @@ __global__ __launch_bounds__(256) void decode_update_kernel(const float* __restr
       worst = sw[i];
       wpos = sp[i];
     }
-  const unsigned long long cn = ((unsigned long long)desc_key_u32(zh[jn]) << 32) | (uint32_t)jn;
+  const unsigned long long cn = ((unsigned long long)desc_key(zh[jn]) << 32) | (uint32_t)jn;
   if (cn > worst) return;  // the new key does not make it (workgroup-uniform)
   if (in_regs) {  // every entry was read before the barrier above: entries behind wpos move one place down
 #pragma unroll

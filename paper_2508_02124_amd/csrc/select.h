@@ -1,4 +1,4 @@
-// The selection of the causal plan, by blocks (select.hip).
+// The selection of the causal plan, by blocks (select.hip), and what the decode selection shares with it.
 #pragma once
 #include "common.h"
 
@@ -30,6 +30,20 @@ __device__ __forceinline__ uint32_t desc_key(float z) {
   u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
   return ~u;
 }
+// Wave-wide inclusive sum, minimum and maximum in registers (data-parallel moves: a lane shuffle through LDS takes ten times as
+// long).
+template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t dpp(uint32_t identity, uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)x, CTRL, ROWS, 0xf, false);
+}
+template <typename F> __device__ __forceinline__ uint32_t wave_scan(uint32_t x, uint32_t identity, F&& op) {
+  x = op(x, dpp<0x111, 0xf>(identity, x));  // row_shr:1, 2, 4, 8
+  x = op(x, dpp<0x112, 0xf>(identity, x));
+  x = op(x, dpp<0x114, 0xf>(identity, x));
+  x = op(x, dpp<0x118, 0xf>(identity, x));
+  x = op(x, dpp<0x142, 0xa>(identity, x));  // row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3
+  return op(x, dpp<0x143, 0xc>(identity, x));
+}
+__device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
 #endif
 
 // longest: upper bound on the documents' length (a wrong one changes no result)

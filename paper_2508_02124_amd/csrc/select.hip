@@ -103,23 +103,9 @@ template <int NT> struct SelShared {
   uint64_t found;
 };
 
-// Wave-wide inclusive sum, minimum and maximum in registers (data-parallel moves: a lane shuffle through LDS takes ten times as
-// long).
-template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t dpp(uint32_t identity, uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)x, CTRL, ROWS, 0xf, false);
-}
-template <typename F> __device__ __forceinline__ uint32_t wave_scan(uint32_t x, uint32_t identity, F&& op) {
-  x = op(x, dpp<0x111, 0xf>(identity, x));  // row_shr:1, 2, 4, 8
-  x = op(x, dpp<0x112, 0xf>(identity, x));
-  x = op(x, dpp<0x114, 0xf>(identity, x));
-  x = op(x, dpp<0x118, 0xf>(identity, x));
-  x = op(x, dpp<0x142, 0xa>(identity, x));  // row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3
-  return op(x, dpp<0x143, 0xc>(identity, x));
-}
 template <int LANE> __device__ __forceinline__ void write_lane(int& v, uint32_t x) {
   asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(x), "n"(LANE));
 }
-__device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
 
 // Exclusive prefix sums of a histogram, in place; seen(bin, count before it, count in it) for every bin.
 template <int NT, typename F>
