@@ -201,6 +201,17 @@ int dma_mask_bwd(const dma_shape* shape, const void* V, const float* W, const fl
                  float* dW, float* dA, void* dV, int accumulate, void* stream);
 
 /*
+ * dma_bwd and then dma_mask_bwd with accumulate: the backward of a whole step.  The arguments are theirs; the same
+ * results, but the two parts of dV are added before they are rounded.  Groups of 1, 2, 4 or 8 q-heads in bf16 save a pass
+ * over dV and two launches, other shapes take the two calls' launches.
+ */
+int dma_bwd_scores(const dma_shape* shape, const void* Q, const void* K, const void* V, const void* O,
+                   const void* dO, const float* LSE, const float* z, const int32_t* expiry,
+                   const void* mask, const int32_t* cu_seqlens, const float* W, const float* A,
+                   void* dQ, void* dK, void* dV, float* dz, float* dW, float* dA, void* ws, size_t ws_bytes,
+                   void* stream);
+
+/*
  * Content scores with the paper's full sampling tensor (Eq. 3 states Delta in R^{n_h x d_h x n_h};
  * Listing 1 flattens the values of all heads of a token before the projection): the score of q-head
  * h contracts the token's value vectors of ALL kv-heads,

@@ -71,6 +71,8 @@ def lib():
         L.dma_fwd.restype = i32
         L.dma_bwd.argtypes = [shp] + [vp] * 15 + [sz, vp]
         L.dma_bwd.restype = i32
+        L.dma_bwd_scores.argtypes = [shp] + [vp] * 19 + [sz, vp]
+        L.dma_bwd_scores.restype = i32
         L.dma_mask_bwd.argtypes = [shp] + [vp] * 7 + [i32, vp]
         L.dma_mask_bwd.restype = i32
         L.dma_scores_xhead.argtypes = [shp] + [vp] * 5
@@ -231,3 +233,10 @@ def dma_bwd(shape, Q, K, V, O, dO, LSE, z, expiry, mask, cu_seqlens, dQ, dK, dV,
     _check(lib().dma_bwd(ctypes.byref(shape), _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(z),
                          _ptr(expiry), _ptr(mask), _ptr(cu_seqlens), _ptr(dQ), _ptr(dK), _ptr(dV), _ptr(dz),
                          _ptr(ws), int(ws_bytes), _stream(stream)), "dma_bwd")
+
+
+def dma_bwd_scores(shape, Q, K, V, O, dO, LSE, z, expiry, mask, cu_seqlens, W, A, dQ, dK, dV, dz, dW, dA, ws, ws_bytes,
+                   stream=None):
+    _check(lib().dma_bwd_scores(ctypes.byref(shape), _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(z),
+                                _ptr(expiry), _ptr(mask), _ptr(cu_seqlens), _ptr(W), _ptr(A), _ptr(dQ), _ptr(dK), _ptr(dV),
+                                _ptr(dz), _ptr(dW), _ptr(dA), _ptr(ws), int(ws_bytes), _stream(stream)), "dma_bwd_scores")

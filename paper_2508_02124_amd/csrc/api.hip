@@ -143,10 +143,11 @@ int dma_fwd(const dma_shape* shape, const void* Q, const void* K, const void* V,
   return launch_fwd(p, Q, K, V, z, expiry, cu_seqlens, O, LSE, (hipStream_t)stream);
 }
 
-int dma_bwd(const dma_shape* shape, const void* Q, const void* K, const void* V, const void* O,
-            const void* dO, const float* LSE, const float* z, const int32_t* expiry,
-            const void* mask, const int32_t* cu_seqlens,
-            void* dQ, void* dK, void* dV, float* dz, void* ws, size_t ws_bytes, void* stream) {
+static int attention_bwd(const dma_shape* shape, const void* Q, const void* K, const void* V, const void* O,
+                         const void* dO, const float* LSE, const float* z, const int32_t* expiry,
+                         const void* mask, const int32_t* cu_seqlens,
+                         void* dQ, void* dK, void* dV, float* dz, const ScoreGrad* sg, void* ws, size_t ws_bytes,
+                         void* stream) {
   int rc = check_shape(shape, 256);
   if (rc != DMA_OK) return rc;
   if (!Q || !K || !V || !O || !dO || !LSE || !z || !expiry || !mask || !cu_seqlens || !dQ || !dK || !dV || !dz)
@@ -162,7 +163,32 @@ int dma_bwd(const dma_shape* shape, const void* Q, const void* K, const void* V,
     return launch_bwd_f32(p, (const float*)Q, (const float*)K, (const float*)V, (const float*)O, (const float*)dO, LSE,
                           z, expiry, cu_seqlens, (float*)dQ, (float*)dK, (float*)dV, dz, (char*)ws,
                           (hipStream_t)stream);
-  return launch_bwd(p, Q, K, V, O, dO, LSE, z, expiry, cu_seqlens, dQ, dK, dV, dz, (char*)ws, (hipStream_t)stream);
+  return launch_bwd(p, Q, K, V, O, dO, LSE, z, expiry, cu_seqlens, dQ, dK, dV, dz, sg, (char*)ws, (hipStream_t)stream);
+}
+
+int dma_bwd(const dma_shape* shape, const void* Q, const void* K, const void* V, const void* O,
+            const void* dO, const float* LSE, const float* z, const int32_t* expiry,
+            const void* mask, const int32_t* cu_seqlens,
+            void* dQ, void* dK, void* dV, float* dz, void* ws, size_t ws_bytes, void* stream) {
+  return attention_bwd(shape, Q, K, V, O, dO, LSE, z, expiry, mask, cu_seqlens, dQ, dK, dV, dz, nullptr, ws, ws_bytes,
+                       stream);
+}
+
+int dma_bwd_scores(const dma_shape* shape, const void* Q, const void* K, const void* V, const void* O,
+                   const void* dO, const float* LSE, const float* z, const int32_t* expiry,
+                   const void* mask, const int32_t* cu_seqlens, const float* W, const float* A,
+                   void* dQ, void* dK, void* dV, float* dz, float* dW, float* dA, void* ws, size_t ws_bytes,
+                   void* stream) {
+  int rc = check_shape(shape, 256);
+  if (rc != DMA_OK) return rc;
+  if (!W || !A || !dW || !dA || !aligned16(W) || !aligned16(dW)) return DMA_EINVAL;
+  if (!mask_bwd_fits(*shape)) return DMA_EUNSUPPORTED;
+  const bool one = kv_scores_fit(*shape);
+  const ScoreGrad sg = {W, A, dW, dA};
+  rc = attention_bwd(shape, Q, K, V, O, dO, LSE, z, expiry, mask, cu_seqlens, dQ, dK, dV, dz, one ? &sg : nullptr, ws,
+                     ws_bytes, stream);
+  if (rc != DMA_OK || one) return rc;
+  return launch_mask_bwd(*shape, V, W, A, dz, dW, dA, dV, 1, (hipStream_t)stream);
 }
 
 int dma_mask_bwd(const dma_shape* shape, const void* V, const float* W, const float* A, const float* dz,

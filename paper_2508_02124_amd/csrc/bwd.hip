@@ -42,6 +42,8 @@ struct BwdArgs {
   int seg_part;  // ... by one partial-mode work item
   size_t zero_n4;  // float4 elements from dK32 to the end of dV32 (cleared by dq_kernel)
   size_t dz_n;     // elements of dz (cleared by dq_kernel)
+  float *dW, *dA;  // gradients of the score parameters (cleared by dq_kernel), or no elements
+  int dW_n, dA_n;
   unsigned grid_dq;  // workgroups of the dq_kernel launch
   unsigned grid_clean;  // workgroups of the slot sweeps in the dkv_kernel launch (a multiple of 8)
 };
@@ -78,6 +80,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
     float4* acc4 = reinterpret_cast<float4*>(p.dK32);
     for (size_t i = gid; i < p.zero_n4; i += nth) acc4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     for (size_t i = gid; i < p.dz_n; i += nth) p.dz[i] = 0.f;
+    for (size_t i = gid; i < (size_t)p.dW_n; i += nth) p.dW[i] = 0.f;
+    for (size_t i = gid; i < (size_t)p.dA_n; i += nth) p.dA[i] = 0.f;
   }
   int h, item;
   if (!xcd_map(wg_id(), p.H_q, p.nblk_cap * HALVES, h, item)) return;
@@ -1053,7 +1057,7 @@ static unsigned grid_for(size_t n, size_t per_block) {
 
 int launch_bwd(const Ptrs& p, const void* Q, const void* K, const void* V, const void* O, const void* dO,
                const float* LSE, const float* z, const int32_t* expiry, const int32_t* cu, void* dQ, void* dK,
-               void* dV, float* dz, char* ws, hipStream_t st) {
+               void* dV, float* dz, const ScoreGrad* sg, char* ws, hipStream_t st) {
   (void)cu;
   (void)z;
   const dma_shape& s = p.s;
@@ -1093,6 +1097,8 @@ int launch_bwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
   const size_t nkv = (size_t)s.T * s.H_kv * s.d;
   a.zero_n4 = ((wl.off_dV - wl.off_dK) / 4 + nkv + 3) / 4;  // (the layout pads both buffers to 256 bytes)
   a.dz_n = (size_t)s.H_q * s.T;
+  a.dW = sg ? sg->dW : nullptr; a.dA = sg ? sg->dA : nullptr;
+  a.dW_n = sg ? s.H_q * s.d : 0; a.dA_n = sg ? s.H_q : 0;
   prof_begin(DMA_STAGE_BWD_ZERO, st);  // (an empty stage: dq_kernel clears the accumulators)
   prof_end(DMA_STAGE_BWD_ZERO, st);
   // dq_kernel: half blocks at 64 channels (three per compute unit), at 256 (four waves with the whole register file each)
@@ -1122,6 +1128,11 @@ int launch_bwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
   const double n = (double)s.T / s.n_docs, share = s.causal && n > s.k ? s.k / n * (1. + std::log(n / s.k)) : 1.;
   // (small calls are all latency: 2048 tokens x 2 heads 6.2 -> 8.1 us)
   const bool sparse = nkv >= 1u << 22 && 1. - std::pow(1. - share, s.H_q / s.H_kv) < 0.6;
+  if (sg) {
+    const int rc = launch_kv_scores(s, V, *sg, dz, dV, {a.dK32, a.dV32, expiry, (uint16_t*)dK}, sparse, st);
+    prof_end(DMA_STAGE_BWD_CVT, st);
+    return rc;
+  }
   const unsigned gcvt = sparse ? (unsigned)((nkv / 4 + CVT_N4 - 1) / CVT_N4) : grid_for(nkv / 4, 1024);
   const CvtArgs ca = {a.dK32, a.dV32, (uint16_t*)dK, (uint16_t*)dV, expiry, s.T, s.H_kv, s.H_q / s.H_kv, nkv / 4, gcvt};
 #define DMA_CVT(DD) (sparse ? cvt_bf16_kernel<DD, true> : cvt_bf16_kernel<DD, false>)<<<gcvt, 256, 0, st>>>(ca)

@@ -135,6 +135,16 @@ struct Ptrs {  // everything the kernels need, resolved by the host API
   float scale;
 };
 
+// The score parameters and their gradients, and the fp32 accumulators of the attention backward with their dK.
+struct ScoreGrad {
+  const float *W, *A;
+  float *dW, *dA;
+};
+struct KvAccum {
+  const float *dK32, *dV32;
+  const int32_t* expiry;
+  uint16_t* dK;
+};
 int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A, const int32_t* cu,
                     float* z, int32_t* expiry, int32_t* topk_idx, hipStream_t st);
 int launch_bias_add(const Ptrs& p, const float* bias, int bias_heads, int per_token, const int32_t* cu, hipStream_t st);
@@ -144,13 +154,19 @@ int launch_fwd(const Ptrs& p, const void* Q, const void* K, const void* V, const
                const int32_t* expiry, const int32_t* cu, void* O, float* LSE, hipStream_t st);
 int launch_bwd(const Ptrs& p, const void* Q, const void* K, const void* V, const void* O, const void* dO,
                const float* LSE, const float* z, const int32_t* expiry, const int32_t* cu,
-               void* dQ, void* dK, void* dV, float* dz, char* ws, hipStream_t st);
+               void* dQ, void* dK, void* dV, float* dz, const ScoreGrad* sg, char* ws, hipStream_t st);
 int launch_fwd_f32(const Ptrs& p, const float* Q, const float* K, const float* V, const float* z,
                    const int32_t* expiry, const int32_t* cu, float* O, float* LSE, hipStream_t st);
 int launch_bwd_f32(const Ptrs& p, const float* Q, const float* K, const float* V, const float* O,
                    const float* dO, const float* LSE, const float* z, const int32_t* expiry,
                    const int32_t* cu, float* dQ, float* dK, float* dV, float* dz, char* ws, hipStream_t st);
 
+// The gradient of the content scores with the conversion of the attention backward's accumulators, for shapes that fit.
+// dW and dA start at zero; sparse: rows that no head of their group ever keeps are not read.
+bool kv_scores_fit(const dma_shape& s);
+bool mask_bwd_fits(const dma_shape& s);
+int launch_kv_scores(const dma_shape& s, const void* V, const ScoreGrad& sg, const float* dz, void* dV, const KvAccum& acc,
+                     bool sparse, hipStream_t st);
 int launch_mask_bwd(const dma_shape& s, const void* V, const float* W, const float* A, const float* dz,
                     float* dW, float* dA, void* dV, int accumulate, hipStream_t st);
 

@@ -169,11 +169,20 @@ __global__ __launch_bounds__(256) void mask_bwd_kernel(const TV* __restrict__ V,
 // 111 -> 71; 16384 tokens, 16 / 4 heads, d = 256 100 -> 32; 8192 tokens, 16 / 4 heads, d = 128 25 -> 19.
 // Groups of 3, 5, 6, 7 and more than 8 q-heads keep the tile kernel (a lane's pairs would belong to several q-heads):
 // 16384 tokens, d = 128, 24 / 8 heads 51 us, 28 / 4 heads 67.
-template <int D, int G>
+//
+// FROM: what the rest of dV comes from.  BF16: dV itself, if accumulate.  F32, F32_KEPT: the attention backward's fp32
+// accumulators of dK and dV; dK is converted on the way and the sum of both parts of dV rounded once.  F32_KEPT does not
+// read a row that no head of the group ever keeps (its accumulators and dz are zero); its expiries are requested two
+// trips ahead.
+// HBM-bound.  Conversion, fill and this kernel as three launches / one, us: packed 65536 tokens x 16 heads of 64 channels 162 / 118
+// (63 % of the rows are not read), 16384 x 32 / 8 heads of 128 63 / 43 (235 MB: 5.4 TB/s), 2 x 4096 x 16 / 4 31 / 21,
+// 256 x 2 of 64 14 / 9.
+enum { BF16, F32, F32_KEPT };
+template <int D, int G, int FROM>
 __global__ __launch_bounds__(256) void mask_bwd_rows_kernel(const uint16_t* __restrict__ V, const float* __restrict__ W,
                                                             const float* __restrict__ A, const float* __restrict__ dz,
                                                             float* dW, float* dA, uint16_t* dV, int accumulate, int T,
-                                                            int H_kv, int rows_per_wg) {
+                                                            int H_kv, int rows_per_wg, KvAccum acc) {
   constexpr int LPR = D / 8, RPW = 64 / LPR, U = 2, STEP = 4 * RPW * U, NR = (U * G + LPR - 1) / LPR;
   static_assert(LPR % G == 0, "a lane's pairs belong to one q-head");
   const int g = blockIdx.y, tid = threadIdx.x, w = tid >> 6, l = tid & 63, sub = l % LPR, rg = l / LPR;
@@ -193,13 +202,54 @@ __global__ __launch_bounds__(256) void mask_bwd_rows_kernel(const uint16_t* __re
   const float* dzh = dz + (size_t)(g * G + hi) * T;
   auto row = [&](int t0, int u) { return t0 + (w * U + u) * RPW + rg; };
   auto offset = [&](int t) { return ((size_t)min(t, t_end - 1) * H_kv + g) * D + 8 * sub; };
+  constexpr int NF = FROM == BF16 ? 0 : 2;  // float4 of an accumulator row per lane
   uint4 vn[U], dn[U];
+  float4 kn[U][NF + 1], an[U][NF + 1];  // rows of the accumulators of dK and dV
   float zn[NR];
+  int en[NR];  // (F32_KEPT) expiries of the trip after the next
+  const int32_t* eh = acc.expiry + (size_t)(g * G + hi) * T;
+  auto request_expiry = [&](int t0) {
+#pragma unroll
+    for (int r = 0; r < NR; r++) {
+      const int pair = sub + r * LPR, t = row(t0, pair / G);
+      en[r] = pair < U * G && t < t_end ? eh[t] : 0;
+    }
+  };
   auto request = [&](int t0) {
+    bool kept[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) kept[u] = true;
+    if constexpr (FROM == F32_KEPT) {
+      uint32_t m[NR];  // the lane group's pairs whose head keeps the row
+#pragma unroll
+      for (int r = 0; r < NR; r++) {
+        const int pair = sub + r * LPR;
+        const uint64_t all = __ballot(pair < U * G && en[r] > row(t0, pair / G));
+        m[r] = (uint32_t)(all >> (rg * LPR)) & (uint32_t)((1ull << LPR) - 1ull);
+      }
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        uint32_t any = 0;
+#pragma unroll
+        for (int i = u * G; i < (u + 1) * G; i++) any |= m[i / LPR] >> (i % LPR) & 1u;
+        kept[u] = any != 0;
+      }
+      request_expiry(t0 + STEP);
+    }
 #pragma unroll
     for (int u = 0; u < U; u++) {
-      vn[u] = *reinterpret_cast<const uint4*>(V + offset(row(t0, u)));
-      dn[u] = accumulate ? *reinterpret_cast<const uint4*>(dV + offset(row(t0, u))) : make_uint4(0, 0, 0, 0);
+      const size_t at = offset(row(t0, u));
+      vn[u] = dn[u] = make_uint4(0, 0, 0, 0);
+      if (kept[u]) vn[u] = *reinterpret_cast<const uint4*>(V + at);
+      if (FROM == BF16 && accumulate) dn[u] = *reinterpret_cast<const uint4*>(dV + at);
+#pragma unroll
+      for (int i = 0; i < NF; i++) {
+        kn[u][i] = an[u][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (kept[u]) {
+          kn[u][i] = *reinterpret_cast<const float4*>(acc.dK32 + at + 4 * i);
+          an[u][i] = *reinterpret_cast<const float4*>(acc.dV32 + at + 4 * i);
+        }
+      }
     }
 #pragma unroll
     for (int r = 0; r < NR; r++) {
@@ -215,14 +265,26 @@ __global__ __launch_bounds__(256) void mask_bwd_rows_kernel(const uint16_t* __re
       o[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
     }
   };
+  if constexpr (FROM == F32_KEPT) request_expiry(t_begin);
   request(t_begin);
   for (int t0 = t_begin; t0 < t_end; t0 += STEP) {
     uint4 vc[U], dc[U];
+    float4 ac[U][NF + 1];
     float zc[NR], x[U][G], dx[NR];
 #pragma unroll
     for (int u = 0; u < U; u++) {
       vc[u] = vn[u];
       dc[u] = dn[u];
+      if constexpr (NF > 0) {
+        bf16x8 o;
+#pragma unroll
+        for (int i = 0; i < NF; i++) {
+          ac[u][i] = an[u][i];
+          const float4 x = kn[u][i];
+          o[4 * i] = (__bf16)x.x; o[4 * i + 1] = (__bf16)x.y; o[4 * i + 2] = (__bf16)x.z; o[4 * i + 3] = (__bf16)x.w;
+        }
+        if (row(t0, u) < t_end) *reinterpret_cast<uint4*>(acc.dK + offset(row(t0, u))) = __builtin_bit_cast(uint4, o);
+      }
     }
 #pragma unroll
     for (int r = 0; r < NR; r++) zc[r] = zn[r];
@@ -259,7 +321,14 @@ __global__ __launch_bounds__(256) void mask_bwd_rows_kernel(const uint16_t* __re
     for (int u = 0; u < U; u++) {
       float v[8], dv[8], old[8];
       unpack(vc[u], v);
-      unpack(dc[u], old);
+      if constexpr (FROM == BF16) {
+        unpack(dc[u], old);
+      } else {
+#pragma unroll
+        for (int i = 0; i < NF; i++) {
+          old[4 * i] = ac[u][i].x; old[4 * i + 1] = ac[u][i].y; old[4 * i + 2] = ac[u][i].z; old[4 * i + 3] = ac[u][i].w;
+        }
+      }
 #pragma unroll
       for (int e = 0; e < 8; e++) dv[e] = 0.f;
 #pragma unroll
@@ -308,14 +377,53 @@ __global__ void fill_zero_kernel(float* a, size_t na, float* b, size_t nb) {
 }
 
 // dynamic LDS of one workgroup; beyond 64 KiB (very many q-heads per kv-head) the shape is refused
-size_t mask_bwd_lds_bytes(const dma_shape& s) {
+static size_t mask_bwd_lds_bytes(const dma_shape& s) {
   const size_t G = (size_t)(s.H_q / s.H_kv), TT = s.d == 256 ? 32 : 64;
   return (TT * s.d + 2 * G * s.d + 2 * G * TT + G) * sizeof(float);
+}
+bool mask_bwd_fits(const dma_shape& s) { return mask_bwd_lds_bytes(s) <= 64 * 1024; }
+
+template <int FROM>
+static void launch_rows(const dma_shape& s, const void* V, const float* W, const float* A, const float* dz, float* dW,
+                        float* dA, void* dV, int accumulate, const KvAccum& acc, hipStream_t st) {
+  const int G = s.H_q / s.H_kv;
+  const int step = 4 * (64 / (s.d / 8)) * 2;  // rows of one trip of a workgroup
+  // Two workgroups per compute unit: every one ends with contended atomics on dW (1024 instead of 512: 29 us instead of
+  // 19 at 8192 tokens x 4 kv-heads), and with rows in flight ahead two are enough.  Up to 512 rows each: beyond
+  // that the atomics are few and shorter workgroups even out the end (65536 x 16: 84 us at 2048 rows, 71 at 512).
+  // Below 64 rows each the atomics weigh more than idle compute units: one workgroup per unit, half of one where a
+  // row is for at most two q-heads (us, 16 or 32 rows -> this: 16384 tokens, one head, d = 128 19.1 -> 13.7; 8192
+  // tokens, one head, d = 256 19.1 -> 12.7; 4096 tokens, 16 / 4 heads, d = 128 16.9 -> 14.5).
+  const long all_rows = (long)s.T * s.H_kv, wgs = G <= 2 ? 128 : 256;
+  long rows = std::max(std::min((all_rows + 511) / 512, 512l), std::min((all_rows + wgs - 1) / wgs, 64l));
+  rows = (rows + step - 1) / step * step;
+  const dim3 rgrid((unsigned)((s.T + rows - 1) / rows), s.H_kv);
+#define DMA_MR(DD, GG) \
+  mask_bwd_rows_kernel<DD, GG, FROM><<<rgrid, 256, 0, st>>>((const uint16_t*)V, W, A, dz, dW, dA, (uint16_t*)dV, accumulate, s.T, s.H_kv, (int)rows, acc)
+#define DMA_MRG(DD) \
+  do { if (G == 1) DMA_MR(DD, 1); else if (G == 2) DMA_MR(DD, 2); else if (G == 4) DMA_MR(DD, 4); else DMA_MR(DD, 8); } while (0)
+  if (s.d == 256) DMA_MRG(256);
+  else if (s.d == 128) DMA_MRG(128);
+  else DMA_MRG(64);
+#undef DMA_MRG
+#undef DMA_MR
+}
+
+bool kv_scores_fit(const dma_shape& s) {
+  const int G = s.H_q / s.H_kv;
+  return s.dtype == DMA_BF16 && (G == 1 || G == 2 || G == 4 || G == 8);
+}
+
+int launch_kv_scores(const dma_shape& s, const void* V, const ScoreGrad& sg, const float* dz, void* dV, const KvAccum& acc,
+                     bool sparse, hipStream_t st) {
+  if (sparse) launch_rows<F32_KEPT>(s, V, sg.W, sg.A, dz, sg.dW, sg.dA, dV, 1, acc, st);
+  else launch_rows<F32>(s, V, sg.W, sg.A, dz, sg.dW, sg.dA, dV, 1, acc, st);
+  return hipGetLastError() == hipSuccess ? DMA_OK : DMA_EHIP;
 }
 
 int launch_mask_bwd(const dma_shape& s, const void* V, const float* W, const float* A, const float* dz,
                     float* dW, float* dA, void* dV, int accumulate, hipStream_t st) {
-  if (mask_bwd_lds_bytes(s) > 64 * 1024) return DMA_EUNSUPPORTED;  // (before the first launch)
+  if (!mask_bwd_fits(s)) return DMA_EUNSUPPORTED;  // (before the first launch)
   const size_t nw = (size_t)s.H_q * s.d;
   fill_zero_kernel<<<(unsigned)((nw + 255) / 256), 256, 0, st>>>(dW, nw, dA, (size_t)s.H_q);
   const int G = s.H_q / s.H_kv;
@@ -323,27 +431,8 @@ int launch_mask_bwd(const dma_shape& s, const void* V, const float* W, const flo
   // and these are short (us at 64 channels, rows / tile kernel: 256 tokens, 2 / 1 heads 10.5 / 7.2; 8192 tokens, 16 / 4
   // heads 17.8 / 16.1; 16384 tokens, 16 / 4 heads 20.1 / 24.8).
   const bool few_rows = s.d == 64 && G > 1 && (long)s.T * s.H_kv <= 32768;
-  if (s.dtype == DMA_BF16 && !few_rows && (G == 1 || G == 2 || G == 4 || G == 8)) {
-    const int step = 4 * (64 / (s.d / 8)) * 2;  // rows of one trip of a workgroup
-    // Two workgroups per compute unit: every one ends with contended atomics on dW (1024 instead of 512: 29 us instead of
-    // 19 at 8192 tokens x 4 kv-heads), and with rows in flight ahead two are enough.  Up to 512 rows each: beyond
-    // that the atomics are few and shorter workgroups even out the end (65536 x 16: 84 us at 2048 rows, 71 at 512).
-    // Below 64 rows each the atomics weigh more than idle compute units: one workgroup per unit, half of one where a
-    // row is for at most two q-heads (us, 16 or 32 rows -> this: 16384 tokens, one head, d = 128 19.1 -> 13.7; 8192
-    // tokens, one head, d = 256 19.1 -> 12.7; 4096 tokens, 16 / 4 heads, d = 128 16.9 -> 14.5).
-    const long all_rows = (long)s.T * s.H_kv, wgs = G <= 2 ? 128 : 256;
-    long rows = std::max(std::min((all_rows + 511) / 512, 512l), std::min((all_rows + wgs - 1) / wgs, 64l));
-    rows = (rows + step - 1) / step * step;
-    const dim3 rgrid((unsigned)((s.T + rows - 1) / rows), s.H_kv);
-#define DMA_MR(DD, GG) \
-  mask_bwd_rows_kernel<DD, GG><<<rgrid, 256, 0, st>>>((const uint16_t*)V, W, A, dz, dW, dA, (uint16_t*)dV, accumulate, s.T, s.H_kv, (int)rows)
-#define DMA_MRG(DD) \
-  do { if (G == 1) DMA_MR(DD, 1); else if (G == 2) DMA_MR(DD, 2); else if (G == 4) DMA_MR(DD, 4); else DMA_MR(DD, 8); } while (0)
-    if (s.d == 256) DMA_MRG(256);
-    else if (s.d == 128) DMA_MRG(128);
-    else DMA_MRG(64);
-#undef DMA_MRG
-#undef DMA_MR
+  if (kv_scores_fit(s) && !few_rows) {
+    launch_rows<BF16>(s, V, W, A, dz, dW, dA, dV, accumulate, KvAccum{}, st);
     return hipGetLastError() == hipSuccess ? DMA_OK : DMA_EHIP;
   }
   const int TT = s.d == 256 ? 32 : 64;  // tokens per tile

@@ -1,7 +1,7 @@
 """torch.autograd glue over the C-ABI library: a differentiable function and a drop-in module.
 
 Nothing here computes: tensors are allocated with torch, their addresses are handed to
-dma_mask_gen / dma_fwd / dma_bwd / dma_mask_bwd, and the results are returned to autograd.
+dma_mask_gen / dma_fwd / dma_bwd_scores, and the results are returned to autograd.
 The paper names this integration as its own future work (Section 7); the operations are
 those of Section 4: Eq. 3-6 forward, Eq. 7-10 backward, and the chain rule of Eq. 3 that
 carries the bias gradient on to the score parameters (Section 6).
@@ -93,9 +93,13 @@ class DynamicMaskAttentionFunction(torch.autograd.Function):
         dQ, dK, dV = torch.empty_like(Q), torch.empty_like(K), torch.empty_like(V)
         dz = torch.empty_like(z)
         dW, dA = torch.empty_like(W), torch.empty_like(A)
-        B.dma_bwd(shape, Q, K, V, O, dO, LSE, z, expiry, mask, cu_seqlens, dQ, dK, dV, dz, ctx.ws, ctx.ws_bytes)
         # dz -> dW, dA, and the part of dV that flows through the content scores, added in place
-        (B.dma_scores_xhead_bwd if ctx.xhead else B.dma_mask_bwd)(shape, V, W, A, dz, dW, dA, dV, True)
+        if ctx.xhead:
+            B.dma_bwd(shape, Q, K, V, O, dO, LSE, z, expiry, mask, cu_seqlens, dQ, dK, dV, dz, ctx.ws, ctx.ws_bytes)
+            B.dma_scores_xhead_bwd(shape, V, W, A, dz, dW, dA, dV, True)
+        else:
+            B.dma_bwd_scores(shape, Q, K, V, O, dO, LSE, z, expiry, mask, cu_seqlens, W, A, dQ, dK, dV, dz, dW, dA,
+                             ctx.ws, ctx.ws_bytes)
         dbias = None
         if ctx.bias_form is not None:   # the bias enters the score like z: its gradient is dz, reduced over what shares it
             bias_heads, bias_per_token, bshape = ctx.bias_form
