@@ -353,6 +353,51 @@ __device__ __forceinline__ float half_swap_sum(float x) {
   return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
 }
 
+// Sum over each group of N = 8, 16 or 32 consecutive lanes, in every lane of it, and the value of lane I of each group:
+// data-parallel moves within rows of 16 lanes instead of shuffles through LDS.  The sum adds in the order of the exchange
+// with lane ^ N / 2, ^ N / 4, ... ^ 1, bit for bit: a rotation reaches the same value as the exchange once the row repeats
+// with the step's period.  Groups of which no lane is active may be among them.
+template <int CTRL> __device__ __forceinline__ float dpp_move(float x) {  // (every lane has a source)
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL, int BANKS> __device__ __forceinline__ float dpp_move(float old, float x) {  // some banks of four lanes
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old), __builtin_bit_cast(int, x), CTRL,
+                                                               0xf, BANKS, false));
+}
+__device__ __forceinline__ float row_swap_sum(float x) {  // x of lane l + x of lane l ^ 16
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+template <int N> __device__ __forceinline__ float group_sum(float x) {
+  static_assert(N == 8 || N == 16 || N == 32, "");
+  if constexpr (N == 32) x = row_swap_sum(x);
+  if constexpr (N >= 16) {
+    x += dpp_move<0x128>(x);  // row_ror:8, 4
+    x += dpp_move<0x124>(x);
+  } else {
+    x += dpp_move<0x114, 0xa>(dpp_move<0x104, 0x5>(x, x), x);  // row_shl:4 into lanes 0-3, 8-11; row_shr:4 into the others
+  }
+  x += dpp_move<0x4e>(x);  // quad_perm: lane ^ 2, lane ^ 1
+  x += dpp_move<0xb1>(x);
+  return x;
+}
+// Sum over the wave's groups, lane by lane: + lane ^ N, ^ 2 N, ... in that order.
+template <int N> __device__ __forceinline__ float sum_groups(float x) {
+  if constexpr (N == 8) x += dpp_move<0x128>(x);  // row_ror:8
+  if constexpr (N <= 16) x = row_swap_sum(x);
+  return half_swap_sum(x);
+}
+template <int N, int I> __device__ __forceinline__ float group_lane(float x) {
+  static_assert(N == 8 || N == 16 || N == 32, "");
+  const float y = dpp_move<0x150 + I % 16>(x);  // row_newbcast
+  if constexpr (N == 8) return dpp_move<0x150 + I + 8, 0xc>(y, x);
+  if constexpr (N == 32) {
+    const unsigned u = __builtin_bit_cast(unsigned, y);
+    return __builtin_bit_cast(float, (unsigned)__builtin_amdgcn_permlane16_swap(u, u, false, false)[I / 16]);
+  }
+  return y;
+}
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 

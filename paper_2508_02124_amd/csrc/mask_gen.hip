@@ -115,6 +115,9 @@ __global__ void fill_i32_kernel(int32_t* p, size_t n, int32_t v) {
 // (the attention kernels start their Q K^T accumulators at it).  A row is held by D / 8 lanes; the
 // loads of the tile's rows are all in flight before the first dot product, and a group of up to
 // GMAX q-heads keeps this lane's 8 weights of every head in registers.
+// Bound by instruction issue until the sums over a row's lanes left LDS and groups of one and two heads got kernels of their own
+// (they took that of four), now by its loads: 65536 tokens x 32 / 8 heads of 128 channels 47 -> 36 us (142 MB: 3.9 TB/s);
+// dma_mask_gen: packed 65536 x 16 of 64 channels 84 -> 76, of 128 138 -> 120, 20000 x 8 of 256 66 -> 47.
 template <typename TV, int D, int GMAX>
 __global__ __launch_bounds__(256) void z_kernel(const TV* __restrict__ V, const float* __restrict__ W,
                                                 const float* __restrict__ A, float* __restrict__ z,
@@ -171,8 +174,7 @@ __global__ __launch_bounds__(256) void z_kernel(const TV* __restrict__ V, const 
         float acc = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; e++) acc = fmaf(v[pass][e], wreg[hh][e], acc);
-#pragma unroll
-        for (int off = LPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+        acc = group_sum<LPR>(acc);
         if (sub == 0 && h0 + hh < G) zs[(h0 + hh) * 64 + r] = acc;
       }
     }
@@ -1013,9 +1015,13 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
 #define DMA_Z(TV, DD, GM) \
   z_kernel<TV, DD, GM><<<grid, 256, sh, st>>>((const TV*)V, W, A, z, zq, inv_scale, s.T, s.H_q, s.H_kv, blocks)
     if (s.dtype == DMA_BF16) {
-      if (s.d == 256) { if (G <= 4) DMA_Z(uint16_t, 256, 4); else DMA_Z(uint16_t, 256, 8); }
-      else if (s.d == 128) { if (G <= 4) DMA_Z(uint16_t, 128, 4); else DMA_Z(uint16_t, 128, 8); }
-      else { if (G <= 4) DMA_Z(uint16_t, 64, 4); else DMA_Z(uint16_t, 64, 8); }
+#define DMA_ZG(DD) \
+  do { if (G == 1) DMA_Z(uint16_t, DD, 1); else if (G == 2) DMA_Z(uint16_t, DD, 2); else if (G <= 4) DMA_Z(uint16_t, DD, 4); \
+       else DMA_Z(uint16_t, DD, 8); } while (0)
+      if (s.d == 256) DMA_ZG(256);
+      else if (s.d == 128) DMA_ZG(128);
+      else DMA_ZG(64);
+#undef DMA_ZG
     } else {
       if (s.d == 256) { if (G <= 4) DMA_Z(float, 256, 4); else DMA_Z(float, 256, 8); }
       else if (s.d == 128) { if (G <= 4) DMA_Z(float, 128, 4); else DMA_Z(float, 128, 8); }
