@@ -521,8 +521,8 @@ __global__ __launch_bounds__(256) void expiry_kernel(SortArgs p) {
 // ------------------------------------------------------------------ slots
 // parent[i] = the key evicted when key i entered (global index, -1 if none); slotid[i] = root of
 // i's eviction chain = its slot column (document-local, < k).
-// EVICTIONS: parent is given (-2: the row's own key never enters) and the expiries are made here; otherwise the other way
-// round.
+// EVICTIONS: parent is given (-2: the row's own key never enters) and the expiries of evicted keys are made here; otherwise
+// the other way round.
 template <bool EVICTIONS>
 __global__ __launch_bounds__(1024) void slot_kernel(const int32_t* __restrict__ cu, int32_t* expiry, int32_t* parent,
                                                     int32_t* slotid, int T, int k) {
@@ -536,8 +536,7 @@ __global__ __launch_bounds__(1024) void slot_kernel(const int32_t* __restrict__ 
   const int tid = threadIdx.x;
   if (n <= k) {
     for (int j = tid; j < n; j += 1024) {
-      if (EVICTIONS) ex[j] = b;
-      else par[j] = -1;
+      if (!EVICTIONS) par[j] = -1;
       sid[j] = j;
     }
     return;
@@ -558,14 +557,9 @@ __global__ __launch_bounds__(1024) void slot_kernel(const int32_t* __restrict__ 
           const int j = j0 + u * 1024;
           if (j < n) {
             link[j] = q[u] >= 0 ? q[u] - a : j;
-            ex[j] = q[u] == -2 ? a + j : b;
+            if (q[u] >= 0) ex[q[u] - a] = a + j;
           }
         }
-      }
-      __syncthreads();
-      for (int j = tid; j < n; j += 1024) {
-        const int q = link[j];
-        if (q != j) ex[q] = a + j;
       }
     } else {
       for (int j = tid; j < n; j += 1024) {
@@ -601,6 +595,62 @@ __global__ __launch_bounds__(1024) void slot_kernel(const int32_t* __restrict__ 
     for (int j = tid; j < n; j += 1024) sid[j] = ls[j];
   } else {
     links(sid);
+  }
+}
+
+// The same for long documents, whose one workgroup per head leaves the chip idle: pieces of SLOT_SEG rows follow their links
+// as far as they stay inside the piece, then every key takes the remaining hops, at most one per piece.  dma_mask_gen, us, one
+// workgroup and the whole scan of slot_rows_kernel -> pieces and checkpoints: 65536 tokens x 32 heads, window 1024 206 -> 168, window
+// 16384 404 -> 384, 50000 x 2 109 -> 79, 100000 x 8 246 -> 111, 20000 x 8 53 -> 43.
+constexpr int SLOT_SEG = 8192, SLOT_LONG = 2 * SLOT_SEG;
+__global__ __launch_bounds__(1024) void slot_pieces_kernel(const int32_t* __restrict__ cu, int n_docs,
+                                                           int32_t* __restrict__ expiry, const int32_t* __restrict__ parent,
+                                                           int32_t* __restrict__ slotid, int T, int k) {
+  __shared__ int link[SLOT_SEG];
+  const int tid = threadIdx.x, d = piece_doc<SLOT_SEG>(cu, n_docs, blockIdx.x);
+  const int a = cu[d], n = cu[d + 1] - a, s0 = SLOT_SEG * ((int)blockIdx.x - piece_slot<SLOT_SEG>(a, d, 0));
+  const int m = min(SLOT_SEG, n - s0);
+  if (m <= 0) return;
+  const size_t hb = (size_t)blockIdx.y * T + a;
+  constexpr int U = SLOT_SEG / 1024;
+  int q[U];
+#pragma unroll
+  for (int u = 0; u < U; u++) q[u] = parent[hb + s0 + min(tid + u * 1024, m - 1)];
+#pragma unroll
+  for (int u = 0; u < U; u++) {
+    const int j = tid + u * 1024;
+    if (j < m) {
+      link[j] = q[u] >= 0 ? q[u] - a : s0 + j;
+      if (q[u] >= 0) expiry[hb + (q[u] - a)] = a + s0 + j;
+    }
+  }
+  __syncthreads();
+  const int stop = max(k, s0);  // roots and earlier pieces
+  for (int r = 0; r < 14; r++) {  // (2^13 links at most)
+    int moved = 0;
+    for (int j = tid; j < m; j += 1024) {
+      const int x = link[j];
+      if (x >= stop && x != s0 + j) {
+        link[j] = link[x - s0];
+        moved = 1;
+      }
+    }
+    if (!__syncthreads_or(moved)) break;
+  }
+  for (int j = tid; j < m; j += 1024) slotid[hb + s0 + j] = link[j];
+}
+__global__ __launch_bounds__(256) void slot_hops_kernel(const int32_t* __restrict__ cu, int n_docs, int32_t* slotid, int T,
+                                                        int k) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  if (t >= T) return;
+  const int a = cu[find_doc(cu, n_docs, t)], j = t - a;
+  if (j < SLOT_SEG) return;
+  int32_t* sid = slotid + (size_t)blockIdx.y * T + a;
+  const int first = sid[j];
+  int q = first;
+  if (q != j) {
+    while (q >= k) q = sid[q];  // (an entry that another thread has advanced is an ancestor too)
+    if (q != first) sid[j] = q;
   }
 }
 
@@ -683,20 +733,28 @@ __device__ __forceinline__ void partial_lists(const int4* __restrict__ blk, cons
   }
 }
 
+// Checkpoints of the selection (select.h), for documents of more than `min` keys.
+struct CkArgs {
+  const int32_t *cu, *idx;
+  int min, k;
+};
+
 // The same table, row by row, in tiles of SLOT_TILE columns.  One workgroup per (chunk of
 // consecutive blocks, head, column tile) keeps in LDS, per slot, the latest key of the slot's chain, with its
 // expiry; a block's own keys are taken in and its row is then one coalesced pass (the key if it
 // outlives the block, -2 - key if it also entered inside it, else -1; nothing is left for a fill
 // launch).  The state at the chunk's first block comes from one scan of the document's
 // earlier keys (exactly one key per chain is still kept at a given row; every column tile repeats
-// the scan, so this kernel serves windows of up to SLOT_TILES_MAX tiles).  The scattered 4-byte
+// the scan, so this kernel serves windows of up to SLOT_TILES_MAX tiles), or, in a long document with checkpoints that hold
+// every key kept there, of the last one's list and the keys since.  The scattered 4-byte
 // stores of the kernel above cost a 64-byte write each; these rows are written whole.
 // The last layer of the grid makes the chunks' partial lists (a launch of its own took 4 to 9 us).
 constexpr int SLOT_TILE = 4096;
 constexpr int SLOT_TILES_MAX = 4;
 __global__ __launch_bounds__(512) void slot_rows_kernel(const int4* __restrict__ blk, const int32_t* __restrict__ expiry,
                                                         const int32_t* __restrict__ slotid, int32_t* slot_tab, int T,
-                                                        int nblk_cap, int kpad, int blocks_per_chunk, ListArgs lists) {
+                                                        int nblk_cap, int kpad, int blocks_per_chunk, ListArgs lists,
+                                                        CkArgs ck) {
   __shared__ unsigned long long cur[SLOT_TILE];  // (key + 1) << 32 | expiry; 0 = no key yet
   const int h = blockIdx.y, tid = threadIdx.x;
   const int b_begin = blockIdx.x * blocks_per_chunk, b_end = min(b_begin + blocks_per_chunk, nblk_cap);
@@ -727,7 +785,17 @@ __global__ __launch_bounds__(512) void slot_rows_kernel(const int4* __restrict__
       // keys in flight per thread: the scan is the latency of its loads (whole kernel, us, one at a time -> eight:
       // 16384 tokens, window 2048, 32 heads 29 -> 17; 65536 tokens 89 -> 43; with window 16384 221 -> 154)
       constexpr int U = 8;
-      for (int j0 = a + tid; j0 < lo; j0 += U * 512) {
+      int from = a;
+      const int n = ck.cu[doc + 1] - a;
+      if (n > ck.min && n > ck.k && ck.k <= CK_SEG && lo - a >= CK_SEG) {
+        from = a + ((lo - a) & ~(CK_SEG - 1));
+        const int32_t* list = ck.idx + (size_t)h * T + from - CK_SEG;
+        for (int i = tid; i < ck_keys(ck.k); i += 512) {
+          const int j = a + list[i], e = ex[j], c = sid[j] - c0;
+          if (e >= lo && c >= 0 && c < nc) cur[c] = ((unsigned long long)(unsigned)(j + 1) << 32) | (unsigned)e;
+        }
+      }
+      for (int j0 = from + tid; j0 < lo; j0 += U * 512) {
         int e[U], c[U];
 #pragma unroll
         for (int u = 0; u < U; u++) {
@@ -1052,6 +1120,7 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
   // Causal: evictions by blocks (select.hip), unless a document may be longer than SELECT_MAX.  The other plans sort.
   const int longest = s.max_seqlen > 0 && s.max_seqlen < s.T ? s.max_seqlen : s.T;
   const bool by_blocks = s.causal && longest <= SELECT_MAX;
+  const int ck_min = by_blocks && longest > CK_DOC ? CK_DOC : 0x7fffffff;
   SortArgs sa;
   sa.z = z; sa.cu = cu; sa.expiry = expiry;
   sa.sk0 = (uint32_t*)(base + L.off_sk0); sa.sk1 = (uint32_t*)(base + L.off_sk1);
@@ -1063,8 +1132,8 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
   sa.nseg_cap = L.nseg_cap; sa.seg = L.seg;
   prof_begin(DMA_STAGE_SORT, st);
   if (by_blocks) {
-    const SelectArgs a = {z, cu, blk, parent, (float*)(base + L.off_sk0), (int32_t*)(base + L.off_si0), s.T, s.n_docs,
-                          L.nblk_cap, s.k, longest > CK_DOC ? CK_DOC : 0x7fffffff};
+    const SelectArgs a = {z, cu, blk, parent, expiry, (float*)(base + L.off_sk0), (int32_t*)(base + L.off_si0), s.T, s.n_docs,
+                          L.nblk_cap, s.k, ck_min};
     launch_evictions(a, longest, s.H_q, st);
   } else if (L.seg == SEG_MIN) {
     sort_wavelet_kernel<SEG_MIN / 1024><<<dim3(L.nseg_cap, s.H_q), 1024, 0, st>>>(sa);
@@ -1093,8 +1162,13 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
     if (!by_blocks) expiry_kernel<false><<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(sa);
     prof_end(DMA_STAGE_EXPIRY, st);
     prof_begin(DMA_STAGE_PLAN, st);
-    (by_blocks ? slot_kernel<true> : slot_kernel<false>)<<<dim3(s.n_docs, s.H_q), 1024, 0, st>>>(cu, expiry, parent, slotid,
-                                                                                              s.T, s.k);
+    if (by_blocks && longest > SLOT_LONG) {
+      slot_pieces_kernel<<<dim3(s.T / SLOT_SEG + s.n_docs, s.H_q), 1024, 0, st>>>(cu, s.n_docs, expiry, parent, slotid, s.T, s.k);
+      slot_hops_kernel<<<dim3((s.T + 255) / 256, s.H_q), 256, 0, st>>>(cu, s.n_docs, slotid, s.T, s.k);
+    } else {
+      (by_blocks ? slot_kernel<true> : slot_kernel<false>)<<<dim3(s.n_docs, s.H_q), 1024, 0, st>>>(cu, expiry, parent, slotid,
+                                                                                                s.T, s.k);
+    }
     const int per = L.nblk_cap / 16 > 4 ? L.nblk_cap / 16 : 4;  // about 16 chunks per head
     int tiles = (L.kpad + SLOT_TILE - 1) / SLOT_TILE;
     if (tiles > SLOT_TILES_MAX) {
@@ -1105,7 +1179,7 @@ int launch_mask_gen(const Ptrs& p, const void* V, const float* W, const float* A
     }
     const ListArgs lists = {parent, pcnt, pent, plist};
     slot_rows_kernel<<<dim3((L.nblk_cap + per - 1) / per, s.H_q, tiles + 1), 512, 0, st>>>(blk, expiry, slotid, slot_tab, s.T,
-                                                                                         L.nblk_cap, L.kpad, per, lists);
+                                                                                         L.nblk_cap, L.kpad, per, lists, {cu, (const int32_t*)(base + L.off_si0), ck_min, s.k});
   }
   if (topk_idx) topk_idx_kernel<<<dim3(s.T, s.H_q), 64, 0, st>>>(cu, s.n_docs, s.causal, expiry, topk_idx, s.T, s.k);
   prof_end(DMA_STAGE_PLAN, st);

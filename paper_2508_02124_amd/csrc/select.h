@@ -16,6 +16,7 @@ struct SelectArgs {
   const int32_t* cu;
   const int4* blk;
   int32_t* parent;     // [H_q][T]: key evicted by each row; -1: none; -2: the row's own key never enters
+  int32_t* expiry;     // [H_q][T]: the document's end, or the row itself if its key never enters (the slot kernels set those of evicted keys)
   float* ck_z;         // [H_q][T]: checkpoints' scores
   int32_t* ck_idx;     // [H_q][T]: and indices in their document
   int T, n_docs, nblk_cap, k;
@@ -23,6 +24,21 @@ struct SelectArgs {
 };
 
 #ifdef __HIPCC__
+// Checkpoints of a document that starts at a: number p stands before its key c = CK_SEG (p + 1) and is stored at the place of
+// the CK_SEG keys before c.  It holds the weakest ck_keys(k) of the keys kept by row c - 1, in any order (k <= CK_SEG: all of
+// them, and up to three more).
+__device__ __forceinline__ int ck_keys(int k) { return k < CK_SEG ? (k + 3) & ~3 : CK_SEG; }
+// Place of piece p of document d among the pieces of SEG keys of all documents.
+template <int SEG> __device__ __forceinline__ int piece_slot(int a, int d, int p) { return a / SEG + d + p; }
+// The document of a place: the largest d with piece_slot(cu[d], d, 0) <= slot.
+template <int SEG> __device__ __forceinline__ int piece_doc(const int32_t* __restrict__ cu, int n_docs, int slot) {
+  int lo = 0, hi = n_docs;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (piece_slot<SEG>(cu[mid], mid, 0) <= slot) lo = mid; else hi = mid;
+  }
+  return lo;
+}
 // Ascending unsigned order of the result == descending float order of z (-0 and +0 compare equal).
 __device__ __forceinline__ uint32_t desc_key(float z) {
   z = z + 0.0f;

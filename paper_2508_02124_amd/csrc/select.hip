@@ -2,7 +2,7 @@
 //
 // While a document has more than k rows, every row admits at most one key and evicts the weakest resident, under
 // (score descending, index ascending).  evict_kernel writes parent[i] = the key that row i evicts (-1: none, -2: row i's
-// own key never enters); slot_kernel turns that into expiries.
+// own key never enters) and the expiries of keys that no row evicts; the slot kernels add the others.
 //
 // A block of BQ rows is worked out by itself, from the scores before it: at most BQ residents are evicted inside it, and
 // these are among the weakest of the residents at its first row.  A histogram of the scores before the block
@@ -226,11 +226,7 @@ __device__ __forceinline__ uint64_t exact_rank(SelShared<NT>& sm, uint32_t* hist
 }
 
 // ------------------------------------------------------------------ checkpoints
-__device__ __forceinline__ int ck_keys(int k) { return k < CK_SEG ? (k + 3) & ~3 : CK_SEG; }
-__device__ __forceinline__ int ck_slot(int a, int d, int p) { return a / CK_SEG + d + p; }
-
-// One workgroup per (checkpoint, head): document d's checkpoint p stands before its key c = CK_SEG (p + 1) and holds, in
-// any order, the weakest ck_keys(k) of the keys kept by row c - 1 (k < CK_SEG: all of them, and up to three more); it is stored at the place of the CK_SEG keys before c.
+// One workgroup per (checkpoint, head).
 // What bounds it: instruction issue over the N scores, three to four passes of loads of 16 bytes per lane: 65536 tokens x
 // 32 heads 44 us (window 16384: 58).
 constexpr int CK_NT = 1024, CK_NQ = 0;
@@ -238,17 +234,9 @@ __global__ __launch_bounds__(CK_NT, 8) void checkpoint_kernel(SelectArgs p) {
   __shared__ SelShared<CK_NT> sm;
   __shared__ __align__(16) uint32_t hist[BINS], exact_hist[BINS];
   const int slot = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
-  int d = 0;
-  {
-    int lo = 0, hi = p.n_docs;  // largest d with ck_slot(cu[d], d, 0) <= slot
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (ck_slot(p.cu[mid], mid, 0) <= slot) lo = mid; else hi = mid;
-    }
-    d = lo;
-  }
+  const int d = piece_doc<CK_SEG>(p.cu, p.n_docs, slot);
   const int a = p.cu[d], n = p.cu[d + 1] - a;
-  const int c = CK_SEG * (slot - ck_slot(a, d, 0) + 1);
+  const int c = CK_SEG * (slot - piece_slot<CK_SEG>(a, d, 0) + 1);
   if (n <= p.ck_min || n <= p.k || c >= n) return;
   Scores<CK_NT, CK_NQ> s;
   s.load(p.z, p.ck_idx, 0, p.z + (size_t)h * p.T + a, c, 0);
@@ -343,8 +331,15 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const int a = info.w, lo = info.y - a, nb = info.z - info.y, n = p.cu[info.x + 1] - a, k = p.k;
   int32_t* par = p.parent + (size_t)h * p.T + info.y;
+  int32_t* ex = p.expiry + (size_t)h * p.T + info.y;
+  auto store = [&](int evicted) __attribute__((always_inline)) {
+    if (tid < nb) {
+      par[tid] = evicted;
+      ex[tid] = evicted == -2 ? info.y + tid : a + n;
+    }
+  };
   if (n <= k || lo + nb <= k) {  // nothing is evicted here
-    if (tid < nb) par[tid] = -1;
+    store(-1);
     return;
   }
   const float* zd = p.z + (size_t)h * p.T + a;
@@ -403,7 +398,7 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
     enters = tid < nb && bn <= b1 && (cap > N || kn < kmax);
     const int e = __syncthreads_count(enters);
     if (e == 0) {
-      if (tid < nb) par[tid] = -2;
+      store(-2);
       return;
     }
     if (enters) atomicAdd(&new_hist[bn], 1u);
@@ -430,7 +425,7 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
     enters = tid < nb && (cap > N || kn < (kept < N ? (uint32_t)(to >> 32) : kmax));
     const int e = __syncthreads_count(enters);
     if (e == 0) {
-      if (tid < nb) par[tid] = -2;
+      store(-2);
       return;
     }
     strong = max(0, kept - min(e, lo + nb - k));
@@ -555,7 +550,7 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
     }
   }
   __syncthreads();
-  if (tid < nb) par[tid] = out[tid];
+  store(out[min(tid, BQ - 1)]);
 }
 
 int launch_evictions(const SelectArgs& a, int longest, int H_q, hipStream_t st) {
