@@ -163,7 +163,7 @@ int dma_bias_bwd(const dma_shape* shape, const float* dz, const int32_t* cu_seql
 /*
  * Forward (Eq. 5-6; online softmax as in Alg. 1, query-stationary).
  *   O   out [T, H_q, d]     LSE out [H_q, T], natural-log sum-exp of the kept scores.
- *   ws  scratch of at least dma_workspace_bytes(shape) (may be NULL if that is 0).
+ *   ws  not used (may be NULL, ws_bytes 0).
  */
 int dma_fwd(const dma_shape* shape, const void* Q, const void* K, const void* V, const float* z,
             const int32_t* expiry, const void* mask, const int32_t* cu_seqlens,

@@ -44,6 +44,11 @@ def _check_inputs(Q, K, V, W, A, cu_seqlens):
         raise TypeError("W, A must be float32 and cu_seqlens int32")
 
 
+def _row_bytes(H_q, T):
+    """Bytes of an [H_q, T] buffer of 32-bit values, to the next whole 256."""
+    return (H_q * T * 4 + 255) // 256 * 256
+
+
 class DynamicMaskAttentionFunction(torch.autograd.Function):
     """O = DMA(Q, K, V; W, A) on packed variable-length documents; differentiable in Q, K, V, W, A."""
 
@@ -64,13 +69,11 @@ class DynamicMaskAttentionFunction(torch.autograd.Function):
         shape = B.make_shape(T, cu_seqlens.numel() - 1, H_q, K.shape[1], d, k, causal=True,
                              dtype=_dtype_code(Q), softmax_scale=softmax_scale, max_seqlen=max_seqlen)
         dev = Q.device
-        z = torch.empty((H_q, T), dtype=torch.float32, device=dev)
-        expiry = torch.empty((H_q, T), dtype=torch.int32, device=dev)
-        mask = torch.empty(B.dma_mask_bytes(shape), dtype=torch.uint8, device=dev)
-        ws_bytes = B.dma_workspace_bytes(shape)
-        ws = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device=dev)
+        # z, expiry, LSE and the mask plan live in one allocation (a short call's time is the host's)
+        per_row = _row_bytes(H_q, T)
+        state = torch.empty(3 * per_row + B.dma_mask_bytes(shape), dtype=torch.uint8, device=dev)
+        z, expiry, LSE, mask = (state.data_ptr() + i * per_row for i in range(4))
         O = torch.empty_like(Q)
-        LSE = torch.empty((H_q, T), dtype=torch.float32, device=dev)
         xhead = K.shape[1] > 1 and W.shape[1] == K.shape[1] * d
         if xhead:
             B.dma_scores_xhead(shape, V, W, A, z)
@@ -79,31 +82,35 @@ class DynamicMaskAttentionFunction(torch.autograd.Function):
             B.dma_mask_gen(shape, V, Wm, Am, cu_seqlens, z, expiry, None, mask)
         else:
             B.dma_mask_gen_bias(shape, V, Wm, Am, cu_seqlens, bias, bias_heads, bias_per_token, z, expiry, None, mask)
-        B.dma_fwd(shape, Q, K, V, z, expiry, mask, cu_seqlens, O, LSE, ws, ws_bytes)
-        ctx.save_for_backward(Q, K, V, W, A, cu_seqlens, z, expiry, mask, O, LSE)
-        ctx.shape, ctx.ws, ctx.ws_bytes, ctx.xhead = shape, ws, ws_bytes, xhead
+        B.dma_fwd(shape, Q, K, V, z, expiry, mask, cu_seqlens, O, LSE, None, 0)
+        ctx.save_for_backward(Q, K, V, W, A, cu_seqlens, state, O)
+        ctx.shape, ctx.xhead = shape, xhead
         ctx.bias_form = None if bias is None else (bias_heads, bias_per_token, tuple(bias.shape))
         return O
 
     @staticmethod
     def backward(ctx, dO):
-        Q, K, V, W, A, cu_seqlens, z, expiry, mask, O, LSE = ctx.saved_tensors
+        Q, K, V, W, A, cu_seqlens, state, O = ctx.saved_tensors
         shape = ctx.shape
         dO = dO.contiguous()
+        per_row, ws_bytes = _row_bytes(Q.shape[1], Q.shape[0]), B.dma_workspace_bytes(shape)
+        z, expiry, LSE, mask = (state.data_ptr() + i * per_row for i in range(4))
         dQ, dK, dV = torch.empty_like(Q), torch.empty_like(K), torch.empty_like(V)
-        dz = torch.empty_like(z)
         dW, dA = torch.empty_like(W), torch.empty_like(A)
+        scratch = torch.empty(per_row + ws_bytes, dtype=torch.uint8, device=Q.device)   # dz, then the workspace
+        dz = scratch.data_ptr()
+        ws = dz + per_row
         # dz -> dW, dA, and the part of dV that flows through the content scores, added in place
         if ctx.xhead:
-            B.dma_bwd(shape, Q, K, V, O, dO, LSE, z, expiry, mask, cu_seqlens, dQ, dK, dV, dz, ctx.ws, ctx.ws_bytes)
+            B.dma_bwd(shape, Q, K, V, O, dO, LSE, z, expiry, mask, cu_seqlens, dQ, dK, dV, dz, ws, ws_bytes)
             B.dma_scores_xhead_bwd(shape, V, W, A, dz, dW, dA, dV, True)
         else:
             B.dma_bwd_scores(shape, Q, K, V, O, dO, LSE, z, expiry, mask, cu_seqlens, W, A, dQ, dK, dV, dz, dW, dA,
-                             ctx.ws, ctx.ws_bytes)
+                             ws, ws_bytes)
         dbias = None
         if ctx.bias_form is not None:   # the bias enters the score like z: its gradient is dz, reduced over what shares it
             bias_heads, bias_per_token, bshape = ctx.bias_form
-            dbias = torch.empty(bshape, dtype=torch.float32, device=dz.device)
+            dbias = torch.empty(bshape, dtype=torch.float32, device=Q.device)
             B.dma_bias_bwd(shape, dz, cu_seqlens, bias_heads, bias_per_token, dbias)
         return dQ, dK, dV, dW, dA, None, None, None, None, dbias
 
