@@ -292,13 +292,16 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
     start_dp();
     static_for<LEAD>([&](auto mc) __attribute__((always_inline)) { frag(mc, shift * (2 * TILE), 0); });
   }
-  // Partial tiles: a unit is active if some key of it is, on any of this wave's 32 rows.
+  // Partial tiles: a unit is active if some key of it is, on any of this wave's 32 rows, and full if every key is on all of
+  // them (nothing to mask).  Backward, us, scores that rise along the keys: packed 65536 x 16 heads of 64 channels 1558 ->
+  // 1545, 20 documents in 30000 x 16 of 128 1048 -> 1038; random scores 1026 -> 1024, 846 -> 843.
   const int rfirst = row0 + 32 * wr;
-  auto active = [&](int tt, int st, int u) __attribute__((always_inline)) {  // unit u of tile tt, in ring stage st
+  auto active = [&](int tt, int st, int u, bool& full) __attribute__((always_inline)) {  // unit u of tile tt, in ring stage st
     const int jl = ids_ring[tt % (2 * NS)][unit0 + 32 * u + n], el = e_ring[st][unit0 + 32 * u + n];
+    full = __all((jl <= rfirst) & (el > rfirst + 31));
     return (bool)__any((jl <= rfirst + 31) & (el > rfirst));  // (an empty entry has el = 0)
   };
-  bool act0 = true;  // this unit is active
+  bool act0 = true, full0 = false;  // this unit is active, is full
   auto tile = [&](auto stc, auto maskedc) __attribute__((always_inline)) {
     constexpr int ST = decltype(stc)::value;  // (t + shift) % NS
     constexpr bool MASKED = decltype(maskedc)::value;
@@ -313,6 +316,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
       constexpr int ss = u + 1 < UT ? ST : (ST + 1) % NS, su = u + 1 < UT ? u + 1 : 0;
       constexpr uint32_t ko = ss * (2 * TILE) + su * UB, vo = ST * (2 * TILE) + u * UB;
       int idv[WL];
+      bool masked = false;
       auto mask = [&]() __attribute__((always_inline)) {
         // pairs outside [j, e_j) get P = 0 and dS = 0 exactly
         const uint32_t js = jlane + 4 * ((t % (2 * NS)) * 64 + 32 * u);
@@ -327,9 +331,11 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
       if constexpr (MASKED) {
         // Skip the step of an inactive unit; the scores of the next one, if that is active, are all there is to do (a P of
         // zero must not meet an infinite value or key)
-        const bool act1 = PIPED ? active(u + 1 < UT ? t : t + 1, ss, su) : active(t, ST, u);
+        bool full = full0;
+        const bool act1 = PIPED ? active(u + 1 < UT ? t : t + 1, ss, su, full0) : active(t, ST, u, full);
         const bool run = PIPED ? act0 : act1;
         act0 = act1;
+        masked = !full;
         if (!run) {
           if constexpr (PIPED) {
             if (act1) {
@@ -345,7 +351,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
           }
           return;
         }
-        if constexpr (PIPED) mask();
+        if constexpr (PIPED)
+          if (masked) mask();
       }
       bf16x8 dsb[2];
       if constexpr (!PIPED) {
@@ -358,7 +365,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
           dpacc = mfma32(lds_load<bf16x8>(kfrag[ks] + (VOFF + vo)), doreg[ks], dpacc);
         }
         if constexpr (u == 0) copy_rows((ST + AHEAD) % NS, idv);
-        if constexpr (MASKED) mask();
+        if constexpr (MASKED)
+          if (masked) mask();
 #pragma unroll
         for (int v = 0; v < 16; v++) dsb[v >> 3][v & 7] = (__bf16)(fast_exp2(fmaf(sc[v], c2, -lse2)) * dpacc[v]);
         static_for<2 * CB>([&](auto ic) __attribute__((always_inline)) {
@@ -411,7 +419,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
     }
     tile(std::integral_constant<int, NS - 1>{}, std::false_type{});
   }
-  if constexpr (PIPED) act0 = active(nc, 0, 0);  // (its ids and scalars are there: tile nc - 1 waited for those of one tile more)
+  if constexpr (PIPED) act0 = active(nc, 0, 0, full0);  // (its ids and scalars are there: tile nc - 1 waited for those of one tile more)
   for (int base = nc; base < nt; base += NS) {
     tile(s0, std::true_type{});
     if (base + 1 < nt) tile(s1, std::true_type{});
