@@ -73,7 +73,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 1) void dq_kernel(BwdArgs p)
   __shared__ __align__(16) int e_ring[NS][64];
 
   // This launch also clears what the key-stationary launches behind it accumulate into with atomics
-  // (the fp32 dK / dV buffers and dz): every workgroup, also one without a block, takes its share of
+  // (the fp32 dK / dV buffers, dz, and dW and dA where they follow): every workgroup, also one without a block, takes its share of
   // the stores; this kernel is bound by the matrix cores, so they cost no time here.
   {
     const size_t nth = (size_t)p.grid_dq * NT, gid = (size_t)wg_id() * NT + thread_id();
