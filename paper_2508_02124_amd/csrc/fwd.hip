@@ -50,7 +50,7 @@ struct FwdArgs {
 // end the first one takes in the others' (all are the same softmax).  For calls of so few blocks that a wave would else
 // walk its keys alone on its SIMD, with nothing to fill the gaps between the products' results and their uses.
 template <int D, int NW, int UT, int PARTS = 1>
-__global__ __launch_bounds__(NW * 64, D == 64 && PARTS == 1 ? 4 : ((NW == 8 || UT == 2 || D == 256) ? 1 : 2)) void fwd_kernel(FwdArgs p) {
+__global__ __launch_bounds__(NW * 64, D == 64 && PARTS == 1 ? 4 : ((NW == 8 || D == 256) ? 1 : 2)) void fwd_kernel(FwdArgs p) {
   using TL = TileLayout<D>;
   constexpr int KS = D / 16;          // contraction steps of K Q^T
   constexpr int CB = D / 32;          // 32-channel blocks of O^T
