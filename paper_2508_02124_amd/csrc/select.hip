@@ -103,8 +103,12 @@ template <int NT> struct SelShared {
   uint64_t found;
 };
 
-template <int LANE> __device__ __forceinline__ void write_lane(int& v, uint32_t x) {
-  asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(x), "n"(LANE));
+// Lane LANE of lo and hi takes a ballot.  The comparison that forms the ballot writes a scalar register, which a vector
+// instruction may read as data two wait states later; the compiler keeps this for its own instructions only, so the wait is
+// part of the statement.
+template <int LANE> __device__ __forceinline__ void write_lane(int& lo, int& hi, uint64_t ballot) {
+  asm("s_nop 1\n\tv_writelane_b32 %0, %2, %4\n\tv_writelane_b32 %1, %3, %4"
+      : "+v"(lo), "+v"(hi) : "s"((uint32_t)ballot), "s"((uint32_t)(ballot >> 32)), "n"(LANE));
 }
 
 // Exclusive prefix sums of a histogram, in place; seen(bin, count before it, count in it) for every bin.
@@ -506,9 +510,7 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
       int lo32 = 0, hi32 = 0;  // lane i: the set of r0 + i + 1
       static_for<64>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
-        const uint64_t m = __ballot(mine <= r0 + i);
-        write_lane<i>(lo32, (uint32_t)m);
-        write_lane<i>(hi32, (uint32_t)(m >> 32));
+        write_lane<i>(lo32, hi32, __ballot(mine <= r0 + i));
       });
       if (r0 + l < ne) sets[(r0 + l) * (BQ / 64) + wd] = (uint64_t)(uint32_t)hi32 << 32 | (uint32_t)lo32;
     }
