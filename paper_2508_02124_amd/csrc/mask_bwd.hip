@@ -304,7 +304,9 @@ __global__ __launch_bounds__(256) void mask_bwd_rows_kernel(const uint16_t* __re
 #pragma unroll
     for (int r = 0; r < NR; r++) {
       const int pair = sub + r * LPR;
-      const bool in = pair < U * G && row(t0, pair / G) < t_end;
+      // (F32_KEPT: the score of a row that was not read is not known, and a gate above 128 makes that of x = 0 infinite: no
+      // gradient, no part in the sums)
+      const bool in = pair < U * G && row(t0, pair / G) < t_end && (FROM != F32_KEPT || zc[r] != 0.f);
       float xi = 0.f;
 #pragma unroll
       for (int i = r * LPR; i < U * G && i < (r + 1) * LPR; i++) xi = sub == i - r * LPR ? x[i / G][i % G] : xi;

@@ -79,3 +79,41 @@ def test_against_the_two_calls(gpu, H_q, H_kv, d, lens, k, kind):
         assert beyond == 0, (name, beyond)
     for got, ref in ((dW, dW2), (dA, dA2)):
         assert float((got - ref).abs().max()) <= 2e-5 * float(ref.abs().max())
+
+
+# Gates above 128, for which the score of a value of zeros is beyond fp32, with values whose scores are not: rows that no head
+# keeps are not read and take no part.
+@pytest.mark.parametrize("H_q,H_kv,d,lens,k", [(4, 4, 64, (16500,), 200), (4, 2, 128, (9001, 7777), 150),
+                                               (4, 1, 256, (10007, 6500), 100)])
+def test_gates_beyond_the_range(gpu, H_q, H_kv, d, lens, k):
+    print(f"[case] bwd_scores {H_q}/{H_kv} d={d} gates of 129 to 200 {lens}", flush=True)
+    inp = wlmod.make_inputs(wlmod.small_workload(f"gates_{d}", 400 + k, H_q, H_kv, d, k, lens))
+    inp.A[:] = np.linspace(129, 200, H_q)
+    inp.W *= 0.5
+    inp.W[:, 0] = -6
+    inp.V[:, :, 0] = 1  # x about -6 +- 0.5: scores of 1.04 to 280
+    inp.bits["V"] = wlmod.f32_to_bf16_bits(inp.V)
+    c = DeviceCase(inp, gpu)
+    c.mask_gen()
+    c.fwd()
+    c.bwd()
+    part = c.host("dV")
+    dW, dA = scores_bwd(c)
+    dz = c.host("dz")
+    assert (dz == 0).mean() > 0.3  # (there are rows that no head keeps)
+    rW, rA, rVz = orc.mask_backward(inp.V, inp.W, inp.A, dz, H_q)
+    # x: an fp32 sum of products whose sizes add up to about 16, in 13 roundings: error up to 16 * 13 * 2^-24 = 1.3e-5; a score's
+    # relative error is up to 200 * sigmoid(-3.6) = 5.5 times that, 7e-5, and the sums' own 1e-5: 1e-4 of the terms' sizes
+    sizes = np.zeros(rVz.shape)
+    for h in range(H_q):
+        v = inp.V[:, h // (H_q // H_kv)].astype(np.float64)
+        x = v @ inp.W[h].astype(np.float64)
+        sp = np.log1p(np.exp(x))
+        weight = np.abs(dz[h]) * np.exp(inp.A[h] * sp)
+        assert abs(dA[h].item() - rA[h]) <= 1e-4 * (weight * sp).sum()
+        mass = (weight * inp.A[h] / (1 + np.exp(-x))) @ np.abs(v)
+        assert (np.abs(dW[h].cpu().numpy() - rW[h]) <= 1e-4 * mass).all()
+        sizes[:, h // (H_q // H_kv)] += np.outer(weight * inp.A[h] / (1 + np.exp(-x)), np.abs(inp.W[h]))
+    # the attention's part comes from dma_bwd, which rounds it to bf16 (2^-9 of it), and the sum, which may cancel, is rounded too
+    ref, got = part + rVz, c.host("dV")
+    assert (np.abs(got - ref) <= 2.0 ** -8 * (np.abs(ref) + np.abs(part)) + 1e-4 * sizes + 1e-4).all()
