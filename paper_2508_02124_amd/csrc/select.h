@@ -62,7 +62,7 @@ template <typename F> __device__ __forceinline__ uint32_t wave_scan(uint32_t x, 
 __device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
 #endif
 
-// longest: upper bound on the documents' length (a wrong one changes no result)
-int launch_evictions(const SelectArgs& a, int longest, int H_q, hipStream_t st);
+// longest: upper bound on the documents' length (a wrong one changes no result).  The caller asks for launch errors.
+void launch_evictions(const SelectArgs& a, int longest, int H_q, hipStream_t st);
 
 }  // namespace dma

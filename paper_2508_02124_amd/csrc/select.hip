@@ -555,11 +555,10 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
   store(out[min(tid, BQ - 1)]);
 }
 
-int launch_evictions(const SelectArgs& a, int longest, int H_q, hipStream_t st) {
+void launch_evictions(const SelectArgs& a, int longest, int H_q, hipStream_t st) {
   if (a.ck_min < longest)
     checkpoint_kernel<<<dim3(a.T / CK_SEG + a.n_docs, H_q), CK_NT, 0, st>>>(a);
   evict_kernel<256, 4><<<dim3(a.nblk_cap, H_q), 256, 0, st>>>(a);
-  return hipGetLastError() == hipSuccess ? DMA_OK : DMA_EHIP;
 }
 
 }  // namespace dma
