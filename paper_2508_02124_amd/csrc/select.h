@@ -1,14 +1,16 @@
 // The selection of the causal plan, by blocks (select.hip), and what the decode selection shares with it.
 #pragma once
 #include "common.h"
+#include "select_bins.h"
 
 namespace dma {
 
 constexpr int CK_SEG = 4096;   // keys between two checkpoints of a long document
 constexpr int CK_DOC = 16384;  // documents longer than this have them (below, their launch costs more than shorter reads save)
-// Documents longer than this are sorted instead: the checkpoints' cost grows with the square of the length.  us of
-// dma_mask_gen, sorted / by blocks, random scores: 65536 tokens x 8 heads 276 / 124, 131072 x 8 470 / 302, 262144 x 8
-// 825 / 590 (32 heads fill the chip, and then the square counts: about equal).
+// Documents longer than this are sorted instead: the checkpoints' cost grows with the square of the length, and scores of few values
+// take more passes.  us of dma_mask_gen, window 2048, sorted / by blocks, random scores and scores of sixteen values: 131072 tokens x
+// 8 heads 482 / 149 and 424 / 234, x 32 810 / 342 and 693 / 498, 262144 x 32 1771 / 770 and 1245 / 1282, 524288 x 32
+// 5107 / 1995 and 2454 / 3787: up to this length neither loses.
 constexpr int SELECT_MAX = 131072;
 
 struct SelectArgs {
@@ -38,13 +40,6 @@ template <int SEG> __device__ __forceinline__ int piece_doc(const int32_t* __res
     if (piece_slot<SEG>(cu[mid], mid, 0) <= slot) lo = mid; else hi = mid;
   }
   return lo;
-}
-// Ascending unsigned order of the result == descending float order of z (-0 and +0 compare equal).
-__device__ __forceinline__ uint32_t desc_key(float z) {
-  z = z + 0.0f;
-  uint32_t u = __float_as_uint(z);
-  u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-  return ~u;
 }
 // Wave-wide inclusive sum, minimum and maximum in registers (data-parallel moves: a lane shuffle through LDS takes ten times as
 // long).

@@ -5,12 +5,11 @@
 // own key never enters) and the expiries of keys that no row evicts; the slot kernels add the others.
 //
 // A block of BQ rows is worked out by itself, from the scores before it: at most BQ residents are evicted inside it, and
-// these are among the weakest of the residents at its first row.  A histogram of the scores before the block
-// (equal bins between the smallest and the largest) gives the bin of the k-th best and with it how many keys of the block
-// can enter (e); the keys between the bins of rank k - e and k, grouped by bin, are ranked against their bin.  A
+// these are among the weakest of the residents at its first row.  A histogram of the scores before the block (Bins,
+// select_bins.h) gives the bin of the k-th best and with it how many keys of the block can enter (e); the keys between the bins of rank k - e and k, grouped by bin, are ranked against their bin.  A
 // key x then leaves at the row where the c-th of the block's keys ranked ahead of x appears, c = the places left behind the
 // residents ahead of x.  Everything is comparison of (score bits, index), so the result is the exact kept set.
-// Where the bins do not separate the scores (ties, outliers, infinities) the two ranks are found exactly, 11 bits of
+// Where the bins do not separate the scores (ties, outliers, infinities) the two ranks are narrowed down together, BIN_BITS of
 // (score bits, index) at a time.
 //
 // Long documents: reading everything before every block grows with the square of the length, so checkpoint_kernel
@@ -20,14 +19,9 @@
 
 namespace dma {
 
-constexpr int BINS = 1024, BIN_BITS = 10;
-constexpr int RUN = 4;    // keys compared at a time
-constexpr int CAP = 768;  // keys that the ranking takes: those between two bins
+constexpr int RUN = 4;      // keys compared at a time
+constexpr int NARROW = 32;  // keys beside a rank that is narrowed down
 
-__device__ __forceinline__ float key_value(uint32_t key) {
-  const uint32_t u = ~key;
-  return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
-}
 __device__ __forceinline__ uint64_t ranked(uint32_t key, int i) { return (uint64_t)key << 32 | (uint32_t)i; }
 
 // The scores before a block: m0 of a checkpoint's list (their indices in the document beside them), then nz of the document
@@ -61,21 +55,17 @@ struct Scores {
   __device__ __forceinline__ int index(int t, int e) const {
     return t < list_q ? list_idx[4 * t + e] : c + 4 * (t - list_q) + e;
   }
-  // f(score, t, e) for every element
-  template <typename F> __device__ __forceinline__ void each(F&& f) const {
+  // f(quad, t) for every quad, f(score, t, e) for every element
+  template <typename F> __device__ __forceinline__ void each_quad(F&& f) const {
 #pragma unroll
     for (int j = 0; j < NQ; j++)
       if (NT * j < nq) {
         const int t = (int)threadIdx.x + NT * j;
-        if (t < nq) {
-#pragma unroll
-          for (int e = 0; e < 4; e++) f(r[j].v[e], t, e);
-        }
+        if (t < nq) f(r[j], t);
       }
-    each_again(f, NQ);
+    quads_again<4>(f, NQ);
   }
-  template <typename F> __device__ __forceinline__ void each_again(F&& f, int j) const {
-    constexpr int U = 4;  // quads in flight
+  template <int U, typename F> __device__ __forceinline__ void quads_again(F&& f, int j) const {  // U quads in flight
 #pragma unroll 1
     for (; NT * j < nq; j += U) {
       Quad q[U];
@@ -84,12 +74,21 @@ struct Scores {
 #pragma unroll
       for (int u = 0; u < U; u++) {
         const int t = (int)threadIdx.x + NT * (j + u);
-        if (t < nq) {
-#pragma unroll
-          for (int e = 0; e < 4; e++) f(q[u].v[e], t, e);
-        }
+        if (t < nq) f(q[u], t);
       }
     }
+  }
+  template <typename F> __device__ __forceinline__ void each(F&& f) const {
+    each_quad([&](const Quad& q, int t) __attribute__((always_inline)) {
+#pragma unroll
+      for (int e = 0; e < 4; e++) f(q.v[e], t, e);
+    });
+  }
+  template <typename F> __device__ __forceinline__ void each_again(F&& f) const {  // (where registers are short: two quads)
+    quads_again<2>([&](const Quad& q, int t) __attribute__((always_inline)) {
+#pragma unroll
+      for (int e = 0; e < 4; e++) f(q.v[e], t, e);
+    }, 0);
   }
 };
 
@@ -100,7 +99,6 @@ template <int NT> struct SelShared {
   uint32_t kmin[NW], kmax[NW];
   uint32_t bin[2], before[2], count[2];
   int fill;
-  uint64_t found;
 };
 
 // Lane LANE of lo and hi takes a ballot.  The comparison that forms the ballot writes a scalar register, which a vector
@@ -112,9 +110,9 @@ template <int LANE> __device__ __forceinline__ void write_lane(int& lo, int& hi,
 }
 
 // Exclusive prefix sums of a histogram, in place; seen(bin, count before it, count in it) for every bin.
-template <int NT, typename F>
+template <int BITS, int NT, typename F>
 __device__ __forceinline__ void scan_bins(SelShared<NT>& sm, uint32_t* hist, F&& seen) {
-  constexpr int PER = BINS / NT, NW = NT / 64;
+  constexpr int PER = (1 << BITS) / NT, NW = NT / 64;
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   uint32_t v[PER], s = 0;
 #pragma unroll
@@ -141,8 +139,8 @@ template <int NT> __device__ __forceinline__ void note_bin(SelShared<NT>& sm, in
   if (rank - before < count) { sm.bin[at] = bin; sm.before[at] = before; sm.count[at] = count; }
 }
 
-template <int NT> __device__ __forceinline__ void clear_bins(uint32_t* hist) {
-  for (int i = threadIdx.x; i < BINS / 4; i += NT) reinterpret_cast<uint4*>(hist)[i] = make_uint4(0, 0, 0, 0);
+template <int BITS, int NT> __device__ __forceinline__ void clear_bins(uint32_t* hist) {
+  for (int i = threadIdx.x; i < (1 << BITS) / 4; i += NT) reinterpret_cast<uint4*>(hist)[i] = make_uint4(0, 0, 0, 0);
 }
 
 // Smallest kmin and largest kmax of all threads.
@@ -161,82 +159,155 @@ template <int NT> __device__ __forceinline__ void reduce_range(SelShared<NT>& sm
     kmax = max(kmax, sm.kmax[i]);
   }
 }
-// Best and worst key; the whole range if a score, or the thread's own one, is infinite or not a number.  (own scores are in
-// the range only if there are no others.)
+// Best key of all scores and worst key of the first `low_q` quads; the whole range if a score, or the thread's own one, is
+// infinite or not a number.  (own scores are in the range only if there are no others.)  sample: one of the thread's scores.
 template <int NT, int NQ>
-__device__ __forceinline__ void key_range(SelShared<NT>& sm, const Scores<NT, NQ>& s, float own, uint32_t& kmin, uint32_t& kmax) {
+__device__ __forceinline__ void key_range(SelShared<NT>& sm, const Scores<NT, NQ>& s, int low_q, float own, uint32_t& kmin,
+                                          uint32_t& kmax, float& sample) {
+  sample = __builtin_nanf("");
   float top = s.nq ? -__builtin_inff() : own, low = s.nq ? __builtin_inff() : own, bad = own * 0.f;
-  s.each([&](float z, int, int) {
-    top = fmaxf(top, z);
-    low = fminf(low, z);
-    bad = fmaf(z, 0.f, bad);
+  s.each_quad([&](const Quad& q, int t) __attribute__((always_inline)) {
+    float worst = __builtin_inff();
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      top = fmaxf(top, q.v[e]);
+      worst = fminf(worst, q.v[e]);
+      bad = fmaf(q.v[e], 0.f, bad);
+    }
+    low = t < low_q ? fminf(low, worst) : low;
+    sample = q.v[0];
   });
   kmin = bad != bad ? 0u : desc_key(top);
   kmax = bad != bad ? 0xffffffffu : desc_key(low);
   reduce_range(sm, kmin, kmax);
 }
-// Equal bins between the best and the worst score.
-struct Bins {
-  float c0, c1;
-  bool ok;  // the scores are finite and not all the same
-  __device__ __forceinline__ void init(uint32_t kmin, uint32_t kmax) {
-    const float top = key_value(kmin), range = top - key_value(kmax);
-    c1 = -(BINS - 1) / range;
-    c0 = -c1 * top;
-    ok = range > 0.f && range < __builtin_inff() && c1 > -__builtin_inff() && fabsf(c0) < __builtin_inff();  // (false for NaN)
-  }
-  // never falls along descending finite scores
-  __device__ __forceinline__ int of(float z) const { return (int)__builtin_amdgcn_fmed3f(fmaf(z, c1, c0), 0.f, BINS - 1); }
-};
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 
-// ranked(key, index) of the score with the given rank among those with pick(score), for any scores: BIN_BITS of (key,
-// index) at a time, the indices taken as `ibits` wide.  hist: another one than the bins'.
-template <int NT, int NQ, typename F>
-__device__ __forceinline__ uint64_t exact_rank(SelShared<NT>& sm, uint32_t* hist, const Scores<NT, NQ>& s, int ibits, uint32_t rank, F&& pick) {
-  uint32_t kmin = 0xffffffffu, kmax = 0;
-  __syncthreads();
-  s.each_again([&](float z, int, int) {
-    if (pick(z)) {
-      kmin = min(kmin, desc_key(z));
-      kmax = max(kmax, desc_key(z));
-    }
-  }, 0);
-  reduce_range(sm, kmin, kmax);
-  uint64_t base = (uint64_t)kmin << ibits;
-  const uint64_t width = (((uint64_t)kmax + 1) << ibits) - base;
-  int shift = max(0, 64 - (int)__clzll((long long)(width - 1)) - BIN_BITS);
+// A rank among the scores, and how far it is known: the key with this rank is one of the `count` keys from base to last, with
+// `before` keys before these.  Keys are (score, index) as key << ibits | index here.
+struct Window {
+  uint64_t base, last;
+  uint32_t rank, before, count;
+  __device__ __forceinline__ void init(uint32_t key0, uint64_t key1, int ibits, uint32_t rank_, uint32_t before_, uint32_t count_) {
+    span(key0, key1, ibits);
+    rank = uniform(rank_); before = uniform(before_); count = uniform(count_);
+  }
+  __device__ __forceinline__ void span(uint32_t key0, uint64_t key1, int ibits) {
+    base = (uint64_t)uniform(key0) << ibits;
+    last = (((uint64_t)uniform((uint32_t)(key1 - 1)) + 1) << ibits) - 1;
+  }
+  template <int BITS> __device__ __forceinline__ int shift() const {
+    return max(0, 64 - (int)__clzll((long long)(last - base)) - BITS);
+  }
+  template <int NT> __device__ __forceinline__ void take(const SelShared<NT>& sm, int at, int shift) {
+    const uint32_t ahead = uniform(sm.before[at]);
+    base += (uint64_t)uniform(sm.bin[at]) << shift;
+    last = base + ((1ull << shift) - 1);
+    before += ahead;
+    rank -= ahead;
+    count = uniform(sm.count[at]);
+  }
+  __device__ __forceinline__ bool holds(uint64_t c) const { return c >= base && c <= last; }
+};
+__device__ __forceinline__ uint64_t composite(uint32_t key, int i, int ibits) { return (uint64_t)key << ibits | (uint32_t)i; }
+// (with ties the lanes mostly agree: one addition for all that agree with the first)
+template <int BITS> __device__ __forceinline__ void count_agreeing(uint32_t* hist, uint64_t bin) {
+  if (bin >> BITS) return;
+  const uint32_t b = (uint32_t)bin, b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+  const uint64_t same = __ballot(b == b0);
+  if (b != b0) atomicAdd(&hist[b], 1u);
+  else if ((same & ((1ull << (threadIdx.x & 63)) - 1ull)) == 0) atomicAdd(&hist[b], (uint32_t)__popcll(same));
+}
+// The histogram of all scores.  Each wave looks at one score per lane first (sample; NaN if a lane has none): where many lanes
+// agree, additions to one counter would wait for each other (evict_kernel, 16384 x 32, a few outliers of 1e30: 166 -> 119 us).
+// ALL: no score is behind the bins' range.
+template <bool ALL, int BITS, int NT, int NQ>
+__device__ __forceinline__ void count_all(uint32_t* hist, const Scores<NT, NQ>& s, const Bins<BITS>& bins, float sample) {
+  const uint32_t b = bins.of_behind(sample);
+  if (__popcll(__ballot(b == (uint32_t)__builtin_amdgcn_readfirstlane((int)b) && b >> BITS == 0)) < 16)
+    s.each([&](float z, int, int) {
+      const uint32_t bin = ALL ? bins.of(z) : bins.of_behind(z);
+      if (ALL || bin >> BITS == 0) atomicAdd(&hist[bin], 1u);
+    });
+  else
+    s.each_again([&](float z, int, int) { count_agreeing<BITS>(hist, bins.of_behind(z)); });
+}
+// The windows of two ranks that are known to their bins.
+template <int BITS>
+__device__ __forceinline__ void windows_of_bins(const Bins<BITS>& bins, int bin0, int bin1, int ibits, uint32_t rank0, uint32_t before0,
+                                                uint32_t count0, uint32_t rank1, uint32_t before1, uint32_t count1, Window& w0,
+                                                Window& w1) {
+  const int l = threadIdx.x & 63;
+  const int ends = (int)bins.bound((uint32_t)((l & 2 ? bin1 : bin0) + (l & 1)));  // lanes 0 to 3
+  const auto end = [&](int lane) { return (uint32_t)__builtin_amdgcn_readlane(ends, lane); };
+  w0.init(end(0), end(1), ibits, rank0 - before0, before0, count0);
+  w1.init(end(2), end(3), ibits, rank1 - before1, before1, count1);
+}
+// Narrows two windows until neither holds more than `limit` keys, both in the same passes over the scores: first to the scores
+// that there are (with ties that is one, and the indices alone are left), then BITS of what is left at a time.  Scores of sixteen
+// different values, whole dma_mask_gen, us, a sort / a search of its own for each rank / this: 16384 x 32 114 / 169 / 114, packed
+// 65536 x 16 157 / 114 / 100, 65536 x 32, window 16384, 483 / 630 / 543.
+template <int BITS, int NT, int NQ>
+__device__ __forceinline__ void narrow(SelShared<NT>& sm, uint32_t* hist0, uint32_t* hist1, const Scores<NT, NQ>& s, int ibits,
+                                       Window& w0, Window& w1, uint32_t limit) {
+  if (w0.count <= limit && w1.count <= limit) return;
+  {
+    const uint32_t a0 = (uint32_t)(w0.base >> ibits), b0 = (uint32_t)(w0.last >> ibits);
+    const uint32_t a1 = (uint32_t)(w1.base >> ibits), b1 = (uint32_t)(w1.last >> ibits);
+    uint32_t min0 = 0xffffffffu, max0 = 0, min1 = 0xffffffffu, max1 = 0;
+    s.each_again([&](float z, int, int) {
+      const uint32_t key = desc_key(z);
+      const bool in0 = key >= a0 && key <= b0, in1 = key >= a1 && key <= b1;
+      min0 = min(min0, in0 ? key : 0xffffffffu);
+      max0 = max(max0, in0 ? key : 0u);
+      min1 = min(min1, in1 ? key : 0xffffffffu);
+      max1 = max(max1, in1 ? key : 0u);
+    });
+    __syncthreads();
+    reduce_range(sm, min0, max0);
+    __syncthreads();
+    reduce_range(sm, min1, max1);
+    if (w0.count > 0) w0.span(min0, (uint64_t)max0 + 1, ibits);
+    if (w1.count > 0) w1.span(min1, (uint64_t)max1 + 1, ibits);
+  }
+#pragma unroll 1
   for (;;) {
-    clear_bins<NT>(hist);
+    const bool go0 = w0.count > limit && w0.base < w0.last, go1 = w1.count > limit && w1.base < w1.last;
+    const bool one = go0 && go1 && w0.base == w1.base && w0.last == w1.last;
+    if (!go0 && !go1) return;
+    const int shift0 = w0.shift<BITS>(), shift1 = w1.shift<BITS>();
+    __syncthreads();
+    clear_bins<BITS, NT>(hist0);
+    clear_bins<BITS, NT>(hist1);
     __syncthreads();
     s.each_again([&](float z, int t, int e) {
-      if (!pick(z)) return;
-      const uint64_t c = (uint64_t)desc_key(z) << ibits | (uint32_t)s.index(t, e), bin = (c - base) >> shift;
-      if (c >= base && bin < BINS) {
-        // (with ties the lanes mostly agree: one addition for all of them)
-        const uint32_t b = (uint32_t)bin, b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
-        const uint64_t same = __ballot(b == b0);
-        if (b != b0) atomicAdd(&hist[b], 1u);
-        else if ((same & ((1ull << (threadIdx.x & 63)) - 1ull)) == 0) atomicAdd(&hist[b], (uint32_t)__popcll(same));
-      }
-    }, 0);
+      const uint64_t c = composite(desc_key(z), s.index(t, e), ibits);
+      if (go0) count_agreeing<BITS>(hist0, (c - w0.base) >> shift0);
+      if (go1 && !one) count_agreeing<BITS>(hist1, (c - w1.base) >> shift1);
+    });
     __syncthreads();
-    scan_bins(sm, hist, [&](int bin, uint32_t before, uint32_t count) { note_bin(sm, 0, rank, bin, before, count); });
-    base += (uint64_t)sm.bin[0] << shift;
-    rank -= sm.before[0];
-    __syncthreads();
-    if (shift == 0) return ranked((uint32_t)(base >> ibits), (int)(base & ((1ull << ibits) - 1)));
-    shift = max(0, shift - BIN_BITS);
+    if (go0)
+      scan_bins<BITS>(sm, hist0, [&](int bin, uint32_t before, uint32_t count) {
+        note_bin(sm, 0, w0.rank, bin, before, count);
+        if (one) note_bin(sm, 1, w1.rank, bin, before, count);
+      });
+    if (go1 && !one)
+      scan_bins<BITS>(sm, hist1, [&](int bin, uint32_t before, uint32_t count) { note_bin(sm, 1, w1.rank, bin, before, count); });
+    if (go0) w0.take(sm, 0, shift0);
+    if (go1) w1.take(sm, 1, shift1);
   }
 }
 
 // ------------------------------------------------------------------ checkpoints
 // One workgroup per (checkpoint, head).
 // What bounds it: instruction issue over the N scores, three to four passes of loads of 16 bytes per lane: 65536 tokens x
-// 32 heads 44 us (window 16384: 58).
+// 32 heads 41 us (window 16384: 49).
 constexpr int CK_NT = 1024, CK_NQ = 0;
 __global__ __launch_bounds__(CK_NT, 8) void checkpoint_kernel(SelectArgs p) {
   __shared__ SelShared<CK_NT> sm;
-  __shared__ __align__(16) uint32_t hist[BINS], exact_hist[BINS];
+  __shared__ __align__(16) uint32_t hist[1 << CK_BIN_BITS], exact_hist[1 << CK_BIN_BITS];
+  __shared__ uint64_t cand1[CAP], found[2];
+  __shared__ int fill[2];
   const int slot = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
   const int d = piece_doc<CK_SEG>(p.cu, p.n_docs, slot);
   const int a = p.cu[d], n = p.cu[d + 1] - a;
@@ -248,61 +319,75 @@ __global__ __launch_bounds__(CK_NT, 8) void checkpoint_kernel(SelectArgs p) {
   uint64_t from = 0, to = ~0ull;  // the weakest m0 of the kept: ranks kept - m0 .. kept - 1
   if (kept < c || m0 < kept) {
     uint32_t kmin, kmax;
-    clear_bins<CK_NT>(hist);
-    key_range(sm, s, 0.f, kmin, kmax);
-    Bins bins;
+    float sample;
+    clear_bins<CK_BIN_BITS, CK_NT>(hist);
+    key_range(sm, s, s.nq, 0.f, kmin, kmax, sample);
+    Bins<CK_BIN_BITS> bins;
     bins.init(kmin, kmax);
     const uint32_t rank0 = kept - m0, rank1 = kept - 1;
+    const bool cut0 = rank0 > 0, cut1 = kept < c;  // (otherwise nothing is left out on that side)
     if (bins.ok) {
-      s.each([&](float z, int, int) { atomicAdd(&hist[bins.of(z)], 1u); });
+      count_all<true>(hist, s, bins, sample);
       __syncthreads();
-      scan_bins(sm, hist, [&](int bin, uint32_t before, uint32_t count) {
+      scan_bins<CK_BIN_BITS>(sm, hist, [&](int bin, uint32_t before, uint32_t count) {
         note_bin(sm, 0, rank0, bin, before, count);
         note_bin(sm, 1, rank1, bin, before, count);
       });
     }
     const uint32_t bin0 = sm.bin[0], before0 = sm.before[0], count0 = sm.count[0];
     const uint32_t bin1 = sm.bin[1], before1 = sm.before[1], count1 = sm.count[1];
-    __syncthreads();
-#pragma unroll 1
-    for (int i = 0; i < 2; i++) {
-      if (i == 0 ? rank0 == 0 : kept == c) continue;  // (nothing is left out on this side)
-      const uint32_t rank = i == 0 ? rank0 : rank1;
-      uint64_t found;
-      const uint32_t bin = i == 0 ? bin0 : bin1, before = i == 0 ? before0 : before1, count = i == 0 ? count0 : count1;
-      if (bins.ok && count <= CAP) {
-        if (tid == 0) sm.fill = 0;
-        __syncthreads();
-        s.each([&](float z, int t, int e) {
-          if ((uint32_t)bins.of(z) == bin) sm.cand[atomicAdd(&sm.fill, 1)] = ranked(desc_key(z), s.index(t, e));
-        });
-        __syncthreads();
-        if (tid < (int)count) {
-          const uint64_t mine = sm.cand[tid];
-          uint32_t ahead = 0;
-          for (uint32_t j = 0; j < count; j++) ahead += sm.cand[j] < mine;
-          if (before + ahead == rank) sm.found = mine;
-        }
-        __syncthreads();
-        found = sm.found;
-        __syncthreads();
+    const int ibits = 32 - __clz(n);
+    const bool by_bin = bins.ok && !(cut0 && count0 > CAP) && !(cut1 && count1 > CAP);
+    Window w0 = {0, 0, rank0, before0, count0}, w1 = {0, 0, rank1, before1, count1};
+    if (!by_bin) {
+      if (bins.ok) {
+        windows_of_bins(bins, bin0, bin1, ibits, rank0, before0, cut0 ? count0 : 0, rank1, before1, cut1 ? count1 : 0, w0, w1);
       } else {
-        // (the bin's keys, or all of them)
-        found = exact_rank(sm, exact_hist, s, 32 - __clz(n), bins.ok ? rank - before : rank,
-                           [&](float z) { return !bins.ok || (uint32_t)bins.of(z) == bin; });
+        w0.init(kmin, (uint64_t)kmax + 1, ibits, rank0, 0, cut0 ? c : 0);
+        w1.init(kmin, (uint64_t)kmax + 1, ibits, rank1, 0, cut1 ? c : 0);
       }
-      if (i == 0) from = found; else to = found;
+      narrow<CK_BIN_BITS>(sm, hist, exact_hist, s, ibits, w0, w1, CAP);
     }
+    __syncthreads();
+    if (tid < 2) fill[tid] = 0;
+    __syncthreads();
+    if (by_bin) {
+      s.each([&](float z, int t, int e) {
+        const uint32_t b = bins.of(z);
+        if (b == bin0 && cut0) sm.cand[atomicAdd(&fill[0], 1)] = ranked(desc_key(z), s.index(t, e));
+        if (b == bin1 && cut1) cand1[atomicAdd(&fill[1], 1)] = ranked(desc_key(z), s.index(t, e));
+      });
+    } else {
+      s.each_again([&](float z, int t, int e) {
+        const int i = s.index(t, e);
+        const uint64_t c2 = composite(desc_key(z), i, ibits);
+        if (cut0 && w0.holds(c2)) sm.cand[atomicAdd(&fill[0], 1)] = ranked(desc_key(z), i);
+        if (cut1 && w1.holds(c2)) cand1[atomicAdd(&fill[1], 1)] = ranked(desc_key(z), i);
+      });
+    }
+    __syncthreads();
+    const auto find = [&](const uint64_t* cand, uint32_t count, uint32_t rank, uint64_t& found) __attribute__((always_inline)) {
+      if (tid >= (int)count) return;
+      const uint64_t mine = cand[tid];
+      uint32_t ahead = 0;
+      for (uint32_t j = 0; j < count; j++) ahead += cand[j] < mine;
+      if (ahead == rank) found = mine;
+    };
+    if (cut0) find(sm.cand, w0.count, rank0 - w0.before, found[0]);
+    if (cut1) find(cand1, w1.count, rank1 - w1.before, found[1]);
+    __syncthreads();
+    if (cut0) from = found[0];
+    if (cut1) to = found[1];
   }
   const size_t out = (size_t)h * p.T + a + (c - CK_SEG);
   __syncthreads();
-  if (tid == 0) sm.fill = 0;
+  if (tid == 0) fill[0] = 0;
   __syncthreads();
   s.each([&](float z, int t, int e) {
     const int i = s.index(t, e);
     const uint64_t r = ranked(desc_key(z), i);
     if (r >= from && r <= to) {
-      const int at = atomicAdd(&sm.fill, 1);
+      const int at = atomicAdd(&fill[0], 1);
       p.ck_z[out + at] = z;
       p.ck_idx[out + at] = i;
     }
@@ -311,15 +396,14 @@ __global__ __launch_bounds__(CK_NT, 8) void checkpoint_kernel(SelectArgs p) {
 
 // ------------------------------------------------------------------ evictions of one block
 // One workgroup per (block, head).  What bounds it: instruction issue; its twelve short phases between barriers take about 14000
-// cycles with 1024 older scores (what a score costs is 15 instructions in all), so seven workgroups share a compute unit.
+// cycles with 1024 older scores (what a score costs is 16 instructions in all).  (Registers for eight workgroups per compute unit
+// instead of seven: 65536 x 32 of window 1024 50 -> 48 us, 16384 x 32 31 -> 33.)
 // Whole selection, us, against a radix sort and wavelet matrix per 4096 or 16384 keys and a range query per key: 256
-// tokens x 2 heads 25 -> 7, 2 x 4096 x 16 52 -> 12, 16384 x 32 76 -> 25, packed 65536 x 16 121 -> 33, 65536 x 32 of
-// window 1024 241 -> 95.  (Scores of sixteen different values, whole dma_mask_gen: 16384 x 32 114 -> 176, packed 155 -> 108:
-// the counters of a few bins are fought over, and ranks are found among long runs.)  1024 bins and 256 threads
-// against 2048 and 512: packed 41 -> 33, 65536 tokens 74 -> 50, 8192 x 32 heads 17.5 -> 19.
+// tokens x 2 heads 25 -> 7, 2 x 4096 x 16 52 -> 12, 16384 x 32 76 -> 29, packed 65536 x 16 121 -> 32, 65536 x 32 of
+// window 1024 241 -> 90.
 template <int NT, int NQ>
 __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
-  constexpr int NW = NT / 64;
+  constexpr int NW = NT / 64, BINS = 1 << BIN_BITS;
   constexpr int XT = (CAP + BQ + NT - 1) / NT;  // keys ranked per thread
   static_assert(NT >= BQ, "one thread per row of the block");
   __shared__ SelShared<NT> sm;
@@ -365,12 +449,16 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
   int strong = 0, nl = 0;
   bool enters = tid < nb;
   int b1 = BINS - 1, b2 = 0, end_before = 0, end = N;  // bins of the last resident and of the first that takes part; keys before and up to the end of b1
-  Bins bins;
+  int first = 0;  // rank of the first that takes part
+  Bins<BIN_BITS> bins;
   uint32_t kmin, kmax;
-  clear_bins<NT>(hist);
-  clear_bins<NT>(new_hist);
+  float sample;
+  clear_bins<BIN_BITS, NT>(hist);
+  clear_bins<BIN_BITS, NT>(new_hist);
   if (tid == 0) sm.bin[1] = sm.before[1] = 0;  // (what is left without older keys)
-  key_range(sm, s, zn, kmin, kmax);
+  // (a full checkpoint: what is behind its last key is not kept, and its range is far shorter than that of all)
+  const bool full = m0 > 0 && c >= k;
+  key_range(sm, s, full ? s.list_q : s.nq, zn, kmin, kmax, sample);
   bins.init(kmin, kmax);
   bool by_bin = bins.ok;
   // the bin of a rank among the older keys, and the count before it
@@ -382,14 +470,19 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
     begin[PER] = tid + 1 < NT ? (int)hist[PER * (tid + 1)] : N;
 #pragma unroll
     for (int i = 0; i < PER; i++)
-      if (begin[i] <= rank && rank < begin[i + 1]) { sm.bin[1] = PER * tid + i; sm.before[1] = begin[i]; }
+      if (begin[i] <= rank && rank < begin[i + 1]) {
+        sm.bin[1] = PER * tid + i;
+        sm.before[1] = begin[i];
+        sm.count[1] = begin[i + 1] - begin[i];
+      }
     __syncthreads();
   };
   if (by_bin) {
-    s.each([&](float z, int, int) { atomicAdd(&hist[bins.of(z)], 1u); });
+    if (full) count_all<false>(hist, s, bins, sample);
+    else count_all<true>(hist, s, bins, sample);
     __syncthreads();
-    const int bn = bins.of(zn);
-    scan_bins(sm, hist, [&](int bin, uint32_t before, uint32_t count) {
+    const int bn = bins.of_any(zn);
+    scan_bins<BIN_BITS>(sm, hist, [&](int bin, uint32_t before, uint32_t count) {
       note_bin(sm, 0, (uint32_t)(kept - 1), bin, before, count);
     });
     // (kept == N: every older key is still there, whatever its rank; with no place left either, a key has to be ahead of
@@ -407,46 +500,54 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
     }
     if (enters) atomicAdd(&new_hist[bn], 1u);
     // (a row evicts nothing before the places are taken)
-    find_bin(max(0, kept - min(e, lo + nb - k)));
+    first = max(0, kept - min(e, lo + nb - k));
+    find_bin(first);
     b2 = sm.bin[1];
     strong = sm.before[1];
     nl = end - strong;
-    by_bin = nl <= CAP;
+    by_bin = nl - (kept - first) <= NEAR;
     if (by_bin) {
       s.each([&](float z, int t, int e2) {
-        const int b = bins.of(z);
-        if (b >= b2 && b <= b1) sm.cand[atomicAdd(&hist[b], 1u) - strong] = ranked(desc_key(z), s.index(t, e2));
+        const uint32_t b = bins.of_behind(z);
+        if (b >= (uint32_t)b2 && b <= (uint32_t)b1) sm.cand[atomicAdd(&hist[b], 1u) - strong] = ranked(desc_key(z), s.index(t, e2));
       });
-      scan_bins(sm, new_hist, [](int, uint32_t, uint32_t) {});
+      scan_bins<BIN_BITS>(sm, new_hist, [](int, uint32_t, uint32_t) {});
       if (enters) new_run[atomicAdd(&new_hist[bn], 1u)] = ranked(kn, lo + tid);
     }
   }
   if (!by_bin && N > 0) {
     const int ibits = 32 - __clz(n);
-    const auto in_bin = [&](int b) __attribute__((always_inline)) { return [&, b](float z) { return !bins.ok || bins.of(z) == b; }; };
-    uint64_t to = ~0ull;
-    if (kept < N) to = exact_rank(sm, new_hist, s, ibits, kept - 1 - (bins.ok ? end_before : 0), in_bin(b1));
-    enters = tid < nb && (cap > N || kn < (kept < N ? (uint32_t)(to >> 32) : kmax));
-    const int e = __syncthreads_count(enters);
-    if (e == 0) {
+    Window w0, w1;  // of the first that takes part and of the last resident
+    if (bins.ok) {
+      windows_of_bins(bins, b2, b1, ibits, first, strong, sm.count[1], kept - 1, end_before, end - end_before, w0, w1);
+    } else {
+      enters = tid < nb && (cap > N || kn < kmax);
+      const int e = __syncthreads_count(enters);
+      if (e == 0) {
+        store(-2);
+        return;
+      }
+      first = max(0, kept - min(e, lo + nb - k));
+      w0.init(kmin, 1ull << 32, ibits, first, 0, N);
+      w1.init(kmin, 1ull << 32, ibits, kept - 1, 0, N);
+    }
+    if (kept == N) w1.count = 0;  // (every older key is still there)
+    narrow<BIN_BITS>(sm, hist, new_hist, s, ibits, w0, w1, NARROW);
+    if (kept < N) enters = enters && composite(kn, lo + tid, ibits) <= w1.last;
+    if (__syncthreads_count(enters) == 0) {
       store(-2);
       return;
     }
-    strong = max(0, kept - min(e, lo + nb - k));
-    nl = kept - strong;
-    int b = 0, before = 0;
-    if (bins.ok) {
-      find_bin(strong);
-      b = sm.bin[1];
-      before = sm.before[1];
-    }
-    const uint64_t from = exact_rank(sm, new_hist, s, ibits, strong - before, in_bin(b));
+    strong = w0.before;
     if (tid == 0) sm.fill = 0;
     __syncthreads();
     s.each_again([&](float z, int t, int e2) {
-      const uint64_t r = ranked(desc_key(z), s.index(t, e2));
-      if (r >= from && r <= to) sm.cand[atomicAdd(&sm.fill, 1)] = r;
-    }, 0);
+      const uint64_t c2 = composite(desc_key(z), s.index(t, e2), ibits);
+      if (c2 >= w0.base && (kept == N || c2 <= w1.last)) sm.cand[atomicAdd(&sm.fill, 1)] = ranked(desc_key(z), s.index(t, e2));
+    });
+    // (the window of a bin that is not narrowed leaves out what shares the last bin from behind the range)
+    __syncthreads();
+    nl = sm.fill;
   }
   const int places = cap - strong;  // for the nl older keys and the new ones
   const uint64_t em = __ballot(enters);
@@ -478,7 +579,7 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
     cx[u] = x < nl ? sm.cand[x] : newc[x - nl];
     int r0 = 0, r1 = nl, n0 = 0, n1 = ne;  // the older and the new keys of its bin, or all of them
     if (by_bin) {
-      const int b = bins.of(key_value((uint32_t)(cx[u] >> 32)));
+      const int b = bins.of_any(key_value((uint32_t)(cx[u] >> 32)));
       r0 = b > b2 ? (int)hist[b - 1] - strong : 0;  // (the counters stand at their bins' ends now)
       r1 = b >= b2 ? (int)hist[b] - strong : 0;
       n0 = b > 0 ? (int)new_hist[b - 1] : 0;

@@ -32,6 +32,14 @@ def scores(kind, H, n, rng):
     elif kind == "outliers":  # one bin holds nearly everything
         z[:, rng.integers(0, n, 3)] = 1e30
         z[:, rng.integers(0, n, 3)] = -1e30
+    elif kind == "climbing":  # positive gates: scores over many powers of two, with a zero
+        z = np.exp(rng.uniform(2, 6, (H, 1)) * np.log1p(np.exp(2 * rng.standard_normal((H, n))))).astype(np.float32)
+        z[:, n // 3] = 0
+    elif kind == "signed":
+        z = rng.standard_normal((H, n)).astype(np.float32)
+    elif kind == "runs":  # few values, each in long runs: the ranks fall among equal keys
+        z = (rng.integers(0, 3, (H, n)) / 4).astype(np.float32)
+        z[:, n // 5:n // 2] = 0.5
     elif kind == "special":  # infinities, zeros of both signs, subnormals, NaNs of both signs
         pick = rng.integers(0, 12, z.shape)
         special = np.array([np.inf, -np.inf, 0.0, -0.0, 1e-40, -1e-40], dtype=np.float32)
@@ -66,7 +74,7 @@ def check(z, lens, k, max_seqlen=None):
             a += n
 
 
-KINDS = ["random", "ties", "equal", "rising", "falling", "outliers", "special"]
+KINDS = ["random", "ties", "equal", "rising", "falling", "outliers", "special", "climbing", "signed", "runs"]
 
 
 @pytest.mark.parametrize("kind", KINDS)
