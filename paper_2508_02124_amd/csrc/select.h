@@ -27,8 +27,8 @@ struct SelectArgs {
 
 #ifdef __HIPCC__
 // Checkpoints of a document that starts at a: number p stands before its key c = CK_SEG (p + 1) and is stored at the place of
-// the CK_SEG keys before c.  It holds the weakest ck_keys(k) of the keys kept by row c - 1, in any order (k <= CK_SEG: all of
-// them, and up to three more).
+// the CK_SEG keys before c.  It holds the weakest ck_keys(k) of the keys kept by row c - 1 (k <= CK_SEG: all of them, and up
+// to three more), in any order, but the last of them first if there are others.
 __device__ __forceinline__ int ck_keys(int k) { return k < CK_SEG ? (k + 3) & ~3 : CK_SEG; }
 // Place of piece p of document d among the pieces of SEG keys of all documents.
 template <int SEG> __device__ __forceinline__ int piece_slot(int a, int d, int p) { return a / SEG + d + p; }

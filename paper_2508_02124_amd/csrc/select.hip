@@ -6,9 +6,10 @@
 //
 // A block of BQ rows is worked out by itself, from the scores before it: at most BQ residents are evicted inside it, and
 // these are among the weakest of the residents at its first row.  A histogram of the scores before the block (Bins,
-// select_bins.h) gives the bin of the k-th best and with it how many keys of the block can enter (e); the keys between the bins of rank k - e and k, grouped by bin, are ranked against their bin.  A
-// key x then leaves at the row where the c-th of the block's keys ranked ahead of x appears, c = the places left behind the
-// residents ahead of x.  Everything is comparison of (score bits, index), so the result is the exact kept set.
+// select_bins.h) gives the bin of the k-th best and with it how many keys of the block can enter (e); the keys between the
+// bins of rank k - e and k, grouped by bin, are ranked against their bin.  A key x then leaves at the row where the c-th of
+// the block's keys ranked ahead of x appears, c = the places left behind the residents ahead of x.  Everything is comparison
+// of (score bits, index), so the result is the exact kept set.
 // Where the bins do not separate the scores (ties, outliers, infinities) the two ranks are narrowed down together, BIN_BITS of
 // (score bits, index) at a time.
 //
@@ -54,6 +55,11 @@ struct Scores {
   // index in the document of element e of quad t
   __device__ __forceinline__ int index(int t, int e) const {
     return t < list_q ? list_idx[4 * t + e] : c + 4 * (t - list_q) + e;
+  }
+  // one of the scores for every thread, over all of them
+  __device__ __forceinline__ float sample() const {
+    const int i = (int)((uint32_t)(4 * nq) * threadIdx.x / NT);
+    return i < 4 * list_q ? list[i] : z[i - 4 * list_q];
   }
   // f(quad, t) for every quad, f(score, t, e) for every element
   template <typename F> __device__ __forceinline__ void each_quad(F&& f) const {
@@ -159,26 +165,12 @@ template <int NT> __device__ __forceinline__ void reduce_range(SelShared<NT>& sm
     kmax = max(kmax, sm.kmax[i]);
   }
 }
-// Best key of all scores and worst key of the first `low_q` quads; the whole range if a score, or the thread's own one, is
-// infinite or not a number.  (own scores are in the range only if there are no others.)  sample: one of the thread's scores.
-template <int NT, int NQ>
-__device__ __forceinline__ void key_range(SelShared<NT>& sm, const Scores<NT, NQ>& s, int low_q, float own, uint32_t& kmin,
-                                          uint32_t& kmax, float& sample) {
-  sample = __builtin_nanf("");
-  float top = s.nq ? -__builtin_inff() : own, low = s.nq ? __builtin_inff() : own, bad = own * 0.f;
-  s.each_quad([&](const Quad& q, int t) __attribute__((always_inline)) {
-    float worst = __builtin_inff();
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-      top = fmaxf(top, q.v[e]);
-      worst = fminf(worst, q.v[e]);
-      bad = fmaf(q.v[e], 0.f, bad);
-    }
-    low = t < low_q ? fminf(low, worst) : low;
-    sample = q.v[0];
-  });
-  kmin = bad != bad ? 0u : desc_key(top);
-  kmax = bad != bad ? 0xffffffffu : desc_key(low);
+// Best and worst key of a score per thread; zeros and infinities apart (kmin > kmax: there are no others).
+template <int NT>
+__device__ __forceinline__ void sample_range(SelShared<NT>& sm, float sample, uint32_t& kmin, uint32_t& kmax) {
+  const bool takes = sample != 0.f && fabsf(sample) < __builtin_inff();
+  kmin = takes ? desc_key(sample) : 0xffffffffu;
+  kmax = takes ? desc_key(sample) : 0u;
   reduce_range(sm, kmin, kmax);
 }
 __device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
@@ -218,58 +210,65 @@ template <int BITS> __device__ __forceinline__ void count_agreeing(uint32_t* his
   if (b != b0) atomicAdd(&hist[b], 1u);
   else if ((same & ((1ull << (threadIdx.x & 63)) - 1ull)) == 0) atomicAdd(&hist[b], (uint32_t)__popcll(same));
 }
-// The histogram of all scores.  Each wave looks at one score per lane first (sample; NaN if a lane has none): where many lanes
-// agree, additions to one counter would wait for each other (evict_kernel, 16384 x 32, a few outliers of 1e30: 166 -> 119 us).
-// ALL: no score is behind the bins' range.
-template <bool ALL, int BITS, int NT, int NQ>
-__device__ __forceinline__ void count_all(uint32_t* hist, const Scores<NT, NQ>& s, const Bins<BITS>& bins, float sample) {
-  const uint32_t b = bins.of_behind(sample);
-  if (__popcll(__ballot(b == (uint32_t)__builtin_amdgcn_readfirstlane((int)b) && b >> BITS == 0)) < 16)
+// The histogram of all scores; true if one of the thread's is not a number.  Each wave looks at one per lane first: where many lanes
+// agree, additions to one counter would wait for each other (evict_kernel, 16384 x 32, nearly all scores in one bin: 166 -> 119
+// us).  CUT: without what is behind the bins' range.
+template <bool CUT, int BITS, int NT, int NQ>
+__device__ __forceinline__ bool count_all(uint32_t* hist, const Scores<NT, NQ>& s, const Bins<BITS>& bins, float sample) {
+  if (NQ > 0) sample = s.r[0].v[0];  // (with its neighbours, whose order may be that of the scores)
+  const uint32_t b = bins.of(sample);
+  bool bad = false;
+  if (__popcll(__ballot(b == (uint32_t)__builtin_amdgcn_readfirstlane((int)b) && !(CUT && bins.behind(sample)))) < 16)
     s.each([&](float z, int, int) {
-      const uint32_t bin = ALL ? bins.of(z) : bins.of_behind(z);
-      if (ALL || bin >> BITS == 0) atomicAdd(&hist[bin], 1u);
+      bad |= z != z;
+      if (!CUT || !bins.behind(z)) atomicAdd(&hist[bins.of(z)], 1u);
     });
   else
-    s.each_again([&](float z, int, int) { count_agreeing<BITS>(hist, bins.of_behind(z)); });
+    s.each_again([&](float z, int, int) {
+      bad |= z != z;
+      if (!CUT || !bins.behind(z)) count_agreeing<BITS>(hist, bins.of(z));
+    });
+  return bad;
 }
 // The windows of two ranks that are known to their bins.
 template <int BITS>
-__device__ __forceinline__ void windows_of_bins(const Bins<BITS>& bins, int bin0, int bin1, int ibits, uint32_t rank0, uint32_t before0,
+__device__ __forceinline__ void windows_of_bins(const Bins<BITS>& bins, bool cut, int bin0, int bin1, int ibits, uint32_t rank0, uint32_t before0,
                                                 uint32_t count0, uint32_t rank1, uint32_t before1, uint32_t count1, Window& w0,
                                                 Window& w1) {
   const int l = threadIdx.x & 63;
-  const int ends = (int)bins.bound((uint32_t)((l & 2 ? bin1 : bin0) + (l & 1)));  // lanes 0 to 3
+  const int ends = (int)bins.bound((uint32_t)((l & 2 ? bin1 : bin0) + (l & 1)), cut);  // lanes 0 to 3
   const auto end = [&](int lane) { return (uint32_t)__builtin_amdgcn_readlane(ends, lane); };
   w0.init(end(0), end(1), ibits, rank0 - before0, before0, count0);
   w1.init(end(2), end(3), ibits, rank1 - before1, before1, count1);
 }
-// Narrows two windows until neither holds more than `limit` keys, both in the same passes over the scores: first to the scores
-// that there are (with ties that is one, and the indices alone are left), then BITS of what is left at a time.  Scores of sixteen
-// different values, whole dma_mask_gen, us, a sort / a search of its own for each rank / this: 16384 x 32 114 / 169 / 114, packed
-// 65536 x 16 157 / 114 / 100, 65536 x 32, window 16384, 483 / 630 / 543.
+// Limits two windows to the scores that there are.
+template <int NT, int NQ>
+__device__ __forceinline__ void tighten(SelShared<NT>& sm, const Scores<NT, NQ>& s, int ibits, Window& w0, Window& w1) {
+  const uint32_t a0 = (uint32_t)(w0.base >> ibits), b0 = (uint32_t)(w0.last >> ibits);
+  const uint32_t a1 = (uint32_t)(w1.base >> ibits), b1 = (uint32_t)(w1.last >> ibits);
+  uint32_t min0 = 0xffffffffu, max0 = 0, min1 = 0xffffffffu, max1 = 0;
+  s.each_again([&](float z, int, int) {
+    const uint32_t key = desc_key(z);
+    const bool in0 = key >= a0 && key <= b0, in1 = key >= a1 && key <= b1;
+    min0 = min(min0, in0 ? key : 0xffffffffu);
+    max0 = max(max0, in0 ? key : 0u);
+    min1 = min(min1, in1 ? key : 0xffffffffu);
+    max1 = max(max1, in1 ? key : 0u);
+  });
+  __syncthreads();
+  reduce_range(sm, min0, max0);
+  __syncthreads();
+  reduce_range(sm, min1, max1);
+  if (w0.count > 0) w0.span(min0, (uint64_t)max0 + 1, ibits);
+  if (w1.count > 0) w1.span(min1, (uint64_t)max1 + 1, ibits);
+}
+// Narrows two windows until neither holds more than `limit` keys, both in the same passes over the scores, BITS of what is left at
+// a time (with ties, of the indices alone: tighten has left one score).  Scores of sixteen different values, whole dma_mask_gen, us, a
+// sort / a search of its own for each rank / this: 16384 x 32 114 / 169 / 117, packed 65536 x 16 157 / 117 / 104, 65536 x 32, window
+// 16384, 487 / 637 / 548.
 template <int BITS, int NT, int NQ>
 __device__ __forceinline__ void narrow(SelShared<NT>& sm, uint32_t* hist0, uint32_t* hist1, const Scores<NT, NQ>& s, int ibits,
                                        Window& w0, Window& w1, uint32_t limit) {
-  if (w0.count <= limit && w1.count <= limit) return;
-  {
-    const uint32_t a0 = (uint32_t)(w0.base >> ibits), b0 = (uint32_t)(w0.last >> ibits);
-    const uint32_t a1 = (uint32_t)(w1.base >> ibits), b1 = (uint32_t)(w1.last >> ibits);
-    uint32_t min0 = 0xffffffffu, max0 = 0, min1 = 0xffffffffu, max1 = 0;
-    s.each_again([&](float z, int, int) {
-      const uint32_t key = desc_key(z);
-      const bool in0 = key >= a0 && key <= b0, in1 = key >= a1 && key <= b1;
-      min0 = min(min0, in0 ? key : 0xffffffffu);
-      max0 = max(max0, in0 ? key : 0u);
-      min1 = min(min1, in1 ? key : 0xffffffffu);
-      max1 = max(max1, in1 ? key : 0u);
-    });
-    __syncthreads();
-    reduce_range(sm, min0, max0);
-    __syncthreads();
-    reduce_range(sm, min1, max1);
-    if (w0.count > 0) w0.span(min0, (uint64_t)max0 + 1, ibits);
-    if (w1.count > 0) w1.span(min1, (uint64_t)max1 + 1, ibits);
-  }
 #pragma unroll 1
   for (;;) {
     const bool go0 = w0.count > limit && w0.base < w0.last, go1 = w1.count > limit && w1.base < w1.last;
@@ -300,8 +299,8 @@ __device__ __forceinline__ void narrow(SelShared<NT>& sm, uint32_t* hist0, uint3
 
 // ------------------------------------------------------------------ checkpoints
 // One workgroup per (checkpoint, head).
-// What bounds it: instruction issue over the N scores, three to four passes of loads of 16 bytes per lane: 65536 tokens x
-// 32 heads 41 us (window 16384: 49).
+// What bounds it: instruction issue over the N scores, three passes of loads of 16 bytes per lane: 65536 tokens x
+// 32 heads 43 us (window 16384: 52).
 constexpr int CK_NT = 1024, CK_NQ = 0;
 __global__ __launch_bounds__(CK_NT, 8) void checkpoint_kernel(SelectArgs p) {
   __shared__ SelShared<CK_NT> sm;
@@ -319,16 +318,15 @@ __global__ __launch_bounds__(CK_NT, 8) void checkpoint_kernel(SelectArgs p) {
   uint64_t from = 0, to = ~0ull;  // the weakest m0 of the kept: ranks kept - m0 .. kept - 1
   if (kept < c || m0 < kept) {
     uint32_t kmin, kmax;
-    float sample;
+    const float sample = s.sample();
     clear_bins<CK_BIN_BITS, CK_NT>(hist);
-    key_range(sm, s, s.nq, 0.f, kmin, kmax, sample);
+    sample_range(sm, sample, kmin, kmax);
     Bins<CK_BIN_BITS> bins;
     bins.init(kmin, kmax);
     const uint32_t rank0 = kept - m0, rank1 = kept - 1;
     const bool cut0 = rank0 > 0, cut1 = kept < c;  // (otherwise nothing is left out on that side)
     if (bins.ok) {
-      count_all<true>(hist, s, bins, sample);
-      __syncthreads();
+      bins.ok = !__syncthreads_or(count_all<false>(hist, s, bins, sample));
       scan_bins<CK_BIN_BITS>(sm, hist, [&](int bin, uint32_t before, uint32_t count) {
         note_bin(sm, 0, rank0, bin, before, count);
         note_bin(sm, 1, rank1, bin, before, count);
@@ -341,11 +339,12 @@ __global__ __launch_bounds__(CK_NT, 8) void checkpoint_kernel(SelectArgs p) {
     Window w0 = {0, 0, rank0, before0, count0}, w1 = {0, 0, rank1, before1, count1};
     if (!by_bin) {
       if (bins.ok) {
-        windows_of_bins(bins, bin0, bin1, ibits, rank0, before0, cut0 ? count0 : 0, rank1, before1, cut1 ? count1 : 0, w0, w1);
+        windows_of_bins(bins, false, bin0, bin1, ibits, rank0, before0, cut0 ? count0 : 0, rank1, before1, cut1 ? count1 : 0, w0, w1);
       } else {
-        w0.init(kmin, (uint64_t)kmax + 1, ibits, rank0, 0, cut0 ? c : 0);
-        w1.init(kmin, (uint64_t)kmax + 1, ibits, rank1, 0, cut1 ? c : 0);
+        w0.init(0, 1ull << 32, ibits, rank0, 0, cut0 ? c : 0);
+        w1.init(0, 1ull << 32, ibits, rank1, 0, cut1 ? c : 0);
       }
+      tighten(sm, s, ibits, w0, w1);
       narrow<CK_BIN_BITS>(sm, hist, exact_hist, s, ibits, w0, w1, CAP);
     }
     __syncthreads();
@@ -381,13 +380,13 @@ __global__ __launch_bounds__(CK_NT, 8) void checkpoint_kernel(SelectArgs p) {
   }
   const size_t out = (size_t)h * p.T + a + (c - CK_SEG);
   __syncthreads();
-  if (tid == 0) fill[0] = 0;
+  if (tid == 0) fill[0] = kept < c ? 1 : 0;
   __syncthreads();
   s.each([&](float z, int t, int e) {
     const int i = s.index(t, e);
     const uint64_t r = ranked(desc_key(z), i);
     if (r >= from && r <= to) {
-      const int at = atomicAdd(&fill[0], 1);
+      const int at = r == to ? 0 : atomicAdd(&fill[0], 1);  // (the last kept key stands first)
       p.ck_z[out + at] = z;
       p.ck_idx[out + at] = i;
     }
@@ -396,11 +395,11 @@ __global__ __launch_bounds__(CK_NT, 8) void checkpoint_kernel(SelectArgs p) {
 
 // ------------------------------------------------------------------ evictions of one block
 // One workgroup per (block, head).  What bounds it: instruction issue; its twelve short phases between barriers take about 14000
-// cycles with 1024 older scores (what a score costs is 16 instructions in all).  (Registers for eight workgroups per compute unit
+// cycles with 1024 older scores (what a score costs is about 15 instructions in all).  (Registers for eight workgroups per compute unit
 // instead of seven: 65536 x 32 of window 1024 50 -> 48 us, 16384 x 32 31 -> 33.)
 // Whole selection, us, against a radix sort and wavelet matrix per 4096 or 16384 keys and a range query per key: 256
 // tokens x 2 heads 25 -> 7, 2 x 4096 x 16 52 -> 12, 16384 x 32 76 -> 29, packed 65536 x 16 121 -> 32, 65536 x 32 of
-// window 1024 241 -> 90.
+// window 1024 241 -> 94.
 template <int NT, int NQ>
 __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
   constexpr int NW = NT / 64, BINS = 1 << BIN_BITS;
@@ -448,18 +447,20 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
   // block's keys can enter.
   int strong = 0, nl = 0;
   bool enters = tid < nb;
-  int b1 = BINS - 1, b2 = 0, end_before = 0, end = N;  // bins of the last resident and of the first that takes part; keys before and up to the end of b1
+  int b1 = BINS - 1, b2 = 0;     // bins of the last resident and of the first that takes part
+  int end_before = 0, end = N;   // keys before b1 and up to its end
   int first = 0;  // rank of the first that takes part
   Bins<BIN_BITS> bins;
-  uint32_t kmin, kmax;
-  float sample;
   clear_bins<BIN_BITS, NT>(hist);
   clear_bins<BIN_BITS, NT>(new_hist);
   if (tid == 0) sm.bin[1] = sm.before[1] = 0;  // (what is left without older keys)
-  // (a full checkpoint: what is behind its last key is not kept, and its range is far shorter than that of all)
-  const bool full = m0 > 0 && c >= k;
-  key_range(sm, s, full ? s.list_q : s.nq, zn, kmin, kmax, sample);
-  bins.init(kmin, kmax);
+  // (a full checkpoint: what is behind its last key is not kept, nor counted; the bins end there)
+  const bool full = m0 > 0 && c > max(m0, k);
+  const uint32_t worst = full ? desc_key(s.list[0]) : 0;
+  const float sample = N > 0 ? s.sample() : zn;
+  uint32_t kmin, kmax;
+  sample_range(sm, sample, kmin, kmax);
+  bins.init(kmin, full ? worst : kmax);
   bool by_bin = bins.ok;
   // the bin of a rank among the older keys, and the count before it
   auto find_bin = [&](int rank) __attribute__((always_inline)) {
@@ -478,21 +479,23 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
     __syncthreads();
   };
   if (by_bin) {
-    if (full) count_all<false>(hist, s, bins, sample);
-    else count_all<true>(hist, s, bins, sample);
-    __syncthreads();
-    const int bn = bins.of_any(zn);
+    bool bad = zn != zn;
+    if (full) bad |= count_all<true>(hist, s, bins, sample);
+    else bad |= count_all<false>(hist, s, bins, sample);
+    by_bin = bins.ok = !__syncthreads_or(bad);
+  }
+  if (by_bin) {
+    const int bn = bins.of(zn);
     scan_bins<BIN_BITS>(sm, hist, [&](int bin, uint32_t before, uint32_t count) {
       note_bin(sm, 0, (uint32_t)(kept - 1), bin, before, count);
     });
-    // (kept == N: every older key is still there, whatever its rank; with no place left either, a key has to be ahead of
-    // the last of them to enter)
+    // (kept == N: every older key is still there, whatever its rank)
     if (kept < N) {
       b1 = sm.bin[0];
       end_before = sm.before[0];
       end = end_before + sm.count[0];
     }
-    enters = tid < nb && bn <= b1 && (cap > N || kn < kmax);
+    enters = tid < nb && bn <= b1 && (!full || kn < worst);
     const int e = __syncthreads_count(enters);
     if (e == 0) {
       store(-2);
@@ -507,9 +510,10 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
     nl = end - strong;
     by_bin = nl - (kept - first) <= NEAR;
     if (by_bin) {
+      const float most = bins.most(b2), least = fmaxf(bins.least(b1), full ? bits_float(bins.last) : -__builtin_inff());
       s.each([&](float z, int t, int e2) {
-        const uint32_t b = bins.of_behind(z);
-        if (b >= (uint32_t)b2 && b <= (uint32_t)b1) sm.cand[atomicAdd(&hist[b], 1u) - strong] = ranked(desc_key(z), s.index(t, e2));
+        const float y = z + bins.add;
+        if (y <= most && y >= least) sm.cand[atomicAdd(&hist[bins.of(z)], 1u) - strong] = ranked(desc_key(z), s.index(t, e2));
       });
       scan_bins<BIN_BITS>(sm, new_hist, [](int, uint32_t, uint32_t) {});
       if (enters) new_run[atomicAdd(&new_hist[bn], 1u)] = ranked(kn, lo + tid);
@@ -519,19 +523,24 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
     const int ibits = 32 - __clz(n);
     Window w0, w1;  // of the first that takes part and of the last resident
     if (bins.ok) {
-      windows_of_bins(bins, b2, b1, ibits, first, strong, sm.count[1], kept - 1, end_before, end - end_before, w0, w1);
+      windows_of_bins(bins, full, b2, b1, ibits, first, strong, sm.count[1], kept - 1, end_before, end - end_before, w0, w1);
+      if (kept == N) w1.count = 0;  // (every older key is still there)
+      tighten(sm, s, ibits, w0, w1);
     } else {
-      enters = tid < nb && (cap > N || kn < kmax);
+      w0.init(0, 1ull << 32, ibits, 0, 0, N);
+      w1 = w0;
+      tighten(sm, s, ibits, w0, w1);
+      // (with no place left, a key has to be ahead of the last older one to enter)
+      enters = tid < nb && (cap > N || kn < (uint32_t)(w0.last >> ibits));
       const int e = __syncthreads_count(enters);
       if (e == 0) {
         store(-2);
         return;
       }
-      first = max(0, kept - min(e, lo + nb - k));
-      w0.init(kmin, 1ull << 32, ibits, first, 0, N);
-      w1.init(kmin, 1ull << 32, ibits, kept - 1, 0, N);
+      w0.rank = uniform(max(0, kept - min(e, lo + nb - k)));
+      w1.rank = uniform(kept - 1);
+      if (kept == N) w1.count = 0;
     }
-    if (kept == N) w1.count = 0;  // (every older key is still there)
     narrow<BIN_BITS>(sm, hist, new_hist, s, ibits, w0, w1, NARROW);
     if (kept < N) enters = enters && composite(kn, lo + tid, ibits) <= w1.last;
     if (__syncthreads_count(enters) == 0) {
@@ -545,7 +554,6 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
       const uint64_t c2 = composite(desc_key(z), s.index(t, e2), ibits);
       if (c2 >= w0.base && (kept == N || c2 <= w1.last)) sm.cand[atomicAdd(&sm.fill, 1)] = ranked(desc_key(z), s.index(t, e2));
     });
-    // (the window of a bin that is not narrowed leaves out what shares the last bin from behind the range)
     __syncthreads();
     nl = sm.fill;
   }
@@ -579,7 +587,7 @@ __global__ __launch_bounds__(NT, 7) void evict_kernel(SelectArgs p) {
     cx[u] = x < nl ? sm.cand[x] : newc[x - nl];
     int r0 = 0, r1 = nl, n0 = 0, n1 = ne;  // the older and the new keys of its bin, or all of them
     if (by_bin) {
-      const int b = bins.of_any(key_value((uint32_t)(cx[u] >> 32)));
+      const int b = bins.of(key_value((uint32_t)(cx[u] >> 32)));
       r0 = b > b2 ? (int)hist[b - 1] - strong : 0;  // (the counters stand at their bins' ends now)
       r1 = b >= b2 ? (int)hist[b] - strong : 0;
       n0 = b > 0 ? (int)new_hist[b - 1] : 0;

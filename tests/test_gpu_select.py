@@ -45,6 +45,7 @@ def scores(kind, H, n, rng):
         special = np.array([np.inf, -np.inf, 0.0, -0.0, 1e-40, -1e-40], dtype=np.float32)
         z = np.where(pick < 6, special[np.minimum(pick, 5)], z).astype(np.float32)
         z[:, n // 3] = np.nan
+        z[:, n // 4] = np.array([0x7F800001], dtype=np.uint32).view(np.float32)[0]
         z[:, n // 2] = np.array([0xFFC00000], dtype=np.uint32).view(np.float32)[0]
     return z
 
@@ -86,7 +87,8 @@ def test_expiries(kind, lens, k):
 
 
 @pytest.mark.parametrize("kind", KINDS)
-@pytest.mark.parametrize("lens,k", [((16385, 300), 333), ((20600, 16384), 4096), ((18000,), 9000), ((65536,), 1500)])
+@pytest.mark.parametrize("lens,k", [((16385, 300), 333), ((20600, 16384), 4096), ((18000,), 9000), ((16600,), 4094), ((17000,), 4097),
+                                    ((65536,), 1500)])
 def test_expiries_of_long_documents(kind, lens, k):
     rng = np.random.default_rng(200 + k)
     check(scores(kind, 1, sum(lens), rng), lens, k)
