@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 def rank_order(z):
     """The order of the scores as the library ranks them: by bits, -0 as +0, a positive NaN above and a negative one below
     everything else; as float64 numbers without infinities."""
-    u = (z + np.float32(0)).view(np.uint32)
+    with np.errstate(invalid="ignore"):  # (a signalling NaN becomes a quiet one, here and there)
+        u = (z + np.float32(0)).view(np.uint32)
     key = np.where(u >> 31, ~u, u | np.uint32(0x80000000))
     return key.astype(np.float64)
 
